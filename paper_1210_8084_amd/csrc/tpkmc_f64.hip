@@ -10,7 +10,9 @@ template void launch_key<double>(const StepArgs<double>&, hipStream_t);
 template void launch_scatter<double>(const StepArgs<double>&, hipStream_t);
 template void launch_prep<double>(Inst<double>*, const double*, int, int, hipStream_t);
 template void launch_search<double>(const StepArgs<double>&, int, int, hipStream_t);
-template void launch_search_mix<double>(const StepArgs<double>&, int, int, bool, hipStream_t);
+template void launch_search_tiles<double>(const StepArgs<double>&, hipStream_t);
+template void launch_search_ties<double>(const StepArgs<double>&, hipStream_t);
+template void launch_search_mix<double>(const StepArgs<double>&, int, bool, hipStream_t);
 template void launch_search_fast<double>(const StepArgs<double>&, int, hipStream_t);
 template void launch_move<double>(const StepArgs<double>&, hipStream_t);
 template void launch_moments<double>(const StepArgs<double>&, hipStream_t);

@@ -27,13 +27,16 @@ enum Phase { PH_CLEAR = 0, PH_KEY, PH_SCAN, PH_SCATTER, PH_SEARCH, PH_MOVE, PH_F
 
 // ---------------------------------------------------------------- kernels
 __global__ void k_clear(int32_t* start, int64_t ncell, unsigned long long* macc, int64_t nwords,
-                        unsigned long long* pair_count) {
+                        unsigned long long* pair_count, uint32_t* ties) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t t = t0; t < ncell; t += stride) start[t] = 0;
     if (macc)
         for (int64_t t = t0; t < nwords; t += stride) macc[t] = 0ull;
-    if (t0 == 0) *pair_count = 0ull;
+    if (t0 == 0) {
+        *pair_count = 0ull;
+        *ties = 0u;
+    }
 }
 
 // Exclusive prefix sum of n int32 in place: per-tile totals, a single
@@ -318,6 +321,7 @@ struct Buffers {
     void* vir;        // colliders' virial terms, 3 reals per particle
     uint8_t* coll;    // collided flags, 1 B per particle
     unsigned long long* pair_count;
+    uint32_t* ties;
     uint32_t* status;
     unsigned long long* mix;  // counters of tpkmc_search_mix (handles only)
 };
@@ -374,6 +378,12 @@ namespace {
 // Target size of one band plane of records (see row_of).
 constexpr double kBandBytes = 1 << 20;
 
+int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
+
+// Sort cells that a handle's scratch holds for `cbins` c-bins and n
+// particles: sub-grids keep kSortCellMin particles a cell.
+int64_t sort_cells(int64_t cbins, int64_t n) { return cbins + n / 8; }
+
 struct Plan {
     int n_inst = 0;
     int64_t ncell_tot = 0, nob_tot = 0, max_nob = 0;
@@ -381,6 +391,8 @@ struct Plan {
     bool adaptive = false;    // some instance takes the adaptive time step
     bool any_search = false;  // some instance takes partners by closest approach
     bool split = false;       // some instance has c-bins split by speed
+    bool subgrid = false;     // some instance's c-bins are cut into sort cells
+    bool any_staged = false, any_tiles = false;  // which searches the instances take
     bool any_random = false;  // some instance takes random partners
     std::vector<Blk> blk;
     std::vector<Chunk> chunks;
@@ -394,13 +406,59 @@ bool bad_state(const tpkmc_particles* s) {
                         bad_ptr(s->vz) || bad_ptr(s->id));
 }
 
+// FP32 instances of at least this many particles per c-bin go to the tile
+// search, sparser ones to the staged lane search: a tile spans 64 / density
+// c-bins along x, and the pairs it tests grow with that span (16M blast at
+// 3.6 per c-bin: staged 1.05 ms, tiles 2.9; Sod tube at 14: 0.47 and 0.36).
+constexpr double kTileDensity = 8.0;
+// Sub-grids: c-bins of at least kSubgridDensity particles are halved along
+// their widest axis, again and again, while a part keeps kSortCellMin
+// particles and its width 0.7 D.  A tile then is compact, and the parts of
+// the neighbourhood out of its reach are skipped: the FP64 Sod tube of 4e5
+// particles on 100 c-bins 7.9 ms whole, 0.12 in sort cells.  Sparser c-bins
+// leave nothing to skip (a tile holds several of them).
+constexpr double kSubgridDensity = 24.0;
+constexpr double kSortCellMin = 8.0;  // sort_cells() counts on it
+constexpr double kSortCellD = 0.7;
+
+template <typename real>
+void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_t Cs, double D, bool planar, bool fp64,
+                       bool subgrid, uint32_t flags) {
+    const int naxes = planar ? 2 : 3;
+    double dens = (double)count / (double)Cs, w[3];
+    if (!(flags & TPKMC_PAIR_RANDOM) && (fp64 || dens >= kTileDensity)) d.flags |= kTiles;
+    // Scale of the tile search's positions: the widest c-bin (half the box on
+    // an axis of one; a planar gas has no extent along z).
+    double wide = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        w[a] = (g.hi[a] - g.lo[a]) / d.nl[a];
+        if (a < naxes) wide = std::max(wide, d.nl[a] > 1 ? w[a] : 0.5 * w[a]);
+    }
+    d.tile_s = (float)(1.0 / wide);
+    if (subgrid && dens >= kSubgridDensity) {
+        while (dens >= 2.0 * kSortCellMin) {
+            int a = -1;
+            for (int b = 0; b < naxes; ++b)
+                if (0.5 * w[b] >= kSortCellD * D && (int64_t)d.n[b] * 2 <= 1 << 24 && (a < 0 || w[b] > w[a])) a = b;
+            if (a < 0) break;
+            d.k[a] *= 2;
+            d.n[a] *= 2;
+            w[a] *= 0.5;
+            dens *= 0.5;
+            d.flags |= kSubgrid | kTiles;
+        }
+        for (int a = 0; a < 3; ++a) d.inv_w[a] = (real)((double)d.n[a] / (g.hi[a] - g.lo[a]));
+    }
+}
+
 // Validates one instance and fills its device descriptor, except the
 // offsets into the c-bin, o-bin, block and chunk tables, which the caller
-// sets.  C and B: its c-bins and o-bins.  nref (split c-bins): the slow
-// particles' c-bins per axis, vc their speed bound.
+// sets.  C and B: its c-bins and o-bins (d.C: its sort cells).  nref (split
+// c-bins): the slow particles' c-bins per axis, vc their speed bound.
+// subgrid: the c-bins may be cut into sort cells.
 template <typename real>
 int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, int64_t& C, int64_t& B,
-              const int32_t* nref = nullptr, double vc = 0.0) {
+              const int32_t* nref = nullptr, double vc = 0.0, bool subgrid = true) {
     const tpkmc_grid& g = q.grid;
     const tpkmc_params& p = q.params;
     if (q.offset < 0 || q.count < 0 || q.offset + q.count > s->n) return TPKMC_EINVAL;
@@ -435,7 +493,8 @@ int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, 
         // configured ones.
         const double L = g.hi[a] - g.lo[a];
         const int32_t nc = nref ? nref[a] : g.ncell[a];
-        d.n[a] = nc;
+        d.n[a] = d.nl[a] = nc;
+        d.k[a] = 1;
         d.ncfg[a] = g.ncell[a];
         d.inv_wc[a] = (real)((double)g.ncell[a] / L);
         d.no[a] = g.nobin[a];
@@ -447,22 +506,28 @@ int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, 
         d.w[a] = (real)(L / (double)g.ncell[a]);
         wd[a] = L / (double)g.ncell[a];
         if (g.ncell[a] > 1 && (dx == 0.0 || L / (double)g.ncell[a] < dx)) dx = L / (double)g.ncell[a];
-        d.inv_w[a] = (real)((double)nc / L);
+        d.inv_w[a] = d.inv_wl[a] = (real)((double)nc / L);
         d.inv_wo[a] = (real)((double)g.nobin[a] / L);
     }
     const bool split = nref && (nref[0] != g.ncell[0] || nref[1] != g.ncell[1] || nref[2] != g.ncell[2]);
-    const int64_t Cf = C;
-    if (split) C = Cf + Cc;
+    const int64_t Cs = C;  // the c-bins that are searched
+    if (split) C = Cs + Cc;
     if (C + 1 > (int64_t)1 << 30 || B > (int64_t)1 << 30) return TPKMC_EINVAL;
+    const double Dp = 0.5 * p.sigma;
+    const double D = planar ? Dp : std::sqrt(p.sigma / M_PI);
+    choose_sort_cells(d, g, q.count, Cs, D, planar, std::is_same<real, double>::value,
+                      subgrid && !(p.flags & TPKMC_PAIR_RANDOM), p.flags);
+    const int64_t Cf = (int64_t)d.n[0] * d.n[1] * d.n[2];
+    const int64_t Csort = split ? Cf + Cc : Cf;
     d.off = q.offset;
     d.cnt = q.count;
-    d.C = (int32_t)C;
+    d.C = (int32_t)Csort;
     d.Cf = (int32_t)Cf;
     d.seed_lo = (uint32_t)p.seed;
     d.seed_hi = (uint32_t)(p.seed >> 32);
     d.step_lo = (uint32_t)p.step;
     d.instance = p.instance;
-    d.flags = p.flags | (s->mass ? kHasMass : 0u);
+    d.flags |= p.flags | (s->mass ? kHasMass : 0u);
     if (split) {
         d.flags |= kSplit;
         d.vc2 = (real)(vc * vc);
@@ -470,7 +535,6 @@ int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, 
     d.dt = (real)p.dt;
     // Largest accepted d_min^2: sigma = pi D^2 in space, sigma = 2 D in
     // the plane (same expressions as the reference).
-    const double Dp = 0.5 * p.sigma;
     d.D2 = planar ? (real)(Dp * Dp) : (real)(p.sigma / M_PI);
     d.mass = (real)p.mass;
     d.mass_d = p.mass;
@@ -524,11 +588,12 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     P.n_inst = n_inst;
     P.adaptive = false;
     P.any_search = false;
-    P.split = false;
+    P.split = P.subgrid = P.any_staged = P.any_tiles = false;
     P.any_random = false;
     P.ncell_tot = 0;
     P.nob_tot = 0;
     P.max_nob = 0;
+    int64_t before = 0, cbins = 0;  // particles of the instances before; c-bins
     for (int k = 0; k < n_inst; ++k) {
         const tpkmc_instance& q = in[k];
         Inst<real>& d = I[k];
@@ -537,13 +602,19 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
         const int rc = fill_inst<real>(s, q, d, C, B, tc ? tc->n : nullptr, tc ? tc->vc : 0.0);
         if (rc) return rc;
         if (d.flags & kSplit) P.split = true;
+        if (d.flags & kSubgrid) P.subgrid = true;
+        if (!(d.flags & (kTiles | TPKMC_PAIR_RANDOM))) P.any_staged = true;
+        if (d.flags & kTiles) P.any_tiles = true;
         spans.push_back({q.offset, q.count});
         if (q.params.flags & TPKMC_PAIR_RANDOM) P.any_random = true;
         else P.any_search = true;
         if (q.params.flags & TPKMC_ADAPTIVE_DT) P.adaptive = true;
         d.cell_off = P.ncell_tot;
         d.obin_off = P.nob_tot;
-        P.ncell_tot += C + 1;
+        d.base = q.offset - before;
+        before += q.count;
+        P.ncell_tot += (int64_t)d.C + 1;
+        cbins += C + 1;
         P.nob_tot += B;
         P.max_nob = std::max(P.max_nob, B);
         d.blk0 = (int32_t)P.blk.size();
@@ -557,7 +628,7 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     std::sort(spans.begin(), spans.end());
     for (size_t k = 1; k < spans.size(); ++k)
         if (spans[k - 1].first + spans[k - 1].second > spans[k].first) return TPKMC_EINVAL;
-    if (P.ncell_tot > h->cell_cap) return TPKMC_ECAPACITY;
+    if (cbins > h->cell_cap) return TPKMC_ECAPACITY;
     if (P.nob_tot > h->max_obins) return TPKMC_ECAPACITY;
     if ((int64_t)P.blk.size() > h->max_blk) return TPKMC_ECAPACITY;
     if ((int64_t)P.chunks.size() > h->max_chunks) return TPKMC_ECAPACITY;
@@ -627,12 +698,12 @@ StepArgs<real> make_args(const Buffers& B, const tpkmc_particles* s, const tpkmc
     a.pairs = o ? o->pairs : nullptr;
     a.pair_cap = (o && o->pairs) ? o->pair_cap : 0;
     a.pair_count = B.pair_count;
+    a.ties = B.ties;
     a.mix = B.mix;
     a.moments = o ? o->moments : nullptr;
     return a;
 }
 
-int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 
 void enqueue_scan(const Buffers& B, int64_t n, hipStream_t s) {
     const int64_t tiles = scan_tiles(n);
@@ -646,11 +717,12 @@ struct Shape {
     int n_inst, nblk, nchunk;
     int64_t ncell_tot, nob_tot, max_nob;
     bool prep, any_search, any_random, split;  // prep: some instance needs the prep kernel
+    bool any_staged, any_tiles;
 };
 
 Shape shape_of(const Plan& P) {
     return Shape{P.n_inst, P.nblk, (int)P.chunks.size(), P.ncell_tot, P.nob_tot, P.max_nob,
-                 P.adaptive || P.split, P.any_search, P.any_random, P.split};
+                 P.adaptive || P.split || P.subgrid, P.any_search, P.any_random, P.split, P.any_staged, P.any_tiles};
 }
 
 // Everything of one step after the tables are on the device.  `h` only
@@ -666,7 +738,7 @@ void enqueue_step(tpkmc_handle* h, const Buffers& B, const StepArgs<real>& a, co
         const int64_t work = std::max<int64_t>(P.ncell_tot + 1, nwords);
         const int64_t grid = std::min<int64_t>((work + 255) / 256, 4096);
         hipLaunchKernelGGL(k_clear, dim3((unsigned)std::max<int64_t>(grid, 1)), dim3(256), 0, s, B.start,
-                           P.ncell_tot + 1, mom ? (unsigned long long*)B.macc : nullptr, nwords, B.pair_count);
+                           P.ncell_tot + 1, mom ? (unsigned long long*)B.macc : nullptr, nwords, B.pair_count, B.ties);
     }
     if (P.nblk > 0) {
         PhaseScope ps(h, PH_KEY, s, prof);
@@ -684,8 +756,10 @@ void enqueue_step(tpkmc_handle* h, const Buffers& B, const StepArgs<real>& a, co
         }
         {
             PhaseScope ps(h, PH_SEARCH, s, prof);
-            if (P.any_search) launch_search<real>(a, search_block, search_group, s);
+            if (P.any_staged) launch_search<real>(a, search_block, search_group, s);
+            if (P.any_tiles) launch_search_tiles<real>(a, s);
             if (P.split) launch_search_fast<real>(a, P.n_inst, s);
+            if (P.any_search) launch_search_ties<real>(a, s);
             if (P.any_random) launch_random_pairs<real>(a, s);
         }
         {
@@ -818,8 +892,8 @@ int grow_cells(tpkmc_handle* h, int64_t need) {
     hipFree(h->b.tiles);
     h->b.start = nullptr;
     h->b.tiles = nullptr;
-    const int64_t tiles = (need + 1 + kScanTile - 1) / kScanTile + 1;
-    if (dalloc(&h->b.start, need + 1) || dalloc(&h->b.tiles, tiles)) {
+    const int64_t cells = sort_cells(need, h->max_n);
+    if (dalloc(&h->b.start, cells + 1) || dalloc(&h->b.tiles, scan_tiles(cells + 1) + 1)) {
         h->cell_cap = 0;
         return TPKMC_ENOMEM;
     }
@@ -966,9 +1040,9 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     a.order = 0;  // shapes are timed in the default work-group order
     // Bin once (clear, key, prefix, scatter); then time only the search.
     hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, h->b.start, P.ncell_tot + 1,
-                       (unsigned long long*)nullptr, (int64_t)0, h->b.pair_count);
+                       (unsigned long long*)nullptr, (int64_t)0, h->b.pair_count, h->b.ties);
     launch_key<real>(a, st);
-    if (P.adaptive || P.split) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
+    if (P.adaptive || P.split || P.subgrid) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
     enqueue_scan(h->b, P.ncell_tot + 1, st);
     launch_scatter<real>(a, st);
     hipEvent_t e0, e1;
@@ -988,12 +1062,17 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
             if (bs <= kBlock / grp && !(grp == 2 && bs == kWave)) shapes.push_back({grp, bs});
     // Warm the caches and clocks first: the first shape timed would
     // otherwise look slower than it is.
-    for (int r = 0; r < 4; ++r) launch_search<real>(a, kWave, 2, st);
+    auto search = [&](int bs, int grp) {
+        if (P.any_staged) launch_search<real>(a, bs, grp, st);
+        if (P.any_tiles) launch_search_tiles<real>(a, st);
+    };
+    if (!P.any_staged) shapes.resize(1);  // the tile search has one shape
+    for (int r = 0; r < 4; ++r) search(kWave, 2);
     for (const auto& sh : shapes) {
         const int grp = sh.first, bs = sh.second;
-        launch_search<real>(a, bs, grp, st);  // warm-up
+        search(bs, grp);  // warm-up
         hipEventRecord(e0, st);
-        for (int r = 0; r < 3; ++r) launch_search<real>(a, bs, grp, st);
+        for (int r = 0; r < 3; ++r) search(bs, grp);
         hipEventRecord(e1, st);
         if (hipEventSynchronize(e1) != hipSuccess) { rc = TPKMC_EHIP; break; }
         float ms = 0.f;
@@ -1019,9 +1098,9 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
         float base_ms = 1e30f;
         for (int order : {kDefaultSearchOrder, 0, 1, 128}) {
             a.order = order;
-            launch_search<real>(a, best_block, best_group, st);  // warm-up
+            search(best_block, best_group);  // warm-up
             hipEventRecord(f0, st);
-            for (int r = 0; r < 3; ++r) launch_search<real>(a, best_block, best_group, st);
+            for (int r = 0; r < 3; ++r) search(best_block, best_group);
             hipEventRecord(f1, st);
             if (hipEventSynchronize(f1) != hipSuccess) { rc = TPKMC_EHIP; break; }
             float ms = 0.f;
@@ -1059,17 +1138,16 @@ int mix_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in
     StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk);
     a.order = h->search_order;
     hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, h->b.start, P.ncell_tot + 1,
-                       (unsigned long long*)nullptr, (int64_t)0, h->b.pair_count);
+                       (unsigned long long*)nullptr, (int64_t)0, h->b.pair_count, h->b.ties);
     launch_key<real>(a, st);
-    if (P.adaptive || P.split) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
+    if (P.adaptive || P.split || P.subgrid) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
     enqueue_scan(h->b, P.ncell_tot + 1, st);
     launch_scatter<real>(a, st);
     if (hipMemsetAsync(h->b.mix, 0, 3 * sizeof(unsigned long long), st) != hipSuccess) return TPKMC_EHIP;
-    launch_search_mix<real>(a, h->search_block, P.n_inst, P.split, st);
+    launch_search_mix<real>(a, P.n_inst, P.split, st);
     if (hipMemcpyAsync(counts, h->b.mix, 3 * sizeof(uint64_t), hipMemcpyDeviceToHost, st) != hipSuccess)
         return TPKMC_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return TPKMC_EHIP;
-    for (int k = 0; k < 3; ++k) counts[k] /= 2u;  // the device counts each unordered pair twice
     h->last_stream = st;
     return hipGetLastError() == hipSuccess ? TPKMC_OK : TPKMC_EHIP;
 }
@@ -1123,11 +1201,13 @@ size_t carve(uintptr_t base, int64_t n, int64_t ncell_tot, int64_t nob, int nblk
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     B.rank = (int32_t*)take(4 * nn);
     B.src = (int32_t*)take(4 * nn);
+    // best and perm serve random partners alone; in FP64 the search's keys
+    // share their place (one instance takes the one or the other).
     B.best = (int32_t*)take(4 * nn);
     B.perm = (int32_t*)take(4 * nn);
     B.rec = take(8 * sizeof(real) * nn);
     B.rmass = masses ? take(sizeof(real) * nn) : nullptr;
-    B.bkey = std::is_same<real, float>::value ? (unsigned long long*)take(8 * nn) : nullptr;
+    B.bkey = std::is_same<real, float>::value ? (unsigned long long*)take(8 * nn) : (unsigned long long*)B.best;
     B.start = (int32_t*)take(4 * (size_t)(ncell_tot + 1));
     B.tiles = (int32_t*)take(4 * (size_t)(scan_tiles(ncell_tot + 1) + 1));
     B.inst = take(sizeof(Inst<real>));
@@ -1139,7 +1219,8 @@ size_t carve(uintptr_t base, int64_t n, int64_t ncell_tot, int64_t nob, int nblk
     B.macc = (ObAcc*)take(sizeof(ObAcc) * (size_t)std::max<int64_t>(nob, 1));
     B.vir = take(3 * sizeof(real) * nn);
     B.coll = (uint8_t*)take(nn);
-    B.pair_count = (unsigned long long*)take(sizeof(unsigned long long));
+    B.pair_count = (unsigned long long*)take(2 * sizeof(unsigned long long));
+    B.ties = (uint32_t*)(B.pair_count + 1);
     B.status = (uint32_t*)take(sizeof(uint32_t));
     return off;
 }
@@ -1162,7 +1243,7 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     if (s->n >= ((int64_t)1 << 27)) return TPKMC_ECAPACITY;
     const int nblk = (int)((s->n + kBlock - 1) / kBlock);
     const int nchunk = (nblk + kChunk - 1) / kChunk;
-    const int64_t ncell_tot = C + 1;
+    int64_t ncell_tot = (int64_t)d.C + 1;
     d.cell_off = 0;
     d.obin_off = 0;
     d.blk0 = 0;
@@ -1170,6 +1251,16 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     d.chunk0 = 0;
     d.nchunk = nchunk;
     Buffers Bf{};
+    if ((d.flags & kSubgrid) &&
+        carve<real>(0, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, Bf) > TPKMC_NOALLOC_SCRATCH_BYTES) {
+        // The sub-grid is an extra: without it where the scratch is short.
+        if ((rc = fill_inst<real>(s, q, d, C, B, nullptr, 0.0, false))) return rc;
+        ncell_tot = (int64_t)d.C + 1;
+        d.blk0 = 0;
+        d.nblk = nblk;
+        d.chunk0 = 0;
+        d.nchunk = nchunk;
+    }
     if (carve<real>(0, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, Bf) > TPKMC_NOALLOC_SCRATCH_BYTES)
         return TPKMC_ECAPACITY;
     int ndev = 0;
@@ -1192,7 +1283,9 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     P.ncell_tot = ncell_tot;
     P.nob_tot = B;
     P.max_nob = B;
-    P.prep = (p->flags & TPKMC_ADAPTIVE_DT) != 0;
+    P.prep = (p->flags & TPKMC_ADAPTIVE_DT) != 0 || (d.flags & kSubgrid) != 0;
+    P.any_staged = !random && !(d.flags & kTiles);
+    P.any_tiles = !random && (d.flags & kTiles);
     P.any_search = !random;
     P.any_random = random;
     P.split = false;
@@ -1246,11 +1339,11 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
     h->max_chunks = h->max_blk / kChunk + cfg->max_instances + 1;
     const size_t rs = cfg->precision == TPKMC_FP64 ? sizeof(double) : sizeof(float);
     const size_t inst_sz = cfg->precision == TPKMC_FP64 ? sizeof(Inst<double>) : sizeof(Inst<float>);
-    const int64_t tiles = (cfg->max_cells + 1 + kScanTile - 1) / kScanTile + 1;
+    const int64_t cells = sort_cells(cfg->max_cells, cfg->max_particles);
     int bad = 0;
     bad |= dalloc(&h->b.rank, h->max_n);
-    bad |= dalloc(&h->b.start, h->max_cells + 1);
-    bad |= dalloc(&h->b.tiles, tiles);
+    bad |= dalloc(&h->b.start, cells + 1);
+    bad |= dalloc(&h->b.tiles, scan_tiles(cells + 1) + 1);
     bad |= dalloc(&h->b.src, h->max_n);
     bad |= dalloc(&h->b.best, h->max_n);
     bad |= dalloc(&h->b.perm, h->max_n);
@@ -1261,12 +1354,12 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
     bad |= dalloc(&h->b.gpart, h->max_blk * kGPart);
     bad |= dalloc(&h->b.chunks, h->max_chunks);
     bad |= dalloc(&h->b.cpart, h->max_chunks * kGPart);
-    if (cfg->precision == TPKMC_FP32) bad |= dalloc(&h->b.bkey, h->max_n);
+    bad |= dalloc(&h->b.bkey, h->max_n);
     bad |= dalloc(&h->b.shift, 3 * std::max<int64_t>(h->max_obins, 1));
     bad |= dalloc(&h->b.macc, std::max<int64_t>(h->max_obins, 1));
     bad |= hipMalloc(&h->b.vir, rs * 3 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
     bad |= dalloc(&h->b.coll, std::max<int64_t>(h->max_n, 1));
-    bad |= dalloc(&h->b.pair_count, 1);
+    bad |= dalloc(&h->b.pair_count, 2);
     bad |= dalloc(&h->b.mix, 3);
     bad |= dalloc(&h->b.status, 1);
     h->stage_bytes = inst_sz * (size_t)h->max_inst + sizeof(Blk) * (size_t)h->max_blk +
@@ -1282,6 +1375,7 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
         bad |= hipStreamCreateWithFlags(&h->own_stream, hipStreamNonBlocking) != hipSuccess;
         bad |= hipDeviceSynchronize() != hipSuccess;
     }
+    if (!bad) h->b.ties = (uint32_t*)(h->b.pair_count + 1);
     if (bad) {
         free_all(h);
         if (h->own_stream) hipStreamDestroy(h->own_stream);

@@ -85,11 +85,29 @@ struct Inst {
     real vc2;
     real inv_wc[3];
     double vmax2_d;
+    // Tile search: 1 / the length its positions are scaled by (the widest
+    // c-bin).
+    float tile_s;
+    // Sub-grids (kSubgrid): nl[] c-bins per axis (the refined ones of split
+    // c-bins), each cut into k[] sort cells, n[a] = nl[a] k[a]; inv_wl: c-bins
+    // per unit length.  Without, k is 1 and n, nl are the same.  vreach: the
+    // largest speed among the records sorted on them (infinite: unknown),
+    // strayed: prep's flag for that.
+    int32_t nl[3], k[3];
+    real inv_wl[3];
+    real vreach;
+    uint32_t strayed;
+    int64_t base;             // record index of the instance's first: base + start[]
 };
 
 // Bit of Inst::flags set by the host (outside the public flag bits): the
 // c-bins are split by speed (slow particles on refined c-bins, see Inst).
 constexpr uint32_t kSplit = 1u << 30;
+
+// Bits of Inst::flags set by the host: partners from the tile search; the
+// c-bins are cut into sort cells (see Inst).
+constexpr uint32_t kTiles = 1u << 29;
+constexpr uint32_t kSubgrid = 1u << 28;
 
 // Bit of Inst::flags, set by the host (outside the public flag bits): the
 // particles carry their own masses.
@@ -126,15 +144,17 @@ struct StepArgs {
     real* mass;               // caller's per-particle masses, or null
     real* rmass;              // masses in record order (with mass only)
     int32_t* src;             // record -> caller index
-    int32_t* best;            // record -> partner record or -1 (FP64 search)
+    int32_t* best;            // random partners: rank in the c-bin; FP64: then the partner record or -1
     int32_t* perm;            // random partners: c-bin-local order -> record
-    unsigned long long* bkey; // record -> (d_min^2 bits, partner record) (FP32 search)
+    unsigned long long* bkey; // record -> (ranking value bits, partner record) of its closest candidate
+    uint32_t* ties;           // nonzero: some FP64 record is marked in coll (see k_search_ties)
     double* gpart;            // [nblk][kGPart]
     double* shift;            // per-o-bin velocity shift (3 per o-bin)
     int32_t order;            // search work-group order: 0 contiguous per XCD, S > 0 chunks of S round-robin
     ObAcc* macc;              // per-o-bin exact sums, or null (no moments)
     real* vir;                // virial terms of each collider (3 per particle, caller index)
-    uint8_t* coll;            // 1 if the particle collided this step (caller index)
+    uint8_t* coll;            // 1 if the particle collided this step (caller index); FP64, until the move:
+                              // 1 if the record's key met an equal one (record index)
     unsigned long long* mix;  // search mix counters (tests, s0 < 0, s0 < 0 < s1), or null
     // outputs
     uint32_t* pairs;
@@ -149,8 +169,9 @@ template <typename real> void launch_scatter(const StepArgs<real>& a, hipStream_
 template <typename real> void launch_prep(Inst<real>* inst, const double* gpart, int n_inst, int max_nblk,
                                          hipStream_t s);
 template <typename real> void launch_search(const StepArgs<real>& a, int block, int group, hipStream_t s);
-template <typename real> void launch_search_mix(const StepArgs<real>& a, int block, int n_inst, bool split,
-                                               hipStream_t s);
+template <typename real> void launch_search_tiles(const StepArgs<real>& a, hipStream_t s);
+template <typename real> void launch_search_ties(const StepArgs<real>& a, hipStream_t s);
+template <typename real> void launch_search_mix(const StepArgs<real>& a, int n_inst, bool split, hipStream_t s);
 template <typename real> void launch_search_fast(const StepArgs<real>& a, int n_inst, hipStream_t s);
 template <typename real> void launch_move(const StepArgs<real>& a, hipStream_t s);
 template <typename real> void launch_moments(const StepArgs<real>& a, hipStream_t s);

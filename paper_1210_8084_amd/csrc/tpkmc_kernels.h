@@ -70,20 +70,16 @@ template <> struct Rec<double> {
     }
 };
 
-// Loads of a record whose index is the same in every lane of the wave: through
-// the constant address space the compiler issues scalar loads (one per wave,
-// into SGPRs); the records are never written while the search runs.
-template <typename real> struct RecU;
-template <typename real> struct RecU {
-    typedef __attribute__((address_space(4))) const real cr;
-    static __device__ __forceinline__ void load(const real* r, int32_t i, real& x, real& y, real& z, uint32_t& id,
-                                                real& vx, real& vy, real& vz) {
-        const cr* p = (const cr*)(r) + 8 * (int64_t)i;
-        x = p[0]; y = p[1]; z = p[2];
-        id = Rec<real>::to_u32(p[3]);
-        vx = p[4]; vy = p[5]; vz = p[6];
-    }
-};
+// Position and velocity of record i.
+__device__ __forceinline__ void load_pv(const float* r, int32_t i, float& x, float& y, float& z, float& vx, float& vy,
+                                        float& vz) {
+    Rec<float>::load6(r, (uint32_t)i, x, y, z, vx, vy, vz);
+}
+__device__ __forceinline__ void load_pv(const double* r, int32_t i, double& x, double& y, double& z, double& vx,
+                                        double& vy, double& vz) {
+    uint32_t id, fl;
+    Rec<double>::load(r, i, x, y, z, id, vx, vy, vz, fl);
+}
 
 // ---------------------------------------------------------------- helpers
 // Bin along one axis: floor((x - lo) * n / L) clamped into [0, n - 1].
@@ -93,6 +89,19 @@ __device__ __forceinline__ int axis_bin(real x, real lo, real inv_w, int n) {
     if (!(t >= real(0))) return 0;
     if (t >= real(n)) return n - 1;
     return (int)t;
+}
+
+// Sort cell of a coordinate along axis ax: its c-bin (refined for the slow
+// particles of split c-bins), cut into k equal parts where the instance has
+// sub-grids.  The c-bin is axis_bin's own, so a sub-grid never moves a
+// particle to another c-bin.
+template <typename real>
+__device__ __forceinline__ int sort_bin(const Inst<real>& I, int ax, real x) {
+    const int c = axis_bin(x, I.lo[ax], I.inv_wl[ax], I.nl[ax]);
+    const int k = I.k[ax];
+    if (k == 1) return c;
+    const real f = ((x - I.lo[ax]) * I.inv_wl[ax] - (real)c) * (real)k;
+    return c * k + (f >= real(1) ? min((int)fmin(f, (real)k), k - 1) : 0);
 }
 
 // Row (y, z) of c-bins as its index in the c-bin order, in units of rows
@@ -182,27 +191,6 @@ __device__ __forceinline__ double block_max(double v, double* lds) {
     double t = lds[0];
     for (int k = 1; k < nw; ++k) t = fmax(t, lds[k]);
     return t;
-}
-
-// Sums (max for index kmax) of N values over the work-group in one LDS pass;
-// the totals land in v[] of thread 0.  lds holds 16 * N doubles.
-template <int N>
-__device__ __forceinline__ void block_reduce(double v[N], int kmax, double* lds) {
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        for (int o = 32; o > 0; o >>= 1) {
-            const double u = __shfl_xor(v[k], o);
-            v[k] = k == kmax ? fmax(v[k], u) : v[k] + u;
-        }
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int k = 0; k < N; ++k) lds[w * N + k] = v[k];
-    __syncthreads();
-    if (threadIdx.x == 0)
-        for (int q = 1; q < nw; ++q)
-#pragma unroll
-            for (int k = 0; k < N; ++k) v[k] = k == kmax ? fmax(v[k], lds[q * N + k]) : v[k] + lds[q * N + k];
 }
 
 // Work-groups are dispatched round-robin over the 8 XCDs; remap so that each
@@ -312,10 +300,7 @@ __device__ __forceinline__ int cbin_key(const StepArgs<real>& a, const Inst<real
         const int cz = axis_bin(z, I.lo[2], I.inv_wc[2], I.ncfg[2]);
         return (int)I.cell_off + I.Cf + cx + I.ncfg[0] * (cy + I.ncfg[1] * cz);
     }
-    const int cx = axis_bin(x, I.lo[0], I.inv_w[0], I.n[0]);
-    const int cy = axis_bin(y, I.lo[1], I.inv_w[1], I.n[1]);
-    const int cz = axis_bin(z, I.lo[2], I.inv_w[2], I.n[2]);
-    return (int)I.cell_off + cx + I.n[0] * row_of(I, cy, cz);
+    return (int)I.cell_off + sort_bin(I, 0, x) + I.n[0] * row_of(I, sort_bin(I, 1, y), sort_bin(I, 2, z));
 }
 
 // The key kernel runs one wave per block-table entry, each lane taking
@@ -338,7 +323,8 @@ __global__ void __launch_bounds__(kWave) k_key(StepArgs<real> a) {
     const Inst<real>& I = a.inst[bt.inst];
     const int lane = threadIdx.x;
     const int64_t end = I.off + I.cnt;
-    const bool want_v2 = (I.flags & (TPKMC_ADAPTIVE_DT | kSplit)) != 0;
+    const bool want_v2 = (I.flags & (TPKMC_ADAPTIVE_DT | kSplit | kSubgrid)) != 0;
+    bool strayed = false;  // a particle outside the box along a periodic axis
     real x[kKeyRec], y[kKeyRec], z[kKeyRec], vx[kKeyRec], vy[kKeyRec], vz[kKeyRec];
     bool alive[kKeyRec];
 #pragma unroll
@@ -367,7 +353,13 @@ __global__ void __launch_bounds__(kWave) k_key(StepArgs<real> a) {
         bool fin = true;
         key[r] = in ? cbin_key(a, I, p, x[r], y[r], z[r], vx[r], vy[r], vz[r], alive[r], fin) : 0;
         if (in && alive[r] && fin) {
-            if (want_v2) v2 = fmax(v2, speed2((double)vx[r], (double)vy[r], (double)vz[r]));
+            if (want_v2) {
+                v2 = fmax(v2, speed2((double)vx[r], (double)vy[r], (double)vz[r]));
+                const real q[3] = {x[r], y[r], z[r]};
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax)
+                    strayed |= I.bc[ax] == TPKMC_BC_PERIODIC && !(q[ax] >= I.lo[ax] && q[ax] < I.hi[ax]);
+            }
         } else if (in) {
             nonfin += (alive[r] && !fin) ? 1.0 : 0.0;
         }
@@ -411,10 +403,11 @@ __global__ void __launch_bounds__(kWave) k_key(StepArgs<real> a) {
     }
     nonfin = wave_reduce<false>(nonfin);
     v2 = wave_reduce<true>(v2);
+    const bool any_strayed = __ballot(strayed) != 0;
     if (lane == 0) {
         double* gp = a.gpart + (int64_t)blockIdx.x * kGPart;
         gp[GP_NONFINITE] = nonfin;
-        gp[GP_VMAX0] = v2;
+        gp[GP_VMAX0] = any_strayed ? -v2 : v2;  // the sign carries the flag (also of a zero)
         gp[GP_FAST] = 0.0;  // counted by the scatter kernel, once dt is known
         // The search kernel may accumulate into these with atomics.
         gp[GP_TESTS2] = 0.0;
@@ -433,7 +426,7 @@ __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
     const int64_t p = (int64_t)bt.first + threadIdx.x;
     bool fast = false;
     if (p < I.off + I.cnt) {
-        const int64_t base = I.off - a.start[I.cell_off];
+        const int64_t base = I.base;
         const bool alive = a.alive ? a.alive[p] != 0 : true;
         const real x = a.x[p], y = a.y[p], z = a.z[p], vx = a.vx[p], vy = a.vy[p], vz = a.vz[p];
         bool fin;
@@ -442,7 +435,8 @@ __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
         const uint32_t fl = alive ? 1u : 0u;
         Rec<real>::store(a.rec, dst, x, y, z, a.id[p], vx, vy, vz, fl);
         if (!(I.flags & TPKMC_ALLOW_REORDER)) a.src[dst] = (int32_t)p;
-        if (a.bkey) a.bkey[dst] = ~0ull;
+        a.bkey[dst] = ~0ull;
+        if constexpr (std::is_same<real, double>::value) a.coll[dst] = 0;  // marks of k_search_ties
         if (a.mass) a.rmass[dst] = a.mass[p];
         // Diagnostic: a particle faster than one c-bin per step on some axis.
         const real dt = I.dt;
@@ -617,6 +611,61 @@ __device__ __forceinline__ uint32_t sortable(float v) {
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+__device__ __forceinline__ unsigned long long sortable(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+
+// The search's result per record is one 64-bit key, the ranking value of
+// criterion 3 above the partner record, lowered by atomicMin in any order
+// (~0: no candidate).  FP32: all 32 bits of the value, partner in the low
+// 32; exact ties go to the lower record.  FP64: the top 33 bits of the value
+// and 31 bits of partner.  Values that agree in those 33 bits are not told
+// apart by the key, so a record that meets two of them while one is its
+// lowest is marked, and k_search_ties settles it with the full values and
+// the tie rule of the reference (lower id); about one record in 10^6 is.
+template <typename real> struct Key;
+
+template <> struct Key<float> {
+    static __device__ __forceinline__ unsigned long long make(float v, uint32_t j) {
+        return (unsigned long long)sortable(v) << 32 | j;
+    }
+    static __device__ __forceinline__ int32_t partner(unsigned long long k) { return (int32_t)(uint32_t)k; }
+    static __device__ __forceinline__ void tied(const StepArgs<float>&, int64_t, unsigned long long,
+                                                unsigned long long) {}
+    // old: the key as read earlier (it only falls, so a key found below k
+    // need not be touched).
+    static __device__ __forceinline__ void lower(const StepArgs<float>& a, int64_t i, unsigned long long k,
+                                                 unsigned long long old) {
+        if (old > k) atomicMin(a.bkey + i, k);
+    }
+};
+
+template <> struct Key<double> {
+    static constexpr int kPartnerBits = 31;
+    static __device__ __forceinline__ unsigned long long make(double v, uint32_t j) {
+        return (sortable(v) >> kPartnerBits << kPartnerBits) | j;
+    }
+    static __device__ __forceinline__ int32_t partner(unsigned long long k) { return (int32_t)(k & 0x7fffffffull); }
+    static __device__ __forceinline__ void tied(const StepArgs<double>& a, int64_t i, unsigned long long old,
+                                                unsigned long long k) {
+        if (((old ^ k) >> kPartnerBits) == 0 && old != k) {
+            a.coll[i] = 1;
+            *a.ties = 1u;
+        }
+    }
+    static __device__ __forceinline__ void lower(const StepArgs<double>& a, int64_t i, unsigned long long k,
+                                                 unsigned long long old) {
+        if (old > k) old = atomicMin(a.bkey + i, k);
+        tied(a, i, old, k);
+    }
+};
+
+template <typename real>
+__device__ __forceinline__ unsigned long long key_now(const StepArgs<real>& a, int64_t i) {
+    return __hip_atomic_load(a.bkey + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Neighbour index along one axis (offset d in -1..1): whether it exists and
 // is not a repeat of another offset (periodic axes with 1 or 2 bins), and the
 // wrapped index.
@@ -643,21 +692,6 @@ __device__ __forceinline__ int x_ranges(int cx, int n, bool periodic, int xa[2],
     xb[0] = cx < n - 1 ? cx + 1 : n - 1;
     return 1;
 }
-
-template <typename real>
-__device__ __forceinline__ int x_lo_of(int32_t f, const StepArgs<real>& a, const Inst<real>& I, int n0, bool per0) {
-    real x, y, z, vx, vy, vz;
-    uint32_t id;
-    RecU<real>::load(a.rec, f, x, y, z, id, vx, vy, vz);
-    int xa[2], xb[2];
-    x_ranges(axis_bin(x, I.lo[0], I.inv_w[0], I.n[0]), n0, per0, xa, xb);
-    return xa[0];
-}
-
-template <typename real>
-__device__ __forceinline__ int cy_of(real y, const Inst<real>& I) { return axis_bin(y, I.lo[1], I.inv_w[1], I.n[1]); }
-template <typename real>
-__device__ __forceinline__ int cz_of(real z, const Inst<real>& I) { return axis_bin(z, I.lo[2], I.inv_w[2], I.n[2]); }
 
 // Visits the record ranges of the neighbourhood of record i (bin cx, cy, cz).
 // HALF: only pairs (i, j) not visited from j's side -- bins of larger index
@@ -698,6 +732,29 @@ __device__ __forceinline__ void for_neighbourhood(const int32_t* start, const In
     for (int k = 0; k < 9; ++k) neighbourhood_row<HALF, COARSE>(start, I, base, n, per, cx, cy, cz, i, k, visit);
 }
 
+// Visits the record ranges of the c-bins neighbouring that of (x, y, z), its
+// own included, on the c-bins sort cells are part of.
+template <typename real, typename F>
+__device__ __forceinline__ void for_logical(const StepArgs<real>& a, const Inst<real>& I, const bool per[3], real x,
+                                            real y, real z, F&& visit) {
+    const int bx = axis_bin(x, I.lo[0], I.inv_wl[0], I.nl[0]), by = axis_bin(y, I.lo[1], I.inv_wl[1], I.nl[1]),
+              bz = axis_bin(z, I.lo[2], I.inv_wl[2], I.nl[2]);
+    int xa[2], xb[2];
+    const int nxr = x_ranges(bx, I.nl[0], per[0], xa, xb);
+    for (int r = 0; r < 9; ++r) {
+        int yy, zz;
+        if (!axis_nb(bz, r / 3 - 1, I.nl[2], per[2], zz)) continue;
+        if (!axis_nb(by, r % 3 - 1, I.nl[1], per[1], yy)) continue;
+        for (int f = 0; f < I.k[1] * I.k[2]; ++f) {
+            const int64_t row = I.cell_off + (int64_t)I.n[0] * row_of(I, yy * I.k[1] + f % I.k[1],
+                                                                      zz * I.k[2] + f / I.k[1]);
+            for (int q = 0; q < nxr; ++q)
+                visit((int32_t)(I.base + a.start[row + (int64_t)xa[q] * I.k[0]]),
+                      (int32_t)(I.base + a.start[row + (int64_t)(xb[q] + 1) * I.k[0]]));
+        }
+    }
+}
+
 // Records per chunk of a wave's staging buffer in LDS (the staged lane mode
 // of the FP32 search, search_staged): kStageCap quads (x, y, z, vx), then
 // kStageCap pairs (vy, vz) in 16-byte slots, so that one address serves
@@ -711,290 +768,636 @@ constexpr int kStageCap = 128;
 constexpr int kStageBytesPerWave = kStageCap * 32;
 static_assert(kStageBytesPerWave % 16 == 0, "each wave's buffer starts on a quad");
 
-// Closest-candidate search with register blocking: one lane owns up to G
-// consecutive records and tests every neighbour record it loads against all
-// of them, so a load serves up to G pair tests.  The lane walks the union of
-// its records' neighbourhoods row by row; record k only takes the records in
-// its own range of that row.  It serves the wave-uniform mode of both
-// precisions and the lane mode of FP64; the FP32 lane mode is search_staged.
-//
-// HALF (FP32): every unordered pair is tested once -- bins of larger index
-// and, in a record's own bin, the records after it -- and a candidate lowers
-// both particles' 64-bit keys (d_min^2 bits, partner record) with atomicMin,
-// which is order independent; exact ties of d_min^2 go to the lower record.
-// Ordered (FP64): each record scans its whole neighbourhood and keeps the
-// smallest d_min^2, ties to the lower id, with the reference's arithmetic, so
-// the choice does not depend on the order of records inside a bin.
-//
-// MIX (a diagnostic build, never the timed one) also counts the pairs the
-// step tests that approach (s0 < 0) and that meet criterion 1 (s0 < 0 < s1),
-// which fix the pair test's arithmetic per pair.
-template <typename real, bool HALF, int PM, int G, bool UNIFORM, bool MIX = false>
-__device__ __forceinline__ void search_group(const StepArgs<real>& a, const Inst<real>& I, int64_t base,
-                                             int32_t i0, int nrec, int32_t wave_first, int wave_ub,
-                                             double& tests, double& cand, uint32_t& n_s0, uint32_t& n_c1) {
-    const Geo<real> G_(I);
-    const int n[3] = {I.n[0], I.n[1], I.n[2]};
-    real xi[G], yi[G], zi[G], vxi[G], vyi[G], vzi[G];
-    int cxk[G];
-    int cy = 0, cz = 0;
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-        uint32_t idk, flk;
-        const int32_t ik = k < nrec ? i0 + k : i0;
-        Rec<real>::load(a.rec, ik, xi[k], yi[k], zi[k], idk, vxi[k], vyi[k], vzi[k], flk);
-        cxk[k] = axis_bin(xi[k], I.lo[0], I.inv_w[0], I.n[0]);
-        if (k == 0) {
-            cy = axis_bin(yi[0], I.lo[1], I.inv_w[1], I.n[1]);
-            cz = axis_bin(zi[0], I.lo[2], I.inv_w[2], I.n[2]);
-        }
-    }
-    if constexpr (UNIFORM) {
-        // Same row for the whole wave (checked by the caller).
-        cy = __builtin_amdgcn_readfirstlane(cy);
-        cz = __builtin_amdgcn_readfirstlane(cz);
-    }
-    // The records share a row (y, z bins) and single x-ranges?  Otherwise
-    // search them one at a time.
-    bool joint = true;
-    int xa[G], xb[G];
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-        int ta[2], tb[2];
-        const int nr = x_ranges(cxk[k], n[0], G_.per[0], ta, tb);
-        xa[k] = ta[0];
-        xb[k] = tb[0];
-        if (k < nrec) {
-            joint &= nr == 1;
-            if (k > 0) {
-                joint &= axis_bin(yi[k], I.lo[1], I.inv_w[1], I.n[1]) == cy;
-                joint &= axis_bin(zi[k], I.lo[2], I.inv_w[2], I.n[2]) == cz;
-            }
-        }
-    }
-    unsigned long long mine[G];
-    int32_t bj[G];
-    real bd2[G];
-    uint32_t bid[G];
-    int32_t seen = 0, nc = 0;
-#pragma unroll
-    for (int k = 0; k < G; ++k) { mine[k] = ~0ull; bj[k] = -1; bd2[k] = real(0); bid[k] = 0; }
+// Exact test of the pair of records (i, j): whether it is a candidate, and
+// its ranking value (criterion 3) if so.  Every search path ends here, so
+// the pairs it accepts and their values are the same whichever found them.
+template <typename real>
+__device__ __forceinline__ bool test_pair(const Geo<real>& G, bool by_time, real xi, real yi, real zi, real vxi,
+                                          real vyi, real vzi, real xj, real yj, real zj, real vxj, real vyj, real vzj,
+                                          real& value) {
+    Screen<real> S;
+    if (!PairTest<real, -1>::stage1(G, xi, yi, zi, vxi, vyi, vzi, xj, yj, zj, vxj, vyj, vzj, S)) return false;
+    if (!PairTest<real, -1>::stage2(G, S)) return false;
+    const real d2 = PairTest<real, -1>::finish(G, S);
+    if (!(d2 >= real(0))) return false;
+    value = by_time ? PairTest<real, -1>::contact(G, S) : d2;
+    return true;
+}
 
-    // Bookkeeping of a pair that passed both screening stages (rare).  The
-    // ranking key of criterion 3 is d_min^2, or with TPKMC_RANK_TIME the
-    // first contact time.
-    const bool by_time = (I.flags & TPKMC_RANK_TIME) != 0;
-    auto hit = [&](int k, int32_t j, uint32_t idj, const Screen<real>& S) {
-        const real d2 = PairTest<real, PM>::finish(G_, S);
-        if (d2 >= real(0)) {
-            ++nc;
-            const real key = by_time ? PairTest<real, PM>::contact(G_, S) : d2;
-            if constexpr (HALF) {
-                const unsigned long long hi = (unsigned long long)sortable((float)key) << 32;
-                atomicMin(a.bkey + j, hi | (uint32_t)(i0 + k));
-                const unsigned long long kk = hi | (uint32_t)j;
-                mine[k] = kk < mine[k] ? kk : mine[k];
-            } else {
-                if (bj[k] < 0 || key < bd2[k] || (key == bd2[k] && idj < bid[k])) {
-                    bj[k] = j; bd2[k] = key; bid[k] = idj;
-                }
-            }
-        }
-    };
-    // Tests record j (loaded) against the lane's records k with take[k] set.
-    auto screen = [&](int32_t j, uint32_t idj, real xj, real yj, real zj, real vxj, real vyj, real vzj,
-                      const bool take[G]) {
-        Screen<real> S[G];
-        bool p1[G];
-        bool any1 = false;
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            // Evaluated on every lane, masked afterwards: no branch.
-            p1[k] = PairTest<real, PM>::stage1(G_, xi[k], yi[k], zi[k], vxi[k], vyi[k], vzi[k], xj, yj, zj, vxj,
-                                                vyj, vzj, S[k]) & take[k];
-            any1 |= p1[k];
-            if constexpr (MIX) {
-                n_s0 += (take[k] && S[k].s0 < real(0)) ? 1u : 0u;
-                n_c1 += p1[k] ? 1u : 0u;
-            }
-        }
-        if (__builtin_amdgcn_ballot_w64(any1) == 0) return;
-        bool p2[G];
-        bool any2 = false;
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            p2[k] = p1[k] && PairTest<real, PM>::stage2(G_, S[k]);
-            any2 |= p2[k];
-        }
-        if (!any2) return;
-#pragma unroll
-        for (int k = 0; k < G; ++k)
-            if (p2[k]) hit(k, j, idj, S[k]);
-    };
-    auto visit = [&](int32_t j, const bool take[G]) {
-        real xj, yj, zj, vxj, vyj, vzj;
-        uint32_t idj = 0;
-        if constexpr (UNIFORM) {
-            RecU<real>::load(a.rec, j, xj, yj, zj, idj, vxj, vyj, vzj);
-        } else if constexpr (HALF) {
-            // FP32 keys carry the record index, not the id: skip that word.
-            Rec<float>::load6(a.rec, (uint32_t)j, xj, yj, zj, vxj, vyj, vzj);
-        } else {
-            uint32_t flj;
-            Rec<real>::load(a.rec, j, xj, yj, zj, idj, vxj, vyj, vzj, flj);
-        }
-        screen(j, idj, xj, yj, zj, vxj, vyj, vzj, take);
-    };
+// ---------------------------------------------------------------- tile search
+// Half search of 64 consecutive records against their neighbourhood, 32 x 32
+// pairs at a time on the matrix units.  With u the relative velocity and r
+// the relative position of a pair, a candidate meets
+//     s0 = r.u < 0,   -(s0 + |u|^2 dt) < 0   (criterion 1), and
+//     |r|^2 - |u|^2 dt^2 - D^2 <= 0          (d_min <= D with t_poca < dt:
+//                                             |r|^2 = d_min^2 + |u|^2 t_poca^2),
+// and all three are bilinear in per-record vectors, so one K = 16 product
+// each (v_mfma_f32_32x32x16_f16) evaluates them for 1024 pairs.  The vectors
+// are rounded to f16 relative to the tile (positions in units of the c-bin
+// width, velocities of 1 / kTileKappa widths per step), and each form is
+// lowered by a bound of its rounding error that is bilinear too, so a pair
+// whose three forms are not all negative is certainly no candidate.  The
+// others, about one in a hundred, go through a queue in LDS to the exact test
+// in the state's own precision (test_pair), which alone decides: the filter
+// never changes a result.
+//
+// Per pair this takes two vector instructions (an AND of the three signs and
+// a shift into a mask) instead of 16 to 30, and no memory access: a lane
+// holds a whole record, and v_permlane32_swap turns 64 records' vectors into
+// the operands of two 32-record tiles.  Measured against the scan it
+// replaced, one lane per record with scalar or gathered loads (search phase):
+// FP64 Sod tube of 4e5 particles on 100 c-bins 19.8 -> 0.12 ms, FP64 blast of
+// 2e6 on 64^3 1.06 -> 0.39, FP32 Noh implosion of 8e6 2.1 -> 1.35, 64
+// instances of 3.4e7 particles in all 16.4 -> 9.8, and 2000 particles in
+// FP64 0.61 -> 0.05.
+//
+// Vector of a record (k = 0..15), j's side:
+//   x y z | vx vy vz | p_hi p_lo | q_hi q_lo | r_hi r_lo | 1 1 | Xm | V1
+// with Xm the largest |coordinate|, V1 the sum of |velocity| components and
+// p, q, r the record's own terms of the three forms, each as two f16.  i's
+// side holds the factors of the same slots, one vector per form.
+//
+// Error bounds, e = 2^-11 (f16 rounding), sums over both records:
+//   r.u:    at most 2e (Xm_i + Xm_j)(V1_i + V1_j) from the rounded vectors,
+//           e Xm V1 from the factor x + 2 v / kappa, the rest (products
+//           summed in FP32, the split terms) below 2^-18 of the same product;
+//           kTileE2 = 3.5e covers them;
+//   |u|^2:  2e V1^2 / kappa and the factor's rounding: kTileE3 = 5e / kappa;
+//   |r|^2:  2e 3 (Xm_i + Xm_j)^2: kTileE6 = 6.6e per ordered product;
+// plus kTileAbs (1 + Xm + V1) for f16 subnormals (2^-25 each).
+constexpr float kTileKappa = 256.0f;
+constexpr float kTileHalfUlp = 1.0f / 2048.0f;
+constexpr float kTileE2 = 3.5f * kTileHalfUlp;
+constexpr float kTileE3 = 5.0f * kTileHalfUlp / kTileKappa;
+constexpr float kTileE6 = 6.6f * kTileHalfUlp;
+constexpr float kTileAbs = 1e-6f;
+// A record outside these (or outside the box along a periodic axis) takes
+// part with forms that are negative against every partner ("wild").
+constexpr float kTileXMax = 64.0f;
+constexpr float kTileVMax = 512.0f;
+constexpr float kTileWild = -50000.0f;  // below minus any tame record's own terms
+constexpr float kTileNever = 60000.0f;  // above them: lanes without a record
 
-    if (UNIFORM || joint) {
-        // UNIFORM: every lane of the wave shares the row and walks the union
-        // of the wave's ranges (first record's lower end, wave_ub upper end)
-        // in lock-step, so j is the same in all lanes.
-        const int own_row = row_of(I, cy, cz);
-        const int ua = UNIFORM ? __builtin_amdgcn_readfirstlane(x_lo_of(wave_first, a, I, n[0], G_.per[0])) : xa[0];
-        int ub = xb[0];
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float acc16_t __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ uint32_t pack2(_Float16 a, _Float16 b) {
+    const half2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+__device__ __forceinline__ uint32_t split_f16(float v) {
+    const _Float16 hi = (_Float16)v;
+    return pack2(hi, (_Float16)(v - (float)hi));
+}
+
+// f16 not below v >= 0 (v is at most a few hundred).
+__device__ __forceinline__ _Float16 up_f16(float v) { return (_Float16)fmaf(v, 1.0f + 2.0f * kTileHalfUlp, 1e-7f); }
+
+// The rounded vector of one record and its own terms of the three forms.
+struct TileRec {
+    _Float16 x[3], v[3];
+    float xm, v1;
+    float p, q, r;
+};
+
+// X: position relative to the tile in c-bin widths, xabs: bound of its
+// absolute error in units of e; V: velocity relative to the tile's, scaled;
+// hd2: half of D^2 in widths^2.  absent: no record here.
+__device__ __forceinline__ TileRec tile_rec(const float X[3], const float V[3], float xabs, float hd2, bool wild,
+                                            bool absent) {
+    TileRec T;
 #pragma unroll
-        for (int k = 1; k < G; ++k)
-            if (k < nrec) ub = xb[k];
-        if (UNIFORM) ub = wave_ub;
-        for (int rr = 0; rr < 9; ++rr) {
-            int y, z;
-            if (!axis_nb(cz, rr / 3 - 1, n[2], G_.per[2], z)) continue;
-            if (!axis_nb(cy, rr % 3 - 1, n[1], G_.per[1], y)) continue;
-            const int row_idx = row_of(I, y, z);
-            if (HALF && row_idx < own_row) continue;
-            const bool own = HALF && row_idx == own_row;
-            const int64_t row = I.cell_off + (int64_t)n[0] * row_idx;
-            int32_t lo[G], hi[G];
+    for (int k = 0; k < 3; ++k) {
+        T.x[k] = (_Float16)X[k];
+        T.v[k] = (_Float16)V[k];
+    }
+    T.xm = fmaxf(fmaxf(fabsf(X[0]), fabsf(X[1])), fabsf(X[2])) + xabs;
+    T.v1 = fabsf(V[0]) + fabsf(V[1]) + fabsf(V[2]);
+    const float x = (float)T.x[0], y = (float)T.x[1], z = (float)T.x[2];
+    const float a = (float)T.v[0], b = (float)T.v[1], c = (float)T.v[2];
+    const float xv = fmaf(z, c, fmaf(y, b, x * a));
+    const float vv = fmaf(c, c, fmaf(b, b, a * a));
+    const float xx = fmaf(z, z, fmaf(y, y, x * x));
+    const float lin = fmaf(kTileAbs, T.xm + T.v1, kTileAbs);
+    const float m = fmaf(kTileE2 * T.xm, T.v1, lin);
+    T.p = xv - m;
+    T.q = fmaf(-1.0f / kTileKappa, vv, -xv) - fmaf(kTileE3 * T.v1, T.v1, m);
+    // |u|^2 <= 2 |v_i|^2 + 2 |v_j|^2, with a margin for the rounded v.
+    T.r = xx - fmaf(2.01f / (kTileKappa * kTileKappa), vv, hd2) - fmaf(kTileE6 * T.xm, T.xm, lin);
+    if (wild || absent) {
 #pragma unroll
-            for (int k = 0; k < G; ++k) {
-                lo[k] = own ? i0 + k + 1 : (int32_t)(base + a.start[row + xa[k]]);
-                hi[k] = (int32_t)(base + a.start[row + xb[k] + 1]);
-                if (k >= nrec || hi[k] < lo[k]) { lo[k] = 0; hi[k] = 0; }
-                seen += hi[k] > lo[k] ? hi[k] - lo[k] : 0;
-            }
-            int32_t u0 = own ? (UNIFORM ? wave_first : i0) + 1 : (int32_t)(base + a.start[row + ua]);
-            int32_t u1 = (int32_t)(base + a.start[row + ub + 1]);
-            int32_t jm = u0;  // from jm on, the range masks need no test
-            bool split = false;
-            if constexpr (UNIFORM) {
-                u0 = __builtin_amdgcn_readfirstlane(u0);
-                u1 = __builtin_amdgcn_readfirstlane(u1);
-                // When every non-empty range ends at u1, all of them are open
-                // from the largest lower end on, which the last lane holds
-                // (records are in c-bin order); checked for every lane.
-                int32_t lo_last = lo[0];
+        for (int k = 0; k < 3; ++k) T.x[k] = T.v[k] = (_Float16)0.0f;
+        T.xm = T.v1 = 0.0f;
+        T.p = T.q = T.r = absent ? kTileNever : kTileWild;
+    }
+    return T;
+}
+
+// Operands of two 32-record tiles from the lanes' 16-vectors w (packed in
+// pairs): tile 0 holds lanes 0..31's records, tile 1 lanes 32..63's; each
+// lane gets the 8 values its half of the wave supplies (k = 0..7 or 8..15).
+__device__ __forceinline__ void tile_operands(const uint32_t w[8], half8_t out[2]) {
+    uint32_t t0[4], t1[4];
 #pragma unroll
-                for (int k = 1; k < G; ++k)
-                    if (k < nrec) lo_last = lo[k];
-                const int last = 63 - __clzll((long long)__ballot(true));
-                jm = __builtin_amdgcn_readlane(lo_last, last);
-                bool open = true;
-#pragma unroll
-                for (int k = 0; k < G; ++k) open &= hi[k] <= lo[k] || (hi[k] == u1 && lo[k] <= jm);
-                split = __ballot(!open) == 0 && jm >= u0 && jm <= u1;
-            }
-            const int32_t um = split ? jm : u1;
-            for (int32_t j = u0; j < um; ++j) {
-                bool take[G];
-#pragma unroll
-                for (int k = 0; k < G; ++k) take[k] = (uint32_t)(j - lo[k]) < (uint32_t)(hi[k] - lo[k]);
-                visit(j, take);
-            }
-            if (split) {  // wave-uniform
-                bool take[G];
-#pragma unroll
-                for (int k = 0; k < G; ++k) take[k] = hi[k] > lo[k];
-                int32_t j = jm;
-                if constexpr (G == 1) {
-                    // Two neighbours per iteration, one vote: the second's
-                    // loads are in flight with the first's, as a second
-                    // record per lane would do for G = 2.
-                    for (; j + 1 < u1; j += 2) {
-                        real xa_, ya_, za_, vxa, vya, vza, xb_, yb_, zb_, vxb, vyb, vzb;
-                        uint32_t ida, idb;
-                        RecU<real>::load(a.rec, j, xa_, ya_, za_, ida, vxa, vya, vza);
-                        RecU<real>::load(a.rec, j + 1, xb_, yb_, zb_, idb, vxb, vyb, vzb);
-                        Screen<real> SA, SB;
-                        const bool pa = PairTest<real, PM>::stage1(G_, xi[0], yi[0], zi[0], vxi[0], vyi[0], vzi[0],
-                                                                   xa_, ya_, za_, vxa, vya, vza, SA) & take[0];
-                        const bool pb = PairTest<real, PM>::stage1(G_, xi[0], yi[0], zi[0], vxi[0], vyi[0], vzi[0],
-                                                                   xb_, yb_, zb_, vxb, vyb, vzb, SB) & take[0];
-                        if constexpr (MIX) {
-                            n_s0 += (take[0] && SA.s0 < real(0)) ? 1u : 0u;
-                            n_s0 += (take[0] && SB.s0 < real(0)) ? 1u : 0u;
-                            n_c1 += (pa ? 1u : 0u) + (pb ? 1u : 0u);
-                        }
-                        if (__builtin_amdgcn_ballot_w64(pa | pb) == 0) continue;
-                        if (pa && PairTest<real, PM>::stage2(G_, SA)) hit(0, j, ida, SA);
-                        if (pb && PairTest<real, PM>::stage2(G_, SB)) hit(0, j + 1, idb, SB);
-                    }
-                }
-                for (; j < u1; ++j) visit(j, take);
-            }
-        }
+    for (int k = 0; k < 4; ++k) {
+        const auto s = __builtin_amdgcn_permlane32_swap(w[k], w[4 + k], false, false);
+        t0[k] = s[0];
+        t1[k] = s[1];
+    }
+    out[0] = __builtin_bit_cast(half8_t, *reinterpret_cast<uint4*>(t0));
+    out[1] = __builtin_bit_cast(half8_t, *reinterpret_cast<uint4*>(t1));
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_movef(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// Sum (or maximum) of a float over the 64 lanes, as wave_reduce.
+template <bool MAX>
+__device__ __forceinline__ float wave_reducef(float v) {
+    auto op = [](float x, float y) { return MAX ? fmaxf(x, y) : x + y; };
+    v = op(v, dpp_movef<kQuadXor1>(v));
+    v = op(v, dpp_movef<kQuadXor2>(v));
+    v = op(v, dpp_movef<kRowRor4>(v));
+    v = op(v, dpp_movef<kRowRor8>(v));
+    auto at = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+    return op(op(at(0), at(16)), op(at(32), at(48)));
+}
+
+// Per-wave LDS of the tile search: pairs that passed the filter (x = i's
+// lane | code << 6, y = record j), the records of the i tile and their keys,
+// and the records of the j block.
+constexpr int kHitQueue = 128;
+template <typename real>
+struct TileLds {
+    uint2 hit[kHitQueue];
+    unsigned long long key[kWave];
+    real pv[6][kWave];
+    uint2 blk[kWave];  // x: record, y: its image (2 bits per axis, shift + 1)
+};
+// Image code of a hit: 2 bits per axis, the box's shift + 1 at which j was
+// met, 3 where any will do; bit 6: the x axis goes by image (a periodic axis
+// of at most three c-bins, all of them neighbours), not by c-bin.
+constexpr uint32_t kCodeAny = 3u, kCodeImagedX = 1u << 6;
+
+// Periodic axes of so few c-bins that the c-bins do not fix which image of a
+// neighbour is the near one: the images are visited one by one ("imaged"),
+// and a pair is taken at the one the pair test's minimum-image rule picks.
+// With four c-bins only pairs half a box apart, from edge to edge of their
+// c-bins, are open; records that close to an edge are wild.
+__device__ __forceinline__ int image_of(double r, double, double halfL, double) {
+    return r > halfL ? 1 : (r < -halfL ? -1 : 0);
+}
+__device__ __forceinline__ int image_of(float r, float, float, float invL) {
+    const float k = rintf(r * invL);
+    return k > 0.0f ? 1 : (k < 0.0f ? -1 : 0);
+}
+
+// Exact tests of `count` queued pairs, one per lane.
+template <typename real>
+__device__ __forceinline__ void tile_hits(const StepArgs<real>& a, const Inst<real>& I, const Geo<real>& G,
+                                          bool by_time, int32_t wbase, TileLds<real>& L, int count, int lane,
+                                          int32_t& nc) {
+    if (lane >= count) return;
+    const uint2 e = L.hit[lane];
+    const int il = (int)(e.x & 63u);
+    const int32_t i = wbase + il, j = (int32_t)e.y;
+    real xj, yj, zj, vxj, vyj, vzj;
+    load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
+    const unsigned long long kj = key_now(a, j);
+    const real xi = L.pv[0][il], yi = L.pv[1][il], zi = L.pv[2][il];
+    const uint32_t code = e.x >> 6;
+    const real r[3] = {xi - xj, yi - yj, zi - zj};
+    if (code & kCodeImagedX) {
+        const uint32_t c = code & 3u;
+        if (c != kCodeAny && image_of(r[0], G.L[0], G.halfL[0], G.invL[0]) != (int)c - 1) return;
     } else {
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            if (k >= nrec) continue;
-            const int32_t ik = i0 + k;
-            for_neighbourhood<HALF>(a.start, I, base, n, G_.per, cxk[k], cy_of(yi[k], I), cz_of(zi[k], I),
-                                    ik, [&](int32_t j0, int32_t j1) {
-                seen += j1 > j0 ? j1 - j0 : 0;
-                for (int32_t j = j0; j < j1; ++j) {
-                    bool take[G];
-#pragma unroll
-                    for (int kk = 0; kk < G; ++kk) take[kk] = kk == k;
-                    visit(j, take);
-                }
-            });
-        }
+        // The tile's x range is wider than i's own: neighbouring c-bins only.
+        const int bi = axis_bin(xi, I.lo[0], I.inv_wl[0], I.nl[0]), bj = axis_bin(xj, I.lo[0], I.inv_wl[0], I.nl[0]);
+        const int d = bj + ((int)(code & 3u) - 1) * I.nl[0] - bi;
+        if (d < -1 || d > 1) return;
     }
-    if constexpr (!HALF) {
-        // Split c-bins: ordered scans also take the fast particles of each
-        // record's configured neighbourhood (binned apart from the slow ones).
-        if (I.flags & kSplit) {
-            const int nc[3] = {I.ncfg[0], I.ncfg[1], I.ncfg[2]};
 #pragma unroll
-            for (int k = 0; k < G; ++k) {
-                if (k >= nrec) continue;
-                const int ccx = axis_bin(xi[k], I.lo[0], I.inv_wc[0], nc[0]);
-                const int ccy = axis_bin(yi[k], I.lo[1], I.inv_wc[1], nc[1]);
-                const int ccz = axis_bin(zi[k], I.lo[2], I.inv_wc[2], nc[2]);
-                for_neighbourhood<false, true>(a.start, I, base, nc, G_.per, ccx, ccy, ccz, i0 + k,
-                                               [&](int32_t j0, int32_t j1) {
-                    seen += j1 > j0 ? j1 - j0 : 0;
-                    for (int32_t j = j0; j < j1; ++j) {
-                        bool take[G];
+    for (int ax = 1; ax < 3; ++ax) {
+        const uint32_t c = (code >> (2 * ax)) & 3u;
+        if (c != kCodeAny && image_of(r[ax], G.L[ax], G.halfL[ax], G.invL[ax]) != (int)c - 1) return;
+    }
+    real value;
+    if (!test_pair(G, by_time, xi, yi, zi, L.pv[3][il], L.pv[4][il], L.pv[5][il], xj, yj, zj, vxj, vyj, vzj, value))
+        return;
+    ++nc;
+    Key<real>::lower(a, j, Key<real>::make(value, (uint32_t)i), kj);
+    const unsigned long long k = Key<real>::make(value, (uint32_t)j);
+    const unsigned long long old = atomicMin(&L.key[il], k);
+    Key<real>::tied(a, i, old, k);
+}
+
+// One periodic or bounded axis of a group's neighbourhood: the sort cells
+// [first, first + count) to visit, unwrapped, times `images` images.
+struct TileAxis {
+    int first, count, images;
+};
+
+// c: the group's sort cell (its lowest, chi its highest); m: cells that a
+// candidate can be away (sub-grids), at least 1.
+template <typename real>
+__device__ __forceinline__ TileAxis tile_axis(const Inst<real>& I, int ax, bool periodic, int c, int chi, int m) {
+    const int n = I.n[ax], nl = I.nl[ax], k = I.k[ax];
+    TileAxis A;
+    const bool near = 2 * ((int64_t)m + 1) < n;  // the nearest image is known
+    A.images = periodic && nl <= 3 && !near ? 3 : 1;
+    if (A.images == 3) {
+        A.first = 0;
+        A.count = n;
+        return A;
+    }
+    int lo = c - m, hi = chi + m;
+    if (!periodic || nl > 3) {
+        lo = max(lo, (c / k - 1) * k);
+        hi = min(hi, (chi / k + 2) * k - 1);
+    }
+    if (!periodic) {
+        lo = max(lo, 0);
+        hi = min(hi, n - 1);
+    }
+    A.first = lo;
+    A.count = hi - lo + 1;
+    return A;
+}
+
+// Called by every lane of a wave holding a live slow record: the records
+// wbase .. wbase + 63 before `stop`, against part `part` of `parts` of their
+// neighbourhood.
+template <typename real>
+__device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32_t wbase, int32_t stop, int part,
+                             int parts, TileLds<real>& L, double& cand) {
+    const Geo<real> G(I);
+    const int lane = (int)(threadIdx.x & 63);
+    const int n[3] = {I.n[0], I.n[1], I.n[2]};
+    const int32_t base = (int32_t)I.base;
+    const int64_t cell_off = I.cell_off;
+    const bool by_time = (I.flags & TPKMC_RANK_TIME) != 0;
+    const bool sub = (I.flags & kSubgrid) != 0;
+    const int32_t i = wbase + lane;
+    const bool valid = i < stop;
+    real pi[3], vi[3];
+    load_pv(a.rec, valid ? i : wbase, pi[0], pi[1], pi[2], vi[0], vi[1], vi[2]);
 #pragma unroll
-                        for (int kk = 0; kk < G; ++kk) take[kk] = kk == k;
-                        real xj, yj, zj, vxj, vyj, vzj;
-                        uint32_t idj, flj;
-                        Rec<real>::load(a.rec, j, xj, yj, zj, idj, vxj, vyj, vzj, flj);
-                        screen(j, idj, xj, yj, zj, vxj, vyj, vzj, take);
+    for (int ax = 0; ax < 3; ++ax) {
+        L.pv[ax][lane] = pi[ax];
+        L.pv[3 + ax][lane] = vi[ax];
+    }
+    L.key[lane] = ~0ull;
+    const int cx = sort_bin(I, 0, pi[0]), cy = sort_bin(I, 1, pi[1]), cz = sort_bin(I, 2, pi[2]);
+    const int own_row = row_of(I, cy, cz);
+    const real sx = (real)I.tile_s;
+    const real sv = I.dt * sx * (real)kTileKappa;
+    // At most 30000: beyond, D spans every tame pair.
+    const float hd2 = fminf(0.5001f * (float)(I.D2 * sx * sx), 30000.0f);
+    const real lo[3] = {I.lo[0], I.lo[1], I.lo[2]}, hi[3] = {I.hi[0], I.hi[1], I.hi[2]};
+    const real iw[3] = {I.inv_w[0], I.inv_w[1], I.inv_w[2]};
+    const real iwl[3] = {I.inv_wl[0], I.inv_wl[1], I.inv_wl[2]};
+    const bool four[3] = {G.per[0] && I.nl[0] == 4, G.per[1] && I.nl[1] == 4, G.per[2] && I.nl[2] == 4};
+    auto untame = [&](const real p[3], const float X[3], const float V[3], float vcap) {
+        const float xm = fmaxf(fmaxf(fabsf(X[0]), fabsf(X[1])), fabsf(X[2]));
+        bool w = !(xm <= kTileXMax && fabsf(V[0]) + fabsf(V[1]) + fabsf(V[2]) <= vcap);
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            w |= G.per[ax] && !(p[ax] >= lo[ax] && p[ax] < hi[ax]);
+            if (four[ax]) {
+                const real t = (p[ax] - lo[ax]) * iwl[ax], f = t - floor(t);
+                w |= !(f > real(1e-4) && f < real(1.0 - 1e-4));
+            }
+        }
+        return w;
+    };
+    int32_t nc = 0;
+    int nq = 0;  // queued hits (wave-uniform)
+    uint64_t pending = __ballot(valid);
+    while (pending) {
+        // One group of lanes per row of sort cells: consecutive lanes with
+        // non-decreasing x cells.
+        const int lead = __ffsll((long long)pending) - 1;
+        const int R = __builtin_amdgcn_readlane(own_row, lead);
+        const bool in = valid && own_row == R;
+        const uint64_t gm = __ballot(in);
+        pending &= ~gm;
+        const int last = 63 - __clzll((long long)gm);
+        const int gcy = __builtin_amdgcn_readlane(cy, lead), gcz = __builtin_amdgcn_readlane(cz, lead);
+        const int cxf = __builtin_amdgcn_readlane(cx, lead), cxl = __builtin_amdgcn_readlane(cx, last);
+        const int32_t after = wbase + lead;  // partners come after the first record (half search)
+        // Tile origin: the middle of the group's cells; its mean velocity.
+        real org[3], Ls[3], vo[3];
+        float xabs = 0.0f;  // rounding of the scaled origins, in units of e
+        const float inv = 1.0f / (float)__popcll(gm);
+        const real mid[3] = {real(0.5) * (real)(cxf + cxl + 1), real(0.5) + (real)gcy, real(0.5) + (real)gcz};
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            org[ax] = (lo[ax] + mid[ax] / iw[ax]) * sx;
+            Ls[ax] = G.L[ax] * sx;
+            vo[ax] = (real)(wave_reducef<false>(in ? (float)(vi[ax] * sv) : 0.0f) * inv);
+            const float big = fabsf((float)org[ax]) + (G.per[ax] ? (float)Ls[ax] : 0.0f);
+            xabs = fmaxf(xabs, big * (sizeof(real) == 4 ? 1.0f / 1024.0f : 1e-9f));
+        }
+        const bool coarse = !(xabs <= 16.0f);  // coordinates too coarse for the filter: all wild
+        half8_t BP[2], BQ[2], BR[2];
+        uint64_t wild_i;
+        float vmax;
+        {
+            float X[3], V[3];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                X[ax] = (float)fma(pi[ax], sx, -org[ax]);
+                V[ax] = (float)fma(vi[ax], sv, -vo[ax]);
+            }
+            const bool wild = coarse || untame(pi, X, V, kTileVMax);
+            wild_i = __ballot(in && wild);
+            const TileRec T = tile_rec(X, V, xabs, hd2, wild, !in);
+            vmax = wave_reducef<true>(T.v1);
+            const _Float16 one = (_Float16)1.0f, nul = (_Float16)0.0f;
+            const _Float16 mv = -up_f16(kTileE2 * T.v1), mx = -up_f16(kTileE2 * T.xm);
+            const uint32_t wp[8] = {pack2(-T.v[0], -T.v[1]), pack2(-T.v[2], -T.x[0]), pack2(-T.x[1], -T.x[2]),
+                                    pack2(one, one), 0u, 0u, split_f16(T.p), pack2(mv, mx)};
+            tile_operands(wp, BP);
+            constexpr float k2 = 2.0f / kTileKappa;
+            const _Float16 f0 = (_Float16)fmaf(k2, (float)T.v[0], (float)T.x[0]);
+            const _Float16 f1 = (_Float16)fmaf(k2, (float)T.v[1], (float)T.x[1]);
+            const _Float16 f2 = (_Float16)fmaf(k2, (float)T.v[2], (float)T.x[2]);
+            const _Float16 mq = -up_f16(fmaf(kTileE2, T.xm, 2.0f * kTileE3 * T.v1));
+            const uint32_t wq[8] = {pack2(T.v[0], T.v[1]), pack2(T.v[2], f0), pack2(f1, f2), 0u,
+                                    pack2(one, one), 0u, split_f16(T.q), pack2(mv, mq)};
+            tile_operands(wq, BQ);
+            const _Float16 two = (_Float16)-2.0f;
+            const uint32_t wr[8] = {pack2(two * T.x[0], two * T.x[1]), pack2(two * T.x[2], nul), 0u, 0u, 0u,
+                                    pack2(one, one), split_f16(T.r), pack2(-up_f16(2.0f * kTileE6 * T.xm), nul)};
+            tile_operands(wr, BR);
+        }
+        // How far apart a candidate pair of this group can start: with
+        // sub-grids from the group's and the instance's largest speeds, so
+        // that a pair's own image is always visited.  Without, only images
+        // other than the unshifted one are skipped, by a bound for partners
+        // up to vcap; faster ones are wild, and wild pairs are taken
+        // unshifted.
+        real reach = real(INFINITY);
+        int m[3] = {1 << 24, 1 << 24, 1 << 24};
+        if (sub) {
+            const float v = in ? (float)sqrt(vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2]) : 0.0f;
+            reach = (sqrt(I.D2) + ((real)wave_reducef<true>(v) + I.vreach) * I.dt) * real(1.001);
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                const real c = reach * iw[ax] + real(1e-3) + real(1e-6) * (real)n[ax];
+                m[ax] = c < (real)(1 << 24) ? 1 + (int)c : 1 << 24;
+            }
+        }
+        const TileAxis AX = tile_axis(I, 0, G.per[0], cxf, cxl, m[0]);
+        const TileAxis AY = tile_axis(I, 1, G.per[1], gcy, gcy, m[1]);
+        const TileAxis AZ = tile_axis(I, 2, G.per[2], gcz, gcz, m[2]);
+        float vcap = kTileVMax;
+        real reach_im = reach;
+        if (!sub && AX.images * AY.images * AZ.images > 1) {
+            vcap = fminf(kTileVMax, 2.0f * vmax + 1e-3f);
+            const float uu = (vmax + vcap) * (1.01f / kTileKappa);
+            if (!wild_i) reach_im = (real)(1.001f * sqrtf(fmaf(uu, uu, 2.0f * hd2))) / sx;
+        }
+        // Along x: the images of a whole row, or the part of the range inside
+        // the box and the parts wrapped at its lower and upper end.
+        const int xend = AX.first + AX.count;  // exclusive, unwrapped
+        const bool lw = AX.images == 1 && AX.first < 0, rw = AX.images == 1 && xend > n[0];
+        const int nx = AX.images == 3 ? 3 : 1 + (lw ? 1 : 0) + (rw ? 1 : 0);
+        const int ny = AY.count * AY.images, nz = AZ.count * AZ.images;
+        const uint32_t any_mask = (AY.images == 1 ? kCodeAny << 2 : 0u) | (AZ.images == 1 ? kCodeAny << 4 : 0u) |
+                                  (G.per[0] && I.nl[0] <= 3 ? kCodeImagedX : 0u);
+        const uint32_t wild_mask = sub ? 0u : (kCodeAny << 2) | (kCodeAny << 4) | (AX.images == 3 ? kCodeAny : 0u);
+        const int64_t total = (int64_t)nx * ny * nz;
+        for (int64_t t0 = 0; t0 < total; t0 += kWave) {
+            // One part of the neighbourhood per lane: a run of records, or
+            // none where it is out of reach.
+            int32_t u0 = 0, len = 0;
+            uint32_t shw = 0;
+            if (t0 + lane < total) {
+                const uint32_t t = (uint32_t)(t0 + lane);
+                const int s = (int)(t % (uint32_t)nx);
+                const int ty = (int)(t / (uint32_t)nx % (uint32_t)ny), tz = (int)(t / (uint32_t)nx / (uint32_t)ny);
+                int y = AY.first + ty % AY.count, z = AZ.first + tz % AZ.count;
+                int shy = 0, shz = 0, shx = 0;
+                if (AY.images == 3) shy = ty / AY.count - 1;
+                else if (y < 0) { y += n[1]; shy = -1; }
+                else if (y >= n[1]) { y -= n[1]; shy = 1; }
+                if (AZ.images == 3) shz = tz / AZ.count - 1;
+                else if (z < 0) { z += n[2]; shz = -1; }
+                else if (z >= n[2]) { z -= n[2]; shz = 1; }
+                int xa = max(AX.first, 0), xb = min(xend, n[0]) - 1;
+                if (AX.images == 3) shx = s - 1;
+                else if (s == 1 && lw) { shx = -1; xa = AX.first + n[0]; xb = n[0] - 1; }
+                else if (s >= 1) { shx = 1; xa = 0; xb = xend - n[0] - 1; }
+                xa = max(xa, 0);
+                xb = min(xb, n[0] - 1);
+                // Gap between the group's row and this one.
+                auto gap = [&](int ax, int d) {
+                    const real g = ((real)(abs(d) - 1) - real(1e-3) - real(1e-6) * (real)n[ax]) / iw[ax];
+                    return g > real(0) ? g : real(0);
+                };
+                const real gy = gap(1, y + shy * n[1] - gcy), gz = gap(2, z + shz * n[2] - gcz);
+                const int xl = xa + shx * n[0], xh = xb + shx * n[0];
+                const real gx = gap(0, xl > cxl ? xl - cxl : (xh < cxf ? cxf - xh : 0));
+                const bool shifted = (AX.images == 3 && shx != 0) || (AY.images == 3 && shy != 0) ||
+                                     (AZ.images == 3 && shz != 0);
+                const real rr = shifted ? reach_im : reach;
+                if (!(gx * gx + gy * gy + gz * gz > rr * rr)) {
+                    const int64_t row = cell_off + (int64_t)n[0] * row_of(I, y, z);
+                    u0 = max(base + a.start[row + xa], after + 1);
+                    len = max(base + a.start[row + xb + 1] - u0, 0);
+                    shw = (uint32_t)(shx + 1) | (uint32_t)(shy + 1) << 2 | (uint32_t)(shz + 1) << 4;
+                }
+            }
+            int32_t end = len;  // inclusive prefix of the lengths
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int32_t v = __shfl_up(end, o);
+                if (lane >= o) end += v;
+            }
+            const int32_t njs = __builtin_amdgcn_readlane(end, kWave - 1);
+            uint64_t runs = __ballot(len > 0);
+            // Blocks of 64 records taken from the runs in order.
+            int32_t jj = 0;
+            uint32_t jc = 0;
+            real pj[3], vj[3];
+            auto fetch = [&](int32_t b) {
+                jj = after;
+                while (runs) {
+                    const int v = __ffsll((long long)runs) - 1;
+                    const int32_t e1 = __builtin_amdgcn_readlane(end, v), l1 = __builtin_amdgcn_readlane(len, v);
+                    if (e1 - l1 >= b + kWave) break;
+                    const int32_t g = b + lane - (e1 - l1);
+                    const bool mine = g >= 0 && g < l1;
+                    const int32_t s = __builtin_amdgcn_readlane(u0, v);
+                    const uint32_t c1 = (uint32_t)__builtin_amdgcn_readlane((int)shw, v);
+                    jj = mine ? s + g : jj;
+                    jc = mine ? c1 : jc;
+                    if (e1 > b + kWave) break;  // goes on in the next block
+                    runs &= runs - 1;
+                }
+                load_pv(a.rec, jj, pj[0], pj[1], pj[2], vj[0], vj[1], vj[2]);
+            };
+            const int32_t step = parts * kWave;
+            if (part * kWave < njs) fetch(part * kWave);
+            for (int32_t b = part * kWave; b < njs; b += step) {
+                float X[3], V[3];
+                const uint32_t code = jc;
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) {
+                    real o = org[ax];
+                    if (G.per[ax]) o -= (real)((int)(code >> (2 * ax) & 3u) - 1) * Ls[ax];
+                    X[ax] = (float)fma(pj[ax], sx, -o);
+                    V[ax] = (float)fma(vj[ax], sv, -vo[ax]);
+                }
+                const bool absent = b + lane >= njs;
+                const bool wild = coarse || untame(pj, X, V, vcap);
+                const bool shifted = !sub && ((AX.images == 3 && (code & 3u) != 1u) ||
+                                              (AY.images == 3 && (code >> 2 & 3u) != 1u) ||
+                                              (AZ.images == 3 && (code >> 4 & 3u) != 1u));
+                const uint64_t wild_j = __ballot(wild && !absent);
+                const uint64_t shift_j = __ballot(shifted && !absent);
+                const TileRec T = tile_rec(X, V, xabs, hd2, wild, absent || (wild && shifted));
+                const _Float16 one = (_Float16)1.0f;
+                const uint32_t w[8] = {pack2(T.x[0], T.x[1]), pack2(T.x[2], T.v[0]), pack2(T.v[1], T.v[2]),
+                                       split_f16(T.p), split_f16(T.q), split_f16(T.r), pack2(one, one),
+                                       pack2(up_f16(T.xm), up_f16(T.v1))};
+                half8_t A[2];
+                tile_operands(w, A);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                L.blk[lane] = make_uint2((uint32_t)jj, code);
+                if (b + step < njs) fetch(b + step);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    if (b + 32 * c >= njs) continue;  // wave-uniform
+                    uint32_t W = 0;
+                    // The later tile's bits end up low: q = 1 first.
+#pragma unroll
+                    for (int q = 1; q >= 0; --q) {
+                        const acc16_t zero = {};
+                        const acc16_t P = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[c], BP[q], zero, 0, 0, 0);
+                        const acc16_t Qf = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[c], BQ[q], zero, 0, 0, 0);
+                        const acc16_t Rf = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[c], BR[q], zero, 0, 0, 0);
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int s = __float_as_int(P[r]) & __float_as_int(Qf[r]) & __float_as_int(Rf[r]);
+                            W = __builtin_amdgcn_alignbit(W, (uint32_t)s, 31);
+                        }
                     }
-                });
+                    // Bit b of W: i tile b >> 4, row r = 15 - (b & 15) of the
+                    // product's layout.
+                    while (__ballot(W != 0)) {
+                        const int bit = W ? __ffs((int)W) - 1 : 0;
+                        bool take = W != 0;
+                        W &= W - 1;
+                        const int r = 15 - (bit & 15);
+                        const int jl = 32 * c + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                        const int il = 32 * (bit >> 4) + (lane & 31);
+                        const uint2 e = L.blk[jl];
+                        take = take && (int32_t)e.x > wbase + il;
+                        uint32_t cd = e.y | any_mask;
+                        if (wild_i | wild_j) {
+                            const bool wi = (wild_i >> il) & 1ull, wj = (wild_j >> jl) & 1ull;
+                            take = take && !(wi && ((shift_j >> jl) & 1ull));
+                            cd = wi || wj ? cd | wild_mask : cd;
+                        }
+                        const uint64_t tm = __ballot(take);
+                        if (take)
+                            L.hit[nq + __popcll(tm & ((1ull << lane) - 1ull))] = make_uint2((uint32_t)il | cd << 6, e.x);
+                        nq += __popcll(tm);
+                        if (nq >= kWave) {
+                            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                            tile_hits(a, I, G, by_time, wbase, L, kWave, lane, nc);
+                            const bool mv = lane < nq - kWave;
+                            uint2 h = make_uint2(0u, 0u);
+                            if (mv) h = L.hit[kWave + lane];
+                            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                            if (mv) L.hit[lane] = h;
+                            nq -= kWave;
+                        }
+                    }
+                }
             }
         }
     }
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-        if (k >= nrec) continue;
-        if constexpr (HALF) {
-            if (mine[k] != ~0ull) atomicMin(a.bkey + i0 + k, mine[k]);
-        } else {
-            a.best[i0 + k] = bj[k];
+    if (nq > 0) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        tile_hits(a, I, G, by_time, wbase, L, nq, lane, nc);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const unsigned long long k = L.key[lane];
+    if (valid && k != ~0ull) Key<real>::lower(a, i, k, key_now(a, i));
+    cand = 2.0 * (double)nc;
+}
+
+// The unordered pairs of one c-bin with itself and with the neighbours of
+// larger index (the search's TPKMC_CNT_TESTS), from the sort cells' prefix.
+template <typename real>
+__device__ double cbin_tests(const StepArgs<real>& a, const Inst<real>& I, int c) {
+    const int nl[3] = {I.nl[0], I.nl[1], I.nl[2]}, k[3] = {I.k[0], I.k[1], I.k[2]};
+    const int x = c % nl[0], y = c / nl[0] % nl[1], z = c / nl[0] / nl[1];
+    // Records of the c-bins xa..xb of c-bin row (yy, zz).
+    auto records = [&](int xa, int xb, int yy, int zz) {
+        int32_t sum = 0;
+        for (int f = 0; f < k[1] * k[2]; ++f) {
+            const int64_t row =
+                I.cell_off + (int64_t)I.n[0] * row_of(I, yy * k[1] + f % k[1], zz * k[2] + f / k[1]);
+            sum += a.start[row + (int64_t)(xb + 1) * k[0]] - a.start[row + (int64_t)xa * k[0]];
+        }
+        return (double)sum;
+    };
+    const double own = records(x, x, y, z);
+    if (own == 0.0) return 0.0;
+    int xa[2], xb[2];
+    const int nxr = x_ranges(x, nl[0], I.bc[0] == TPKMC_BC_PERIODIC, xa, xb);
+    double other = 0.0;
+    for (int r = 0; r < 9; ++r) {
+        int yy, zz;
+        if (!axis_nb(z, r / 3 - 1, nl[2], I.bc[2] == TPKMC_BC_PERIODIC, zz)) continue;
+        if (!axis_nb(y, r % 3 - 1, nl[1], I.bc[1] == TPKMC_BC_PERIODIC, yy)) continue;
+        // Each pair of c-bins once: from the one of smaller plain index.
+        const int d = (yy + nl[1] * zz) - (y + nl[1] * z);
+        if (d < 0) continue;
+        for (int q = 0; q < nxr; ++q) {
+            const int a0 = d > 0 ? xa[q] : max(xa[q], x + 1);
+            if (a0 <= xb[q]) other += records(a0, xb[q], yy, zz);
         }
     }
-    // Ordered scans see every pair twice and count the record itself once.
-    tests = HALF ? (double)seen : 0.5 * (double)(seen - nrec);
-    cand = HALF ? 2.0 * (double)nc : (double)nc;
+    return own * (0.5 * (own - 1.0) + other);
+}
+
+// Plain half scan of one record, counting what the pair tests meet (the
+// diagnostic mix): the pairs that cbin_tests counts, record by record.
+template <typename real>
+__device__ void count_mix(const StepArgs<real>& a, const Inst<real>& I, int32_t i, double& tests, uint32_t& n_s0,
+                          uint32_t& n_c1) {
+    const Geo<real> G(I);
+    real xi, yi, zi, vxi, vyi, vzi;
+    load_pv(a.rec, i, xi, yi, zi, vxi, vyi, vzi);
+    int64_t seen = 0;
+    for_logical(a, I, G.per, xi, yi, zi, [&](int32_t j0, int32_t j1) {
+        if (j0 <= i) j0 = i + 1;
+        seen += j1 > j0 ? j1 - j0 : 0;
+        for (int32_t j = j0; j < j1; ++j) {
+            real xj, yj, zj, vxj, vyj, vzj;
+            load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
+            Screen<real> S;
+            const bool p1 = PairTest<real, -1>::stage1(G, xi, yi, zi, vxi, vyi, vzi, xj, yj, zj, vxj, vyj, vzj, S);
+            n_s0 += S.s0 < real(0) ? 1u : 0u;
+            n_c1 += p1 ? 1u : 0u;
+        }
+    });
+    tests = (double)seen;
 }
 
 // Lane mode of the FP32 half scans, staged through LDS.  A wave that owns
 // 64 G consecutive records takes them in G passes of 64, one record per lane
 // (record wbase + 64 p + lane in pass p), so that its registers are those of
-// one record whatever G is; G > 1 pays off in the wave-uniform mode instead.
+// one record whatever G is; G > 1 saves work-groups.
 // In each pass, the lanes whose records share one row walk every neighbour
 // row together: the wave copies the union of their ranges in that row, a
 // contiguous run of records, into its LDS buffer in chunks of kStageCap, and
@@ -1002,13 +1405,12 @@ __device__ __forceinline__ void search_group(const StepArgs<real>& a, const Inst
 // is then fetched from memory once per wave instead of once per lane whose
 // range holds it.  Records whose x-neighbourhood wraps around a periodic
 // axis walk their own rows with global loads.  The pairs tested, the
-// arithmetic and the combination of the keys are those of search_group, so
-// the results are too.  Called by every lane of a wave holding a live slow
+// arithmetic and the combination of the keys are those of the tile search,
+// so the results are too.  Called by every lane of a wave holding a live slow
 // record; stop ends the slow records.
-template <int PM, int G, bool MIX>
+template <int PM, int G>
 __device__ __forceinline__ void search_staged(const StepArgs<float>& a, const Inst<float>& I, int64_t base,
-                                              int32_t wbase, int32_t stop, double& tests, double& cand,
-                                              uint32_t& n_s0, uint32_t& n_c1) {
+                                              int32_t wbase, int32_t stop, double& tests, double& cand) {
     const Geo<float> G_(I);
     const int n[3] = {I.n[0], I.n[1], I.n[2]};
     extern __shared__ float4 tpkmc_stage[];
@@ -1038,10 +1440,6 @@ __device__ __forceinline__ void search_staged(const StepArgs<float>& a, const In
             const bool a1 = fmaf(S.vv, G_.dt, S.s0) > 0.0f;
             const uint64_t m = __builtin_amdgcn_ballot_w64(a0) & __builtin_amdgcn_ballot_w64(a1);
             const bool p1 = a0 & a1;
-            if constexpr (MIX) {
-                n_s0 += (take && S.s0 < 0.0f) ? 1u : 0u;
-                n_c1 += p1 ? 1u : 0u;
-            }
             if (m == 0) return;
             if (p1 && PairTest<float, PM>::stage2(G_, S)) {
                 const float d2 = PairTest<float, PM>::finish(G_, S);
@@ -1073,10 +1471,6 @@ __device__ __forceinline__ void search_staged(const StepArgs<float>& a, const In
             const uint64_t m = (__builtin_amdgcn_ballot_w64(qa0) & __builtin_amdgcn_ballot_w64(qa1)) |
                                (__builtin_amdgcn_ballot_w64(qb0) & __builtin_amdgcn_ballot_w64(qb1));
             const bool pa1 = qa0 & qa1, pb1 = qb0 & qb1;
-            if constexpr (MIX) {
-                n_s0 += (qa0 ? 1u : 0u) + (qb0 ? 1u : 0u);
-                n_c1 += (pa1 ? 1u : 0u) + (pb1 ? 1u : 0u);
-            }
             if (m == 0) return;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -1320,103 +1714,7 @@ __device__ __forceinline__ double fast_reach(const Inst<real>& I, double v2) {
     return (sqrt((double)I.D2) + (sqrt(v2) + sqrt((double)I.vc2)) * (double)I.dt) * (1.0 + 1.0 / 64.0);
 }
 
-// Lexicographic minimum over the wave of (key, id) with a partner (j >= 0),
-// the tie-break of the ordered scans.
-template <typename real>
-__device__ __forceinline__ void wave_best(int32_t& bj, real& bd2, uint32_t& bid) {
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
-        const int32_t oj = __shfl_xor(bj, m);
-        const real od = __shfl_xor(bd2, m);
-        const uint32_t oi = __shfl_xor(bid, m);
-        if (oj >= 0 && (bj < 0 || od < bd2 || (od == bd2 && oi < bid))) { bj = oj; bd2 = od; bid = oi; }
-    }
-}
-
-// FP64: one fast record i of split c-bins, searched by a whole wave.  Every
-// particle of its configured neighbourhood is a possible partner, as on the
-// unsplit grid: the slow ones in the fine rows of fast_span (lanes take
-// rows; a record is kept only when its configured c-bin is a neighbour), the
-// fast ones on the configured c-bins (lanes take the nine rows).  The slow
-// records' ordered scans take the fast particles of their configured
-// neighbourhood (search_group).  The pair test, the ranking key and the
-// tie-breaks are search_group's.
-template <typename real, bool MIX>
-__device__ void fast_record(const StepArgs<real>& a, const Inst<real>& I, int64_t base, int32_t i, int lane,
-                            double& tests, double& cand, uint32_t& n_s0, uint32_t& n_c1) {
-    const Geo<real> G_(I);
-    const bool by_time = (I.flags & TPKMC_RANK_TIME) != 0;
-    const int nf[3] = {I.n[0], I.n[1], I.n[2]};
-    const int nc[3] = {I.ncfg[0], I.ncfg[1], I.ncfg[2]};
-    real xi, yi, zi, vxi, vyi, vzi;
-    uint32_t idi;
-    RecU<real>::load(a.rec, i, xi, yi, zi, idi, vxi, vyi, vzi);
-    const real pi[3] = {xi, yi, zi};
-    const double reach = fast_reach(I, speed2((double)vxi, (double)vyi, (double)vzi));
-    int cc[3], first[3], span[3];
-    bool chk[3];
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        cc[ax] = axis_bin(pi[ax], I.lo[ax], I.inv_wc[ax], nc[ax]);
-        coarse_nb(I, ax, pi[ax], reach, cc[ax], G_.per[ax], first[ax], span[ax], chk[ax]);
-    }
-    int32_t bj = -1;
-    real bd2 = real(0);
-    uint32_t bid = 0;
-    int32_t seen = 0, found = 0;
-    auto test = [&](int32_t j, bool check) {
-        real xj, yj, zj, vxj, vyj, vzj;
-        uint32_t idj, flj;
-        Rec<real>::load(a.rec, j, xj, yj, zj, idj, vxj, vyj, vzj, flj);
-        if (check && !coarse_in(I, chk, nc, first, span, xj, yj, zj)) return;
-        ++seen;
-        Screen<real> S;
-        const bool p1 = PairTest<real, -1>::stage1(G_, xi, yi, zi, vxi, vyi, vzi, xj, yj, zj, vxj, vyj, vzj, S);
-        if constexpr (MIX) {
-            n_s0 += S.s0 < real(0) ? 1u : 0u;
-            n_c1 += p1 ? 1u : 0u;
-        }
-        if (!p1 || !PairTest<real, -1>::stage2(G_, S)) return;
-        const real d2 = PairTest<real, -1>::finish(G_, S);
-        if (!(d2 >= real(0))) return;
-        ++found;
-        const real key = by_time ? PairTest<real, -1>::contact(G_, S) : d2;
-        if (bj < 0 || key < bd2 || (key == bd2 && idj < bid)) { bj = j; bd2 = key; bid = idj; }
-    };
-    int xa[2], xb[2], ya[2], yb[2], za[2], zb[2];
-    const int nxr = fast_span(I, 0, xi, reach, cc[0], G_.per[0], xa, xb);
-    const int nyr = fast_span(I, 1, yi, reach, cc[1], G_.per[1], ya, yb);
-    const int nzr = fast_span(I, 2, zi, reach, cc[2], G_.per[2], za, zb);
-    const int ly0 = nyr ? yb[0] - ya[0] + 1 : 0, lz0 = nzr ? zb[0] - za[0] + 1 : 0;
-    const int ny = ly0 + (nyr > 1 ? yb[1] - ya[1] + 1 : 0);
-    const int nz = lz0 + (nzr > 1 ? zb[1] - za[1] + 1 : 0);
-    for (int t = lane; t < ny * nz; t += kWave) {
-        const int y = span_at(ya, yb, ly0, t % ny), z = span_at(za, zb, lz0, t / ny);
-        const int64_t row = I.cell_off + (int64_t)nf[0] * row_of(I, y, z);
-        for (int rx = 0; rx < nxr; ++rx) {
-            const int32_t j0 = (int32_t)(base + a.start[row + xa[rx]]);
-            const int32_t j1 = (int32_t)(base + a.start[row + xb[rx] + 1]);
-            for (int32_t j = j0; j < j1; ++j) test(j, true);
-        }
-    }
-    if (lane < 9)
-        neighbourhood_row<false, true>(a.start, I, base, nc, G_.per, cc[0], cc[1], cc[2], i, lane,
-                                       [&](int32_t j0, int32_t j1) {
-            for (int32_t j = j0; j < j1; ++j) test(j, false);
-        });
-    double sn = (double)seen, fn = (double)found;
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
-        sn += __shfl_xor(sn, m);
-        fn += __shfl_xor(fn, m);
-    }
-    wave_best(bj, bd2, bid);
-    if (lane == 0) a.best[i] = bj;
-    tests += 0.5 * (sn - 1.0);  // the record met itself once
-    cand += fn;
-}
-
-// FP32: the fast records' searches as a flat list of tasks, one per lane:
+// The fast records' searches as a flat list of tasks, one per lane:
 // (fast record, row) for the fine rows of fast_span (index t < ny * nz) and
 // for the nine rows of configured c-bins of the fast particles (half
 // neighbourhood), so lanes stay busy however few rows a record has or
@@ -1426,18 +1724,18 @@ __device__ void fast_record(const StepArgs<real>& a, const Inst<real>& I, int64_
 // one record may run in any lanes and any order.
 constexpr int kLongRow = 64;
 
-template <bool MIX>
-__device__ void fast_tasks(const StepArgs<float>& a, const Inst<float>& I, int64_t base, int64_t f0, int64_t ntask,
+template <typename real, bool MIX>
+__device__ void fast_tasks(const StepArgs<real>& a, const Inst<real>& I, int64_t base, int64_t f0, int64_t ntask,
                            int per_rec, int rmax, int64_t q, int lane, double& seen, double& cand, uint32_t& n_s0,
                            uint32_t& n_c1) {
-    const Geo<float> G_(I);
+    const Geo<real> G_(I);
     const bool by_time = (I.flags & TPKMC_RANK_TIME) != 0;
     const int nf[3] = {I.n[0], I.n[1], I.n[2]};
     const int nc[3] = {I.ncfg[0], I.ncfg[1], I.ncfg[2]};
     const bool valid = q < ntask;
     int32_t i = 0;
     int t = 0;
-    float xi = 0.f, yi = 0.f, zi = 0.f, vxi = 0.f, vyi = 0.f, vzi = 0.f;
+    real xi = 0, yi = 0, zi = 0, vxi = 0, vyi = 0, vzi = 0;
     int cc[3] = {0, 0, 0}, first[3] = {0, 0, 0}, span[3] = {0, 0, 0};
     bool chk[3] = {false, false, false};
     int32_t ja[2] = {0, 0}, jb[2] = {0, 0};
@@ -1445,8 +1743,8 @@ __device__ void fast_tasks(const StepArgs<float>& a, const Inst<float>& I, int64
     if (valid) {
         i = (int32_t)(f0 + q / per_rec);
         t = (int)(q % per_rec);
-        Rec<float>::load6(a.rec, (uint32_t)i, xi, yi, zi, vxi, vyi, vzi);
-        const float pi[3] = {xi, yi, zi};
+        load_pv(a.rec, i, xi, yi, zi, vxi, vyi, vzi);
+        const real pi[3] = {xi, yi, zi};
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) cc[ax] = axis_bin(pi[ax], I.lo[ax], I.inv_wc[ax], nc[ax]);
         if (t < rmax) {
@@ -1475,26 +1773,21 @@ __device__ void fast_tasks(const StepArgs<float>& a, const Inst<float>& I, int64
     }
     // Tests slow or fast record j against fast record ii (the lane's own or,
     // for long rows, the owner lane's, whose values are passed in).
-    auto test = [&](int32_t ii, float x0, float y0, float z0, float u0, float u1, float u2, int32_t j,
-                    unsigned long long& mine) {
-        float xj, yj, zj, vxj, vyj, vzj;
-        Rec<float>::load6(a.rec, (uint32_t)j, xj, yj, zj, vxj, vyj, vzj);
+    auto test = [&](int32_t ii, real x0, real y0, real z0, real u0, real u1, real u2, int32_t j, real xj, real yj,
+                    real zj, real vxj, real vyj, real vzj) {
         seen += 1.0;
-        Screen<float> S;
-        const bool p1 = PairTest<float, -1>::stage1(G_, x0, y0, z0, u0, u1, u2, xj, yj, zj, vxj, vyj, vzj, S);
         if constexpr (MIX) {
-            n_s0 += S.s0 < 0.0f ? 1u : 0u;
+            Screen<real> S;
+            const bool p1 = PairTest<real, -1>::stage1(G_, x0, y0, z0, u0, u1, u2, xj, yj, zj, vxj, vyj, vzj, S);
+            n_s0 += S.s0 < real(0) ? 1u : 0u;
             n_c1 += p1 ? 1u : 0u;
+        } else {
+            real value;
+            if (!test_pair(G_, by_time, x0, y0, z0, u0, u1, u2, xj, yj, zj, vxj, vyj, vzj, value)) return;
+            cand += 2.0;  // both orders
+            Key<real>::lower(a, j, Key<real>::make(value, (uint32_t)ii), key_now(a, j));
+            Key<real>::lower(a, ii, Key<real>::make(value, (uint32_t)j), key_now(a, ii));
         }
-        if (!p1 || !PairTest<float, -1>::stage2(G_, S)) return;
-        const float d2 = PairTest<float, -1>::finish(G_, S);
-        if (!(d2 >= 0.0f)) return;
-        cand += 2.0;  // both orders, as search_group counts
-        const float key = by_time ? PairTest<float, -1>::contact(G_, S) : d2;
-        const unsigned long long hi = (unsigned long long)sortable(key) << 32;
-        atomicMin(a.bkey + j, hi | (uint32_t)ii);
-        const unsigned long long kk = hi | (uint32_t)j;
-        mine = kk < mine ? kk : mine;
     };
     const int len = slow ? (jb[0] - ja[0]) + (jb[1] - ja[1]) : 0;
     // Long slow rows: the whole wave, one owner lane at a time.
@@ -1503,8 +1796,8 @@ __device__ void fast_tasks(const StepArgs<float>& a, const Inst<float>& I, int64
         const int o = __ffsll((long long)longm) - 1;
         longm &= longm - 1;
         const int32_t io = __builtin_amdgcn_readlane(i, o);
-        const float xo = __shfl(xi, o), yo = __shfl(yi, o), zo = __shfl(zi, o);
-        const float uo0 = __shfl(vxi, o), uo1 = __shfl(vyi, o), uo2 = __shfl(vzi, o);
+        const real xo = __shfl(xi, o), yo = __shfl(yi, o), zo = __shfl(zi, o);
+        const real uo0 = __shfl(vxi, o), uo1 = __shfl(vyi, o), uo2 = __shfl(vzi, o);
         int fo[3], so[3];
         bool co[3];
 #pragma unroll
@@ -1513,66 +1806,46 @@ __device__ void fast_tasks(const StepArgs<float>& a, const Inst<float>& I, int64
             so[ax] = __builtin_amdgcn_readlane(span[ax], o);
             co[ax] = __builtin_amdgcn_readlane((int)chk[ax], o) != 0;
         }
-        unsigned long long mo = ~0ull;
 #pragma unroll
         for (int rx = 0; rx < 2; ++rx) {
             const int32_t a0 = __builtin_amdgcn_readlane(ja[rx], o), b0 = __builtin_amdgcn_readlane(jb[rx], o);
             for (int32_t j = a0 + lane; j < b0; j += kWave) {
-                float xj, yj, zj, vxj, vyj, vzj;
-                Rec<float>::load6(a.rec, (uint32_t)j, xj, yj, zj, vxj, vyj, vzj);
-                if (coarse_in(I, co, nc, fo, so, xj, yj, zj)) test(io, xo, yo, zo, uo0, uo1, uo2, j, mo);
+                real xj, yj, zj, vxj, vyj, vzj;
+                load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
+                if (coarse_in(I, co, nc, fo, so, xj, yj, zj))
+                    test(io, xo, yo, zo, uo0, uo1, uo2, j, xj, yj, zj, vxj, vyj, vzj);
             }
         }
-        if (mo != ~0ull) atomicMin(a.bkey + io, mo);
     }
-    unsigned long long mine = ~0ull;
     if (slow && len <= kLongRow) {
 #pragma unroll
         for (int rx = 0; rx < 2; ++rx)
             for (int32_t j = ja[rx]; j < jb[rx]; ++j) {
-                float xj, yj, zj, vxj, vyj, vzj;
-                Rec<float>::load6(a.rec, (uint32_t)j, xj, yj, zj, vxj, vyj, vzj);
-                if (coarse_in(I, chk, nc, first, span, xj, yj, zj)) test(i, xi, yi, zi, vxi, vyi, vzi, j, mine);
+                real xj, yj, zj, vxj, vyj, vzj;
+                load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
+                if (coarse_in(I, chk, nc, first, span, xj, yj, zj))
+                    test(i, xi, yi, zi, vxi, vyi, vzi, j, xj, yj, zj, vxj, vyj, vzj);
             }
     } else if (valid && t >= rmax) {
         neighbourhood_row<true, true>(a.start, I, base, nc, G_.per, cc[0], cc[1], cc[2], i, t - rmax,
                                       [&](int32_t j0, int32_t j1) {
-            for (int32_t j = j0; j < j1; ++j) test(i, xi, yi, zi, vxi, vyi, vzi, j, mine);
+            for (int32_t j = j0; j < j1; ++j) {
+                real xj, yj, zj, vxj, vyj, vzj;
+                load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
+                test(i, xi, yi, zi, vxi, vyi, vzi, j, xj, yj, zj, vxj, vyj, vzj);
+            }
         });
     }
-    if (mine != ~0ull) atomicMin(a.bkey + i, mine);
 }
 
-// search_group for the instance's periodic axes: FP32 has builds for the
-// masks of the usual boxes (none; z, as in the Noh implosions and the planar
-// gases; y and z, as in the Sod tubes; all three), which leave the other axes
-// out of the pair test; other masks, and FP64, read them at run time.
-template <typename real, bool HALF, int G, bool UNIFORM, bool MIX>
-__device__ __forceinline__ void search_for_axes(int pm, const StepArgs<real>& a, const Inst<real>& I, int64_t base,
-                                                int32_t i0, int nrec, int32_t wave_first, int wave_ub,
-                                                double& tests, double& cand, uint32_t& n_s0, uint32_t& n_c1) {
-#define TPKMC_SEARCH(PMV) \
-    search_group<real, HALF, PMV, G, UNIFORM, MIX>(a, I, base, i0, nrec, wave_first, wave_ub, tests, cand, n_s0, n_c1)
-    if constexpr (std::is_same<real, float>::value) {
-        switch (pm) {
-            case 0: TPKMC_SEARCH(0); break;
-            case 4: TPKMC_SEARCH(4); break;
-            case 6: TPKMC_SEARCH(6); break;
-            case 7: TPKMC_SEARCH(7); break;
-            default: TPKMC_SEARCH(-1); break;
-        }
-    } else {
-        if (pm == 0) TPKMC_SEARCH(0);
-        else TPKMC_SEARCH(-1);
-    }
-#undef TPKMC_SEARCH
-}
-
-template <int G, bool MIX>
+template <int G>
 __device__ __forceinline__ void search_staged_for_axes(int pm, const StepArgs<float>& a, const Inst<float>& I,
                                                        int64_t base, int32_t wbase, int32_t stop, double& tests,
-                                                       double& cand, uint32_t& n_s0, uint32_t& n_c1) {
-#define TPKMC_STAGED(PMV) search_staged<PMV, G, MIX>(a, I, base, wbase, stop, tests, cand, n_s0, n_c1)
+                                                       double& cand) {
+#define TPKMC_STAGED(PMV) search_staged<PMV, G>(a, I, base, wbase, stop, tests, cand)
+    // Builds for the periodic masks of the usual boxes (none; z, as in the
+    // Noh implosions and the planar gases; y and z, as in the Sod tubes; all
+    // three) leave the other axes out of the pair test.
     switch (pm) {
         case 0: TPKMC_STAGED(0); break;
         case 4: TPKMC_STAGED(4); break;
@@ -1583,121 +1856,108 @@ __device__ __forceinline__ void search_staged_for_axes(int pm, const StepArgs<fl
 #undef TPKMC_STAGED
 }
 
-// One table entry (kBlock records) is covered by kBlock / G lanes, split
-// into work-groups of blockDim.x lanes.  FP32 launches carry one LDS staging
-// buffer per wave (kStageBytesPerWave of dynamic LDS).
-// The FP32 two-records-per-lane shape (the usual autotuner choice) is held to
-// at most 72 VGPRs, 7 waves per SIMD (with a lane mode walking both records
-// at once it needed 78, and the seventh wave was worth 3-4% on the search);
+// First and last (exclusive) live slow record of an instance; with split
+// c-bins the fast ones after them are searched by k_search_fast.
+template <typename real>
+__device__ __forceinline__ int64_t slow_stop(const StepArgs<real>& a, const Inst<real>& I, int64_t base) {
+    const int64_t end = I.off + I.cnt;
+    const int64_t live = base + a.start[I.cell_off + ((I.flags & kSplit) ? I.Cf : I.C)];
+    return live < end ? live : end;
+}
+
+// Adds a work-group's share of the search's work counters to entry's row.
+__device__ __forceinline__ void add_work(double* gpart, int entry, double tests, double cand, double* lds) {
+    const double t = block_sum(tests, lds);
+    const double c = block_sum(cand, lds);
+    if (threadIdx.x == 0 && (t != 0.0 || c != 0.0)) {
+        double* gp = gpart + (int64_t)entry * kGPart;
+        unsafeAtomicAdd(gp + GP_TESTS2, 2.0 * t);
+        unsafeAtomicAdd(gp + GP_CAND, c);
+    }
+}
+
+// FP32 search of the sparse instances.  One table entry (kBlock
+// records) is covered by kBlock / G lanes, split into work-groups of
+// blockDim.x lanes, with one LDS staging buffer per wave
+// (kStageBytesPerWave of dynamic LDS).
+// The two-records-per-lane shape (the usual autotuner choice) is held to at
+// most 72 VGPRs, 7 waves per SIMD (with a lane mode walking both records at
+// once it needed 78, and the seventh wave was worth 3-4% on the search);
 // with the staged lane mode, one record per pass, it needs 68.
-template <typename real, bool HALF, int G, bool MIX = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((HALF && G == 2) ? 7 : 1, 8)))
-k_search(StepArgs<real> a) {
+template <int G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 2 ? 7 : 1, 8)))
+k_search(StepArgs<float> a) {
     __shared__ double lds[16];
     const int lanes = kBlock / G;
     const int sub = lanes / blockDim.x;
     const int lb = a.order > 0 ? xcd_chunk_remap(blockIdx.x, gridDim.x, a.order) : xcd_remap(blockIdx.x, gridDim.x);
     const int entry = lb / sub;
     const Blk bt = a.blk[entry];
-    const Inst<real>& I = a.inst[bt.inst];
-    if (I.flags & TPKMC_PAIR_RANDOM) return;  // partners from k_rp_* instead
-    const int64_t i0 = (int64_t)bt.first + ((int64_t)(lb % sub) * blockDim.x + threadIdx.x) * G;
-    const int64_t base = I.off - a.start[I.cell_off];
-    const int64_t live_end = base + a.start[I.cell_off + I.C];
-    const int64_t end = I.off + I.cnt;
+    const Inst<float>& I = a.inst[bt.inst];
+    if (I.flags & (TPKMC_PAIR_RANDOM | kTiles)) return;  // partners from k_rp_* or k_search_tiles
+    const int64_t i0 = (int64_t)bt.first + ((int64_t)(lb % sub) * blockDim.x + (threadIdx.x & ~63u)) * G;
+    const int64_t base = I.base;
+    const int64_t stop = slow_stop(a, I, base);
     const int pm = (I.bc[0] == TPKMC_BC_PERIODIC ? 1 : 0) | (I.bc[1] == TPKMC_BC_PERIODIC ? 2 : 0) |
                    (I.bc[2] == TPKMC_BC_PERIODIC ? 4 : 0);
     double tests = 0.0, cand = 0.0;
-    const int64_t live_stop = live_end < end ? live_end : end;
-    const int nrec = i0 < live_stop ? (int)(live_stop - i0 < G ? live_stop - i0 : G) : 0;
-    // Split c-bins: the slow records come first; the fast ones after them are
-    // searched by k_search_fast.
-    const int64_t slow_stop = (I.flags & kSplit) ? min(base + a.start[I.cell_off + I.Cf], live_stop) : live_stop;
-    const int nslow = i0 < slow_stop ? (int)(slow_stop - i0 < nrec ? slow_stop - i0 : nrec) : 0;
-    // Wave-uniform mode when the wave's live slow records lie in at most two
-    // neighbouring bins of one row (dense bins): decided on the first and
-    // last of them, so the branch is uniform.  Otherwise the lane mode:
-    // staged through LDS in FP32 (search_staged), per lane in FP64.
-    const uint64_t live = __ballot(nslow > 0);
-    bool uni = false;
-    int32_t wfirst = 0;
-    int wub = 0;
-    if (live) {
-        const int fl = __ffsll((long long)live) - 1;
-        const int ll = 63 - __clzll((long long)live);
-        wfirst = __builtin_amdgcn_readlane((int32_t)i0, fl);
-        const int32_t wlast = __builtin_amdgcn_readlane((int32_t)(i0 + nslow - 1), ll);
-        real xf, yf, zf, vxf, vyf, vzf, xl, yl, zl, vxl, vyl, vzl;
-        uint32_t idf, idl;
-        RecU<real>::load(a.rec, wfirst, xf, yf, zf, idf, vxf, vyf, vzf);
-        RecU<real>::load(a.rec, wlast, xl, yl, zl, idl, vxl, vyl, vzl);
-        const int cxf = axis_bin(xf, I.lo[0], I.inv_w[0], I.n[0]);
-        const int cxl = axis_bin(xl, I.lo[0], I.inv_w[0], I.n[0]);
-        const bool per0 = I.bc[0] == TPKMC_BC_PERIODIC;
-        int xa[2], xb[2];
-        const int nrf = x_ranges(cxf, I.n[0], per0, xa, xb);
-        const int nrl = x_ranges(cxl, I.n[0], per0, xa, xb);
-        wub = xb[0];
-        uni = nrf == 1 && nrl == 1 && cxl - cxf <= 1 &&
-              axis_bin(yf, I.lo[1], I.inv_w[1], I.n[1]) == axis_bin(yl, I.lo[1], I.inv_w[1], I.n[1]) &&
-              axis_bin(zf, I.lo[2], I.inv_w[2], I.n[2]) == axis_bin(zl, I.lo[2], I.inv_w[2], I.n[2]);
-    }
-    uint32_t n_s0 = 0, n_c1 = 0;
-    if (uni) {
-        if (nslow > 0)
-            search_for_axes<real, HALF, G, true, MIX>(pm, a, I, base, (int32_t)i0, nslow, wfirst, wub, tests, cand,
-                                                      n_s0, n_c1);
-    } else if constexpr (HALF) {
-        if (live) {  // wave-uniform: every lane of the wave takes part
-            const int32_t wbase = (int32_t)(i0 - (int64_t)(threadIdx.x & 63) * G);
-            search_staged_for_axes<G, MIX>(pm, a, I, base, wbase, (int32_t)slow_stop, tests, cand, n_s0, n_c1);
-        }
-    } else if (nslow > 0) {
-        search_for_axes<real, HALF, G, false, MIX>(pm, a, I, base, (int32_t)i0, nslow, 0, 0, tests, cand, n_s0,
-                                                   n_c1);
-    }
+    if (i0 < stop)  // wave-uniform: every lane of the wave takes part
+        search_staged_for_axes<G>(pm, a, I, base, __builtin_amdgcn_readfirstlane((int32_t)i0), (int32_t)stop, tests,
+                                  cand);
+    add_work(a.gpart, entry, tests, cand, lds);
+}
 
-    if constexpr (MIX) {
-        // Counted twice per unordered pair, so every work-group's share is an
-        // integer: ordered scans meet each pair from both sides (s0 is
-        // symmetric in i and j bit for bit), half scans once (doubled here).
-        // The host halves the totals.
-        const double f = HALF ? 2.0 : 1.0;
-        const double t0 = block_sum(2.0 * tests, lds), t1 = block_sum(f * (double)n_s0, lds),
-                     t2 = block_sum(f * (double)n_c1, lds);
-        if (threadIdx.x == 0) {
-            atomicAdd(a.mix + 0, (unsigned long long)t0);
-            atomicAdd(a.mix + 1, (unsigned long long)t1);
-            atomicAdd(a.mix + 2, (unsigned long long)t2);
-        }
-        return;
-    }
-    if (!HALF) {
-        for (int k = nrec; k < G; ++k)
-            if (i0 + k < end) a.best[i0 + k] = -1;
-    }
-    const double t = block_sum(tests, lds);
-    const double c = block_sum(cand, lds);
+// The instances of the tile search (all in FP64, the dense ones in FP32),
+// one wave per 64 records; the work-groups of an instance share the count of
+// its pair tests.
+template <typename real>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(real) == 4 ? 3 : 2)))
+k_search_tiles(StepArgs<real> a) {
+    __shared__ double lds[16];
+    __shared__ TileLds<real> tl[kBlock / kWave];
+    const int entry =
+        a.order > 0 ? xcd_chunk_remap(blockIdx.x, gridDim.x, a.order) : xcd_remap(blockIdx.x, gridDim.x);
+    const Blk bt = a.blk[entry];
+    const Inst<real>& I = a.inst[bt.inst];
+    if (!(I.flags & kTiles)) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int32_t i0 = bt.first + wave * kWave;
+    const int64_t stop = slow_stop(a, I, I.base);
+    double tests = 0.0, cand = 0.0;
+    if (i0 < stop) search_tiles(a, I, i0, (int32_t)stop, (int)blockIdx.y, (int)gridDim.y, tl[wave], cand);
+    const int64_t ncb = (int64_t)I.nl[0] * I.nl[1] * I.nl[2];
+    const int64_t share = (int64_t)(entry - I.blk0) * gridDim.y + blockIdx.y;
+    for (int64_t c = share * kBlock + threadIdx.x; c < ncb; c += (int64_t)I.nblk * gridDim.y * kBlock)
+        tests += cbin_tests(a, I, (int)c);
+    add_work(a.gpart, entry, tests, cand, lds);
+}
+
+// Diagnostic: counts of the pair tests (never part of a step).
+template <typename real>
+__global__ void __launch_bounds__(kBlock) k_search_mix(StepArgs<real> a) {
+    __shared__ double lds[16];
+    const Blk bt = a.blk[blockIdx.x];
+    const Inst<real>& I = a.inst[bt.inst];
+    if (I.flags & TPKMC_PAIR_RANDOM) return;
+    const int64_t i = (int64_t)bt.first + threadIdx.x;
+    const int64_t base = I.base;
+    double tests = 0.0;
+    uint32_t n_s0 = 0, n_c1 = 0;
+    if (i < slow_stop(a, I, base)) count_mix(a, I, (int32_t)i, tests, n_s0, n_c1);
+    const double t0 = block_sum(tests, lds), t1 = block_sum((double)n_s0, lds), t2 = block_sum((double)n_c1, lds);
     if (threadIdx.x == 0) {
-        double* gp = a.gpart + (int64_t)entry * kGPart;
-        if (sub == 1) {
-            gp[GP_TESTS2] = 2.0 * t;
-            gp[GP_CAND] = c;
-        } else {
-            unsafeAtomicAdd(gp + GP_TESTS2, 2.0 * t);
-            unsafeAtomicAdd(gp + GP_CAND, c);
-        }
+        atomicAdd(a.mix + 0, (unsigned long long)t0);
+        atomicAdd(a.mix + 1, (unsigned long long)t1);
+        atomicAdd(a.mix + 2, (unsigned long long)t2);
     }
 }
 
-// The fast records of split c-bins, in a launch of their own after k_search
-// (FP32 keys combine with atomicMin in any order; in FP64 each fast record
-// writes its own partner), so that the slow records' search keeps its
-// register budget.  FP32 strides over the task list of fast_tasks; FP64 runs
-// one fast record per wave (fast_record).  The search's work counters are
-// summed per work-group and instance, and added to the instance's first
-// block-table entry.
-template <typename real, bool HALF, bool MIX = false>
+// The fast records of split c-bins, in a launch of their own after the slow
+// ones' search (the keys combine with atomicMin in any order), striding over
+// the task list of fast_tasks.  The search's work counters are summed per
+// work-group and instance, and added to the instance's first block-table
+// entry.
+template <typename real, bool MIX = false>
 __global__ void __launch_bounds__(256) k_search_fast(StepArgs<real> a, int n_inst) {
     __shared__ double lds[16];
     const int lane = threadIdx.x & (kWave - 1);
@@ -1708,53 +1968,129 @@ __global__ void __launch_bounds__(256) k_search_fast(StepArgs<real> a, int n_ins
     for (int k = 0; k < n_inst; ++k) {
         const Inst<real>& I = a.inst[k];
         if (!(I.flags & kSplit) || (I.flags & TPKMC_PAIR_RANDOM)) continue;
-        const int64_t base = I.off - a.start[I.cell_off];
+        const int64_t base = I.base;
         const int64_t f0 = base + a.start[I.cell_off + I.Cf];
         const int64_t live_end = base + a.start[I.cell_off + I.C];
         const int64_t f1 = live_end < I.off + I.cnt ? live_end : I.off + I.cnt;
         double t = 0.0, c = 0.0;
-        if constexpr (HALF) {
-            // Rows per fast record: the fine rows within the largest reach
-            // of this step's fastest particle, then the nine coarse rows.
-            const double reach = fast_reach(I, I.vmax2_d);
-            const bool per1 = I.bc[1] == TPKMC_BC_PERIODIC, per2 = I.bc[2] == TPKMC_BC_PERIODIC;
-            const int rmax = fast_span_len(I, 1, reach, per1) * fast_span_len(I, 2, reach, per2);
-            const int per_rec = rmax + 9;
-            const int64_t ntask = (f1 - f0) * per_rec;
-            for (int64_t q0 = tid - lane; q0 < ntask; q0 += nth)  // wave-uniform
-                fast_tasks<MIX>(a, I, base, f0, ntask, per_rec, rmax, q0 + lane, lane, t, c, n_s0, n_c1);
-        } else {
-            const int64_t wave = tid / kWave, nwaves = nth / kWave;
-            for (int64_t r = f0 + wave; r < f1; r += nwaves) {
-                double tr = 0.0, cr = 0.0;
-                const int32_t ri = __builtin_amdgcn_readfirstlane((int32_t)r);  // wave-uniform
-                fast_record<real, MIX>(a, I, base, ri, lane, tr, cr, n_s0, n_c1);
-                t += lane == 0 ? tr : 0.0;
-                c += lane == 0 ? cr : 0.0;
-            }
-        }
-        if constexpr (MIX) {
-            mt += t;
-        } else {
-            // Uniform over the work-group (the instance loop is), so every
-            // thread takes part in the sums.
-            const double ts = block_sum(t, lds), cs = block_sum(c, lds);
-            if (threadIdx.x == 0) {
-                double* gp = a.gpart + (int64_t)I.blk0 * kGPart;
-                if (ts > 0.0) unsafeAtomicAdd(gp + GP_TESTS2, 2.0 * ts);
-                if (cs > 0.0) unsafeAtomicAdd(gp + GP_CAND, cs);
-            }
-        }
+        // Rows per fast record: the fine rows within the largest reach of
+        // this step's fastest particle, then the nine coarse rows.
+        const double reach = fast_reach(I, I.vmax2_d);
+        const bool per1 = I.bc[1] == TPKMC_BC_PERIODIC, per2 = I.bc[2] == TPKMC_BC_PERIODIC;
+        const int rmax = fast_span_len(I, 1, reach, per1) * fast_span_len(I, 2, reach, per2);
+        const int per_rec = rmax + 9;
+        const int64_t ntask = (f1 - f0) * per_rec;
+        for (int64_t q0 = tid - lane; q0 < ntask; q0 += nth)  // wave-uniform
+            fast_tasks<real, MIX>(a, I, base, f0, ntask, per_rec, rmax, q0 + lane, lane, t, c, n_s0, n_c1);
+        // Uniform over the work-group (the instance loop is), so every
+        // thread takes part in the sums.
+        if constexpr (MIX) mt += t;
+        else add_work(a.gpart, I.blk0, t, c, lds);
     }
     if constexpr (MIX) {
-        // The counting convention of k_search's diagnostic build.
-        const double f = HALF ? 2.0 : 1.0;
-        const double t0 = block_sum(2.0 * mt, lds), t1 = block_sum(f * (double)n_s0, lds),
-                     t2 = block_sum(f * (double)n_c1, lds);
+        const double t0 = block_sum(mt, lds), t1 = block_sum((double)n_s0, lds), t2 = block_sum((double)n_c1, lds);
         if (threadIdx.x == 0) {
             if (t0 > 0.0) atomicAdd(a.mix + 0, (unsigned long long)t0);
             if (t1 > 0.0) atomicAdd(a.mix + 1, (unsigned long long)t1);
             if (t2 > 0.0) atomicAdd(a.mix + 2, (unsigned long long)t2);
+        }
+    }
+}
+
+// Lexicographic minimum over the wave of (value, id) with a partner
+// (j >= 0), the tie rule of the reference.
+__device__ __forceinline__ void wave_best(int32_t& bj, double& bv, uint32_t& bid) {
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+        const int32_t oj = __shfl_xor(bj, m);
+        const double ov = __shfl_xor(bv, m);
+        const uint32_t oi = __shfl_xor(bid, m);
+        if (oj >= 0 && (bj < 0 || ov < bv || (ov == bv && oi < bid))) { bj = oj; bv = ov; bid = oi; }
+    }
+}
+
+// The partner of record i by the full ranking value and, where that is
+// equal, the lower id: a whole wave scans every record that may be a
+// candidate of i.  Without split c-bins, its neighbourhood; with them, the
+// slow records (of the fine rows in reach of a fast i, of the neighbouring
+// fine c-bins of a slow i) and the fast records of its configured
+// neighbourhood.
+inline __device__ void settle_tie(const StepArgs<double>& a, const Inst<double>& I, int64_t base, int32_t i, int lane) {
+    const Geo<double> G(I);
+    const bool by_time = (I.flags & TPKMC_RANK_TIME) != 0;
+    const bool split = (I.flags & kSplit) != 0;
+    const int nf[3] = {I.n[0], I.n[1], I.n[2]}, nc[3] = {I.ncfg[0], I.ncfg[1], I.ncfg[2]};
+    double xi, yi, zi, vxi, vyi, vzi;
+    uint32_t idi, fl;
+    Rec<double>::load(a.rec, i, xi, yi, zi, idi, vxi, vyi, vzi, fl);
+    const double pi[3] = {xi, yi, zi};
+    int32_t bj = -1;
+    double bv = 0.0;
+    uint32_t bid = 0;
+    int first[3] = {0, 0, 0}, span[3] = {0, 0, 0}, cc[3];
+    bool chk[3] = {false, false, false};
+    auto scan = [&](int32_t j0, int32_t j1, bool check) {
+        for (int32_t j = j0 + lane; j < j1; j += kWave) {
+            double xj, yj, zj, vxj, vyj, vzj;
+            uint32_t idj, flj;
+            Rec<double>::load(a.rec, j, xj, yj, zj, idj, vxj, vyj, vzj, flj);
+            if (check && !coarse_in(I, chk, nc, first, span, xj, yj, zj)) continue;
+            Screen<double> S;
+            if (!PairTest<double, -1>::stage1(G, xi, yi, zi, vxi, vyi, vzi, xj, yj, zj, vxj, vyj, vzj, S)) continue;
+            if (!PairTest<double, -1>::stage2(G, S)) continue;
+            const double d2 = PairTest<double, -1>::finish(G, S);
+            if (!(d2 >= 0.0)) continue;
+            const double v = by_time ? PairTest<double, -1>::contact(G, S) : d2;
+            if (bj < 0 || v < bv || (v == bv && idj < bid)) { bj = j; bv = v; bid = idj; }
+        }
+    };
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) cc[ax] = axis_bin(pi[ax], I.lo[ax], I.inv_wc[ax], nc[ax]);
+    if (split && i >= base + a.start[I.cell_off + I.Cf]) {
+        const double reach = fast_reach(I, speed2(vxi, vyi, vzi));
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) coarse_nb(I, ax, pi[ax], reach, cc[ax], G.per[ax], first[ax], span[ax], chk[ax]);
+        int xa[2], xb[2], ya[2], yb[2], za[2], zb[2];
+        const int nxr = fast_span(I, 0, xi, reach, cc[0], G.per[0], xa, xb);
+        const int nyr = fast_span(I, 1, yi, reach, cc[1], G.per[1], ya, yb);
+        const int nzr = fast_span(I, 2, zi, reach, cc[2], G.per[2], za, zb);
+        const int ly0 = nyr ? yb[0] - ya[0] + 1 : 0, lz0 = nzr ? zb[0] - za[0] + 1 : 0;
+        const int ny = ly0 + (nyr > 1 ? yb[1] - ya[1] + 1 : 0), nz = lz0 + (nzr > 1 ? zb[1] - za[1] + 1 : 0);
+        for (int t = 0; t < ny * nz; ++t) {
+            const int64_t row = I.cell_off + (int64_t)nf[0] * row_of(I, span_at(ya, yb, ly0, t % ny),
+                                                                     span_at(za, zb, lz0, t / ny));
+            for (int rx = 0; rx < nxr; ++rx)
+                scan((int32_t)(base + a.start[row + xa[rx]]), (int32_t)(base + a.start[row + xb[rx] + 1]), true);
+        }
+    } else {
+        for_logical(a, I, G.per, xi, yi, zi, [&](int32_t j0, int32_t j1) { scan(j0, j1, false); });
+    }
+    if (split)
+        for_neighbourhood<false, true>(a.start, I, base, nc, G.per, cc[0], cc[1], cc[2], i,
+                                       [&](int32_t j0, int32_t j1) { scan(j0, j1, false); });
+    wave_best(bj, bv, bid);
+    if (lane == 0 && bj >= 0) a.bkey[i] = (unsigned long long)(uint32_t)bj;
+}
+
+// FP64 records whose lowest key met an equal one (see Key): settled one by
+// one.  Returns at once where there is none, the usual case.
+template <typename real>
+__global__ void __launch_bounds__(kBlock) k_search_ties(StepArgs<real> a) {
+    if (*a.ties == 0u) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int entry = blockIdx.x; entry < a.nblk; entry += gridDim.x) {
+        const Blk bt = a.blk[entry];
+        const Inst<real>& I = a.inst[bt.inst];
+        if (I.flags & TPKMC_PAIR_RANDOM) continue;
+        const int64_t base = I.base;
+        const int32_t i0 = bt.first + wave * kWave;
+        const int64_t i = (int64_t)i0 + lane;
+        uint64_t marked = __ballot(i < I.off + I.cnt && a.coll[i] != 0);
+        while (marked) {
+            const int l = __ffsll((long long)marked) - 1;
+            marked &= marked - 1;
+            settle_tie(a, I, base, i0 + l, lane);
         }
     }
 }
@@ -1799,7 +2135,7 @@ __global__ void __launch_bounds__(kBlock) k_rp_key(StepArgs<real> a) {
     const Blk bt = a.blk[blockIdx.x];
     const Inst<real>& I = a.inst[bt.inst];
     if (!(I.flags & TPKMC_PAIR_RANDOM)) return;
-    const int64_t base = I.off - a.start[I.cell_off];
+    const int64_t base = I.base;
     const int64_t live_end = base + a.start[I.cell_off + I.C];
     const int64_t i = (int64_t)bt.first + threadIdx.x;
     if (i < live_end && i < I.off + I.cnt)
@@ -1812,7 +2148,7 @@ __global__ void __launch_bounds__(kBlock) k_rp_rank(StepArgs<real> a) {
     const Blk bt = a.blk[blockIdx.x];
     const Inst<real>& I = a.inst[bt.inst];
     if (!(I.flags & TPKMC_PAIR_RANDOM)) return;
-    const int64_t base = I.off - a.start[I.cell_off];
+    const int64_t base = I.base;
     const int64_t live_end = base + a.start[I.cell_off + I.C];
     const int64_t i = (int64_t)bt.first + threadIdx.x;
     if (!(i < live_end && i < I.off + I.cnt)) return;
@@ -1838,7 +2174,7 @@ __global__ void __launch_bounds__(kBlock) k_rp_partner(StepArgs<real> a) {
     const Blk bt = a.blk[blockIdx.x];
     const Inst<real>& I = a.inst[bt.inst];
     if (!(I.flags & TPKMC_PAIR_RANDOM)) return;
-    const int64_t base = I.off - a.start[I.cell_off];
+    const int64_t base = I.base;
     const int64_t live_end = base + a.start[I.cell_off + I.C];
     const int64_t i = (int64_t)bt.first + threadIdx.x;
     double formed = 0.0, paired = 0.0;
@@ -1892,14 +2228,14 @@ __device__ __forceinline__ bool random_pair_collides(const StepArgs<real>& a, co
 }
 
 // ---------------------------------------------------------------- 5. move
-// Partner record of record i after the search, or -1.
-template <typename real> __device__ __forceinline__ int32_t partner_of(const StepArgs<real>& a, int64_t i);
-template <> __device__ __forceinline__ int32_t partner_of<double>(const StepArgs<double>& a, int64_t i) {
-    return a.best[i];
-}
-template <> __device__ __forceinline__ int32_t partner_of<float>(const StepArgs<float>& a, int64_t i) {
+// Partner record of record i after the search, or -1 (random partners of an
+// FP64 state come as plain indices in `best`).
+template <typename real>
+__device__ __forceinline__ int32_t partner_of(const StepArgs<real>& a, const Inst<real>& I, int64_t i) {
+    if constexpr (std::is_same<real, double>::value)
+        if (I.flags & TPKMC_PAIR_RANDOM) return a.best[i];
     const unsigned long long k = a.bkey[i];
-    return k == ~0ull ? -1 : (int32_t)(uint32_t)k;
+    return k == ~0ull ? -1 : Key<real>::partner(k);
 }
 
 // o-bin (with the instance's offset) of a position.
@@ -2112,7 +2448,7 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
     int32_t npj_ = -1;
     if (i_first < end) {
         Rec<real>::load(a.rec, i_first, nx_, ny_, nz_, nid_, nvx_, nvy_, nvz_, nfl_);
-        npj_ = partner_of<real>(a, i_first);
+        npj_ = partner_of<real>(a, I, i_first);
     }
 #pragma unroll 1
     for (int r = 0; r < kMoveRec; ++r) {
@@ -2124,7 +2460,7 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
         const int32_t j_pre = npj_;
         if (r + 1 < kMoveRec && i + 1 < end) {
             Rec<real>::load(a.rec, i + 1, nx_, ny_, nz_, nid_, nvx_, nvy_, nvz_, nfl_);
-            npj_ = partner_of<real>(a, i + 1);
+            npj_ = partner_of<real>(a, I, i + 1);
         }
         if (i < end) {
             const int64_t dst = reorder ? i : (int64_t)a.src[i];
@@ -2141,7 +2477,7 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
                 const real dt = I.dt;
                 const real mi = has_mass ? a.rmass[i] : I.mass;
                 const int32_t j = j_pre;
-                bool mutual = j >= 0 && partner_of<real>(a, j) == (int32_t)i;
+                bool mutual = j >= 0 && partner_of<real>(a, I, j) == (int32_t)i;
                 ghave += j >= 0 ? 1.0 : 0.0;
                 real nx = x, ny = y, nz = z, nvx = vx, nvy = vy, nvz = vz;
                 double virx = 0, viry = 0, virz = 0;
@@ -2474,15 +2810,22 @@ __global__ void __launch_bounds__(256) k_prep(Inst<real>* inst, const double* gp
     __shared__ double lds[16];
     __shared__ bool last;
     Inst<real>& I = inst[blockIdx.y];
-    if (!(I.flags & (TPKMC_ADAPTIVE_DT | kSplit))) return;  // whole work-group
+    if (!(I.flags & (TPKMC_ADAPTIVE_DT | kSplit | kSubgrid))) return;  // whole work-group
     double v = 0.0;
+    bool strayed = false;
     const double* g0 = gpart + (int64_t)I.blk0 * kGPart;
     for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < I.nblk; b += gridDim.x * blockDim.x)
-        v = fmax(v, g0[(int64_t)b * kGPart + GP_VMAX0]);
+    {
+        const double g = g0[(int64_t)b * kGPart + GP_VMAX0];
+        v = fmax(v, fabs(g));
+        strayed |= signbit(g);
+    }
     v = block_max(v, lds);
+    const bool any_strayed = __syncthreads_or(strayed) != 0;
     if (threadIdx.x == 0) {
         // Non-negative doubles order like their bit patterns.
         atomicMax(&I.run_v2, (unsigned long long)__double_as_longlong(v));
+        if (any_strayed) atomicOr(&I.strayed, 1u);
         __threadfence();
         last = atomicAdd(&I.prep_done, 1u) == gridDim.x - 1;
     }
@@ -2492,6 +2835,11 @@ __global__ void __launch_bounds__(256) k_prep(Inst<real>* inst, const double* gp
     const double vmax2 = __longlong_as_double((long long)atomicExch(&I.run_v2, 0ull));
     atomicExch(&I.prep_done, 0u);
     I.vmax2_d = vmax2;
+    // Largest speed among the records of the sub-grid, the bound of its
+    // reach; none where a particle lies outside the box along a periodic axis
+    // (its cell does not say where its nearest image is).
+    const double vr = (I.flags & kSplit) ? (double)I.vc2 : vmax2;
+    I.vreach = atomicExch(&I.strayed, 0u) ? (real)INFINITY : (real)(sqrt(vr) * (1.0 + 1e-6));
     if (I.flags & TPKMC_ADAPTIVE_DT) {
         double dt = I.dt_cap;
         if (I.dx_d > 0.0 && vmax2 > 0.0) {
@@ -2552,33 +2900,43 @@ void launch_speed_stats(const StepArgs<real>& a, hipStream_t s) {
 }
 template <typename real>
 void launch_search(const StepArgs<real>& a, int block, int group, hipStream_t s) {
-    constexpr bool half = std::is_same<real, float>::value;
-    const int lanes = kBlock / group;
-    const int bs = block < lanes ? block : lanes;
-    const unsigned grid = (unsigned)a.nblk * (unsigned)(lanes / bs);
-    const size_t lds = half ? (size_t)(bs / kWave) * kStageBytesPerWave : 0;  // staging buffers
-    if (group == 4) hipLaunchKernelGGL((k_search<real, half, 4>), dim3(grid), dim3(bs), lds, s, a);
-    else if (group == 2) hipLaunchKernelGGL((k_search<real, half, 2>), dim3(grid), dim3(bs), lds, s, a);
-    else hipLaunchKernelGGL((k_search<real, half, 1>), dim3(grid), dim3(bs), lds, s, a);
+    if constexpr (std::is_same<real, float>::value) {
+        const int lanes = kBlock / group;
+        const int bs = block < lanes ? block : lanes;
+        const unsigned grid = (unsigned)a.nblk * (unsigned)(lanes / bs);
+        const size_t lds = (size_t)(bs / kWave) * kStageBytesPerWave;  // staging buffers
+        if (group == 4) hipLaunchKernelGGL((k_search<4>), dim3(grid), dim3(bs), lds, s, a);
+        else if (group == 2) hipLaunchKernelGGL((k_search<2>), dim3(grid), dim3(bs), lds, s, a);
+        else hipLaunchKernelGGL((k_search<1>), dim3(grid), dim3(bs), lds, s, a);
+    }
+}
+constexpr int kTileParts = 16, kTileWaves = 4096;
+template <typename real>
+void launch_search_tiles(const StepArgs<real>& a, hipStream_t s) {
+    // Small launches split each tile's neighbourhood over several waves, up
+    // to kTileWaves waves in all (4 a work-group).
+    const int parts = std::max(1, std::min(kTileParts, kTileWaves / (4 * a.nblk)));
+    hipLaunchKernelGGL(k_search_tiles<real>, dim3(a.nblk, parts), dim3(kBlock), 0, s, a);
 }
 template <typename real>
-void launch_search_mix(const StepArgs<real>& a, int block, int n_inst, bool split, hipStream_t s) {
-    constexpr bool half = std::is_same<real, float>::value;
-    const int lanes = kBlock / 2;
-    const int bs = block < lanes ? block : lanes;
-    const unsigned grid = (unsigned)a.nblk * (unsigned)(lanes / bs);
-    const size_t lds = half ? (size_t)(bs / kWave) * kStageBytesPerWave : 0;
-    hipLaunchKernelGGL((k_search<real, half, 2, true>), dim3(grid), dim3(bs), lds, s, a);
+void launch_search_ties(const StepArgs<real>& a, hipStream_t s) {
+    if constexpr (std::is_same<real, double>::value) {
+        const unsigned grid = (unsigned)std::max(1, std::min(1024, a.nblk));
+        hipLaunchKernelGGL(k_search_ties<real>, dim3(grid), dim3(kBlock), 0, s, a);
+    }
+}
+template <typename real>
+void launch_search_mix(const StepArgs<real>& a, int n_inst, bool split, hipStream_t s) {
+    hipLaunchKernelGGL(k_search_mix<real>, dim3(a.nblk), dim3(kBlock), 0, s, a);
     if (split) {
         const unsigned fg = (unsigned)std::max(1, std::min(2048, a.nblk));
-        hipLaunchKernelGGL((k_search_fast<real, half, true>), dim3(fg), dim3(256), 0, s, a, n_inst);
+        hipLaunchKernelGGL((k_search_fast<real, true>), dim3(fg), dim3(256), 0, s, a, n_inst);
     }
 }
 template <typename real>
 void launch_search_fast(const StepArgs<real>& a, int n_inst, hipStream_t s) {
-    constexpr bool half = std::is_same<real, float>::value;
     const unsigned fg = (unsigned)std::max(1, std::min(2048, a.nblk));
-    hipLaunchKernelGGL((k_search_fast<real, half>), dim3(fg), dim3(256), 0, s, a, n_inst);
+    hipLaunchKernelGGL((k_search_fast<real>), dim3(fg), dim3(256), 0, s, a, n_inst);
 }
 template <typename real>
 void launch_random_pairs(const StepArgs<real>& a, hipStream_t s) {

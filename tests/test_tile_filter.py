@@ -1,0 +1,117 @@
+"""The tile search's filter never loses a candidate.
+
+The search evaluates three bilinear forms per pair on f16 vectors, each
+lowered by a bound of its rounding error, and tests exactly only the pairs
+whose forms are all negative.  Here the same forms are built in numpy (f16
+rounding of the same quantities, products summed in FP32) over the ranges the
+filter takes: thermal gases, cold ones, cold ones with a bulk flow, mixtures
+of hot and cold, tiles of one c-bin and tiles that span many.  Every pair
+that meets the criteria exactly, in float64, must pass; and the filter must
+reject most of the others, or it would be no filter."""
+import numpy as np
+import pytest
+
+KAPPA = 256.0
+E = 1.0 / 2048.0
+E2, E3, E6, ABS = 3.5 * E, 5.0 * E / KAPPA, 6.6 * E, 1e-6
+F = np.float32
+
+
+def f16(a):
+    return np.asarray(a, dtype=np.float16).astype(F)
+
+
+def split(v):
+    hi = f16(v)
+    return hi + f16(v - hi)
+
+
+def up(v):
+    return f16(v * F(1.0 + 2.0 * E) + F(1e-7))
+
+
+def record(X, V, hd2):
+    X, V = X.astype(F), V.astype(F)
+    x, v = f16(X), f16(V)
+    xm, v1 = np.abs(X).max(1), np.abs(V).sum(1)
+    xv, vv, xx = (x * v).sum(1), (v * v).sum(1), (x * x).sum(1)
+    lin = F(ABS) * (xm + v1) + F(ABS)
+    m = F(E2) * xm * v1 + lin
+    return dict(x=x, v=v, xm=xm, v1=v1, p=split(xv - m), q=split(-vv / F(KAPPA) - xv - (F(E3) * v1 * v1 + m)),
+                r=split(xx - (F(2.01 / KAPPA ** 2) * vv + F(hd2)) - (F(E6) * xm * xm + lin)))
+
+
+def forms(i, j):
+    """P, Q, R of every (i, j), the sums in FP32."""
+    f = f16(F(2.0 / KAPPA) * i["v"] + i["x"])
+    mv, mx = -up(F(E2) * i["v1"]), -up(F(E2) * i["xm"])
+    mq = -up(F(E2) * i["xm"] + F(2.0 * E3) * i["v1"])
+    xm, v1 = up(j["xm"]), up(j["v1"])
+    P = i["p"][:, None] + j["p"] - i["v"] @ j["x"].T - i["x"] @ j["v"].T + mv[:, None] * xm + mx[:, None] * v1
+    Q = i["q"][:, None] + j["q"] + i["v"] @ j["x"].T + f @ j["v"].T + mv[:, None] * xm + mq[:, None] * v1
+    R = i["r"][:, None] + j["r"] - F(2.0) * (i["x"] @ j["x"].T) - up(F(2.0 * E6) * i["xm"])[:, None] * xm
+    return P, Q, R
+
+
+CASES = {
+    # speed of the gas and of its hot part, bulk speed (widths per step), D
+    # (widths), extent of the tile along x (widths)
+    "thermal": (0.2, 0.2, 0.0, 0.25, 1.0),
+    "thermal, wide D": (0.17, 0.17, 0.0, 25.0, 3.0),
+    "cold": (5e-4, 5e-4, 0.0, 0.6, 9.0),
+    "very cold": (1e-6, 1e-6, 0.0, 0.6, 9.0),
+    "cold with a bulk flow": (2e-4, 2e-4, 0.35, 0.25, 1.0),
+    "hot in cold": (5e-4, 0.5, 0.0, 0.6, 6.0),
+    "fast": (0.4, 0.4, 0.0, 0.1, 2.0),
+    "tiny D": (0.2, 0.2, 0.0, 1e-3, 1.0),
+    "long tile": (0.1, 0.1, 0.0, 0.5, 30.0),
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("seed", [1, 2, 3])
+def test_no_candidate_is_lost(case, seed):
+    cold, hot, bulk, D, span = CASES[case]
+    rng = np.random.default_rng(seed)
+    ni, nj = 64, 20000
+
+    def draw(n, ext):
+        X = np.stack([rng.uniform(-0.5 * ext, 0.5 * ext, n), rng.uniform(-1.5, 1.5, n), rng.uniform(-1.5, 1.5, n)], 1)
+        s = np.where(rng.uniform(size=n) < 0.3, hot, cold) / np.sqrt(3.0)
+        V = rng.normal(size=(n, 3)) * s[:, None] + bulk * np.array([0.6, -0.7, 0.3])
+        return X, V * KAPPA
+
+    Xi, Vi = draw(ni, span)
+    Xj, Vj = draw(nj, span + 2.0)
+    # Half of the partners are set up to be near misses and near hits: placed
+    # where they meet a record of the tile within the step, close to D.
+    k = rng.integers(0, ni, nj // 2)
+    u = Vi[k] - Vj[:nj // 2]
+    un = np.linalg.norm(u, axis=1, keepdims=True)
+    e = np.cross(u, rng.normal(size=u.shape))
+    e /= np.linalg.norm(e, axis=1, keepdims=True)
+    t = rng.uniform(-0.01, 1.01, size=(len(k), 1))
+    miss = D * (1.0 + rng.normal(size=(len(k), 1)) * 10.0 ** rng.uniform(-4, 0, size=(len(k), 1)))
+    Xj[:nj // 2] = Xi[k] + u * t / KAPPA - e * np.minimum(np.abs(miss), 2.0)
+    assert (un > 0).all()
+    # As the kernel takes them: FP32, relative to the tile's mean velocity.
+    vo = Vi.mean(0)
+    Xi, Xj = Xi.astype(F).astype(float), Xj.astype(F).astype(float)
+    Vi, Vj = (Vi - vo).astype(F).astype(float), (Vj - vo).astype(F).astype(float)
+    hd2 = min(0.5001 * D * D, 30000.0)
+    tame = np.abs(Vj).sum(1) <= 512.0
+    Xj, Vj = Xj[tame], Vj[tame]
+    assert (np.abs(Vi).sum(1) <= 512.0).all()
+    P, Q, R = forms(record(Xi, Vi, hd2), record(Xj, Vj, hd2))
+    passed = (P < 0) & (Q < 0) & (R < 0)
+    r = Xi[:, None] - Xj[None]
+    w = Vi[:, None] - Vj[None]
+    s0, ww = (r * w).sum(2), (w * w).sum(2)
+    tp = -s0 / ww * KAPPA  # in steps
+    d2 = ((r + w * (tp / KAPPA)[..., None]) ** 2).sum(2)
+    cand = (s0 < 0) & (s0 + ww / KAPPA > 0) & (d2 <= D * D)
+    assert cand.sum() > 20
+    lost = cand & ~passed
+    assert not lost.any(), f"{lost.sum()} of {cand.sum()} candidates lost"
+    far = passed[:, tame.nonzero()[0] >= nj // 2] if tame.all() else passed
+    assert far.mean() < 0.35, f"the filter passes {far.mean():.2f} of all pairs"
