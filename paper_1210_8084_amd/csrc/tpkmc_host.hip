@@ -441,7 +441,7 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
             for (int b = 0; b < naxes; ++b)
                 if (0.5 * w[b] >= kSortCellD * D && (int64_t)d.n[b] * 2 <= 1 << 24 && (a < 0 || w[b] > w[a])) a = b;
             if (a < 0) break;
-            d.k[a] *= 2;
+            d.kl[a] += 1;
             d.n[a] *= 2;
             w[a] *= 0.5;
             dens *= 0.5;
@@ -449,6 +449,7 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
         }
         for (int a = 0; a < 3; ++a) d.inv_w[a] = (real)((double)d.n[a] / (g.hi[a] - g.lo[a]));
     }
+    for (int a = 0; a < 3; ++a) d.w_sort[a] = (real)((g.hi[a] - g.lo[a]) / d.n[a]);
 }
 
 // Validates one instance and fills its device descriptor, except the
@@ -494,7 +495,6 @@ int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, 
         const double L = g.hi[a] - g.lo[a];
         const int32_t nc = nref ? nref[a] : g.ncell[a];
         d.n[a] = d.nl[a] = nc;
-        d.k[a] = 1;
         d.ncfg[a] = g.ncell[a];
         d.inv_wc[a] = (real)((double)g.ncell[a] / L);
         d.no[a] = g.nobin[a];

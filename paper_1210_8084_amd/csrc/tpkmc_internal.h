@@ -89,12 +89,13 @@ struct Inst {
     // c-bin).
     float tile_s;
     // Sub-grids (kSubgrid): nl[] c-bins per axis (the refined ones of split
-    // c-bins), each cut into k[] sort cells, n[a] = nl[a] k[a]; inv_wl: c-bins
-    // per unit length.  Without, k is 1 and n, nl are the same.  vreach: the
+    // c-bins), each cut into 2^kl[] sort cells, n[a] = nl[a] 2^kl[a]; inv_wl:
+    // c-bins per unit length.  Without, kl is 0 and n, nl are the same.  vreach: the
     // largest speed among the records sorted on them (infinite: unknown),
     // strayed: prep's flag for that.
-    int32_t nl[3], k[3];
+    int32_t nl[3], kl[3];
     real inv_wl[3];
+    real w_sort[3];           // width of a sort cell
     real vreach;
     uint32_t strayed;
     int64_t base;             // record index of the instance's first: base + start[]

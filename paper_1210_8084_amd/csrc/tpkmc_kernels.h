@@ -81,6 +81,39 @@ __device__ __forceinline__ void load_pv(const double* r, int32_t i, double& x, d
     Rec<double>::load(r, i, x, y, z, id, vx, vy, vz, fl);
 }
 
+// A record as it was loaded, in whole vectors: a value carried round a loop
+// in them is not copied (and so waited for) before it is used.
+template <typename real> struct RawRec;
+
+template <> struct RawRec<float> {
+    typedef float vec __attribute__((ext_vector_type(4)));
+    vec a, b;
+    __device__ __forceinline__ void load(const float* r, int32_t i) {
+        const char* p = reinterpret_cast<const char*>(r) + (uint32_t)i * 32u;
+        a = *reinterpret_cast<const vec*>(p);
+        b = *reinterpret_cast<const vec*>(p + 16);
+    }
+    __device__ __forceinline__ void get(float p[3], float v[3]) {
+        asm volatile("" : "+v"(a), "+v"(b));  // keeps the vectors whole
+        p[0] = a.x; p[1] = a.y; p[2] = a.z;
+        v[0] = b.x; v[1] = b.y; v[2] = b.z;
+    }
+};
+
+template <> struct RawRec<double> {
+    typedef double vec __attribute__((ext_vector_type(2)));
+    vec a, b, c, d;
+    __device__ __forceinline__ void load(const double* r, int32_t i) {
+        const vec* p = reinterpret_cast<const vec*>(r + 8 * (int64_t)i);
+        a = p[0]; b = p[1]; c = p[2]; d = p[3];
+    }
+    __device__ __forceinline__ void get(double p[3], double v[3]) {
+        asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+        p[0] = a.x; p[1] = a.y; p[2] = b.x;
+        v[0] = c.x; v[1] = c.y; v[2] = d.x;
+    }
+};
+
 // ---------------------------------------------------------------- helpers
 // Bin along one axis: floor((x - lo) * n / L) clamped into [0, n - 1].
 template <typename real>
@@ -92,13 +125,13 @@ __device__ __forceinline__ int axis_bin(real x, real lo, real inv_w, int n) {
 }
 
 // Sort cell of a coordinate along axis ax: its c-bin (refined for the slow
-// particles of split c-bins), cut into k equal parts where the instance has
+// particles of split c-bins), cut into 2^kl equal parts where the instance has
 // sub-grids.  The c-bin is axis_bin's own, so a sub-grid never moves a
 // particle to another c-bin.
 template <typename real>
 __device__ __forceinline__ int sort_bin(const Inst<real>& I, int ax, real x) {
     const int c = axis_bin(x, I.lo[ax], I.inv_wl[ax], I.nl[ax]);
-    const int k = I.k[ax];
+    const int k = 1 << I.kl[ax];
     if (k == 1) return c;
     const real f = ((x - I.lo[ax]) * I.inv_wl[ax] - (real)c) * (real)k;
     return c * k + (f >= real(1) ? min((int)fmin(f, (real)k), k - 1) : 0);
@@ -415,10 +448,76 @@ __global__ void __launch_bounds__(kWave) k_key(StepArgs<real> a) {
     }
 }
 
+// Neighbour index along one axis (offset d in -1..1): whether it exists and
+// is not a repeat of another offset (periodic axes with 1 or 2 bins), and the
+// wrapped index.
+__device__ __forceinline__ bool axis_nb(int c, int d, int n, bool periodic, int& out) {
+    int v = c + d;
+    if (periodic) {
+        if (n == 1 && d != 0) return false;
+        if (n == 2 && d == 1) return false;
+        v = v < 0 ? v + n : (v >= n ? v - n : v);
+    } else if (v < 0 || v >= n) {
+        return false;
+    }
+    out = v;
+    return true;
+}
+
+// x-extent of the neighbourhood as at most two contiguous bin ranges; the
+// first always contains cx.
+__device__ __forceinline__ int x_ranges(int cx, int n, bool periodic, int xa[2], int xb[2]) {
+    if (periodic && n > 3 && cx == 0) { xa[0] = 0; xb[0] = 1; xa[1] = n - 1; xb[1] = n - 1; return 2; }
+    if (periodic && n > 3 && cx == n - 1) { xa[0] = n - 2; xb[0] = n - 1; xa[1] = 0; xb[1] = 0; return 2; }
+    if (periodic && n <= 3) { xa[0] = 0; xb[0] = n - 1; return 1; }
+    xa[0] = cx > 0 ? cx - 1 : 0;
+    xb[0] = cx < n - 1 ? cx + 1 : n - 1;
+    return 1;
+}
+
+// The unordered pairs of c-bin c with itself and with its neighbours, each
+// pair of c-bins once (the search's TPKMC_CNT_TESTS), from the sort cells'
+// prefix.  With sub-grids a c-bin spans many rows of sort cells, which the
+// 64 lanes of a wave share (c is then the same in all of them); without, each
+// lane takes a c-bin of its own.  Returns the lane's (the wave's) count.
+template <typename real>
+__device__ double cbin_tests(const StepArgs<real>& a, const Inst<real>& I, int c, int lane) {
+    const int nl[3] = {I.nl[0], I.nl[1], I.nl[2]}, k[3] = {1 << I.kl[0], 1 << I.kl[1], 1 << I.kl[2]};
+    const bool sub = (I.flags & kSubgrid) != 0;
+    const int x = c % nl[0], y = c / nl[0] % nl[1], z = c / nl[0] / nl[1], nf = k[1] * k[2];
+    int xa[2], xb[2];
+    const int nxr = x_ranges(x, nl[0], I.bc[0] == TPKMC_BC_PERIODIC, xa, xb);
+    double own = 0.0, other = 0.0;
+    for (int t = sub ? lane : 0; t < 9 * nf; t += sub ? kWave : 1) {
+        const int r = t >> (I.kl[1] + I.kl[2]), f = t & (nf - 1);
+        int yy, zz;
+        if (!axis_nb(z, r / 3 - 1, nl[2], I.bc[2] == TPKMC_BC_PERIODIC, zz)) continue;
+        if (!axis_nb(y, r % 3 - 1, nl[1], I.bc[1] == TPKMC_BC_PERIODIC, yy)) continue;
+        const int d = (yy + nl[1] * zz) - (y + nl[1] * z);
+        if (d < 0) continue;  // counted from there
+        const int32_t* row = a.start + I.cell_off +
+                             (int64_t)I.n[0] * row_of(I, yy * k[1] + (f & (k[1] - 1)), zz * k[2] + (f >> I.kl[1]));
+        auto records = [&](int c0, int c1) { return (double)(row[(int64_t)(c1 + 1) * k[0]] - row[(int64_t)c0 * k[0]]); };
+        if (d == 0) own += records(x, x);
+        for (int q = 0; q < nxr; ++q) {
+            const int a0 = d > 0 ? xa[q] : max(xa[q], x + 1);
+            if (a0 <= xb[q]) other += records(a0, xb[q]);
+        }
+    }
+    if (sub) {
+        own = wave_reduce<false>(own);
+        other = wave_reduce<false>(other);
+    }
+    return own * (0.5 * (own - 1.0) + other);
+}
+
 // ---------------------------------------------------------------- 3. scatter
 // Caller-order particle -> its c-bin-ordered record.  The permutation back to
 // the caller's order is kept only when the state is written back in that
-// order (without TPKMC_ALLOW_REORDER).
+// order (without TPKMC_ALLOW_REORDER).  The work-groups of a tile search's
+// instance also share the count of its pair tests: here other waves hide its
+// loads (in the search, with 3 waves a SIMD, it cost 0.03 ms of the FP64
+// blast's 0.4).
 template <typename real>
 __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
     const Blk bt = a.blk[blockIdx.x];
@@ -442,6 +541,25 @@ __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
         const real dt = I.dt;
         fast = alive && fin &&
                (fabs(vx) * dt > I.w[0] || fabs(vy) * dt > I.w[1] || fabs(vz) * dt > I.w[2]);
+    }
+    if (I.flags & kTiles) {
+        const int64_t ncb = (int64_t)I.nl[0] * I.nl[1] * I.nl[2];
+        const bool sub = (I.flags & kSubgrid) != 0;
+        const int lane = threadIdx.x & (kWave - 1);
+        const int64_t me = (int64_t)((int)blockIdx.x - I.blk0) * kBlock + threadIdx.x, all = (int64_t)I.nblk * kBlock;
+        double tests = 0.0;
+        if (sub) {
+            for (int64_t c = me / kWave; c < ncb; c += all / kWave) {
+                const double t = cbin_tests(a, I, __builtin_amdgcn_readfirstlane((int)c), lane);
+                tests += lane == 0 ? t : 0.0;
+            }
+        } else {
+            for (int64_t c = me; c < ncb; c += all) tests += cbin_tests(a, I, (int)c, lane);
+        }
+        if (__ballot(tests != 0.0)) {
+            tests = wave_reduce<false>(tests);
+            if (lane == 0) unsafeAtomicAdd(a.gpart + (int64_t)blockIdx.x * kGPart + GP_TESTS2, 2.0 * tests);
+        }
     }
     const uint64_t fm = __ballot(fast);
     if (fm && (threadIdx.x & 63) == __ffsll((long long)fm) - 1)
@@ -666,33 +784,6 @@ __device__ __forceinline__ unsigned long long key_now(const StepArgs<real>& a, i
     return __hip_atomic_load(a.bkey + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Neighbour index along one axis (offset d in -1..1): whether it exists and
-// is not a repeat of another offset (periodic axes with 1 or 2 bins), and the
-// wrapped index.
-__device__ __forceinline__ bool axis_nb(int c, int d, int n, bool periodic, int& out) {
-    int v = c + d;
-    if (periodic) {
-        if (n == 1 && d != 0) return false;
-        if (n == 2 && d == 1) return false;
-        v = v < 0 ? v + n : (v >= n ? v - n : v);
-    } else if (v < 0 || v >= n) {
-        return false;
-    }
-    out = v;
-    return true;
-}
-
-// x-extent of the neighbourhood as at most two contiguous bin ranges; the
-// first always contains cx.
-__device__ __forceinline__ int x_ranges(int cx, int n, bool periodic, int xa[2], int xb[2]) {
-    if (periodic && n > 3 && cx == 0) { xa[0] = 0; xb[0] = 1; xa[1] = n - 1; xb[1] = n - 1; return 2; }
-    if (periodic && n > 3 && cx == n - 1) { xa[0] = n - 2; xb[0] = n - 1; xa[1] = 0; xb[1] = 0; return 2; }
-    if (periodic && n <= 3) { xa[0] = 0; xb[0] = n - 1; return 1; }
-    xa[0] = cx > 0 ? cx - 1 : 0;
-    xb[0] = cx < n - 1 ? cx + 1 : n - 1;
-    return 1;
-}
-
 // Visits the record ranges of the neighbourhood of record i (bin cx, cy, cz).
 // HALF: only pairs (i, j) not visited from j's side -- bins of larger index
 // and, in i's own bin, records after i -- so every unordered pair is met once.
@@ -740,17 +831,18 @@ __device__ __forceinline__ void for_logical(const StepArgs<real>& a, const Inst<
     const int bx = axis_bin(x, I.lo[0], I.inv_wl[0], I.nl[0]), by = axis_bin(y, I.lo[1], I.inv_wl[1], I.nl[1]),
               bz = axis_bin(z, I.lo[2], I.inv_wl[2], I.nl[2]);
     int xa[2], xb[2];
+    const int k[3] = {1 << I.kl[0], 1 << I.kl[1], 1 << I.kl[2]};
     const int nxr = x_ranges(bx, I.nl[0], per[0], xa, xb);
     for (int r = 0; r < 9; ++r) {
         int yy, zz;
         if (!axis_nb(bz, r / 3 - 1, I.nl[2], per[2], zz)) continue;
         if (!axis_nb(by, r % 3 - 1, I.nl[1], per[1], yy)) continue;
-        for (int f = 0; f < I.k[1] * I.k[2]; ++f) {
-            const int64_t row = I.cell_off + (int64_t)I.n[0] * row_of(I, yy * I.k[1] + f % I.k[1],
-                                                                      zz * I.k[2] + f / I.k[1]);
+        for (int f = 0; f < k[1] * k[2]; ++f) {
+            const int64_t row = I.cell_off + (int64_t)I.n[0] * row_of(I, yy * k[1] + (f & (k[1] - 1)),
+                                                                      zz * k[2] + (f >> I.kl[1]));
             for (int q = 0; q < nxr; ++q)
-                visit((int32_t)(I.base + a.start[row + (int64_t)xa[q] * I.k[0]]),
-                      (int32_t)(I.base + a.start[row + (int64_t)(xb[q] + 1) * I.k[0]]));
+                visit((int32_t)(I.base + a.start[row + (int64_t)xa[q] * k[0]]),
+                      (int32_t)(I.base + a.start[row + (int64_t)(xb[q] + 1) * k[0]]));
         }
     }
 }
@@ -910,6 +1002,13 @@ __device__ __forceinline__ void tile_operands(const uint32_t w[8], half8_t out[2
     out[1] = __builtin_bit_cast(half8_t, *reinterpret_cast<uint4*>(t1));
 }
 
+// Each lane's value of lane l & 31 (out[0]) and of lane 32 + (l & 31) (out[1]).
+__device__ __forceinline__ void both_halves(int32_t v, int32_t out[2]) {
+    const auto s = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    out[0] = (int32_t)s[0];
+    out[1] = (int32_t)s[1];
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp_movef(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
@@ -936,12 +1035,12 @@ struct TileLds {
     uint2 hit[kHitQueue];
     unsigned long long key[kWave];
     real pv[6][kWave];
-    uint2 blk[kWave];  // x: record, y: its image (2 bits per axis, shift + 1)
+    uint2 blk[kWave];  // x: record, y: its image (2 bits per axis, shift + 1) | (x c-bin + 2) << 6
 };
 // Image code of a hit: 2 bits per axis, the box's shift + 1 at which j was
-// met, 3 where any will do; bit 6: the x axis goes by image (a periodic axis
-// of at most three c-bins, all of them neighbours), not by c-bin.
-constexpr uint32_t kCodeAny = 3u, kCodeImagedX = 1u << 6;
+// met, 3 where any will do.
+constexpr uint32_t kCodeAny = 3u, kCodeAllAny = 63u;
+constexpr uint32_t kCodeHome = 1u | 1u << 2 | 1u << 4;  // no shift
 
 // Periodic axes of so few c-bins that the c-bins do not fix which image of a
 // neighbour is the near one: the images are visited one by one ("imaged"),
@@ -956,11 +1055,13 @@ __device__ __forceinline__ int image_of(float r, float, float, float invL) {
     return k > 0.0f ? 1 : (k < 0.0f ? -1 : 0);
 }
 
-// Exact tests of `count` queued pairs, one per lane.
+// Exact tests of `count` queued pairs, one per lane.  (Loading a batch's
+// partners when it leaves the queue and testing it when the next one does
+// hides the wait, but its registers spill: 4.96 ms against 4.42 on the planar
+// equilibration of 2e7 particles, where every particle has 14 candidates.)
 template <typename real>
-__device__ __forceinline__ void tile_hits(const StepArgs<real>& a, const Inst<real>& I, const Geo<real>& G,
-                                          bool by_time, int32_t wbase, TileLds<real>& L, int count, int lane,
-                                          int32_t& nc) {
+__device__ __forceinline__ void tile_hits(const StepArgs<real>& a, const Geo<real>& G, bool by_time, int32_t wbase,
+                                          TileLds<real>& L, int count, int lane, int32_t& nc) {
     if (lane >= count) return;
     const uint2 e = L.hit[lane];
     const int il = (int)(e.x & 63u);
@@ -970,20 +1071,13 @@ __device__ __forceinline__ void tile_hits(const StepArgs<real>& a, const Inst<re
     const unsigned long long kj = key_now(a, j);
     const real xi = L.pv[0][il], yi = L.pv[1][il], zi = L.pv[2][il];
     const uint32_t code = e.x >> 6;
-    const real r[3] = {xi - xj, yi - yj, zi - zj};
-    if (code & kCodeImagedX) {
-        const uint32_t c = code & 3u;
-        if (c != kCodeAny && image_of(r[0], G.L[0], G.halfL[0], G.invL[0]) != (int)c - 1) return;
-    } else {
-        // The tile's x range is wider than i's own: neighbouring c-bins only.
-        const int bi = axis_bin(xi, I.lo[0], I.inv_wl[0], I.nl[0]), bj = axis_bin(xj, I.lo[0], I.inv_wl[0], I.nl[0]);
-        const int d = bj + ((int)(code & 3u) - 1) * I.nl[0] - bi;
-        if (d < -1 || d > 1) return;
-    }
+    if (code != kCodeAllAny) {
+        const real r[3] = {xi - xj, yi - yj, zi - zj};
 #pragma unroll
-    for (int ax = 1; ax < 3; ++ax) {
-        const uint32_t c = (code >> (2 * ax)) & 3u;
-        if (c != kCodeAny && image_of(r[ax], G.L[ax], G.halfL[ax], G.invL[ax]) != (int)c - 1) return;
+        for (int ax = 0; ax < 3; ++ax) {
+            const uint32_t c = (code >> (2 * ax)) & 3u;
+            if (c != kCodeAny && image_of(r[ax], G.L[ax], G.halfL[ax], G.invL[ax]) != (int)c - 1) return;
+        }
     }
     real value;
     if (!test_pair(G, by_time, xi, yi, zi, L.pv[3][il], L.pv[4][il], L.pv[5][il], xj, yj, zj, vxj, vyj, vzj, value))
@@ -1005,7 +1099,7 @@ struct TileAxis {
 // candidate can be away (sub-grids), at least 1.
 template <typename real>
 __device__ __forceinline__ TileAxis tile_axis(const Inst<real>& I, int ax, bool periodic, int c, int chi, int m) {
-    const int n = I.n[ax], nl = I.nl[ax], k = I.k[ax];
+    const int n = I.n[ax], nl = I.nl[ax], kl = I.kl[ax];
     TileAxis A;
     const bool near = 2 * ((int64_t)m + 1) < n;  // the nearest image is known
     A.images = periodic && nl <= 3 && !near ? 3 : 1;
@@ -1016,8 +1110,8 @@ __device__ __forceinline__ TileAxis tile_axis(const Inst<real>& I, int ax, bool 
     }
     int lo = c - m, hi = chi + m;
     if (!periodic || nl > 3) {
-        lo = max(lo, (c / k - 1) * k);
-        hi = min(hi, (chi / k + 2) * k - 1);
+        lo = max(lo, ((c >> kl) - 1) << kl);
+        hi = min(hi, (((chi >> kl) + 2) << kl) - 1);
     }
     if (!periodic) {
         lo = max(lo, 0);
@@ -1059,23 +1153,35 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
     const float hd2 = fminf(0.5001f * (float)(I.D2 * sx * sx), 30000.0f);
     const real lo[3] = {I.lo[0], I.lo[1], I.lo[2]}, hi[3] = {I.hi[0], I.hi[1], I.hi[2]};
     const real iw[3] = {I.inv_w[0], I.inv_w[1], I.inv_w[2]};
+    const real ws[3] = {I.w_sort[0], I.w_sort[1], I.w_sort[2]};
     const real iwl[3] = {I.inv_wl[0], I.inv_wl[1], I.inv_wl[2]};
-    const bool four[3] = {G.per[0] && I.nl[0] == 4, G.per[1] && I.nl[1] == 4, G.per[2] && I.nl[2] == 4};
+    const int nl0 = I.nl[0];
+    // The box along the periodic axes; records outside are wild.
+    real box_lo[3], box_hi[3];
+    bool four[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        box_lo[ax] = G.per[ax] ? lo[ax] : -real(INFINITY);
+        box_hi[ax] = G.per[ax] ? hi[ax] : real(INFINITY);
+        four[ax] = G.per[ax] && I.nl[ax] == 4;
+    }
+    const bool any_four = four[0] || four[1] || four[2];
     auto untame = [&](const real p[3], const float X[3], const float V[3], float vcap) {
         const float xm = fmaxf(fmaxf(fabsf(X[0]), fabsf(X[1])), fabsf(X[2]));
-        bool w = !(xm <= kTileXMax && fabsf(V[0]) + fabsf(V[1]) + fabsf(V[2]) <= vcap);
+        bool t = (xm <= kTileXMax) & (fabsf(V[0]) + fabsf(V[1]) + fabsf(V[2]) <= vcap);
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            w |= G.per[ax] && !(p[ax] >= lo[ax] && p[ax] < hi[ax]);
-            if (four[ax]) {
-                const real t = (p[ax] - lo[ax]) * iwl[ax], f = t - floor(t);
-                w |= !(f > real(1e-4) && f < real(1.0 - 1e-4));
+        for (int ax = 0; ax < 3; ++ax) t &= (p[ax] >= box_lo[ax]) & (p[ax] < box_hi[ax]);
+        if (any_four)
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                const real u = (p[ax] - lo[ax]) * iwl[ax], f = u - floor(u);
+                t &= !four[ax] | ((f > real(1e-4)) & (f < real(1.0 - 1e-4)));
             }
-        }
-        return w;
+        return !t;
     };
     int32_t nc = 0;
     int nq = 0;  // queued hits (wave-uniform)
+    const int j_row = 4 * (lane >> 5);  // the lane's first row of a product
     uint64_t pending = __ballot(valid);
     while (pending) {
         // One group of lanes per row of sort cells: consecutive lanes with
@@ -1091,12 +1197,12 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
         const int32_t after = wbase + lead;  // partners come after the first record (half search)
         // Tile origin: the middle of the group's cells; its mean velocity.
         real org[3], Ls[3], vo[3];
-        float xabs = 0.0f;  // rounding of the scaled origins, in units of e
+        float xabs = 0.0f;  // rounding of a shifted origin, in units of e (unshifted it is i's and j's alike)
         const float inv = 1.0f / (float)__popcll(gm);
         const real mid[3] = {real(0.5) * (real)(cxf + cxl + 1), real(0.5) + (real)gcy, real(0.5) + (real)gcz};
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            org[ax] = (lo[ax] + mid[ax] / iw[ax]) * sx;
+            org[ax] = (lo[ax] + mid[ax] * ws[ax]) * sx;
             Ls[ax] = G.L[ax] * sx;
             vo[ax] = (real)(wave_reducef<false>(in ? (float)(vi[ax] * sv) : 0.0f) * inv);
             const float big = fabsf((float)org[ax]) + (G.per[ax] ? (float)Ls[ax] : 0.0f);
@@ -1115,7 +1221,7 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             }
             const bool wild = coarse || untame(pi, X, V, kTileVMax);
             wild_i = __ballot(in && wild);
-            const TileRec T = tile_rec(X, V, xabs, hd2, wild, !in);
+            const TileRec T = tile_rec(X, V, 0.0f, hd2, wild, !in);
             vmax = wave_reducef<true>(T.v1);
             const _Float16 one = (_Float16)1.0f, nul = (_Float16)0.0f;
             const _Float16 mv = -up_f16(kTileE2 * T.v1), mx = -up_f16(kTileE2 * T.xm);
@@ -1160,7 +1266,22 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
         if (!sub && AX.images * AY.images * AZ.images > 1) {
             vcap = fminf(kTileVMax, 2.0f * vmax + 1e-3f);
             const float uu = (vmax + vcap) * (1.01f / kTileKappa);
-            if (!wild_i) reach_im = (real)(1.001f * sqrtf(fmaf(uu, uu, 2.0f * hd2))) / sx;
+            if (!wild_i) reach_im = (real)(1.001f * sqrtf(fmaf(uu, uu, 2.0f * hd2)) / I.tile_s);
+        }
+        // The group's extent along the imaged axes (elsewhere its cells'),
+        // widened by the rounding of the cells, in sort cells.
+        real ext_lo[3] = {(real)cxf, (real)gcy, (real)gcz}, ext_hi[3] = {(real)(cxl + 1), (real)(gcy + 1), (real)(gcz + 1)};
+        const int images[3] = {AX.images, AY.images, AZ.images};
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            if (images[ax] == 3) {
+                const float t = (float)((pi[ax] - lo[ax]) * iw[ax]);
+                ext_hi[ax] = (real)wave_reducef<true>(in ? t : -INFINITY);
+                ext_lo[ax] = -(real)wave_reducef<true>(in ? -t : -INFINITY);
+            }
+            const real eps = real(1e-3) + real(1e-6) * (real)n[ax];
+            ext_lo[ax] -= eps;
+            ext_hi[ax] += eps;
         }
         // Along x: the images of a whole row, or the part of the range inside
         // the box and the parts wrapped at its lower and upper end.
@@ -1168,10 +1289,22 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
         const bool lw = AX.images == 1 && AX.first < 0, rw = AX.images == 1 && xend > n[0];
         const int nx = AX.images == 3 ? 3 : 1 + (lw ? 1 : 0) + (rw ? 1 : 0);
         const int ny = AY.count * AY.images, nz = AZ.count * AZ.images;
-        const uint32_t any_mask = (AY.images == 1 ? kCodeAny << 2 : 0u) | (AZ.images == 1 ? kCodeAny << 4 : 0u) |
-                                  (G.per[0] && I.nl[0] <= 3 ? kCodeImagedX : 0u);
-        const uint32_t wild_mask = sub ? 0u : (kCodeAny << 2) | (kCodeAny << 4) | (AX.images == 3 ? kCodeAny : 0u);
+        // A periodic x axis of at most three c-bins, all of them neighbours,
+        // goes by image; else the c-bins decide, as the tile's x range is
+        // wider than a record's own.
+        const bool by_image = G.per[0] && nl0 <= 3;
+        const uint32_t any_mask = (by_image ? 0u : kCodeAny) | (AY.images == 1 ? kCodeAny << 2 : 0u) |
+                                  (AZ.images == 1 ? kCodeAny << 4 : 0u);
+        const uint32_t wild_mask =
+            sub ? 0u : (kCodeAny << 2) | (kCodeAny << 4) | (AX.images == 3 ? kCodeAny : 0u);
+        int32_t bi[2];  // x c-bin + 1 of the lane's record in either i tile
+        both_halves(by_image ? 2 : (cx >> I.kl[0]) + 1, bi);
         const int64_t total = (int64_t)nx * ny * nz;
+        // Quotients of the small numbers below by their float reciprocals:
+        // exact while the dividend is below 2^20.
+        const float inx = __builtin_amdgcn_rcpf((float)nx), iny = __builtin_amdgcn_rcpf((float)ny);
+        const float iay = __builtin_amdgcn_rcpf((float)AY.count), iaz = __builtin_amdgcn_rcpf((float)AZ.count);
+        auto quot = [](uint32_t t, float inv) { return (uint32_t)(((float)t + 0.5f) * inv); };
         for (int64_t t0 = 0; t0 < total; t0 += kWave) {
             // One part of the neighbourhood per lane: a run of records, or
             // none where it is out of reach.
@@ -1179,14 +1312,18 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             uint32_t shw = 0;
             if (t0 + lane < total) {
                 const uint32_t t = (uint32_t)(t0 + lane);
-                const int s = (int)(t % (uint32_t)nx);
-                const int ty = (int)(t / (uint32_t)nx % (uint32_t)ny), tz = (int)(t / (uint32_t)nx / (uint32_t)ny);
-                int y = AY.first + ty % AY.count, z = AZ.first + tz % AZ.count;
+                const bool small = total < (1 << 20);  // uniform
+                const uint32_t tr = small ? quot(t, inx) : t / (uint32_t)nx;
+                const uint32_t tz = small ? quot(tr, iny) : tr / (uint32_t)ny;
+                const int s = (int)(t - tr * (uint32_t)nx), ty = (int)(tr - tz * (uint32_t)ny);
+                const int qy = small ? (int)quot((uint32_t)ty, iay) : ty / AY.count;
+                const int qz = small ? (int)quot(tz, iaz) : (int)tz / AZ.count;
+                int y = AY.first + ty - qy * AY.count, z = AZ.first + (int)tz - qz * AZ.count;
                 int shy = 0, shz = 0, shx = 0;
-                if (AY.images == 3) shy = ty / AY.count - 1;
+                if (AY.images == 3) shy = qy - 1;
                 else if (y < 0) { y += n[1]; shy = -1; }
                 else if (y >= n[1]) { y -= n[1]; shy = 1; }
-                if (AZ.images == 3) shz = tz / AZ.count - 1;
+                if (AZ.images == 3) shz = qz - 1;
                 else if (z < 0) { z += n[2]; shz = -1; }
                 else if (z >= n[2]) { z -= n[2]; shz = 1; }
                 int xa = max(AX.first, 0), xb = min(xend, n[0]) - 1;
@@ -1195,14 +1332,13 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                 else if (s >= 1) { shx = 1; xa = 0; xb = xend - n[0] - 1; }
                 xa = max(xa, 0);
                 xb = min(xb, n[0] - 1);
-                // Gap between the group's row and this one.
-                auto gap = [&](int ax, int d) {
-                    const real g = ((real)(abs(d) - 1) - real(1e-3) - real(1e-6) * (real)n[ax]) / iw[ax];
-                    return g > real(0) ? g : real(0);
+                // Gap between the group and the sort cells c0..c1 (unwrapped).
+                auto gap = [&](int ax, int c0, int c1) {
+                    const real g = fmax((real)c0 - ext_hi[ax], ext_lo[ax] - (real)(c1 + 1));
+                    return g > real(0) ? g * ws[ax] : real(0);
                 };
-                const real gy = gap(1, y + shy * n[1] - gcy), gz = gap(2, z + shz * n[2] - gcz);
-                const int xl = xa + shx * n[0], xh = xb + shx * n[0];
-                const real gx = gap(0, xl > cxl ? xl - cxl : (xh < cxf ? cxf - xh : 0));
+                const real gx = gap(0, xa + shx * n[0], xb + shx * n[0]);
+                const real gy = gap(1, y + shy * n[1], y + shy * n[1]), gz = gap(2, z + shz * n[2], z + shz * n[2]);
                 const bool shifted = (AX.images == 3 && shx != 0) || (AY.images == 3 && shy != 0) ||
                                      (AZ.images == 3 && shz != 0);
                 const real rr = shifted ? reach_im : reach;
@@ -1221,11 +1357,11 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             const int32_t njs = __builtin_amdgcn_readlane(end, kWave - 1);
             uint64_t runs = __ballot(len > 0);
             // Blocks of 64 records taken from the runs in order.
-            int32_t jj = 0;
-            uint32_t jc = 0;
-            real pj[3], vj[3];
+            int32_t nj = 0;
+            uint32_t ncode = kCodeHome;
+            RawRec<real> next;  // the next block's records, on their way
             auto fetch = [&](int32_t b) {
-                jj = after;
+                nj = after;
                 while (runs) {
                     const int v = __ffsll((long long)runs) - 1;
                     const int32_t e1 = __builtin_amdgcn_readlane(end, v), l1 = __builtin_amdgcn_readlane(len, v);
@@ -1234,42 +1370,52 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                     const bool mine = g >= 0 && g < l1;
                     const int32_t s = __builtin_amdgcn_readlane(u0, v);
                     const uint32_t c1 = (uint32_t)__builtin_amdgcn_readlane((int)shw, v);
-                    jj = mine ? s + g : jj;
-                    jc = mine ? c1 : jc;
+                    nj = mine ? s + g : nj;
+                    ncode = mine ? c1 : ncode;
                     if (e1 > b + kWave) break;  // goes on in the next block
                     runs &= runs - 1;
                 }
-                load_pv(a.rec, jj, pj[0], pj[1], pj[2], vj[0], vj[1], vj[2]);
+                next.load(a.rec, nj);
             };
             const int32_t step = parts * kWave;
             if (part * kWave < njs) fetch(part * kWave);
             for (int32_t b = part * kWave; b < njs; b += step) {
+                const int32_t jj = nj;
+                const uint32_t code = ncode;
+                real pj[3], vj[3];
+                next.get(pj, vj);
+                if (b + step < njs) fetch(b + step);
                 float X[3], V[3];
-                const uint32_t code = jc;
+                const bool home = __ballot(code != kCodeHome) == 0;  // wave-uniform
 #pragma unroll
-                for (int ax = 0; ax < 3; ++ax) {
-                    real o = org[ax];
-                    if (G.per[ax]) o -= (real)((int)(code >> (2 * ax) & 3u) - 1) * Ls[ax];
-                    X[ax] = (float)fma(pj[ax], sx, -o);
-                    V[ax] = (float)fma(vj[ax], sv, -vo[ax]);
+                for (int ax = 0; ax < 3; ++ax) V[ax] = (float)fma(vj[ax], sv, -vo[ax]);
+                if (home) {
+#pragma unroll
+                    for (int ax = 0; ax < 3; ++ax) X[ax] = (float)fma(pj[ax], sx, -org[ax]);
+                } else {
+#pragma unroll
+                    for (int ax = 0; ax < 3; ++ax)
+                        X[ax] = (float)fma(pj[ax], sx, (real)((int)(code >> (2 * ax) & 3u) - 1) * Ls[ax] - org[ax]);
                 }
                 const bool absent = b + lane >= njs;
-                const bool wild = coarse || untame(pj, X, V, vcap);
-                const bool shifted = !sub && ((AX.images == 3 && (code & 3u) != 1u) ||
-                                              (AY.images == 3 && (code >> 2 & 3u) != 1u) ||
-                                              (AZ.images == 3 && (code >> 4 & 3u) != 1u));
+                const bool wild = coarse | untame(pj, X, V, vcap);
+                const bool shifted = !home && !sub && ((AX.images == 3 && (code & 3u) != 1u) ||
+                                                       (AY.images == 3 && (code >> 2 & 3u) != 1u) ||
+                                                       (AZ.images == 3 && (code >> 4 & 3u) != 1u));
                 const uint64_t wild_j = __ballot(wild && !absent);
                 const uint64_t shift_j = __ballot(shifted && !absent);
-                const TileRec T = tile_rec(X, V, xabs, hd2, wild, absent || (wild && shifted));
+                const TileRec T =
+                    tile_rec(X, V, code != kCodeHome ? xabs : 0.0f, hd2, wild, absent || (wild && shifted));
                 const _Float16 one = (_Float16)1.0f;
                 const uint32_t w[8] = {pack2(T.x[0], T.x[1]), pack2(T.x[2], T.v[0]), pack2(T.v[1], T.v[2]),
                                        split_f16(T.p), split_f16(T.q), split_f16(T.r), pack2(one, one),
                                        pack2(up_f16(T.xm), up_f16(T.v1))};
                 half8_t A[2];
                 tile_operands(w, A);
+                int bj = 0;
+                if (!by_image) bj = axis_bin(pj[0], lo[0], iwl[0], nl0) + ((int)(code & 3u) - 1) * nl0;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                L.blk[lane] = make_uint2((uint32_t)jj, code);
-                if (b + step < njs) fetch(b + step);
+                L.blk[lane] = make_uint2((uint32_t)jj, code | (uint32_t)(bj + 2) << 6);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
@@ -1283,23 +1429,23 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                         const acc16_t Qf = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[c], BQ[q], zero, 0, 0, 0);
                         const acc16_t Rf = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[c], BR[q], zero, 0, 0, 0);
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) {
+                        for (int r = 15; r >= 0; --r) {
                             const int s = __float_as_int(P[r]) & __float_as_int(Qf[r]) & __float_as_int(Rf[r]);
                             W = __builtin_amdgcn_alignbit(W, (uint32_t)s, 31);
                         }
                     }
-                    // Bit b of W: i tile b >> 4, row r = 15 - (b & 15) of the
-                    // product's layout.
+                    // Bit b of W: i tile b >> 4, row b & 15 of the product's
+                    // layout.
                     while (__ballot(W != 0)) {
                         const int bit = W ? __ffs((int)W) - 1 : 0;
                         bool take = W != 0;
                         W &= W - 1;
-                        const int r = 15 - (bit & 15);
-                        const int jl = 32 * c + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                        const int il = 32 * (bit >> 4) + (lane & 31);
+                        const int jl = j_row + 32 * c + (bit & 15) + (bit & 12);
+                        const int il = (lane & 31) + 2 * (bit & 16);
                         const uint2 e = L.blk[jl];
-                        take = take && (int32_t)e.x > wbase + il;
-                        uint32_t cd = e.y | any_mask;
+                        const uint32_t dx = (e.y >> 6) - (uint32_t)((bit & 16) ? bi[1] : bi[0]);
+                        take = take && (int32_t)e.x > wbase + il && dx <= 2u;
+                        uint32_t cd = (e.y & 63u) | any_mask;
                         if (wild_i | wild_j) {
                             const bool wi = (wild_i >> il) & 1ull, wj = (wild_j >> jl) & 1ull;
                             take = take && !(wi && ((shift_j >> jl) & 1ull));
@@ -1311,7 +1457,7 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                         nq += __popcll(tm);
                         if (nq >= kWave) {
                             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                            tile_hits(a, I, G, by_time, wbase, L, kWave, lane, nc);
+                            tile_hits(a, G, by_time, wbase, L, kWave, lane, nc);
                             const bool mv = lane < nq - kWave;
                             uint2 h = make_uint2(0u, 0u);
                             if (mv) h = L.hit[kWave + lane];
@@ -1324,50 +1470,12 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             }
         }
     }
-    if (nq > 0) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        tile_hits(a, I, G, by_time, wbase, L, nq, lane, nc);
-    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    tile_hits(a, G, by_time, wbase, L, nq, lane, nc);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const unsigned long long k = L.key[lane];
     if (valid && k != ~0ull) Key<real>::lower(a, i, k, key_now(a, i));
     cand = 2.0 * (double)nc;
-}
-
-// The unordered pairs of one c-bin with itself and with the neighbours of
-// larger index (the search's TPKMC_CNT_TESTS), from the sort cells' prefix.
-template <typename real>
-__device__ double cbin_tests(const StepArgs<real>& a, const Inst<real>& I, int c) {
-    const int nl[3] = {I.nl[0], I.nl[1], I.nl[2]}, k[3] = {I.k[0], I.k[1], I.k[2]};
-    const int x = c % nl[0], y = c / nl[0] % nl[1], z = c / nl[0] / nl[1];
-    // Records of the c-bins xa..xb of c-bin row (yy, zz).
-    auto records = [&](int xa, int xb, int yy, int zz) {
-        int32_t sum = 0;
-        for (int f = 0; f < k[1] * k[2]; ++f) {
-            const int64_t row =
-                I.cell_off + (int64_t)I.n[0] * row_of(I, yy * k[1] + f % k[1], zz * k[2] + f / k[1]);
-            sum += a.start[row + (int64_t)(xb + 1) * k[0]] - a.start[row + (int64_t)xa * k[0]];
-        }
-        return (double)sum;
-    };
-    const double own = records(x, x, y, z);
-    if (own == 0.0) return 0.0;
-    int xa[2], xb[2];
-    const int nxr = x_ranges(x, nl[0], I.bc[0] == TPKMC_BC_PERIODIC, xa, xb);
-    double other = 0.0;
-    for (int r = 0; r < 9; ++r) {
-        int yy, zz;
-        if (!axis_nb(z, r / 3 - 1, nl[2], I.bc[2] == TPKMC_BC_PERIODIC, zz)) continue;
-        if (!axis_nb(y, r % 3 - 1, nl[1], I.bc[1] == TPKMC_BC_PERIODIC, yy)) continue;
-        // Each pair of c-bins once: from the one of smaller plain index.
-        const int d = (yy + nl[1] * zz) - (y + nl[1] * z);
-        if (d < 0) continue;
-        for (int q = 0; q < nxr; ++q) {
-            const int a0 = d > 0 ? xa[q] : max(xa[q], x + 1);
-            if (a0 <= xb[q]) other += records(a0, xb[q], yy, zz);
-        }
-    }
-    return own * (0.5 * (own - 1.0) + other);
 }
 
 // Plain half scan of one record, counting what the pair tests meet (the
@@ -1908,8 +2016,7 @@ k_search(StepArgs<float> a) {
 }
 
 // The instances of the tile search (all in FP64, the dense ones in FP32),
-// one wave per 64 records; the work-groups of an instance share the count of
-// its pair tests.
+// one wave per 64 records and part of their neighbourhood (blockIdx.y).
 template <typename real>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(real) == 4 ? 3 : 2)))
 k_search_tiles(StepArgs<real> a) {
@@ -1923,13 +2030,9 @@ k_search_tiles(StepArgs<real> a) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int32_t i0 = bt.first + wave * kWave;
     const int64_t stop = slow_stop(a, I, I.base);
-    double tests = 0.0, cand = 0.0;
+    double cand = 0.0;
     if (i0 < stop) search_tiles(a, I, i0, (int32_t)stop, (int)blockIdx.y, (int)gridDim.y, tl[wave], cand);
-    const int64_t ncb = (int64_t)I.nl[0] * I.nl[1] * I.nl[2];
-    const int64_t share = (int64_t)(entry - I.blk0) * gridDim.y + blockIdx.y;
-    for (int64_t c = share * kBlock + threadIdx.x; c < ncb; c += (int64_t)I.nblk * gridDim.y * kBlock)
-        tests += cbin_tests(a, I, (int)c);
-    add_work(a.gpart, entry, tests, cand, lds);
+    add_work(a.gpart, entry, 0.0, cand, lds);
 }
 
 // Diagnostic: counts of the pair tests (never part of a step).
