@@ -534,8 +534,10 @@ __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
         const uint32_t fl = alive ? 1u : 0u;
         Rec<real>::store(a.rec, dst, x, y, z, a.id[p], vx, vy, vz, fl);
         if (!(I.flags & TPKMC_ALLOW_REORDER)) a.src[dst] = (int32_t)p;
-        a.bkey[dst] = ~0ull;
-        if constexpr (std::is_same<real, double>::value) a.coll[dst] = 0;  // marks of k_search_ties
+        // Every record of the instance starts without a partner; which of
+        // them this thread clears is free, so the stores are consecutive.
+        a.bkey[p] = ~0ull;
+        if constexpr (std::is_same<real, double>::value) a.coll[p] = 0;  // marks of k_search_ties
         if (a.mass) a.rmass[dst] = a.mass[p];
         // Diagnostic: a particle faster than one c-bin per step on some axis.
         const real dt = I.dt;
@@ -3024,7 +3026,7 @@ void launch_search_tiles(const StepArgs<real>& a, hipStream_t s) {
 template <typename real>
 void launch_search_ties(const StepArgs<real>& a, hipStream_t s) {
     if constexpr (std::is_same<real, double>::value) {
-        const unsigned grid = (unsigned)std::max(1, std::min(1024, a.nblk));
+        const unsigned grid = (unsigned)std::max(1, std::min(64, a.nblk));
         hipLaunchKernelGGL(k_search_ties<real>, dim3(grid), dim3(kBlock), 0, s, a);
     }
 }
