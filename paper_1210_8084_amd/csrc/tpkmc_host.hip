@@ -26,21 +26,57 @@ constexpr int kDefaultSearchOrder = 16;
 enum Phase { PH_CLEAR = 0, PH_KEY, PH_SCAN, PH_SCATTER, PH_SEARCH, PH_MOVE, PH_FINAL };
 
 // ---------------------------------------------------------------- kernels
-__global__ void k_clear(int32_t* start, int64_t ncell, unsigned long long* macc, int64_t nwords,
-                        unsigned long long* pair_count, uint32_t* ties) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t t = t0; t < ncell; t += stride) start[t] = 0;
-    if (macc)
-        for (int64_t t = t0; t < nwords; t += stride) macc[t] = 0ull;
+// What a step clears before it starts.
+struct ClearArgs {
+    int32_t* start;
+    int64_t ncell;
+    unsigned long long* macc;  // exact o-bin sums, or null
+    int64_t nwords;
+    unsigned long long* pair_count;
+    uint32_t* ties;
+    double* shift;             // velocity shifts to clear, or null
+    int64_t nshift;
+    uint32_t* status;          // status word to clear, or null
+};
+
+__device__ __forceinline__ void clear_all(const ClearArgs& c, int64_t t0, int64_t stride) {
+    for (int64_t t = t0; t < c.ncell; t += stride) c.start[t] = 0;
+    if (c.macc)
+        for (int64_t t = t0; t < c.nwords; t += stride) c.macc[t] = 0ull;
+    if (c.shift)
+        for (int64_t t = t0; t < c.nshift; t += stride) c.shift[t] = 0.0;
     if (t0 == 0) {
-        *pair_count = 0ull;
-        *ties = 0u;
+        *c.pair_count = 0ull;
+        *c.ties = 0u;
+        if (c.status) *c.status = 0u;
     }
 }
 
-// Exclusive prefix sum of n int32 in place: per-tile totals, a single
-// work-group scan of the totals, then per-tile scans with the tile offset.
+__global__ void __launch_bounds__(256) k_clear(ClearArgs c) {
+    clear_all(c, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+}
+
+// The same for a step of one instance, which also writes its tables: the
+// instance descriptor comes as a kernel argument and the block and chunk
+// tables follow from it, so that no host staging or copy is needed.
+template <typename real>
+__global__ void __launch_bounds__(256) k_begin(Inst<real> one, Inst<real>* inst, Blk* blk, Chunk* chunks, ClearArgs c) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t0 == 0) *inst = one;
+    for (int64_t t = t0; t < one.nblk; t += stride) blk[t] = Blk{0, (int32_t)(one.off + t * kBlock)};
+    for (int64_t t = t0; t < one.nchunk; t += stride)
+        chunks[t] = Chunk{(int32_t)(t * kChunk), (int32_t)min<int64_t>(kChunk, one.nblk - t * kChunk)};
+    clear_all(c, t0, stride);
+}
+
+// Exclusive prefix sum of n int32 in place: per-tile totals, then per-tile
+// scans that add the totals of the tiles before (read again by every tile, at
+// most kScanTop of them; for more a single work-group scans the totals in
+// between).  One tile takes the scan alone.  The launches are what a small
+// state's scan costs: 10 us with all three, 3 us with one.
+constexpr int64_t kScanTop = 2048;
+
 __global__ void __launch_bounds__(kScanBlock) k_scan_reduce(const int32_t* d, int64_t n, int32_t* tile_sum) {
     __shared__ int32_t lds[kScanBlock / 64];
     const int64_t b0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
@@ -93,7 +129,9 @@ __global__ void __launch_bounds__(1024) k_scan_top(int32_t* tile_sum, int64_t nt
     }
 }
 
-__global__ void __launch_bounds__(kScanBlock) k_scan_apply(int32_t* d, int64_t n, const int32_t* tile_off) {
+// tile_off: the tiles' offsets (scanned = true) or totals; null for one tile.
+__global__ void __launch_bounds__(kScanBlock) k_scan_apply(int32_t* d, int64_t n, const int32_t* tile_off,
+                                                           bool scanned) {
     __shared__ int32_t lds[kScanBlock / 64];
     const int64_t b0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int32_t v[kScanItems];
@@ -103,8 +141,18 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_apply(int32_t* d, int64_t n
         v[k] = b0 + k < n ? d[b0 + k] : 0;
         s += v[k];
     }
+    int32_t before = 0;
+    if (tile_off) {
+        if (scanned) {
+            before = tile_off[blockIdx.x];
+        } else {
+            int32_t part = 0;
+            for (int t = threadIdx.x; t < (int)blockIdx.x; t += kScanBlock) part += tile_off[t];
+            block_exscan(part, lds, &before);
+        }
+    }
     int32_t total;
-    int32_t run = tile_off[blockIdx.x] + block_exscan(s, lds, &total);
+    int32_t run = before + block_exscan(s, lds, &total);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         if (b0 + k < n) d[b0 + k] = run;
@@ -132,6 +180,10 @@ struct NSum {
 // the sixteen lanes combines their partials with a commutative step, so all
 // sixteen end with the same total.
 constexpr int kSlotLanes = 256 / kGPart;
+// Instances of at most this many chunks are folded by the last launch alone
+// (k_finalize), which saves one: 5 us against 9 for one chunk, but 27 against
+// 13 for four.
+constexpr int kDirectChunks = 1;
 static_assert(kSlotLanes * kGPart == 256 && (kSlotLanes & (kSlotLanes - 1)) == 0, "slot lanes");
 
 __device__ __forceinline__ void reduce_slots(const double* rows, int nrows, double* out) {
@@ -168,25 +220,33 @@ __global__ void __launch_bounds__(256) k_reduce_chunks(const Chunk* chunks, cons
     reduce_slots(rows, c.count, cpart + (int64_t)blockIdx.x * kGPart);
 }
 
+// Counters and globals of one instance, from its chunks' partials (cpart) or,
+// with gpart given, from the work-groups' own, at most one chunk of them,
+// folded as k_reduce_chunks does.
+constexpr int kMomentRows = 256;  // o-bins per work-group of the moments
 template <typename real>
-__global__ void __launch_bounds__(256) k_finalize(Inst<real>* inst, const double* cpart, uint64_t* counters,
-                                                 double* globals, uint32_t* status,
-                                                 const unsigned long long* pair_count, int64_t pair_cap,
-                                                 int advance_step) {
-    __shared__ double tot[kGPart];
-    __shared__ double rows[kChunk * kGPart];
-    Inst<real>& I = inst[blockIdx.x];
-    // Chunk partials of this instance, staged in LDS kChunk rows at a time
-    // (folded in order, so the result does not depend on the launch shape).
+__device__ void finalize_one(Inst<real>& I, int k0, const double* cpart, const double* gpart, uint64_t* counters,
+                             double* globals, uint32_t* status, const unsigned long long* pair_count,
+                             int64_t pair_cap, int advance_step, double* rows) {
+    __shared__ double tot[kGPart], part[kGPart];
+    // Partials of this instance, staged in LDS kChunk rows at a time (folded
+    // in order, so the result does not depend on the launch shape).
     double acc = 0.0;
     NSum ns;
-    for (int c0 = 0; c0 < I.nchunk; c0 += kChunk) {
-        const int nr = min(kChunk, I.nchunk - c0);
+    const int nrows = gpart ? I.nblk : I.nchunk;
+    const double* src = gpart ? gpart + (int64_t)I.blk0 * kGPart : cpart + (int64_t)I.chunk0 * kGPart;
+    for (int c0 = 0; c0 < nrows; c0 += kChunk) {
+        const int nr = min(kChunk, nrows - c0);
         __syncthreads();
-        for (int t = threadIdx.x; t < nr * kGPart; t += blockDim.x)
-            rows[t] = cpart[(int64_t)(I.chunk0 + c0) * kGPart + t];
+        for (int t = threadIdx.x; t < nr * kGPart; t += blockDim.x) rows[t] = src[(int64_t)c0 * kGPart + t];
         __syncthreads();
-        reduce_slots(rows, nr, tot);
+        if (gpart) {  // the one chunk's partial, then that as its only row
+            reduce_slots(rows, nr, part);
+            __syncthreads();
+            reduce_slots(part, 1, tot);
+        } else {
+            reduce_slots(rows, nr, tot);
+        }
         __syncthreads();
         if (threadIdx.x < kGPart) {
             const int k = threadIdx.x;
@@ -199,7 +259,6 @@ __global__ void __launch_bounds__(256) k_finalize(Inst<real>* inst, const double
     if (threadIdx.x < kGPart) tot[threadIdx.x] = threadIdx.x < GP_ALIVE && threadIdx.x != GP_VMAX2 ? ns.value() : acc;
     __syncthreads();
     if (threadIdx.x != 0) return;
-    const int k0 = blockIdx.x;
     if (counters) {
         uint64_t* c = counters + 8 * k0;
         c[TPKMC_CNT_ALIVE] = (uint64_t)tot[GP_ALIVE];
@@ -237,13 +296,11 @@ __global__ void __launch_bounds__(256) k_finalize(Inst<real>* inst, const double
 // Each work-group (256 threads) stages its 256 o-bins' output rows through
 // LDS, so the stores are coalesced; every output value is written.
 template <typename real>
-__global__ void __launch_bounds__(256) k_moments_final(const Inst<real>* inst, const ObAcc* macc, double* moments,
-                                                       double* shift) {
-    constexpr int kRows = 256;
-    __shared__ double rows[kRows * TPKMC_MOMENT_STRIDE];
-    const Inst<real>& I = inst[blockIdx.y];
+__device__ void moments_final(const Inst<real>& I, int block, const ObAcc* macc, double* moments, double* shift,
+                              double* rows) {
+    constexpr int kRows = kMomentRows;
     const int64_t nb = (int64_t)I.no[0] * I.no[1] * I.no[2];
-    const int64_t b0 = (int64_t)blockIdx.x * kRows;
+    const int64_t b0 = (int64_t)block * kRows;
     if (b0 >= nb) return;  // whole work-group
     const int nloc = (int)min<int64_t>(kRows, nb - b0);
     if ((int)threadIdx.x < nloc) {
@@ -284,25 +341,21 @@ __global__ void __launch_bounds__(256) k_moments_final(const Inst<real>* inst, c
     for (int t = threadIdx.x; t < nloc * TPKMC_MOMENT_STRIDE; t += kRows) M0[t] = rows[t];
 }
 
-// Tables of the allocation-free entry point, written on the device so that
-// no host staging or copy is needed: its one instance descriptor (passed by
-// value as a kernel argument), the block and chunk tables, and the o-bin
-// velocity shifts and status word, cleared because the static scratch keeps
-// the previous call's contents.
+// The step's last launch: work-group 0 of each instance (blockIdx.y) writes
+// its counters and globals, the others its o-bins' moments.
 template <typename real>
-__global__ void __launch_bounds__(256) k_setup_one(Inst<real> one, Inst<real>* inst, Blk* blk, int nblk,
-                                                  Chunk* chunks, int nchunk, double* shift, int64_t nshift,
-                                                  uint32_t* status) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t0 == 0) {
-        *inst = one;
-        *status = 0u;
-    }
-    for (int64_t t = t0; t < nblk; t += stride) blk[t] = Blk{0, (int32_t)(one.off + t * kBlock)};
-    for (int64_t t = t0; t < nchunk; t += stride)
-        chunks[t] = Chunk{(int32_t)(t * kChunk), (int32_t)min<int64_t>(kChunk, nblk - t * kChunk)};
-    for (int64_t t = t0; t < nshift; t += stride) shift[t] = 0.0;
+__global__ void __launch_bounds__(256) k_finalize(Inst<real>* inst, const double* cpart, const double* gpart,
+                                                 uint64_t* counters, double* globals, uint32_t* status,
+                                                 const unsigned long long* pair_count, int64_t pair_cap,
+                                                 int advance_step, const ObAcc* macc, double* moments, double* shift) {
+    __shared__ double rows[kChunk * kGPart];
+    static_assert(kChunk * kGPart >= kMomentRows * TPKMC_MOMENT_STRIDE, "rows hold either");
+    Inst<real>& I = inst[blockIdx.y];
+    if (blockIdx.x == 0)
+        finalize_one(I, (int)blockIdx.y, cpart, gpart, counters, globals, status, pair_count, pair_cap, advance_step,
+                     rows);
+    else
+        moments_final(I, (int)blockIdx.x - 1, macc, moments, shift, rows);
 }
 
 }  // namespace
@@ -394,7 +447,8 @@ struct Plan {
     bool subgrid = false;     // some instance's c-bins are cut into sort cells
     bool any_staged = false, any_tiles = false;  // which searches the instances take
     bool any_random = false;  // some instance takes random partners
-    std::vector<Blk> blk;
+    int nchunk = 0, max_chunks = 0;
+    std::vector<Blk> blk;      // empty for one instance (see make_plan)
     std::vector<Chunk> chunks;
     std::vector<char> inst_bytes;
 };
@@ -575,7 +629,7 @@ const tpkmc_handle::Cells* tuned_cells(const tpkmc_handle* h, int k, const tpkmc
 
 template <typename real>
 int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in, int n_inst, Plan& P,
-              bool configured = false) {
+              bool configured = false, bool tables = true) {
     if (!s || !in || n_inst < 1) return TPKMC_EINVAL;
     if (n_inst > h->max_inst) return TPKMC_ECAPACITY;
     if (s->n < 0) return TPKMC_EINVAL;
@@ -593,6 +647,7 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     P.ncell_tot = 0;
     P.nob_tot = 0;
     P.max_nob = 0;
+    P.nblk = P.nchunk = P.max_chunks = 0;
     int64_t before = 0, cbins = 0;  // particles of the instances before; c-bins
     for (int k = 0; k < n_inst; ++k) {
         const tpkmc_instance& q = in[k];
@@ -617,22 +672,25 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
         cbins += C + 1;
         P.nob_tot += B;
         P.max_nob = std::max(P.max_nob, B);
-        d.blk0 = (int32_t)P.blk.size();
+        d.blk0 = (int32_t)P.nblk;
+        d.nblk = (int32_t)((q.count + kBlock - 1) / kBlock);
+        d.chunk0 = P.nchunk;
+        d.nchunk = (d.nblk + kChunk - 1) / kChunk;
+        P.nblk += d.nblk;
+        P.nchunk += d.nchunk;
+        P.max_chunks = std::max(P.max_chunks, d.nchunk);
+        if (!tables) continue;
         for (int64_t o = 0; o < q.count; o += kBlock) P.blk.push_back({k, (int32_t)(q.offset + o)});
-        d.nblk = (int32_t)P.blk.size() - d.blk0;
-        d.chunk0 = (int32_t)P.chunks.size();
         for (int32_t b = 0; b < d.nblk; b += kChunk)
             P.chunks.push_back({d.blk0 + b, std::min<int32_t>(kChunk, d.nblk - b)});
-        d.nchunk = (int32_t)P.chunks.size() - d.chunk0;
     }
     std::sort(spans.begin(), spans.end());
     for (size_t k = 1; k < spans.size(); ++k)
         if (spans[k - 1].first + spans[k - 1].second > spans[k].first) return TPKMC_EINVAL;
     if (cbins > h->cell_cap) return TPKMC_ECAPACITY;
     if (P.nob_tot > h->max_obins) return TPKMC_ECAPACITY;
-    if ((int64_t)P.blk.size() > h->max_blk) return TPKMC_ECAPACITY;
-    if ((int64_t)P.chunks.size() > h->max_chunks) return TPKMC_ECAPACITY;
-    P.nblk = (int)P.blk.size();
+    if (P.nblk > h->max_blk) return TPKMC_ECAPACITY;
+    if (P.nchunk > h->max_chunks) return TPKMC_ECAPACITY;
     P.inst_bytes.resize(sizeof(Inst<real>) * n_inst);
     std::memcpy(P.inst_bytes.data(), I.data(), P.inst_bytes.size());
     return TPKMC_OK;
@@ -707,38 +765,68 @@ StepArgs<real> make_args(const Buffers& B, const tpkmc_particles* s, const tpkmc
 
 void enqueue_scan(const Buffers& B, int64_t n, hipStream_t s) {
     const int64_t tiles = scan_tiles(n);
-    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, B.start, n, B.tiles);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, B.tiles, tiles);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, B.start, n, B.tiles);
+    const bool top = tiles > kScanTop;
+    if (tiles > 1) hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, B.start, n, B.tiles);
+    if (top) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, B.tiles, tiles);
+    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, B.start, n,
+                       tiles > 1 ? B.tiles : nullptr, top);
 }
 
 // Shape of one launch sequence: what enqueue_step needs of a Plan.
 struct Shape {
-    int n_inst, nblk, nchunk;
+    int n_inst, nblk, nchunk, max_chunks;  // max_chunks: of one instance
     int64_t ncell_tot, nob_tot, max_nob;
     bool prep, any_search, any_random, split;  // prep: some instance needs the prep kernel
     bool any_staged, any_tiles;
 };
 
 Shape shape_of(const Plan& P) {
-    return Shape{P.n_inst, P.nblk, (int)P.chunks.size(), P.ncell_tot, P.nob_tot, P.max_nob,
+    return Shape{P.n_inst, P.nblk, P.nchunk, P.max_chunks, P.ncell_tot, P.nob_tot, P.max_nob,
                  P.adaptive || P.split || P.subgrid, P.any_search, P.any_random, P.split, P.any_staged, P.any_tiles};
 }
 
-// Everything of one step after the tables are on the device.  `h` only
-// records phase timings (null: none).
+ClearArgs clear_args(const Buffers& B, const Shape& P, bool mom, bool fresh) {
+    ClearArgs c{};
+    c.start = B.start;
+    c.ncell = P.ncell_tot + 1;
+    c.macc = mom ? (unsigned long long*)B.macc : nullptr;
+    c.nwords = mom ? P.nob_tot * (int64_t)(sizeof(ObAcc) / 8) : 0;
+    c.pair_count = B.pair_count;
+    c.ties = B.ties;
+    if (fresh) {
+        c.shift = B.shift;
+        c.nshift = 3 * std::max<int64_t>(P.nob_tot, 1);
+        c.status = B.status;
+    }
+    return c;
+}
+
+// A step of one instance writes its tables on the device; fresh: its scratch
+// keeps an earlier call's contents, so shifts and status word are cleared too.
+template <typename real>
+struct One {
+    Inst<real> inst;
+    bool fresh;
+};
+
+// Everything of one step.  `one`: of one instance, whose tables it writes
+// (null: they are on the device).  `h` only records phase timings (null:
+// none).
 template <typename real>
 void enqueue_step(tpkmc_handle* h, const Buffers& B, const StepArgs<real>& a, const tpkmc_outputs* o,
                   const Shape& P, int search_block, int search_group, hipStream_t s, bool prof,
-                  int advance_step) {
+                  int advance_step, const One<real>* one) {
     const bool mom = o && o->moments;
-    const int64_t nwords = mom ? P.nob_tot * (int64_t)(sizeof(ObAcc) / 8) : 0;
     {
         PhaseScope ps(h, PH_CLEAR, s, prof);
-        const int64_t work = std::max<int64_t>(P.ncell_tot + 1, nwords);
-        const int64_t grid = std::min<int64_t>((work + 255) / 256, 4096);
-        hipLaunchKernelGGL(k_clear, dim3((unsigned)std::max<int64_t>(grid, 1)), dim3(256), 0, s, B.start,
-                           P.ncell_tot + 1, mom ? (unsigned long long*)B.macc : nullptr, nwords, B.pair_count, B.ties);
+        const ClearArgs c = clear_args(B, P, mom, one && one->fresh);
+        const int64_t work = std::max<int64_t>(std::max<int64_t>(c.ncell, c.nwords), one ? P.nblk : 0);
+        const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((work + 255) / 256, 4096));
+        if (one)
+            hipLaunchKernelGGL(k_begin<real>, dim3(grid), dim3(256), 0, s, one->inst, (Inst<real>*)B.inst, B.blk,
+                               B.chunks, c);
+        else
+            hipLaunchKernelGGL(k_clear, dim3(grid), dim3(256), 0, s, c);
     }
     if (P.nblk > 0) {
         PhaseScope ps(h, PH_KEY, s, prof);
@@ -770,17 +858,15 @@ void enqueue_step(tpkmc_handle* h, const Buffers& B, const StepArgs<real>& a, co
     }
     {
         PhaseScope ps(h, PH_FINAL, s, prof);
-        if (P.nchunk > 0)
+        const bool direct = P.max_chunks <= kDirectChunks;
+        if (P.nchunk > 0 && !direct)
             hipLaunchKernelGGL(k_reduce_chunks, dim3((unsigned)P.nchunk), dim3(256), 0, s,
                                (const Chunk*)B.chunks, (const double*)B.gpart, B.cpart);
-        hipLaunchKernelGGL(k_finalize<real>, dim3(P.n_inst), dim3(256), 0, s, (Inst<real>*)B.inst, B.cpart,
-                           o ? o->counters : nullptr, o ? o->globals : nullptr, B.status, B.pair_count,
-                           a.pair_cap, advance_step);
-        if (mom && P.max_nob > 0) {
-            const unsigned gx = (unsigned)((P.max_nob + 255) / 256);
-            hipLaunchKernelGGL(k_moments_final<real>, dim3(gx, P.n_inst), dim3(256), 0, s,
-                               (const Inst<real>*)B.inst, (const ObAcc*)B.macc, o->moments, B.shift);
-        }
+        const unsigned gx = 1 + (mom ? (unsigned)((P.max_nob + kMomentRows - 1) / kMomentRows) : 0u);
+        hipLaunchKernelGGL(k_finalize<real>, dim3(gx, P.n_inst), dim3(256), 0, s, (Inst<real>*)B.inst,
+                           (const double*)B.cpart, direct ? (const double*)B.gpart : (const double*)nullptr,
+                           o ? o->counters : nullptr, o ? o->globals : nullptr, B.status, B.pair_count, a.pair_cap,
+                           advance_step, (const ObAcc*)B.macc, mom ? o->moments : nullptr, B.shift);
     }
 }
 
@@ -806,15 +892,20 @@ int upload(tpkmc_handle* h, const Plan& P, hipStream_t s) {
 template <typename real>
 int step_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in, int n_inst,
               const tpkmc_outputs* o, hipStream_t st) {
+    // One instance: its tables are written by the step's first launch.
+    const bool single = n_inst == 1;
     Plan P;
-    int rc = make_plan<real>(h, s, in, n_inst, P);
+    int rc = make_plan<real>(h, s, in, n_inst, P, false, !single);
     if (rc) return rc;
     if ((rc = check_outputs(o))) return rc;
     if (hipSetDevice(h->device) != hipSuccess) return TPKMC_EHIP;
-    if ((rc = upload(h, P, st))) return rc;
+    One<real> one{};
+    if (single) std::memcpy(&one.inst, P.inst_bytes.data(), sizeof(one.inst));
+    else if ((rc = upload(h, P, st))) return rc;
     StepArgs<real> a = make_args<real>(h->b, s, o, P.nblk);
     a.order = h->search_order;
-    enqueue_step<real>(h, h->b, a, o, shape_of(P), h->search_block, h->search_group, st, h->profiling, 0);
+    enqueue_step<real>(h, h->b, a, o, shape_of(P), h->search_block, h->search_group, st, h->profiling, 0,
+                       single ? &one : nullptr);
     h->last_stream = st;
     return hipGetLastError() == hipSuccess ? TPKMC_OK : TPKMC_EHIP;
 }
@@ -854,7 +945,8 @@ int run_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in
     }
     hipGraph_t graph = nullptr;
     if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess) return TPKMC_EHIP;
-    enqueue_step<real>(nullptr, h->b, a, o, shape_of(P), h->search_block, h->search_group, st, false, 1);
+    enqueue_step<real>(nullptr, h->b, a, o, shape_of(P), h->search_block, h->search_group, st, false, 1,
+                       (const One<real>*)nullptr);
     if (hipStreamEndCapture(st, &graph) != hipSuccess || !graph) return TPKMC_EHIP;
     if (hipGraphInstantiate(&h->gexec, graph, nullptr, nullptr, 0) != hipSuccess) {
         hipGraphDestroy(graph);
@@ -1039,8 +1131,7 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk);
     a.order = 0;  // shapes are timed in the default work-group order
     // Bin once (clear, key, prefix, scatter); then time only the search.
-    hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, h->b.start, P.ncell_tot + 1,
-                       (unsigned long long*)nullptr, (int64_t)0, h->b.pair_count, h->b.ties);
+    hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, clear_args(h->b, shape_of(P), false, false));
     launch_key<real>(a, st);
     if (P.adaptive || P.split || P.subgrid) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
     enqueue_scan(h->b, P.ncell_tot + 1, st);
@@ -1137,8 +1228,7 @@ int mix_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in
     tpkmc_outputs none{};
     StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk);
     a.order = h->search_order;
-    hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, h->b.start, P.ncell_tot + 1,
-                       (unsigned long long*)nullptr, (int64_t)0, h->b.pair_count, h->b.ties);
+    hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, clear_args(h->b, shape_of(P), false, false));
     launch_key<real>(a, st);
     if (P.adaptive || P.split || P.subgrid) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
     enqueue_scan(h->b, P.ncell_tot + 1, st);
@@ -1270,16 +1360,12 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     unsigned char* base = nullptr;
     if ((rc = scratch_of(device, &base))) return rc;
     carve<real>((uintptr_t)base, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, Bf);
-    const int64_t nshift = 3 * std::max<int64_t>(B, 1);
-    const int64_t work = std::max<int64_t>(std::max<int64_t>(nblk, nchunk), nshift);
-    const unsigned sgrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((work + 255) / 256, 1024));
-    hipLaunchKernelGGL(k_setup_one<real>, dim3(sgrid), dim3(256), 0, st, d, (Inst<real>*)Bf.inst, Bf.blk, nblk,
-                       Bf.chunks, nchunk, Bf.shift, nshift, Bf.status);
     const bool random = (p->flags & TPKMC_PAIR_RANDOM) != 0;
     Shape P{};
     P.n_inst = 1;
     P.nblk = nblk;
     P.nchunk = nchunk;
+    P.max_chunks = nchunk;
     P.ncell_tot = ncell_tot;
     P.nob_tot = B;
     P.max_nob = B;
@@ -1290,7 +1376,8 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     P.any_random = random;
     P.split = false;
     StepArgs<real> a = make_args<real>(Bf, s, o, nblk);
-    enqueue_step<real>(nullptr, Bf, a, o, P, kWave, 2, st, false, 0);
+    const One<real> one{d, true};
+    enqueue_step<real>(nullptr, Bf, a, o, P, kWave, 2, st, false, 0, &one);
     return hipGetLastError() == hipSuccess ? TPKMC_OK : TPKMC_EHIP;
 }
 
