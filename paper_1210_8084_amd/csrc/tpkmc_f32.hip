@@ -13,7 +13,7 @@ template void launch_search_ties<float>(const StepArgs<float>&, hipStream_t);
 template void launch_search_mix<float>(const StepArgs<float>&, int, bool, hipStream_t);
 template void launch_search_fast<float>(const StepArgs<float>&, int, hipStream_t);
 template void launch_move<float>(const StepArgs<float>&, hipStream_t);
-template void launch_moments<float>(const StepArgs<float>&, hipStream_t);
+template void launch_moments<float>(const StepArgs<float>&, bool, hipStream_t);
 template void launch_random_pairs<float>(const StepArgs<float>&, hipStream_t);
 template void launch_speed_stats<float>(const StepArgs<float>&, hipStream_t);
 }  // namespace tpkmc

@@ -15,7 +15,7 @@ template void launch_search_ties<double>(const StepArgs<double>&, hipStream_t);
 template void launch_search_mix<double>(const StepArgs<double>&, int, bool, hipStream_t);
 template void launch_search_fast<double>(const StepArgs<double>&, int, hipStream_t);
 template void launch_move<double>(const StepArgs<double>&, hipStream_t);
-template void launch_moments<double>(const StepArgs<double>&, hipStream_t);
+template void launch_moments<double>(const StepArgs<double>&, bool, hipStream_t);
 template void launch_random_pairs<double>(const StepArgs<double>&, hipStream_t);
 template void launch_speed_stats<double>(const StepArgs<double>&, hipStream_t);
 }  // namespace tpkmc

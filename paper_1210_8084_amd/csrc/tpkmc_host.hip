@@ -365,7 +365,7 @@ __global__ void __launch_bounds__(256) k_finalize(Inst<real>* inst, const double
 // out of the static scratch array by the allocation-free entry point.
 struct Buffers {
     int32_t *rank, *start, *tiles, *src, *best, *perm;
-    void *rec, *rmass, *inst;
+    void *rec, *rec2, *rmass, *inst;
     Blk* blk;
     Chunk* chunks;
     unsigned long long* bkey;
@@ -446,6 +446,7 @@ struct Plan {
     bool split = false;       // some instance has c-bins split by speed
     bool subgrid = false;     // some instance's c-bins are cut into sort cells
     bool any_staged = false, any_tiles = false;  // which searches the instances take
+    bool caller_order = false;  // some instance keeps the caller's order
     bool any_random = false;  // some instance takes random partners
     int nchunk = 0, max_chunks = 0;
     std::vector<Blk> blk;      // empty for one instance (see make_plan)
@@ -642,7 +643,7 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     P.n_inst = n_inst;
     P.adaptive = false;
     P.any_search = false;
-    P.split = P.subgrid = P.any_staged = P.any_tiles = false;
+    P.split = P.subgrid = P.any_staged = P.any_tiles = P.caller_order = false;
     P.any_random = false;
     P.ncell_tot = 0;
     P.nob_tot = 0;
@@ -660,6 +661,7 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
         if (d.flags & kSubgrid) P.subgrid = true;
         if (!(d.flags & (kTiles | TPKMC_PAIR_RANDOM))) P.any_staged = true;
         if (d.flags & kTiles) P.any_tiles = true;
+        if (!(q.params.flags & TPKMC_ALLOW_REORDER)) P.caller_order = true;
         spans.push_back({q.offset, q.count});
         if (q.params.flags & TPKMC_PAIR_RANDOM) P.any_random = true;
         else P.any_search = true;
@@ -742,6 +744,7 @@ StepArgs<real> make_args(const Buffers& B, const tpkmc_particles* s, const tpkmc
     a.rank = B.rank;
     a.start = B.start;
     a.rec = (real*)B.rec;
+    a.rec2 = (real*)B.rec2;
     a.mass = (real*)s->mass;
     a.rmass = (real*)B.rmass;
     a.src = B.src;
@@ -778,11 +781,12 @@ struct Shape {
     int64_t ncell_tot, nob_tot, max_nob;
     bool prep, any_search, any_random, split;  // prep: some instance needs the prep kernel
     bool any_staged, any_tiles;
+    bool caller_order;  // some instance keeps the caller's order
 };
 
 Shape shape_of(const Plan& P) {
     return Shape{P.n_inst, P.nblk, P.nchunk, P.max_chunks, P.ncell_tot, P.nob_tot, P.max_nob,
-                 P.adaptive || P.split || P.subgrid, P.any_search, P.any_random, P.split, P.any_staged, P.any_tiles};
+                 P.adaptive || P.split || P.subgrid, P.any_search, P.any_random, P.split, P.any_staged, P.any_tiles, P.caller_order};
 }
 
 ClearArgs clear_args(const Buffers& B, const Shape& P, bool mom, bool fresh) {
@@ -853,7 +857,7 @@ void enqueue_step(tpkmc_handle* h, const Buffers& B, const StepArgs<real>& a, co
         {
             PhaseScope ps(h, PH_MOVE, s, prof);
             launch_move<real>(a, s);
-            if (mom) launch_moments<real>(a, s);
+            launch_moments<real>(a, P.caller_order, s);
         }
     }
     {
@@ -1249,7 +1253,7 @@ void free_all(tpkmc_handle* h) {
         if (h->stage_ev[k]) hipEventDestroy(h->stage_ev[k]);
     }
     hipFree(h->b.rank); hipFree(h->b.start); hipFree(h->b.tiles);
-    hipFree(h->b.src); hipFree(h->b.best); hipFree(h->b.perm); hipFree(h->b.rec); hipFree(h->b.rmass); hipFree(h->b.inst);
+    hipFree(h->b.src); hipFree(h->b.best); hipFree(h->b.perm); hipFree(h->b.rec); hipFree(h->b.rec2); hipFree(h->b.rmass); hipFree(h->b.inst);
     hipFree(h->b.blk); hipFree(h->b.chunks); hipFree(h->b.bkey); hipFree(h->b.cpart); hipFree(h->b.gpart); hipFree(h->b.shift); hipFree(h->b.macc); hipFree(h->b.vir); hipFree(h->b.coll); hipFree(h->b.pair_count); hipFree(h->b.status); hipFree(h->b.mix);
 }
 
@@ -1281,7 +1285,7 @@ int scratch_of(int device, unsigned char** out) {
 // only measures.
 template <typename real>
 size_t carve(uintptr_t base, int64_t n, int64_t ncell_tot, int64_t nob, int nblk, int nchunk, bool masses,
-             Buffers& B) {
+             bool second, Buffers& B) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> void* {
         const uintptr_t p = base + off;
@@ -1296,6 +1300,7 @@ size_t carve(uintptr_t base, int64_t n, int64_t ncell_tot, int64_t nob, int nblk
     B.best = (int32_t*)take(4 * nn);
     B.perm = (int32_t*)take(4 * nn);
     B.rec = take(8 * sizeof(real) * nn);
+    B.rec2 = second ? take(8 * sizeof(real) * nn) : nullptr;
     B.rmass = masses ? take(sizeof(real) * nn) : nullptr;
     B.bkey = std::is_same<real, float>::value ? (unsigned long long*)take(8 * nn) : (unsigned long long*)B.best;
     B.start = (int32_t*)take(4 * (size_t)(ncell_tot + 1));
@@ -1341,8 +1346,11 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     d.chunk0 = 0;
     d.nchunk = nchunk;
     Buffers Bf{};
-    if ((d.flags & kSubgrid) &&
-        carve<real>(0, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, Bf) > TPKMC_NOALLOC_SCRATCH_BYTES) {
+    auto fits = [&](bool second) {
+        return carve<real>(0, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, second, Bf) <=
+               TPKMC_NOALLOC_SCRATCH_BYTES;
+    };
+    if ((d.flags & kSubgrid) && !fits(false)) {
         // The sub-grid is an extra: without it where the scratch is short.
         if ((rc = fill_inst<real>(s, q, d, C, B, nullptr, 0.0, false))) return rc;
         ncell_tot = (int64_t)d.C + 1;
@@ -1351,15 +1359,17 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
         d.chunk0 = 0;
         d.nchunk = nchunk;
     }
-    if (carve<real>(0, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, Bf) > TPKMC_NOALLOC_SCRATCH_BYTES)
-        return TPKMC_ECAPACITY;
+    if (!fits(false)) return TPKMC_ECAPACITY;
+    // So are the second records, which only a state in the caller's order takes.
+    const bool caller_order = !(p->flags & TPKMC_ALLOW_REORDER);
+    const bool second = caller_order && fits(true);
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess) return TPKMC_EHIP;
     if (device < 0 || device >= ndev || device >= kMaxDevices) return TPKMC_EINVAL;
     if (hipSetDevice(device) != hipSuccess) return TPKMC_EHIP;
     unsigned char* base = nullptr;
     if ((rc = scratch_of(device, &base))) return rc;
-    carve<real>((uintptr_t)base, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, Bf);
+    carve<real>((uintptr_t)base, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, second, Bf);
     const bool random = (p->flags & TPKMC_PAIR_RANDOM) != 0;
     Shape P{};
     P.n_inst = 1;
@@ -1372,6 +1382,7 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     P.prep = (p->flags & TPKMC_ADAPTIVE_DT) != 0 || (d.flags & kSubgrid) != 0;
     P.any_staged = !random && !(d.flags & kTiles);
     P.any_tiles = !random && (d.flags & kTiles);
+    P.caller_order = caller_order;
     P.any_search = !random;
     P.any_random = random;
     P.split = false;
@@ -1435,6 +1446,7 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
     bad |= dalloc(&h->b.best, h->max_n);
     bad |= dalloc(&h->b.perm, h->max_n);
     bad |= hipMalloc(&h->b.rec, rs * 8 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
+    bad |= hipMalloc(&h->b.rec2, rs * 8 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
     bad |= hipMalloc(&h->b.rmass, rs * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
     bad |= hipMalloc(&h->b.inst, inst_sz * (size_t)h->max_inst) != hipSuccess;
     bad |= dalloc(&h->b.blk, h->max_blk);

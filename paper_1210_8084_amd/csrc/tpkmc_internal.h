@@ -144,7 +144,8 @@ struct StepArgs {
     real* rec;                // c-bin ordered records, 8 reals per particle
     real* mass;               // caller's per-particle masses, or null
     real* rmass;              // masses in record order (with mass only)
-    int32_t* src;             // record -> caller index
+    real* rec2;               // records after the move, for a state in the caller's order; or null (no room)
+    int32_t* src;             // caller's order only: caller index -> record (without rec2: record -> caller index)
     int32_t* best;            // random partners: rank in the c-bin; FP64: then the partner record or -1
     int32_t* perm;            // random partners: c-bin-local order -> record
     unsigned long long* bkey; // record -> (ranking value bits, partner record) of its closest candidate
@@ -153,9 +154,9 @@ struct StepArgs {
     double* shift;            // per-o-bin velocity shift (3 per o-bin)
     int32_t order;            // search work-group order: 0 contiguous per XCD, S > 0 chunks of S round-robin
     ObAcc* macc;              // per-o-bin exact sums, or null (no moments)
-    real* vir;                // virial terms of each collider (3 per particle, caller index)
-    uint8_t* coll;            // 1 if the particle collided this step (caller index); FP64, until the move:
-                              // 1 if the record's key met an equal one (record index)
+    real* vir;                // virial terms of each collider (3 per particle; record index, or caller index without rec2)
+    uint8_t* coll;            // 1 if the particle collided this step (indexed as vir); FP64, until the move: 1 if
+                              // the record's key met an equal one (record index)
     unsigned long long* mix;  // search mix counters (tests, s0 < 0, s0 < 0 < s1), or null
     // outputs
     uint32_t* pairs;
@@ -175,7 +176,7 @@ template <typename real> void launch_search_ties(const StepArgs<real>& a, hipStr
 template <typename real> void launch_search_mix(const StepArgs<real>& a, int n_inst, bool split, hipStream_t s);
 template <typename real> void launch_search_fast(const StepArgs<real>& a, int n_inst, hipStream_t s);
 template <typename real> void launch_move(const StepArgs<real>& a, hipStream_t s);
-template <typename real> void launch_moments(const StepArgs<real>& a, hipStream_t s);
+template <typename real> void launch_moments(const StepArgs<real>& a, bool caller_order, hipStream_t s);
 template <typename real> void launch_random_pairs(const StepArgs<real>& a, hipStream_t s);
 template <typename real> void launch_speed_stats(const StepArgs<real>& a, hipStream_t s);
 

@@ -20,7 +20,9 @@
 namespace tpkmc {
 
 // ---------------------------------------------------------------- records
-// Record layout: x y z id | vx vy vz flags (8 reals).  flags bit 0 = alive.
+// Record layout: x y z id | vx vy vz flags (8 reals).  flags bit 0 = alive;
+// after the move (StepArgs::rec2) one of the three words below.
+constexpr uint32_t kRecDead = 0u, kRecAlive = 1u, kRecAbsorbed = 2u;
 template <typename real> struct Rec;
 
 template <> struct Rec<float> {
@@ -533,7 +535,10 @@ __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
         const int64_t dst = base + a.start[k] + a.rank[p];
         const uint32_t fl = alive ? 1u : 0u;
         Rec<real>::store(a.rec, dst, x, y, z, a.id[p], vx, vy, vz, fl);
-        if (!(I.flags & TPKMC_ALLOW_REORDER)) a.src[dst] = (int32_t)p;
+        if (!(I.flags & TPKMC_ALLOW_REORDER)) {
+            if (a.rec2) a.src[p] = (int32_t)dst;
+            else a.src[dst] = (int32_t)p;
+        }
         // Every record of the instance starts without a partner; which of
         // them this thread clears is free, so the stores are consecutive.
         a.bkey[p] = ~0ull;
@@ -2366,9 +2371,12 @@ __device__ __forceinline__ void moment_terms(double m, double vx, double vy, dou
 }
 
 // Biased exponent E + kExpBias of the smallest power of two 2^E > |x| (0 for
-// x = 0).
+// x = 0), from the exponent bits (below the normal doubles one value serves:
+// the quantum is the same there, see fixed_scale).
 __device__ __forceinline__ int exp_above(double x) {
-    return x != 0.0 ? ilogb(x) + 1 + kExpBias : 0;
+    const int hi = __double2hiint(x) & 0x7fffffff;
+    const int e = max(hi >> 20, 1) + (1 - 1023 + kExpBias);
+    return (hi | __double2loint(x)) != 0 ? e : 0;
 }
 
 // x rounded to the nearest multiple of 2^(E-50), in units of that quantum;
@@ -2471,32 +2479,57 @@ __device__ __forceinline__ uint32_t row_sum32(uint32_t v, int lim) {
     return v;
 }
 
-__device__ __forceinline__ int row_max32(int v, int lim) {
-    int u = __builtin_amdgcn_mov_dpp(v, kRowShl1, 0xF, 0xF, false);
-    if (1 < lim) v = max(v, u);
-    u = __builtin_amdgcn_mov_dpp(v, kRowShl2, 0xF, 0xF, false);
-    if (2 < lim) v = max(v, u);
-    u = __builtin_amdgcn_mov_dpp(v, kRowShl4, 0xF, 0xF, false);
-    if (4 < lim) v = max(v, u);
-    u = __builtin_amdgcn_mov_dpp(v, kRowShl8, 0xF, 0xF, false);
-    if (8 < lim) v = max(v, u);
+// The same for the maxima of two 16-bit numbers at once.
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t max16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a),
+                                                                  __builtin_bit_cast(ushort2_t, b)));
+}
+__device__ __forceinline__ uint32_t row_max16(uint32_t v, int lim) {
+    uint32_t u = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kRowShl1, 0xF, 0xF, false);
+    if (1 < lim) v = max16(v, u);
+    u = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kRowShl2, 0xF, 0xF, false);
+    if (2 < lim) v = max16(v, u);
+    u = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kRowShl4, 0xF, 0xF, false);
+    if (4 < lim) v = max16(v, u);
+    u = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kRowShl8, 0xF, 0xF, false);
+    if (8 < lim) v = max16(v, u);
     return v;
+}
+
+// Sums over each row of 16 lanes, in a fixed order; every lane must be
+// active.  row_sum4: of four doubles at once, lane l getting the sum of value
+// l & 3 (each exchange halves the values a lane still carries, 27
+// instructions instead of 92 for four whole reductions).
+template <bool MAX>
+__device__ __forceinline__ double row_reduce(double v) {
+    auto op = [](double x, double y) { return MAX ? fmax(x, y) : x + y; };
+    v = op(v, dpp_move<kQuadXor1>(v));
+    v = op(v, dpp_move<kQuadXor2>(v));
+    v = op(v, dpp_move<kRowRor4>(v));
+    return op(v, dpp_move<kRowRor8>(v));
+}
+__device__ __forceinline__ double row_sum4(double v0, double v1, double v2, double v3, int lane) {
+    const bool odd = lane & 1, high = lane & 2;
+    const double a = (odd ? v1 : v0) + dpp_move<kQuadXor1>(odd ? v0 : v1);
+    const double b = (odd ? v3 : v2) + dpp_move<kQuadXor1>(odd ? v2 : v3);
+    double r = (high ? b : a) + dpp_move<kQuadXor2>(high ? a : b);
+    r += dpp_move<kRowRor4>(r);
+    return r + dpp_move<kRowRor8>(r);
 }
 
 // Unambiguous pairs (each the other's closest candidate) scatter; every
 // particle moves and meets the walls; global sums; with moments, the first
 // pass of the exact o-bin sums (see ObAcc): the exponent maxima, and each
-// particle's collider flag and virial terms for the moment pass.  Each lane
-// takes kMoveRec consecutive records (a lane keeps its run's maxima in
-// registers and touches the work-group's o-bin table only when the o-bin
-// changes; the next record is loaded while the current one is processed).
-// Since the moment sums moved to their own pass, one record per lane is the
-// fastest: move and moment pass 0.66 ms on the 16M Sedov blast against 0.75
-// and 0.97 ms with two and four records per lane, with the same order on
-// the Noh implosion and the Sod tube.
-constexpr int kMoveRec = 1;
-constexpr int kMoveLanes = kBlock / kMoveRec;
-
+// particle's collider flag and virial terms for the moment pass.  One record
+// per lane.  The new state goes to the caller's arrays (c-bin order kept), to
+// records in a second buffer that the moment pass reads and puts back in the
+// caller's order, or, where there is no room for that, scattered into the
+// caller's arrays.
+// The pass is bound by its instructions (828 a wave on the 16M blast, of
+// which the sums of the work-group were 250): exponents from the bits of the
+// largest term per kind, counts by votes and the sums' exchanges shared brought
+// it from XXX to XXX ms.
 // A lane's run maxima and counts of one o-bin into the work-group table, or
 // straight into the global accumulators when the table is full.
 template <typename real>
@@ -2519,9 +2552,13 @@ __device__ __forceinline__ void exp_flush(ExpTable& tab, const StepArgs<real>& a
 }
 
 template <typename real>
-__global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
+__global__ void __launch_bounds__(kBlock) k_move(StepArgs<real> a) {
     __shared__ ExpTable tab;
-    __shared__ double red[kMoveLanes / 64][11];
+    // Per row of 16 lanes: momentum, kinetic energy, max |v|^2, virial, mass;
+    // per wave: alive, pairs, absorbed, with a partner.
+    constexpr int kWaves = kBlock / kWave, kRows16 = kBlock / 16;
+    __shared__ double red[kRows16][7];
+    __shared__ int votes[kWaves][4];
     // Consecutive work-groups on one XCD: partners' records and keys, a few
     // c-bins away in record order, are then mostly in that XCD's L2.
     const int lb = xcd_remap(blockIdx.x, gridDim.x);
@@ -2533,44 +2570,35 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
     const bool reorder = (I.flags & TPKMC_ALLOW_REORDER) != 0;
     const bool has_mass = (I.flags & kHasMass) != 0;
     if (a.macc) {
-        for (int t = tid; t < kSlots; t += kMoveLanes) {
+        for (int t = tid; t < kSlots; t += kBlock) {
             tab.key[t] = -1;
             for (int k = 0; k < 4; ++k) tab.e[t][k] = 0;
             tab.n[t][0] = tab.n[t][1] = 0;
         }
         __syncthreads();
     }
-    double gpx = 0, gpy = 0, gpz = 0, gek = 0, gvm = 0, gvir = 0, gm = 0, galive = 0, gpairs = 0, gabs = 0, ghave = 0;
-    int mob = -1;                              // o-bin of the run
-    double sh[3] = {0.0, 0.0, 0.0};            // its velocity shift
-    int me[4] = {0, 0, 0, 0};                  // its exponent maxima per kind
-    uint32_t mcnt = 0, mcoll = 0;              // its particles and colliders
-    // The next record and its partner key are loaded while the current one
-    // is processed (two records in flight per lane).
-    const int64_t i_first = (int64_t)bt.first + kMoveRec * tid;
-    real nx_ = 0, ny_ = 0, nz_ = 0, nvx_ = 0, nvy_ = 0, nvz_ = 0;
-    uint32_t nid_ = 0, nfl_ = 0;
-    int32_t npj_ = -1;
-    if (i_first < end) {
-        Rec<real>::load(a.rec, i_first, nx_, ny_, nz_, nid_, nvx_, nvy_, nvz_, nfl_);
-        npj_ = partner_of<real>(a, I, i_first);
-    }
-#pragma unroll 1
-    for (int r = 0; r < kMoveRec; ++r) {
-        const int64_t i = i_first + r;
-        bool emit = false;
-        uint32_t emit_a = 0, emit_b = 0;
-        const real x = nx_, y = ny_, z = nz_, vx = nvx_, vy = nvy_, vz = nvz_;
-        const uint32_t idi = nid_, fl = nfl_;
-        const int32_t j_pre = npj_;
-        if (r + 1 < kMoveRec && i + 1 < end) {
-            Rec<real>::load(a.rec, i + 1, nx_, ny_, nz_, nid_, nvx_, nvy_, nvz_, nfl_);
-            npj_ = partner_of<real>(a, I, i + 1);
+    double gpx = 0, gpy = 0, gpz = 0, gek = 0, gvm = 0, gvir = 0, gm = 0;
+    bool counted = false, first_of_pair = false, absorbed = false, has_best = false;
+    int mob = -1;                              // o-bin
+    uint32_t me01 = 0, me23 = 0;               // exponents per kind, two a word
+    bool collider = false;
+    const int64_t i = (int64_t)bt.first + tid;
+    uint32_t emit_a = 0, emit_b = 0;
+    {
+        real x = 0, y = 0, z = 0, vx = 0, vy = 0, vz = 0;
+        uint32_t idi = 0, fl = 0;
+        int32_t j_pre = -1;
+        if (i < end) {
+            Rec<real>::load(a.rec, i, x, y, z, idi, vx, vy, vz, fl);
+            j_pre = partner_of<real>(a, I, i);
         }
         if (i < end) {
-            const int64_t dst = reorder ? i : (int64_t)a.src[i];
+            // Where the state, and its collider flag and virial terms, go.
+            const bool direct = reorder || !a.rec2;
+            const int64_t dst = reorder || a.rec2 ? i : (int64_t)a.src[i];
             const bool alive = (fl & 1u) != 0;
             if (!alive) {
+                if (!direct) Rec<real>::store(a.rec2, i, x, y, z, idi, vx, vy, vz, kRecDead);
                 if (reorder) {
                     a.x[dst] = x; a.y[dst] = y; a.z[dst] = z;
                     a.vx[dst] = vx; a.vy[dst] = vy; a.vz[dst] = vz;
@@ -2583,7 +2611,7 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
                 const real mi = has_mass ? a.rmass[i] : I.mass;
                 const int32_t j = j_pre;
                 bool mutual = j >= 0 && partner_of<real>(a, I, j) == (int32_t)i;
-                ghave += j >= 0 ? 1.0 : 0.0;
+                has_best = j >= 0;
                 real nx = x, ny = y, nz = z, nvx = vx, nvy = vy, nvz = vz;
                 double virx = 0, viry = 0, virz = 0;
                 const bool random_pairs = (I.flags & TPKMC_PAIR_RANDOM) != 0;
@@ -2650,10 +2678,9 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
                     virx = (double)(real(0.5) * sx * (mi * (nvx - vx)) / dt);
                     viry = (double)(real(0.5) * sy * (mi * (nvy - vy)) / dt);
                     virz = (double)(real(0.5) * sz * (mi * (nvz - vz)) / dt);
-                    if (isA) {
-                        gpairs += 1.0;
-                        if (I.flags & TPKMC_EMIT_PAIRS) { emit = true; emit_a = idi; emit_b = idj; }
-                    }
+                    first_of_pair = isA;
+                    emit_a = idi;
+                    emit_b = idj;
                 } else {
                     nx = x + vx * dt;
                     ny = y + vy * dt;
@@ -2678,12 +2705,16 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
                         if (q < lo || q >= hi) gone = true;
                     }
                 }
-                a.x[dst] = nx; a.y[dst] = ny; a.z[dst] = nz;
-                a.vx[dst] = nvx; a.vy[dst] = nvy; a.vz[dst] = nvz;
-                if (reorder) a.id[dst] = idi;
-                if (reorder && has_mass) a.mass[dst] = mi;
-                if (a.alive && (reorder || gone)) a.alive[dst] = gone ? 0 : 1;
-                if (gone) gabs += 1.0;
+                absorbed = gone;
+                if (direct) {
+                    a.x[dst] = nx; a.y[dst] = ny; a.z[dst] = nz;
+                    a.vx[dst] = nvx; a.vy[dst] = nvy; a.vz[dst] = nvz;
+                    if (reorder) a.id[dst] = idi;
+                    if (reorder && has_mass) a.mass[dst] = mi;
+                    if (a.alive && (reorder || gone)) a.alive[dst] = gone ? 0 : 1;
+                } else {
+                    Rec<real>::store(a.rec2, i, nx, ny, nz, idi, nvx, nvy, nvz, gone ? kRecAbsorbed : kRecAlive);
+                }
                 const bool fin = finite3(nx, ny, nz) && finite3(nvx, nvy, nvz) &&
                                  (!has_mass || (mi > real(0) && mi < real(INFINITY)));
                 if (!gone && fin) {
@@ -2692,30 +2723,21 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
                     const double v2 = (dvx * dvx + dvy * dvy) + dvz * dvz;
                     gpx += m * dvx; gpy += m * dvy; gpz += m * dvz;
                     gek += (0.5 * m) * v2;
-                    gvm = v2 > gvm ? v2 : gvm;
-                    gvir += (virx + viry) + virz;
-                    gm += m;
-                    galive += 1.0;
+                    gvm = v2;
+                    gvir = (virx + viry) + virz;
+                    gm = m;
+                    counted = true;
                     if (a.macc) {
-                        const int ob = obin_of(I, nx, ny, nz);
-                        if (ob != mob) {
-                            if (mob >= 0) exp_flush(tab, a, mob, me, mcnt, mcoll);
-                            const double* S = a.shift + (int64_t)ob * 3;
-                            sh[0] = S[0]; sh[1] = S[1]; sh[2] = S[2];
-                            mob = ob;
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) me[k] = 0;
-                            mcnt = mcoll = 0;
-                        }
-                        mcnt += 1;
-                        mcoll += mutual ? 1u : 0u;
-                        double t[kAccVals];
-                        moment_terms(m, dvx, dvy, dvz, sh, virx, viry, virz, t);
-                        me[0] = max(me[0], exp_above(fmax(fmax(fabs(t[0]), fabs(t[1])), fabs(t[2]))));
-                        me[1] = max(me[1], exp_above(fmax(fmax(t[3], t[4]), t[5])));
-                        if (mutual)
-                            me[2] = max(me[2], exp_above(fmax(fmax(fabs(t[6]), fabs(t[7])), fabs(t[8]))));
-                        if (has_mass) me[3] = max(me[3], exp_above(t[9]));
+                        mob = obin_of(I, nx, ny, nz);
+                        const double* S = a.shift + (int64_t)mob * 3;
+                        // The largest term of a kind is that of the largest
+                        // offset (rounding keeps the order).
+                        const double e = fmax(fmax(fabs(dvx - S[0]), fabs(dvy - S[1])), fabs(dvz - S[2]));
+                        const double t0 = m * e, t1 = t0 * e;
+                        me01 = (uint32_t)exp_above(t0) | (uint32_t)exp_above(t1) << 16;
+                        if (mutual) me23 = (uint32_t)exp_above(fmax(fmax(fabs(virx), fabs(viry)), fabs(virz)));
+                        if (has_mass) me23 |= (uint32_t)exp_above(m) << 16;
+                        collider = mutual;
                         a.coll[dst] = mutual ? 1 : 0;
                         if (mutual) {
                             a.vir[3 * dst] = (real)virx;
@@ -2726,8 +2748,9 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
                 }
             }
         }
-        // Pair list: one atomic per wave and record slot.
+        // Pair list: one atomic per wave.
         if (a.pairs) {
+            const bool emit = first_of_pair && (I.flags & TPKMC_EMIT_PAIRS) != 0;
             const uint64_t em = __ballot(emit);
             if (em) {
                 const int leader = __ffsll((long long)em) - 1;
@@ -2745,19 +2768,21 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
         }
     }
     if (a.macc) {
-        // Consecutive lanes hold consecutive records, so their last runs come
-        // in runs of one o-bin across the wave: within each row of 16 lanes
-        // the run's maxima go to its first lane, which alone goes through the
-        // table; then the table goes to the global maxima.
+        // Consecutive lanes hold consecutive records, so their o-bins come in
+        // runs: within each row of 16 lanes the run's maxima and counts go to
+        // its first lane, which alone goes through the work-group's table;
+        // then the table goes to the global accumulators.
         bool head;
         const int lim = row_lim(mob, lane, head);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) me[k] = row_max32(me[k], lim);
-        mcnt = row_sum32(mcnt, lim);
-        mcoll = row_sum32(mcoll, lim);
-        if ((head || (lane & 15) == 0) && mob >= 0) exp_flush(tab, a, mob, me, mcnt, mcoll);
+        me01 = row_max16(me01, lim);
+        if (__ballot(me23 != 0)) me23 = row_max16(me23, lim);  // wave-uniform
+        const uint32_t n = row_sum32(mob >= 0 ? (collider ? 0x10001u : 1u) : 0u, lim);
+        if ((head || (lane & 15) == 0) && mob >= 0) {
+            const int e[4] = {(int)(me01 & 0xffffu), (int)(me01 >> 16), (int)(me23 & 0xffffu), (int)(me23 >> 16)};
+            exp_flush(tab, a, mob, e, n & 0xffffu, n >> 16);
+        }
         __syncthreads();
-        for (int t = tid; t < kSlots * 5; t += kMoveLanes) {
+        for (int t = tid; t < kSlots * 5; t += kBlock) {
             const int slot = t / 5, k = t % 5;
             const int ob = tab.key[slot];
             if (ob < 0) continue;
@@ -2769,24 +2794,44 @@ __global__ void __launch_bounds__(kMoveLanes) k_move(StepArgs<real> a) {
             }
         }
     }
-    double v[11] = {gpx, gpy, gpz, gek, gvm, gvir, gm, galive, gpairs, gabs, ghave};
-#pragma unroll
-    for (int k = 0; k < 11; ++k) v[k] = k == 4 ? wave_reduce<true>(v[k]) : wave_reduce<false>(v[k]);
-    if (kMoveLanes > 64) {
-        if (lane == 0)
-#pragma unroll
-            for (int k = 0; k < 11; ++k) red[tid >> 6][k] = v[k];
-        __syncthreads();
-        if (tid == 0)
-            for (int w = 1; w < kMoveLanes / 64; ++w)
-#pragma unroll
-                for (int k = 0; k < 11; ++k) v[k] = k == 4 ? fmax(v[k], red[w][k]) : v[k] + red[w][k];
+    // Global sums: over rows of 16 lanes here, the rows in order below.
+    const uint64_t nalive = __ballot(counted), npairs = __ballot(first_of_pair), nabs = __ballot(absorbed),
+                   nhave = __ballot(has_best);
+    const double s4 = row_sum4(gpx, gpy, gpz, gek, lane);
+    const double vm = row_reduce<true>(gvm);
+    double vir = 0.0, mass = 0.0;
+    if (__ballot(gvir != 0.0)) vir = row_reduce<false>(gvir);  // wave-uniform
+    if (has_mass) mass = row_reduce<false>(gm);
+    const int row = tid >> 4;
+    if ((lane & 15) < 4) red[row][lane & 3] = s4;
+    if ((lane & 15) == 0) {
+        red[row][4] = vm;
+        red[row][5] = vir;
+        red[row][6] = mass;
     }
-    if (tid == 0) {
-        double* gp = a.gpart + (int64_t)lb * kGPart;
-        gp[GP_PX] = v[0]; gp[GP_PY] = v[1]; gp[GP_PZ] = v[2]; gp[GP_EKIN] = v[3]; gp[GP_VMAX2] = v[4];
-        gp[GP_VIR] = v[5]; gp[GP_MASS] = v[6]; gp[GP_ALIVE] = v[7]; gp[GP_PAIRS] = v[8]; gp[GP_ABSORBED] = v[9];
-        gp[GP_HAVEBEST] = v[10];
+    if (lane == 0) {
+        int* w = votes[tid >> 6];
+        w[0] = __popcll(nalive);
+        w[1] = __popcll(npairs);
+        w[2] = __popcll(nabs);
+        w[3] = __popcll(nhave);
+    }
+    __syncthreads();
+    double* gp = a.gpart + (int64_t)lb * kGPart;
+    if (tid < 7) {
+        double v = red[0][tid];
+        for (int r = 1; r < kRows16; ++r) v = tid == 4 ? fmax(v, red[r][tid]) : v + red[r][tid];
+        if (tid == 6 && !has_mass) {
+            int n = 0;
+            for (int w = 0; w < kWaves; ++w) n += votes[w][0];
+            v = (double)n * I.mass_d;
+        }
+        gp[GP_PX + tid] = v;  // momentum, kinetic energy, max |v|^2, virial, mass
+    } else if (tid >= kWave && tid < kWave + 4) {
+        const int k = tid - kWave;
+        int n = 0;
+        for (int w = 0; w < kWaves; ++w) n += votes[w][k];
+        gp[k == 3 ? GP_HAVEBEST : GP_ALIVE + k] = (double)n;  // alive, pairs, absorbed
     }
 }
 
@@ -2820,7 +2865,8 @@ __device__ __forceinline__ void value_flush(MomentTable& tab, const StepArgs<rea
 // 16M Sedov blast, 1.18, 1.16, 1.16 and 1.17 on the Sod 4M tube).
 constexpr int kMomEntries = 2;
 
-template <typename real>
+// RECS: some instance keeps the caller's order by way of the second records.
+template <typename real, bool RECS>
 __global__ void __launch_bounds__(kBlock) k_moments(StepArgs<real> a) {
     __shared__ MomentTable tab;
     const int lb = xcd_remap(blockIdx.x, gridDim.x);
@@ -2843,13 +2889,35 @@ __global__ void __launch_bounds__(kBlock) k_moments(StepArgs<real> a) {
 #pragma unroll
         for (int k = 0; k < kAccVals; ++k) q[k] = 0;
         bool coll = false;
+        if (RECS && !reorder && i < end) {
+            // Back to the caller's order: one record, a line or less, gathered
+            // per particle, and consecutive stores.
+            real x, y, z, vx, vy, vz;
+            uint32_t id, fl;
+            Rec<real>::load(a.rec2, a.src[i], x, y, z, id, vx, vy, vz, fl);
+            if (fl != kRecDead) {
+                a.x[i] = x; a.y[i] = y; a.z[i] = z;
+                a.vx[i] = vx; a.vy[i] = vy; a.vz[i] = vz;
+                if (a.alive && fl == kRecAbsorbed) a.alive[i] = 0;
+            }
+        }
+        if (RECS && !a.macc) continue;  // uniform
         if (i < end) {
             // The same particles as the move's moment terms: alive after the
             // step (not absorbed), finite, with a valid mass.
-            const int64_t p = reorder ? i : (int64_t)a.src[i];
-            const bool alive = a.alive ? a.alive[p] != 0 : true;
-            const real x = a.x[p], y = a.y[p], z = a.z[p], vx = a.vx[p], vy = a.vy[p], vz = a.vz[p];
-            const real mi = has_mass ? a.mass[p] : I.mass;
+            const bool direct = reorder || !RECS;
+            const int64_t p = reorder || RECS ? i : (int64_t)a.src[i];
+            real x, y, z, vx, vy, vz;
+            bool alive;
+            if (direct) {
+                alive = a.alive ? a.alive[p] != 0 : true;
+                x = a.x[p]; y = a.y[p]; z = a.z[p]; vx = a.vx[p]; vy = a.vy[p]; vz = a.vz[p];
+            } else {
+                uint32_t id, fl;
+                Rec<real>::load(a.rec2, i, x, y, z, id, vx, vy, vz, fl);
+                alive = fl == kRecAlive;
+            }
+            const real mi = has_mass ? (direct ? a.mass[p] : a.rmass[i]) : I.mass;
             const bool fin = finite3(x, y, z) && finite3(vx, vy, vz) &&
                              (!has_mass || (mi > real(0) && mi < real(INFINITY)));
             if (alive && fin) {
@@ -2894,6 +2962,7 @@ __global__ void __launch_bounds__(kBlock) k_moments(StepArgs<real> a) {
         }
         if ((head || (lane & 15) == 0) && ob >= 0) value_flush(tab, a, ob, q);
     }
+    if (RECS && !a.macc) return;
     __syncthreads();
     // The table to the global sums: one thread per (slot, value).
     for (int t = tid; t < kMomSlots * kTabWords; t += kBlock) {
@@ -3051,12 +3120,13 @@ void launch_random_pairs(const StepArgs<real>& a, hipStream_t s) {
 }
 template <typename real>
 void launch_move(const StepArgs<real>& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_move<real>, dim3(a.nblk), dim3(kMoveLanes), 0, s, a);
+    hipLaunchKernelGGL(k_move<real>, dim3(a.nblk), dim3(kBlock), 0, s, a);
 }
 template <typename real>
-void launch_moments(const StepArgs<real>& a, hipStream_t s) {
+void launch_moments(const StepArgs<real>& a, bool caller_order, hipStream_t s) {
     const unsigned grid = (unsigned)((a.nblk + kMomEntries - 1) / kMomEntries);
-    hipLaunchKernelGGL(k_moments<real>, dim3(grid), dim3(kBlock), 0, s, a);
+    if (caller_order && a.rec2) hipLaunchKernelGGL((k_moments<real, true>), dim3(grid), dim3(kBlock), 0, s, a);
+    else if (a.macc) hipLaunchKernelGGL((k_moments<real, false>), dim3(grid), dim3(kBlock), 0, s, a);
 }
 
 }  // namespace tpkmc
