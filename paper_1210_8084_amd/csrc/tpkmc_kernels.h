@@ -479,18 +479,17 @@ __device__ __forceinline__ int x_ranges(int cx, int n, bool periodic, int xa[2],
 
 // The unordered pairs of c-bin c with itself and with its neighbours, each
 // pair of c-bins once (the search's TPKMC_CNT_TESTS), from the sort cells'
-// prefix.  With sub-grids a c-bin spans many rows of sort cells, which the
-// 64 lanes of a wave share (c is then the same in all of them); without, each
+// prefix.  Where a c-bin spans many rows of sort cells (`shared`), the 64
+// lanes of a wave share them (c is then the same in all of them), else each
 // lane takes a c-bin of its own.  Returns the lane's (the wave's) count.
 template <typename real>
-__device__ double cbin_tests(const StepArgs<real>& a, const Inst<real>& I, int c, int lane) {
+__device__ double cbin_tests(const StepArgs<real>& a, const Inst<real>& I, int c, int lane, bool shared) {
     const int nl[3] = {I.nl[0], I.nl[1], I.nl[2]}, k[3] = {1 << I.kl[0], 1 << I.kl[1], 1 << I.kl[2]};
-    const bool sub = (I.flags & kSubgrid) != 0;
     const int x = c % nl[0], y = c / nl[0] % nl[1], z = c / nl[0] / nl[1], nf = k[1] * k[2];
     int xa[2], xb[2];
     const int nxr = x_ranges(x, nl[0], I.bc[0] == TPKMC_BC_PERIODIC, xa, xb);
     double own = 0.0, other = 0.0;
-    for (int t = sub ? lane : 0; t < 9 * nf; t += sub ? kWave : 1) {
+    for (int t = shared ? lane : 0; t < 9 * nf; t += shared ? kWave : 1) {
         const int r = t >> (I.kl[1] + I.kl[2]), f = t & (nf - 1);
         int yy, zz;
         if (!axis_nb(z, r / 3 - 1, nl[2], I.bc[2] == TPKMC_BC_PERIODIC, zz)) continue;
@@ -506,7 +505,7 @@ __device__ double cbin_tests(const StepArgs<real>& a, const Inst<real>& I, int c
             if (a0 <= xb[q]) other += records(a0, xb[q]);
         }
     }
-    if (sub) {
+    if (shared) {
         own = wave_reduce<false>(own);
         other = wave_reduce<false>(other);
     }
@@ -551,17 +550,19 @@ __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
     }
     if (I.flags & kTiles) {
         const int64_t ncb = (int64_t)I.nl[0] * I.nl[1] * I.nl[2];
-        const bool sub = (I.flags & kSubgrid) != 0;
+        // Four rows a c-bin and fewer go lane by lane: the Noh implosion's
+        // two rows took 0.09 ms shared.
+        const bool shared = I.kl[1] + I.kl[2] > 2;
         const int lane = threadIdx.x & (kWave - 1);
         const int64_t me = (int64_t)((int)blockIdx.x - I.blk0) * kBlock + threadIdx.x, all = (int64_t)I.nblk * kBlock;
         double tests = 0.0;
-        if (sub) {
+        if (shared) {
             for (int64_t c = me / kWave; c < ncb; c += all / kWave) {
-                const double t = cbin_tests(a, I, __builtin_amdgcn_readfirstlane((int)c), lane);
+                const double t = cbin_tests(a, I, __builtin_amdgcn_readfirstlane((int)c), lane, true);
                 tests += lane == 0 ? t : 0.0;
             }
         } else {
-            for (int64_t c = me; c < ncb; c += all) tests += cbin_tests(a, I, (int)c, lane);
+            for (int64_t c = me; c < ncb; c += all) tests += cbin_tests(a, I, (int)c, lane, false);
         }
         if (__ballot(tests != 0.0)) {
             tests = wave_reduce<false>(tests);
@@ -2410,17 +2411,22 @@ __device__ __forceinline__ void global_acc_add(ObAcc& G, int k, long long v) {
 
 // Work-group tables keyed by o-bin (open addressing), flushed to the global
 // accumulators once per work-group: exponent maxima in the move, value sums
-// in the moment pass.
+// in the moment pass.  Probes are limited: where a work-group meets more
+// o-bins than the table holds, the rest go to the global accumulators at once
+// instead of probing the whole table first (DSMC box of 2e5, 6 particles an
+// o-bin: move 25 -> 21 us, moments 34 -> 24; 16M blast: move 476 -> 447).
+// The moment pass takes more of them, since a global add there is 8 atomics
+// wide (16M blast at 8 probes: 377 us, at 24: 362).
 constexpr int kSlots = 64;       // exponent table (the move's 256 records)
 constexpr int kMomSlots = 128;   // value table (the moment pass's kMomEntries * 256 records)
 constexpr int kTabWords = kAccVals;  // the values' integer sums
 struct MomentTable {
-    static constexpr int kN = kMomSlots;
+    static constexpr int kN = kMomSlots, kProbes = 24;
     int key[kN];
     long long val[kN][kTabWords];
 };
 struct ExpTable {
-    static constexpr int kN = kSlots;
+    static constexpr int kN = kSlots, kProbes = 8;
     int key[kN];
     int e[kN][4];
     uint32_t n[kN][2];  // particles, colliders
@@ -2430,7 +2436,9 @@ template <typename Table>
 __device__ __forceinline__ int table_slot(Table& T, int ob) {
     constexpr int N = Table::kN;
     const int h = (int)((ob * 0x9E3779B1u) >> 24);  // 8 bits
-    for (int probe = 0; probe < N; ++probe) {
+// Unrolled, the moment pass took 359 us instead of 303 on the 20M equilibrium.
+#pragma unroll 1
+    for (int probe = 0; probe < Table::kProbes; ++probe) {
         const int s = (h + probe) & (N - 1);
         const int cur = T.key[s];
         if (cur == ob) return s;
@@ -2526,10 +2534,9 @@ __device__ __forceinline__ double row_sum4(double v0, double v1, double v2, doub
 // records in a second buffer that the moment pass reads and puts back in the
 // caller's order, or, where there is no room for that, scattered into the
 // caller's arrays.
-// The pass is bound by its instructions (828 a wave on the 16M blast, of
-// which the sums of the work-group were 250): exponents from the bits of the
-// largest term per kind, counts by votes and the sums' exchanges shared brought
-// it from XXX to XXX ms.
+// On the 16M blast it takes 0.44 ms; without the o-bin part it takes 0.28,
+// near what its 128 B a particle need, so the o-bins' exponents are taken from
+// the bits of the largest term per kind and their counts by votes.
 // A lane's run maxima and counts of one o-bin into the work-group table, or
 // straight into the global accumulators when the table is full.
 template <typename real>
