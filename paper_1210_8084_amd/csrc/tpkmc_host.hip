@@ -786,7 +786,8 @@ struct Shape {
 
 Shape shape_of(const Plan& P) {
     return Shape{P.n_inst, P.nblk, P.nchunk, P.max_chunks, P.ncell_tot, P.nob_tot, P.max_nob,
-                 P.adaptive || P.split || P.subgrid, P.any_search, P.any_random, P.split, P.any_staged, P.any_tiles, P.caller_order};
+                 P.adaptive || P.subgrid, P.any_search, P.any_random, P.split, P.any_staged, P.any_tiles,
+                 P.caller_order};
 }
 
 ClearArgs clear_args(const Buffers& B, const Shape& P, bool mom, bool fresh) {
@@ -835,7 +836,7 @@ void enqueue_step(tpkmc_handle* h, const Buffers& B, const StepArgs<real>& a, co
     if (P.nblk > 0) {
         PhaseScope ps(h, PH_KEY, s, prof);
         launch_key<real>(a, s);
-        if (P.prep) launch_prep<real>((Inst<real>*)B.inst, B.gpart, P.n_inst, P.nblk, s);
+        if (P.prep) launch_prep<real>((Inst<real>*)B.inst, B.gpart, P.n_inst, P.max_chunks * kChunk, s);
     }
     {
         PhaseScope ps(h, PH_SCAN, s, prof);
@@ -1137,7 +1138,8 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     // Bin once (clear, key, prefix, scatter); then time only the search.
     hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, clear_args(h->b, shape_of(P), false, false));
     launch_key<real>(a, st);
-    if (P.adaptive || P.split || P.subgrid) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
+    if (P.adaptive || P.subgrid)
+        launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.max_chunks * kChunk, st);
     enqueue_scan(h->b, P.ncell_tot + 1, st);
     launch_scatter<real>(a, st);
     hipEvent_t e0, e1;
@@ -1234,7 +1236,8 @@ int mix_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in
     a.order = h->search_order;
     hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, clear_args(h->b, shape_of(P), false, false));
     launch_key<real>(a, st);
-    if (P.adaptive || P.split || P.subgrid) launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.nblk, st);
+    if (P.adaptive || P.subgrid)
+        launch_prep<real>((Inst<real>*)h->b.inst, h->b.gpart, P.n_inst, P.max_chunks * kChunk, st);
     enqueue_scan(h->b, P.ncell_tot + 1, st);
     launch_scatter<real>(a, st);
     if (hipMemsetAsync(h->b.mix, 0, 3 * sizeof(unsigned long long), st) != hipSuccess) return TPKMC_EHIP;

@@ -79,12 +79,11 @@ struct Inst {
     // particles are binned on the n[] c-bins (the first Cf of the C), the
     // others on the configured ncfg[] c-bins after them, numbered
     // x + ncfg[0] * (y + ncfg[1] * z).  inv_wc: configured c-bins per unit
-    // length.  vmax2_d: this step's largest |v|^2 before the move.
+    // length.
     int32_t ncfg[3];
     int32_t Cf;
     real vc2;
     real inv_wc[3];
-    double vmax2_d;
     // Tile search: 1 / the length its positions are scaled by (the widest
     // c-bin).
     float tile_s;

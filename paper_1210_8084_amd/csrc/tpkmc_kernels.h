@@ -1758,20 +1758,6 @@ __device__ __forceinline__ int fast_span(const Inst<real>& I, int ax, real x, do
     return 1;
 }
 
-// Largest number of fine c-bins fast_span gives on one axis for a reach of
-// at most `reach` (the task list's stride per fast record).
-template <typename real>
-__device__ __forceinline__ int fast_span_len(const Inst<real>& I, int ax, double reach, bool periodic) {
-    const int nc = I.ncfg[ax], nf = I.n[ax];
-    const double eps = 1e-3 + 1e-6 * (double)nf;
-    int len = (int)floor(2.0 * reach * (double)I.inv_w[ax] + 2.0 * eps) + 2;
-    if (!(periodic && nc <= 3)) {
-        const int nb = nf == nc ? 3 : (int)floor(3.0 * (double)nf / (double)nc + 2.0 * eps) + 2;
-        len = len < nb ? len : nb;
-    }
-    return len < nf ? len : nf;
-}
-
 // Index t of the concatenation of at most two ranges [a[r], b[r]].
 __device__ __forceinline__ int span_at(const int a[2], const int b[2], int len0, int t) {
     return t < len0 ? a[0] + t : a[1] + (t - len0);
@@ -1830,128 +1816,124 @@ __device__ __forceinline__ double fast_reach(const Inst<real>& I, double v2) {
     return (sqrt((double)I.D2) + (sqrt(v2) + sqrt((double)I.vc2)) * (double)I.dt) * (1.0 + 1.0 / 64.0);
 }
 
-// The fast records' searches as a flat list of tasks, one per lane:
-// (fast record, row) for the fine rows of fast_span (index t < ny * nz) and
-// for the nine rows of configured c-bins of the fast particles (half
-// neighbourhood), so lanes stay busy however few rows a record has or
-// however many fast records there are.  A slow row longer than kLongRow
-// records (dense bins) is walked by the whole wave, lanes striding over its
-// records.  Every candidate lowers both keys with atomicMin, so the tasks of
-// one record may run in any lanes and any order.
-constexpr int kLongRow = 64;
+// The search of fast record i by a whole wave.  Its rows (the fine rows of
+// fast_span and the nine rows of configured c-bins of the fast particles, half
+// neighbourhood) are found one per lane, and their records are then taken 64
+// at a time from the rows laid end to end, so that a wave loads whole runs of
+// records and its lanes stay busy however short the rows are.  Of `parts`
+// waves that share a record, this one takes every parts-th 64.  Every
+// candidate lowers both keys with atomicMin, in any order.
+struct FastRows {
+    int32_t end[kWave];  // inclusive prefix of the rows' lengths
+    int4 row[kWave];     // place p: record x + p below place z, else y + p
+};
 
 template <typename real, bool MIX>
-__device__ void fast_tasks(const StepArgs<real>& a, const Inst<real>& I, int64_t base, int64_t f0, int64_t ntask,
-                           int per_rec, int rmax, int64_t q, int lane, double& seen, double& cand, uint32_t& n_s0,
-                           uint32_t& n_c1) {
+__device__ void fast_record(const StepArgs<real>& a, const Inst<real>& I, int64_t base, int32_t i, int part, int parts,
+                            int lane, FastRows& R, uint32_t& seen, uint32_t& cand, uint32_t& n_s0, uint32_t& n_c1) {
     const Geo<real> G_(I);
     const bool by_time = (I.flags & TPKMC_RANK_TIME) != 0;
     const int nf[3] = {I.n[0], I.n[1], I.n[2]};
     const int nc[3] = {I.ncfg[0], I.ncfg[1], I.ncfg[2]};
-    const bool valid = q < ntask;
-    int32_t i = 0;
-    int t = 0;
-    real xi = 0, yi = 0, zi = 0, vxi = 0, vyi = 0, vzi = 0;
-    int cc[3] = {0, 0, 0}, first[3] = {0, 0, 0}, span[3] = {0, 0, 0};
-    bool chk[3] = {false, false, false};
-    int32_t ja[2] = {0, 0}, jb[2] = {0, 0};
-    bool slow = false;
-    if (valid) {
-        i = (int32_t)(f0 + q / per_rec);
-        t = (int)(q % per_rec);
-        load_pv(a.rec, i, xi, yi, zi, vxi, vyi, vzi);
-        const real pi[3] = {xi, yi, zi};
+    real pi[3], vxi, vyi, vzi;
+    load_pv(a.rec, i, pi[0], pi[1], pi[2], vxi, vyi, vzi);
+    const double reach = fast_reach(I, speed2((double)vxi, (double)vyi, (double)vzi));
+    // The three axes' spans, found by a lane each.
+    int cc[3], first[3], span[3], n_r[3], fa[3][2], fb[3][2];
+    bool chk[3];
+    {
+        const int ax = min(lane, 2);
+        const real p = ax == 0 ? pi[0] : ax == 1 ? pi[1] : pi[2];
+        const bool per = ax == 0 ? G_.per[0] : ax == 1 ? G_.per[1] : G_.per[2];
+        const int c = axis_bin(p, I.lo[ax], I.inv_wc[ax], I.ncfg[ax]);
+        int f, s, a2[2] = {0, 0}, b2[2] = {0, 0};
+        bool ck;
+        coarse_nb(I, ax, p, reach, c, per, f, s, ck);
+        const int r = fast_span(I, ax, p, reach, c, per, a2, b2);
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) cc[ax] = axis_bin(pi[ax], I.lo[ax], I.inv_wc[ax], nc[ax]);
-        if (t < rmax) {
-            const double reach = fast_reach(I, speed2((double)vxi, (double)vyi, (double)vzi));
+        for (int l = 0; l < 3; ++l) {
+            cc[l] = __builtin_amdgcn_readlane(c, l);
+            first[l] = __builtin_amdgcn_readlane(f, l);
+            span[l] = __builtin_amdgcn_readlane(s, l);
+            chk[l] = __builtin_amdgcn_readlane((int)ck, l) != 0;
+            n_r[l] = __builtin_amdgcn_readlane(r, l);
 #pragma unroll
-            for (int ax = 0; ax < 3; ++ax)
-                coarse_nb(I, ax, pi[ax], reach, cc[ax], G_.per[ax], first[ax], span[ax], chk[ax]);
-            int ya[2], yb[2], za[2], zb[2];
-            const int nyr = fast_span(I, 1, yi, reach, cc[1], G_.per[1], ya, yb);
-            const int nzr = fast_span(I, 2, zi, reach, cc[2], G_.per[2], za, zb);
-            const int ly0 = nyr ? yb[0] - ya[0] + 1 : 0, lz0 = nzr ? zb[0] - za[0] + 1 : 0;
-            const int ny = ly0 + (nyr > 1 ? yb[1] - ya[1] + 1 : 0);
-            const int nz = lz0 + (nzr > 1 ? zb[1] - za[1] + 1 : 0);
-            if (t < ny * nz) {
-                int xa[2], xb[2];
-                const int nxr = fast_span(I, 0, xi, reach, cc[0], G_.per[0], xa, xb);
-                const int y = span_at(ya, yb, ly0, t % ny), z = span_at(za, zb, lz0, t / ny);
-                const int64_t row = I.cell_off + (int64_t)nf[0] * row_of(I, y, z);
-                for (int rx = 0; rx < nxr; ++rx) {
-                    ja[rx] = (int32_t)(base + a.start[row + xa[rx]]);
-                    jb[rx] = (int32_t)(base + a.start[row + xb[rx] + 1]);
-                }
-                slow = true;
+            for (int q = 0; q < 2; ++q) {
+                fa[l][q] = __builtin_amdgcn_readlane(a2[q], l);
+                fb[l][q] = __builtin_amdgcn_readlane(b2[q], l);
             }
         }
     }
-    // Tests slow or fast record j against fast record ii (the lane's own or,
-    // for long rows, the owner lane's, whose values are passed in).
-    auto test = [&](int32_t ii, real x0, real y0, real z0, real u0, real u1, real u2, int32_t j, real xj, real yj,
-                    real zj, real vxj, real vyj, real vzj) {
-        seen += 1.0;
-        if constexpr (MIX) {
-            Screen<real> S;
-            const bool p1 = PairTest<real, -1>::stage1(G_, x0, y0, z0, u0, u1, u2, xj, yj, zj, vxj, vyj, vzj, S);
-            n_s0 += S.s0 < real(0) ? 1u : 0u;
-            n_c1 += p1 ? 1u : 0u;
-        } else {
-            real value;
-            if (!test_pair(G_, by_time, x0, y0, z0, u0, u1, u2, xj, yj, zj, vxj, vyj, vzj, value)) return;
-            cand += 2.0;  // both orders
-            Key<real>::lower(a, j, Key<real>::make(value, (uint32_t)ii), key_now(a, j));
-            Key<real>::lower(a, ii, Key<real>::make(value, (uint32_t)j), key_now(a, ii));
-        }
-    };
-    const int len = slow ? (jb[0] - ja[0]) + (jb[1] - ja[1]) : 0;
-    // Long slow rows: the whole wave, one owner lane at a time.
-    uint64_t longm = __ballot(len > kLongRow);
-    while (longm) {
-        const int o = __ffsll((long long)longm) - 1;
-        longm &= longm - 1;
-        const int32_t io = __builtin_amdgcn_readlane(i, o);
-        const real xo = __shfl(xi, o), yo = __shfl(yi, o), zo = __shfl(zi, o);
-        const real uo0 = __shfl(vxi, o), uo1 = __shfl(vyi, o), uo2 = __shfl(vzi, o);
-        int fo[3], so[3];
-        bool co[3];
+    const int *xa = fa[0], *xb = fb[0], *ya = fa[1], *yb = fb[1], *za = fa[2], *zb = fb[2];
+    const int nxr = n_r[0], nyr = n_r[1], nzr = n_r[2];
+    const int ly0 = nyr ? yb[0] - ya[0] + 1 : 0, lz0 = nzr ? zb[0] - za[0] + 1 : 0;
+    const int ny = ly0 + (nyr > 1 ? yb[1] - ya[1] + 1 : 0);
+    const int nz = lz0 + (nzr > 1 ? zb[1] - za[1] + 1 : 0);
+    const int slow = nxr ? ny * nz : 0;
+    unsigned long long best = ~0ull;
+    for (int r0 = 0; r0 < slow + 9; r0 += kWave) {
+        const int t = r0 + lane;
+        int32_t j0[2] = {0, 0}, len[2] = {0, 0};
+        if (t < slow) {
+            const int y = span_at(ya, yb, ly0, t % ny), z = span_at(za, zb, lz0, t / ny);
+            const int64_t row = I.cell_off + (int64_t)nf[0] * row_of(I, y, z);
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            fo[ax] = __builtin_amdgcn_readlane(first[ax], o);
-            so[ax] = __builtin_amdgcn_readlane(span[ax], o);
-            co[ax] = __builtin_amdgcn_readlane((int)chk[ax], o) != 0;
+            for (int rx = 0; rx < 2; ++rx) {
+                if (rx >= nxr) continue;
+                j0[rx] = (int32_t)(base + a.start[row + xa[rx]]);
+                len[rx] = (int32_t)(base + a.start[row + xb[rx] + 1]) - j0[rx];
+            }
+        } else if (t < slow + 9) {
+            int k = 0;
+            neighbourhood_row<true, true>(a.start, I, base, nc, G_.per, cc[0], cc[1], cc[2], i, t - slow,
+                                          [&](int32_t u0, int32_t u1) {
+                const int32_t l = max(u1 - u0, 0);
+                if (k == 0) { j0[0] = u0; len[0] = l; }
+                else { j0[1] = u0; len[1] = l; }
+                ++k;
+            });
         }
+        int32_t end = len[0] + len[1];
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int32_t v = __shfl_up(end, o);
+            if (lane >= o) end += v;
+        }
+        const int32_t total = __builtin_amdgcn_readlane(end, kWave - 1);
+        const int32_t second = end - len[1];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        R.end[lane] = end;
+        R.row[lane] = make_int4(j0[0] - (second - len[0]), j0[1] - second, second, t);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int32_t p = part * kWave + lane; p < total; p += parts * kWave) {
+            int o = 0;  // the row place p lies in: the rows that end at or before it
 #pragma unroll
-        for (int rx = 0; rx < 2; ++rx) {
-            const int32_t a0 = __builtin_amdgcn_readlane(ja[rx], o), b0 = __builtin_amdgcn_readlane(jb[rx], o);
-            for (int32_t j = a0 + lane; j < b0; j += kWave) {
-                real xj, yj, zj, vxj, vyj, vzj;
-                load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
-                if (coarse_in(I, co, nc, fo, so, xj, yj, zj))
-                    test(io, xo, yo, zo, uo0, uo1, uo2, j, xj, yj, zj, vxj, vyj, vzj);
+            for (int h = kWave / 2; h; h >>= 1) o += R.end[o + h - 1] <= p ? h : 0;
+            const int4 row = R.row[o];
+            const int32_t j = p + (p < row.z ? row.x : row.y);
+            real xj, yj, zj, vxj, vyj, vzj;
+            load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
+            if (row.w < slow && !coarse_in(I, chk, nc, first, span, xj, yj, zj)) continue;
+            ++seen;
+            if constexpr (MIX) {
+                Screen<real> S;
+                const bool p1 = PairTest<real, -1>::stage1(G_, pi[0], pi[1], pi[2], vxi, vyi, vzi, xj, yj, zj, vxj,
+                                                           vyj, vzj, S);
+                n_s0 += S.s0 < real(0) ? 1u : 0u;
+                n_c1 += p1 ? 1u : 0u;
+            } else {
+                real value;
+                if (!test_pair(G_, by_time, pi[0], pi[1], pi[2], vxi, vyi, vzi, xj, yj, zj, vxj, vyj, vzj, value))
+                    continue;
+                cand += 2;  // both orders
+                Key<real>::lower(a, j, Key<real>::make(value, (uint32_t)i), key_now(a, j));
+                const unsigned long long k = Key<real>::make(value, (uint32_t)j);
+                if constexpr (sizeof(real) == 4) best = k < best ? k : best;
+                else Key<real>::lower(a, i, k, key_now(a, i));
             }
         }
     }
-    if (slow && len <= kLongRow) {
-#pragma unroll
-        for (int rx = 0; rx < 2; ++rx)
-            for (int32_t j = ja[rx]; j < jb[rx]; ++j) {
-                real xj, yj, zj, vxj, vyj, vzj;
-                load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
-                if (coarse_in(I, chk, nc, first, span, xj, yj, zj))
-                    test(i, xi, yi, zi, vxi, vyi, vzi, j, xj, yj, zj, vxj, vyj, vzj);
-            }
-    } else if (valid && t >= rmax) {
-        neighbourhood_row<true, true>(a.start, I, base, nc, G_.per, cc[0], cc[1], cc[2], i, t - rmax,
-                                      [&](int32_t j0, int32_t j1) {
-            for (int32_t j = j0; j < j1; ++j) {
-                real xj, yj, zj, vxj, vyj, vzj;
-                load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
-                test(i, xi, yi, zi, vxi, vyi, vzi, j, xj, yj, zj, vxj, vyj, vzj);
-            }
-        });
-    }
+    if constexpr (!MIX && sizeof(real) == 4)
+        if (best != ~0ull) Key<real>::lower(a, i, best, key_now(a, i));
 }
 
 template <int G>
@@ -2064,18 +2046,22 @@ __global__ void __launch_bounds__(kBlock) k_search_mix(StepArgs<real> a) {
 }
 
 // The fast records of split c-bins, in a launch of their own after the slow
-// ones' search (the keys combine with atomicMin in any order), striding over
-// the task list of fast_tasks.  The search's work counters are summed per
-// work-group and instance, and added to the instance's first block-table
-// entry.
+// ones' search (the keys combine with atomicMin in any order), one wave per
+// record.  All instances' records are dealt to the waves in turn, as one list;
+// an instance with fewer records than waves has up to kFastParts waves on each.
+// It waits for its loads: with a lane per row of a record, each walking its
+// row alone, the 4M tube took 0.164 ms, the 64-instance ensemble 4.6 ms late in
+// its run; with a wave per record 0.066 and 0.80 ms.
+constexpr int kFastParts = 8;
 template <typename real, bool MIX = false>
 __global__ void __launch_bounds__(256) k_search_fast(StepArgs<real> a, int n_inst) {
     __shared__ double lds[16];
+    __shared__ FastRows rows[256 / kWave];
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nth = (int64_t)gridDim.x * blockDim.x;
-    double mt = 0.0;
-    uint32_t n_s0 = 0, n_c1 = 0;
+    const int own = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const uint32_t nw = gridDim.x * (256 / kWave), wave = blockIdx.x * (256 / kWave) + own;
+    uint32_t turn = wave;  // this wave's first place in the instance's list
+    uint32_t n_seen = 0, n_s0 = 0, n_c1 = 0;
     for (int k = 0; k < n_inst; ++k) {
         const Inst<real>& I = a.inst[k];
         if (!(I.flags & kSplit) || (I.flags & TPKMC_PAIR_RANDOM)) continue;
@@ -2083,23 +2069,28 @@ __global__ void __launch_bounds__(256) k_search_fast(StepArgs<real> a, int n_ins
         const int64_t f0 = base + a.start[I.cell_off + I.Cf];
         const int64_t live_end = base + a.start[I.cell_off + I.C];
         const int64_t f1 = live_end < I.off + I.cnt ? live_end : I.off + I.cnt;
-        double t = 0.0, c = 0.0;
-        // Rows per fast record: the fine rows within the largest reach of
-        // this step's fastest particle, then the nine coarse rows.
-        const double reach = fast_reach(I, I.vmax2_d);
-        const bool per1 = I.bc[1] == TPKMC_BC_PERIODIC, per2 = I.bc[2] == TPKMC_BC_PERIODIC;
-        const int rmax = fast_span_len(I, 1, reach, per1) * fast_span_len(I, 2, reach, per2);
-        const int per_rec = rmax + 9;
-        const int64_t ntask = (f1 - f0) * per_rec;
-        for (int64_t q0 = tid - lane; q0 < ntask; q0 += nth)  // wave-uniform
-            fast_tasks<real, MIX>(a, I, base, f0, ntask, per_rec, rmax, q0 + lane, lane, t, c, n_s0, n_c1);
-        // Uniform over the work-group (the instance loop is), so every
-        // thread takes part in the sums.
-        if constexpr (MIX) mt += t;
-        else add_work(a.gpart, I.blk0, t, c, lds);
+        if (f1 <= f0) continue;
+        const uint32_t n = (uint32_t)(f1 - f0), parts = n >= nw ? 1u : min(nw / n, (uint32_t)kFastParts);
+        uint32_t seen = 0, cand = 0;
+        uint64_t q = turn;
+        for (; q < (uint64_t)n * parts; q += nw)
+            fast_record<real, MIX>(a, I, base, (int32_t)(f0 + (uint32_t)q / parts), (int)((uint32_t)q % parts),
+                                   (int)parts, lane, rows[own], seen, cand, n_s0, n_c1);
+        turn = (uint32_t)(q - (uint64_t)n * parts);
+        if constexpr (MIX) {
+            n_seen += seen;
+        } else if (__ballot(seen != 0)) {
+            const double t = wave_reduce<false>((double)seen), c = wave_reduce<false>((double)cand);
+            if (lane == 0) {
+                double* gp = a.gpart + (int64_t)(I.blk0 + (int)(wave % (uint32_t)I.nblk)) * kGPart;
+                unsafeAtomicAdd(gp + GP_TESTS2, 2.0 * t);
+                unsafeAtomicAdd(gp + GP_CAND, c);
+            }
+        }
     }
     if constexpr (MIX) {
-        const double t0 = block_sum(mt, lds), t1 = block_sum((double)n_s0, lds), t2 = block_sum((double)n_c1, lds);
+        const double t0 = block_sum((double)n_seen, lds), t1 = block_sum((double)n_s0, lds);
+        const double t2 = block_sum((double)n_c1, lds);
         if (threadIdx.x == 0) {
             if (t0 > 0.0) atomicAdd(a.mix + 0, (unsigned long long)t0);
             if (t1 > 0.0) atomicAdd(a.mix + 1, (unsigned long long)t1);
@@ -2991,7 +2982,7 @@ __global__ void __launch_bounds__(256) k_prep(Inst<real>* inst, const double* gp
     __shared__ double lds[16];
     __shared__ bool last;
     Inst<real>& I = inst[blockIdx.y];
-    if (!(I.flags & (TPKMC_ADAPTIVE_DT | kSplit | kSubgrid))) return;  // whole work-group
+    if (!(I.flags & (TPKMC_ADAPTIVE_DT | kSubgrid))) return;  // whole work-group
     double v = 0.0;
     bool strayed = false;
     const double* g0 = gpart + (int64_t)I.blk0 * kGPart;
@@ -3015,7 +3006,6 @@ __global__ void __launch_bounds__(256) k_prep(Inst<real>* inst, const double* gp
     __threadfence();
     const double vmax2 = __longlong_as_double((long long)atomicExch(&I.run_v2, 0ull));
     atomicExch(&I.prep_done, 0u);
-    I.vmax2_d = vmax2;
     // Largest speed among the records of the sub-grid, the bound of its
     // reach; none where a particle lies outside the box along a periodic axis
     // (its cell does not say where its nearest image is).
@@ -3116,7 +3106,7 @@ void launch_search_mix(const StepArgs<real>& a, int n_inst, bool split, hipStrea
 }
 template <typename real>
 void launch_search_fast(const StepArgs<real>& a, int n_inst, hipStream_t s) {
-    const unsigned fg = (unsigned)std::max(1, std::min(2048, a.nblk));
+    const unsigned fg = (unsigned)std::max(64, std::min(2048, 4 * a.nblk));
     hipLaunchKernelGGL((k_search_fast<real>), dim3(fg), dim3(256), 0, s, a, n_inst);
 }
 template <typename real>

@@ -219,6 +219,25 @@ def test_fp64_speeds_raised_after_tuning_equal_oracle(T, oracle):
     cells, vc, n_fast = fp64_steps_equal_oracle(T, oracle, w, after_tune=raise_speeds)
     assert np.prod(cells) > np.prod(w.grid["ncell"]) and n_fast > 1000
 
+
+@pytest.mark.parametrize("count", [1, 65, 5000])
+@pytest.mark.parametrize("factor", [6.0, 500.0])
+def test_fp64_fast_records_by_waves(T, oracle, count, factor):
+    """From fewer fast records than waves (several share one) to more, that
+    reach a few rows of slow c-bins or all of them (with the nine rows of the
+    fast ones more than a wave's 64 lanes)."""
+    w = tube(n=30_000)
+
+    def raise_speeds(st):
+        sel = np.arange(w.n) * 7919 % w.n < count
+        for k in ("vx", "vy", "vz"):
+            st[k] = np.where(sel, factor * st[k], st[k])
+
+    cells, vc, n_fast = fp64_steps_equal_oracle(T, oracle, w, after_tune=raise_speeds)
+    print(count, factor, "cells", cells, "fast", n_fast, flush=True)
+    assert cells[1] * cells[2] + 9 > 64 and n_fast >= count // 2
+
+
 def _fp32_pairs(T, w, tune, steps=2, graph=False):
     g, p = w.grid, w.params
     eng = engine(T, w, T.FP32)
