@@ -30,8 +30,8 @@ enum Phase { PH_CLEAR = 0, PH_KEY, PH_SCAN, PH_SCATTER, PH_SEARCH, PH_MOVE, PH_F
 struct ClearArgs {
     int32_t* start;
     int64_t ncell;
-    unsigned long long* macc;  // exact o-bin sums, or null
-    int64_t nwords;
+    unsigned long long *macc, *mexp;  // exact o-bin sums and their exponents, or null
+    int64_t nwords, nexp;
     unsigned long long* pair_count;
     uint32_t* ties;
     double* shift;             // velocity shifts to clear, or null
@@ -41,8 +41,10 @@ struct ClearArgs {
 
 __device__ __forceinline__ void clear_all(const ClearArgs& c, int64_t t0, int64_t stride) {
     for (int64_t t = t0; t < c.ncell; t += stride) c.start[t] = 0;
-    if (c.macc)
+    if (c.macc) {
         for (int64_t t = t0; t < c.nwords; t += stride) c.macc[t] = 0ull;
+        for (int64_t t = t0; t < c.nexp; t += stride) c.mexp[t] = 0ull;
+    }
     if (c.shift)
         for (int64_t t = t0; t < c.nshift; t += stride) c.shift[t] = 0.0;
     if (t0 == 0) {
@@ -296,8 +298,8 @@ __device__ void finalize_one(Inst<real>& I, int k0, const double* cpart, const d
 // Each work-group (256 threads) stages its 256 o-bins' output rows through
 // LDS, so the stores are coalesced; every output value is written.
 template <typename real>
-__device__ void moments_final(const Inst<real>& I, int block, const ObAcc* macc, double* moments, double* shift,
-                              double* rows) {
+__device__ void moments_final(const Inst<real>& I, int block, const ObAcc* macc, const char* mexp, int stride,
+                              double* moments, double* shift, double* rows) {
     constexpr int kRows = kMomentRows;
     const int64_t nb = (int64_t)I.no[0] * I.no[1] * I.no[2];
     const int64_t b0 = (int64_t)block * kRows;
@@ -306,9 +308,10 @@ __device__ void moments_final(const Inst<real>& I, int block, const ObAcc* macc,
     if ((int)threadIdx.x < nloc) {
         const int64_t ob = I.obin_off + b0 + threadIdx.x;
         const ObAcc& A = macc[ob];
+        const ObExp& X = *reinterpret_cast<const ObExp*>(mexp + ob * stride);
         double* M = rows + threadIdx.x * TPKMC_MOMENT_STRIDE;
         double* S = shift + ob * 3;
-        const unsigned long long cnt = A.nc & 0xffffffffull, coll = A.nc >> 32;
+        const unsigned long long cnt = X.nc & 0xffffffffull, coll = X.nc >> 32;
         for (int k = 0; k < TPKMC_MOMENT_STRIDE; ++k) M[k] = 0.0;
         if (cnt > 0) {
             // Quanta 2^(E-50+h) of the four kinds (as in the moment pass); each
@@ -316,7 +319,7 @@ __device__ void moments_final(const Inst<real>& I, int block, const ObAcc* macc,
             const int h = acc_headroom(cnt);
             double inv[4];
             for (int k = 0; k < 4; ++k) {
-                const int e = A.e[k] > 0 ? A.e[k] - kExpBias : 0;
+                const int e = X.e[k] > 0 ? X.e[k] - kExpBias : 0;
                 inv[k] = ldexp(1.0, max(e, -969) - 50 + h);
             }
             double v[kAccVals];
@@ -347,7 +350,8 @@ template <typename real>
 __global__ void __launch_bounds__(256) k_finalize(Inst<real>* inst, const double* cpart, const double* gpart,
                                                  uint64_t* counters, double* globals, uint32_t* status,
                                                  const unsigned long long* pair_count, int64_t pair_cap,
-                                                 int advance_step, const ObAcc* macc, double* moments, double* shift) {
+                                                 int advance_step, const ObAcc* macc, const char* mexp, int stride,
+                                                 double* moments, double* shift) {
     __shared__ double rows[kChunk * kGPart];
     static_assert(kChunk * kGPart >= kMomentRows * TPKMC_MOMENT_STRIDE, "rows hold either");
     Inst<real>& I = inst[blockIdx.y];
@@ -355,7 +359,7 @@ __global__ void __launch_bounds__(256) k_finalize(Inst<real>* inst, const double
         finalize_one(I, (int)blockIdx.y, cpart, gpart, counters, globals, status, pair_count, pair_cap, advance_step,
                      rows);
     else
-        moments_final(I, (int)blockIdx.x - 1, macc, moments, shift, rows);
+        moments_final(I, (int)blockIdx.x - 1, macc, mexp, stride, moments, shift, rows);
 }
 
 }  // namespace
@@ -371,6 +375,7 @@ struct Buffers {
     unsigned long long* bkey;
     double *gpart, *cpart, *shift;
     ObAcc* macc;      // exact o-bin sums, 128 B per o-bin
+    char* mexp;       // their exponents and counts; null: within the sums
     void* vir;        // colliders' virial terms, 3 reals per particle
     uint8_t* coll;    // collided flags, 1 B per particle
     unsigned long long* pair_count;
@@ -732,7 +737,7 @@ struct PhaseScope {
 };
 
 template <typename real>
-StepArgs<real> make_args(const Buffers& B, const tpkmc_particles* s, const tpkmc_outputs* o, int nblk) {
+StepArgs<real> make_args(const Buffers& B, const tpkmc_particles* s, const tpkmc_outputs* o, int nblk, int64_t nob) {
     StepArgs<real> a{};
     a.x = (real*)s->x; a.y = (real*)s->y; a.z = (real*)s->z;
     a.vx = (real*)s->vx; a.vy = (real*)s->vy; a.vz = (real*)s->vz;
@@ -754,6 +759,8 @@ StepArgs<real> make_args(const Buffers& B, const tpkmc_particles* s, const tpkmc
     a.gpart = B.gpart;
     a.shift = B.shift;
     a.macc = (o && o->moments) ? B.macc : nullptr;
+    a.mexp = B.mexp ? B.mexp : (char*)&B.macc->shared;
+    a.exp_stride = B.mexp ? exp_stride(nob) : (int)sizeof(ObAcc);
     a.vir = (real*)B.vir;
     a.coll = B.coll;
     a.pairs = o ? o->pairs : nullptr;
@@ -795,7 +802,9 @@ ClearArgs clear_args(const Buffers& B, const Shape& P, bool mom, bool fresh) {
     c.start = B.start;
     c.ncell = P.ncell_tot + 1;
     c.macc = mom ? (unsigned long long*)B.macc : nullptr;
-    c.nwords = mom ? P.nob_tot * (int64_t)(sizeof(ObAcc) / 8) : 0;
+    c.nwords = P.nob_tot * (int64_t)(sizeof(ObAcc) / 8);
+    c.mexp = (unsigned long long*)B.mexp;
+    c.nexp = B.mexp ? exp_bytes(P.nob_tot) / 8 : 0;
     c.pair_count = B.pair_count;
     c.ties = B.ties;
     if (fresh) {
@@ -871,7 +880,8 @@ void enqueue_step(tpkmc_handle* h, const Buffers& B, const StepArgs<real>& a, co
         hipLaunchKernelGGL(k_finalize<real>, dim3(gx, P.n_inst), dim3(256), 0, s, (Inst<real>*)B.inst,
                            (const double*)B.cpart, direct ? (const double*)B.gpart : (const double*)nullptr,
                            o ? o->counters : nullptr, o ? o->globals : nullptr, B.status, B.pair_count, a.pair_cap,
-                           advance_step, (const ObAcc*)B.macc, mom ? o->moments : nullptr, B.shift);
+                           advance_step, (const ObAcc*)B.macc, (const char*)a.mexp, a.exp_stride,
+                           mom ? o->moments : nullptr, B.shift);
     }
 }
 
@@ -907,7 +917,7 @@ int step_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     One<real> one{};
     if (single) std::memcpy(&one.inst, P.inst_bytes.data(), sizeof(one.inst));
     else if ((rc = upload(h, P, st))) return rc;
-    StepArgs<real> a = make_args<real>(h->b, s, o, P.nblk);
+    StepArgs<real> a = make_args<real>(h->b, s, o, P.nblk, P.nob_tot);
     a.order = h->search_order;
     enqueue_step<real>(h, h->b, a, o, shape_of(P), h->search_block, h->search_group, st, h->profiling, 0,
                        single ? &one : nullptr);
@@ -941,7 +951,7 @@ int run_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in
     if (!h->shape_chosen && (rc = tune_impl<real>(h, s, in, n_inst, st))) return rc;
     if ((rc = make_plan<real>(h, s, in, n_inst, P))) return rc;  // with the tuned c-bins
     if ((rc = upload(h, P, st))) return rc;
-    StepArgs<real> a = make_args<real>(h->b, s, o, P.nblk);
+    StepArgs<real> a = make_args<real>(h->b, s, o, P.nblk, P.nob_tot);
     a.order = h->search_order;
     if (h->gexec) {
         hipStreamSynchronize(h->last_stream ? h->last_stream : st);
@@ -1052,7 +1062,7 @@ int choose_cells(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance
             }
             if ((rc = upload(h, P, st))) return rc;
             tpkmc_outputs none{};
-            StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk);
+            StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk, P.nob_tot);
             launch_speed_stats<real>(a, st);
             std::vector<double> gp((size_t)P.nblk * kGPart);
             if (hipMemcpyAsync(gp.data(), h->b.gpart, sizeof(double) * gp.size(), hipMemcpyDeviceToHost, st) !=
@@ -1133,7 +1143,7 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     if (hipSetDevice(h->device) != hipSuccess) return TPKMC_EHIP;
     if ((rc = upload(h, P, st))) return rc;
     tpkmc_outputs none{};
-    StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk);
+    StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk, P.nob_tot);
     a.order = 0;  // shapes are timed in the default work-group order
     // Bin once (clear, key, prefix, scatter); then time only the search.
     hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, clear_args(h->b, shape_of(P), false, false));
@@ -1232,7 +1242,7 @@ int mix_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in
     if (hipSetDevice(h->device) != hipSuccess) return TPKMC_EHIP;
     if ((rc = upload(h, P, st))) return rc;
     tpkmc_outputs none{};
-    StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk);
+    StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk, P.nob_tot);
     a.order = h->search_order;
     hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, clear_args(h->b, shape_of(P), false, false));
     launch_key<real>(a, st);
@@ -1257,7 +1267,7 @@ void free_all(tpkmc_handle* h) {
     }
     hipFree(h->b.rank); hipFree(h->b.start); hipFree(h->b.tiles);
     hipFree(h->b.src); hipFree(h->b.best); hipFree(h->b.perm); hipFree(h->b.rec); hipFree(h->b.rec2); hipFree(h->b.rmass); hipFree(h->b.inst);
-    hipFree(h->b.blk); hipFree(h->b.chunks); hipFree(h->b.bkey); hipFree(h->b.cpart); hipFree(h->b.gpart); hipFree(h->b.shift); hipFree(h->b.macc); hipFree(h->b.vir); hipFree(h->b.coll); hipFree(h->b.pair_count); hipFree(h->b.status); hipFree(h->b.mix);
+    hipFree(h->b.blk); hipFree(h->b.chunks); hipFree(h->b.bkey); hipFree(h->b.cpart); hipFree(h->b.gpart); hipFree(h->b.shift); hipFree(h->b.macc); hipFree(h->b.mexp); hipFree(h->b.vir); hipFree(h->b.coll); hipFree(h->b.pair_count); hipFree(h->b.status); hipFree(h->b.mix);
 }
 
 // ---------------------------------------------------------------- static scratch
@@ -1288,7 +1298,7 @@ int scratch_of(int device, unsigned char** out) {
 // only measures.
 template <typename real>
 size_t carve(uintptr_t base, int64_t n, int64_t ncell_tot, int64_t nob, int nblk, int nchunk, bool masses,
-             bool second, Buffers& B) {
+             bool second, bool apart, Buffers& B) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> void* {
         const uintptr_t p = base + off;
@@ -1315,6 +1325,7 @@ size_t carve(uintptr_t base, int64_t n, int64_t ncell_tot, int64_t nob, int nblk
     B.cpart = (double*)take(sizeof(double) * kGPart * (size_t)nchunk);
     B.shift = (double*)take(sizeof(double) * 3 * (size_t)std::max<int64_t>(nob, 1));
     B.macc = (ObAcc*)take(sizeof(ObAcc) * (size_t)std::max<int64_t>(nob, 1));
+    B.mexp = apart ? (char*)take((size_t)exp_bytes(nob)) : nullptr;
     B.vir = take(3 * sizeof(real) * nn);
     B.coll = (uint8_t*)take(nn);
     B.pair_count = (unsigned long long*)take(2 * sizeof(unsigned long long));
@@ -1349,11 +1360,11 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     d.chunk0 = 0;
     d.nchunk = nchunk;
     Buffers Bf{};
-    auto fits = [&](bool second) {
-        return carve<real>(0, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, second, Bf) <=
+    auto fits = [&](bool second, bool apart) {
+        return carve<real>(0, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, second, apart, Bf) <=
                TPKMC_NOALLOC_SCRATCH_BYTES;
     };
-    if ((d.flags & kSubgrid) && !fits(false)) {
+    if ((d.flags & kSubgrid) && !fits(false, false)) {
         // The sub-grid is an extra: without it where the scratch is short.
         if ((rc = fill_inst<real>(s, q, d, C, B, nullptr, 0.0, false))) return rc;
         ncell_tot = (int64_t)d.C + 1;
@@ -1362,17 +1373,18 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
         d.chunk0 = 0;
         d.nchunk = nchunk;
     }
-    if (!fits(false)) return TPKMC_ECAPACITY;
-    // So are the second records, which only a state in the caller's order takes.
+    if (!fits(false, false)) return TPKMC_ECAPACITY;
+    // So are the second records, which only a state in the caller's order takes,
+    // and the o-bins' exponents apart from their sums.
     const bool caller_order = !(p->flags & TPKMC_ALLOW_REORDER);
-    const bool second = caller_order && fits(true);
+    const bool second = caller_order && fits(true, false), apart = fits(second, true);
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess) return TPKMC_EHIP;
     if (device < 0 || device >= ndev || device >= kMaxDevices) return TPKMC_EINVAL;
     if (hipSetDevice(device) != hipSuccess) return TPKMC_EHIP;
     unsigned char* base = nullptr;
     if ((rc = scratch_of(device, &base))) return rc;
-    carve<real>((uintptr_t)base, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, second, Bf);
+    carve<real>((uintptr_t)base, s->n, ncell_tot, B, nblk, nchunk, s->mass != nullptr, second, apart, Bf);
     const bool random = (p->flags & TPKMC_PAIR_RANDOM) != 0;
     Shape P{};
     P.n_inst = 1;
@@ -1389,7 +1401,7 @@ int step_noalloc_impl(int device, const tpkmc_grid* g, const tpkmc_params* p, co
     P.any_search = !random;
     P.any_random = random;
     P.split = false;
-    StepArgs<real> a = make_args<real>(Bf, s, o, nblk);
+    StepArgs<real> a = make_args<real>(Bf, s, o, nblk, B);
     const One<real> one{d, true};
     enqueue_step<real>(nullptr, Bf, a, o, P, kWave, 2, st, false, 0, &one);
     return hipGetLastError() == hipSuccess ? TPKMC_OK : TPKMC_EHIP;
@@ -1459,6 +1471,7 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
     bad |= dalloc(&h->b.bkey, h->max_n);
     bad |= dalloc(&h->b.shift, 3 * std::max<int64_t>(h->max_obins, 1));
     bad |= dalloc(&h->b.macc, std::max<int64_t>(h->max_obins, 1));
+    bad |= dalloc(&h->b.mexp, std::max(exp_bytes(h->max_obins), exp_bytes(std::min(h->max_obins, kSpreadObins))));
     bad |= hipMalloc(&h->b.vir, rs * 3 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
     bad |= dalloc(&h->b.coll, std::max<int64_t>(h->max_n, 1));
     bad |= dalloc(&h->b.pair_count, 2);

@@ -37,13 +37,28 @@ enum GPart {
 // per o-bin); the four exponents (biased by kExpBias; 0: no nonzero term).
 constexpr int kAccVals = 10;
 constexpr int kExpBias = 1100;
-struct ObAcc {
-    long long sum[kAccVals];
+// The moment pass reads the exponents and counts for every particle while it
+// adds to the sums, and a line that atomics go to is slow to read: with both in
+// one line of 128 B the pass took 153 us instead of 75 on the 4M tube, 363
+// instead of 290 on the 16M blast.  So the exponents lie apart, a line each up
+// to kSpreadObins o-bins (packed, the move's atomics on few o-bins meet in the
+// same lines: 4M tube 156 us instead of 117), packed above (16M blast, 262144
+// o-bins: 5 us less in the moment pass, 7 in the last kernel).  Where the
+// scratch is short they share the sums' line.
+struct ObExp {
     unsigned long long nc;
     int32_t e[4];
-    unsigned long long pad[3];
+    unsigned long long pad;
 };
-static_assert(sizeof(ObAcc) == 128, "one o-bin accumulator is 128 B");
+struct ObAcc {
+    long long sum[kAccVals];
+    unsigned long long pad[2];
+    ObExp shared;
+};
+static_assert(sizeof(ObAcc) == 128 && sizeof(ObExp) == 32, "a line an o-bin");
+constexpr int64_t kSpreadObins = 4096;
+inline int exp_stride(int64_t nob) { return nob <= kSpreadObins ? (int)sizeof(ObAcc) : (int)sizeof(ObExp); }
+inline int64_t exp_bytes(int64_t nob) { return nob * exp_stride(nob); }
 __host__ __device__ inline int acc_headroom(unsigned long long n) {
     const int c = n <= 1 ? 0 : 64 - __builtin_clzll(n - 1);  // ceil(log2 n)
     return c > 12 ? c - 12 : 0;
@@ -153,6 +168,8 @@ struct StepArgs {
     double* shift;            // per-o-bin velocity shift (3 per o-bin)
     int32_t order;            // search work-group order: 0 contiguous per XCD, S > 0 chunks of S round-robin
     ObAcc* macc;              // per-o-bin exact sums, or null (no moments)
+    char* mexp;               // their exponents and counts, exp_stride bytes apart
+    int exp_stride;
     real* vir;                // virial terms of each collider (3 per particle; record index, or caller index without rec2)
     uint8_t* coll;            // 1 if the particle collided this step (indexed as vir); FP64, until the move: 1 if
                               // the record's key met an equal one (record index)

@@ -2528,6 +2528,11 @@ __device__ __forceinline__ double row_sum4(double v0, double v1, double v2, doub
 // On the 16M blast it takes 0.44 ms; without the o-bin part it takes 0.28,
 // near what its 128 B a particle need, so the o-bins' exponents are taken from
 // the bits of the largest term per kind and their counts by votes.
+template <typename real>
+__device__ __forceinline__ ObExp& exp_of(const StepArgs<real>& a, int64_t ob) {
+    return *reinterpret_cast<ObExp*>(a.mexp + ob * a.exp_stride);
+}
+
 // A lane's run maxima and counts of one o-bin into the work-group table, or
 // straight into the global accumulators when the table is full.
 template <typename real>
@@ -2539,13 +2544,13 @@ __device__ __forceinline__ void exp_flush(ExpTable& tab, const StepArgs<real>& a
     for (int k = 0; k < 4; ++k) {
         if (!e[k]) continue;
         if (d) atomicMax(d + k, e[k]);
-        else atomicMax(&a.macc[ob].e[k], e[k]);
+        else atomicMax(&exp_of(a, ob).e[k], e[k]);
     }
     if (d) {
         if (cnt) atomicAdd(&tab.n[slot][0], cnt);
         if (coll) atomicAdd(&tab.n[slot][1], coll);
     } else if (cnt) {
-        atomicAdd(&a.macc[ob].nc, (unsigned long long)cnt | ((unsigned long long)coll << 32));
+        atomicAdd(&exp_of(a, ob).nc, (unsigned long long)cnt | ((unsigned long long)coll << 32));
     }
 }
 
@@ -2785,9 +2790,9 @@ __global__ void __launch_bounds__(kBlock) k_move(StepArgs<real> a) {
             const int ob = tab.key[slot];
             if (ob < 0) continue;
             if (k < 4) {
-                if (tab.e[slot][k]) atomicMax(&a.macc[ob].e[k], tab.e[slot][k]);
+                if (tab.e[slot][k]) atomicMax(&exp_of(a, ob).e[k], tab.e[slot][k]);
             } else if (tab.n[slot][0]) {
-                atomicAdd(&a.macc[ob].nc,
+                atomicAdd(&exp_of(a, ob).nc,
                           (unsigned long long)tab.n[slot][0] | ((unsigned long long)tab.n[slot][1] << 32));
             }
         }
@@ -2933,7 +2938,7 @@ __global__ void __launch_bounds__(kBlock) k_moments(StepArgs<real> a) {
                 moment_terms(m, (double)vx, (double)vy, (double)vz, S, vir[0], vir[1], vir[2], t);
                 // The quanta of the o-bin: its exponents and the headroom of its
                 // particle count, both from the move.
-                const ObAcc& G = a.macc[ob];
+                const ObExp& G = exp_of(a, ob);
                 const int h = acc_headroom(G.nc & 0xffffffffull);
                 const double s0 = fixed_scale(G.e[0], h), s1 = fixed_scale(G.e[1], h);
 #pragma unroll
