@@ -1196,7 +1196,10 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     // the XCDs by construction: where the work concentrates as a run goes on
     // (the shocked core of an implosion, the shell of a blast), contiguous
     // ranges leave it to one or two XCDs, which the initial state does not
-    // show (on the Noh 8M implosion 9.7 against 6.8 ms per step).
+    // show (on the Noh 8M implosion 9.7 against 6.8 ms per step).  The tile
+    // search's work grows with the density, so it is not given contiguous
+    // ranges at all: the same implosion's uniform start runs 5% faster on
+    // them, steps 40 to 280 at 1.95 to 3.9 ms, in chunks of 16 at 1.75 to 2.4.
     int best_order = kDefaultSearchOrder;
     if (!rc) {
         hipEvent_t f0, f1;
@@ -1204,6 +1207,7 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
         hipEventCreate(&f1);
         float base_ms = 1e30f;
         for (int order : {kDefaultSearchOrder, 0, 1, 128}) {
+            if (order == 0 && P.any_tiles) continue;
             a.order = order;
             search(best_block, best_group);  // warm-up
             hipEventRecord(f0, st);
