@@ -265,8 +265,9 @@ int tpkmc_version(void);
 const char* tpkmc_strerror(int code);
 
 /* Allocates a handle and all its device scratch on cfg->device (memory is
- * sized from the capacities: about 74 B per particle in FP32, 122 B in FP64,
- * 8 B per c-bin, 152 B per o-bin).  *out is NULL on failure. */
+ * sized from the capacities: about 107 B per particle in FP32, 187 B in FP64,
+ * 8 B per c-bin, 184 B per o-bin, 280 B up to 4096 of them).  *out is NULL on
+ * failure. */
 int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out);
 
 /* Waits for the handle's work, frees everything.  NULL is a no-op. */
@@ -294,7 +295,10 @@ int tpkmc_step(tpkmc_handle* h, const tpkmc_grid* g, const tpkmc_params* p,
  * Returns TPKMC_ECAPACITY, before anything is launched, when the step's
  * scratch exceeds the array: about 105 B per particle in FP64 (113 with
  * per-particle masses), 69 B in FP32 (73), plus 4 B per c-bin and 152 B per
- * o-bin, so at most about 0.6M particles in FP64 and 0.9M in FP32.
+ * o-bin, so at most about 0.6M particles in FP64 and 0.9M in FP32.  Where
+ * the array has room for them, a step also uses sort cells of dense c-bins (4 B
+ * each), second records (32 or 64 B per particle) and o-bin exponents apart
+ * from their sums (32 or 128 B each); the results are the same without.
  * Every call on a GPU uses that GPU's one array, and the array keeps the
  * last call's contents (the call clears what must start at zero), so calls
  * that overlap in time on one GPU race: order them on one stream.  There

@@ -2517,17 +2517,6 @@ __device__ __forceinline__ double row_sum4(double v0, double v1, double v2, doub
     return r + dpp_move<kRowRor8>(r);
 }
 
-// Unambiguous pairs (each the other's closest candidate) scatter; every
-// particle moves and meets the walls; global sums; with moments, the first
-// pass of the exact o-bin sums (see ObAcc): the exponent maxima, and each
-// particle's collider flag and virial terms for the moment pass.  One record
-// per lane.  The new state goes to the caller's arrays (c-bin order kept), to
-// records in a second buffer that the moment pass reads and puts back in the
-// caller's order, or, where there is no room for that, scattered into the
-// caller's arrays.
-// On the 16M blast it takes 0.44 ms; without the o-bin part it takes 0.28,
-// near what its 128 B a particle need, so the o-bins' exponents are taken from
-// the bits of the largest term per kind and their counts by votes.
 template <typename real>
 __device__ __forceinline__ ObExp& exp_of(const StepArgs<real>& a, int64_t ob) {
     return *reinterpret_cast<ObExp*>(a.mexp + ob * a.exp_stride);
@@ -2554,6 +2543,17 @@ __device__ __forceinline__ void exp_flush(ExpTable& tab, const StepArgs<real>& a
     }
 }
 
+// Unambiguous pairs (each the other's closest candidate) scatter; every
+// particle moves and meets the walls; global sums; with moments, the first
+// pass of the exact o-bin sums (see ObAcc): the exponent maxima, and each
+// particle's collider flag and virial terms for the moment pass.  One record
+// per lane.  The new state goes to the caller's arrays (c-bin order kept), to
+// records in a second buffer that the moment pass reads and puts back in the
+// caller's order, or, where there is no room for that, scattered into the
+// caller's arrays.
+// On the 16M blast it takes 0.44 ms; without the o-bin part it takes 0.28,
+// near what its 85 B a particle need, so the o-bins' exponents are taken from
+// the bits of the largest term per kind and their counts by votes.
 template <typename real>
 __global__ void __launch_bounds__(kBlock) k_move(StepArgs<real> a) {
     __shared__ ExpTable tab;
