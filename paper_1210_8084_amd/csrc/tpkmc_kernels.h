@@ -1145,16 +1145,21 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
     const bool sub = (I.flags & kSubgrid) != 0;
     const int32_t i = wbase + lane;
     const bool valid = i < stop;
-    real pi[3], vi[3];
-    load_pv(a.rec, valid ? i : wbase, pi[0], pi[1], pi[2], vi[0], vi[1], vi[2]);
+    // In FP32 a group reads the records again from LDS, which leaves the
+    // registers to its loops (spilled 26 -> 9; Noh implosion 1.15 -> 1.12 ms,
+    // planar gas of 1e5 31 -> 29.6 us); in FP64, which has registers left, that
+    // only adds a wait (2M blast 377 -> 390 us).
+    constexpr bool kReload = sizeof(real) == 4;
+    real p0[3], v0[3];
+    load_pv(a.rec, valid ? i : wbase, p0[0], p0[1], p0[2], v0[0], v0[1], v0[2]);
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        L.pv[ax][lane] = pi[ax];
-        L.pv[3 + ax][lane] = vi[ax];
+        L.pv[ax][lane] = p0[ax];
+        L.pv[3 + ax][lane] = v0[ax];
     }
     L.key[lane] = ~0ull;
-    const int cx = sort_bin(I, 0, pi[0]), cy = sort_bin(I, 1, pi[1]), cz = sort_bin(I, 2, pi[2]);
-    const int own_row = row_of(I, cy, cz);
+    const int c0[3] = {sort_bin(I, 0, p0[0]), sort_bin(I, 1, p0[1]), sort_bin(I, 2, p0[2])};
+    const int own_row = row_of(I, c0[1], c0[2]);
     const real sx = (real)I.tile_s;
     const real sv = I.dt * sx * (real)kTileKappa;
     // At most 30000: beyond, D spans every tame pair.
@@ -1200,6 +1205,16 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
         const uint64_t gm = __ballot(in);
         pending &= ~gm;
         const int last = 63 - __clzll((long long)gm);
+        if (kReload) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        real pi[3], vi[3];
+        int ci[3];
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            pi[ax] = kReload ? L.pv[ax][lane] : p0[ax];
+            vi[ax] = kReload ? L.pv[3 + ax][lane] : v0[ax];
+            ci[ax] = kReload ? sort_bin(I, ax, pi[ax]) : c0[ax];
+        }
+        const int cx = ci[0], cy = ci[1], cz = ci[2];
         const int gcy = __builtin_amdgcn_readlane(cy, lead), gcz = __builtin_amdgcn_readlane(cz, lead);
         const int cxf = __builtin_amdgcn_readlane(cx, lead), cxl = __builtin_amdgcn_readlane(cx, last);
         const int32_t after = wbase + lead;  // partners come after the first record (half search)
