@@ -889,9 +889,10 @@ __device__ __forceinline__ bool test_pair(const Geo<real>& G, bool by_time, real
 // pairs at a time on the matrix units.  With u the relative velocity and r
 // the relative position of a pair, a candidate meets
 //     s0 = r.u < 0,   -(s0 + |u|^2 dt) < 0   (criterion 1), and
-//     |r|^2 - |u|^2 dt^2 - D^2 <= 0          (d_min <= D with t_poca < dt:
-//                                             |r|^2 = d_min^2 + |u|^2 t_poca^2),
-// and all three are bilinear in per-record vectors, so one K = 16 product
+//     |r|^2 + r.u dt - D^2 <= 0              (d_min <= D with t_poca < dt:
+//         |r|^2 = d_min^2 + |u|^2 t_poca^2, and r.u dt = -|u|^2 t_poca dt),
+// the last of them the sphere over the partner's path of the step, widened by
+// D; and all three are bilinear in per-record vectors, so one K = 16 product
 // each (v_mfma_f32_32x32x16_f16) evaluates them for 1024 pairs.  The vectors
 // are rounded to f16 relative to the tile (positions in units of the c-bin
 // width, velocities of 1 / kTileKappa widths per step), and each form is
@@ -923,13 +924,17 @@ __device__ __forceinline__ bool test_pair(const Geo<real>& G, bool by_time, real
 //           summed in FP32, the split terms) below 2^-18 of the same product;
 //           kTileE2 = 3.5e covers them;
 //   |u|^2:  2e V1^2 / kappa and the factor's rounding: kTileE3 = 5e / kappa;
-//   |r|^2:  2e 3 (Xm_i + Xm_j)^2: kTileE6 = 6.6e per ordered product;
+//   |r|^2:  2e 3 (Xm_i + Xm_j)^2: kTileE6 = 6.6e per ordered product, and
+//           6e Xm_i Xm_j from the factor 2 x + v / kappa: kTileE18 = 19.2e for
+//           both products of two records;
+//   r.u dt: as r.u, / kappa;
 // plus kTileAbs (1 + Xm + V1) for f16 subnormals (2^-25 each).
 constexpr float kTileKappa = 256.0f;
 constexpr float kTileHalfUlp = 1.0f / 2048.0f;
 constexpr float kTileE2 = 3.5f * kTileHalfUlp;
 constexpr float kTileE3 = 5.0f * kTileHalfUlp / kTileKappa;
 constexpr float kTileE6 = 6.6f * kTileHalfUlp;
+constexpr float kTileE18 = 19.2f * kTileHalfUlp;
 constexpr float kTileAbs = 1e-6f;
 // A record outside these (or outside the box along a periodic axis) takes
 // part with forms that are negative against every partner ("wild").
@@ -984,8 +989,8 @@ __device__ __forceinline__ TileRec tile_rec(const float X[3], const float V[3], 
     const float m = fmaf(kTileE2 * T.xm, T.v1, lin);
     T.p = xv - m;
     T.q = fmaf(-1.0f / kTileKappa, vv, -xv) - fmaf(kTileE3 * T.v1, T.v1, m);
-    // |u|^2 <= 2 |v_i|^2 + 2 |v_j|^2, with a margin for the rounded v.
-    T.r = xx - fmaf(2.01f / (kTileKappa * kTileKappa), vv, hd2) - fmaf(kTileE6 * T.xm, T.xm, lin);
+    T.r = fmaf(1.0f / kTileKappa, xv, xx) - hd2 -
+          fmaf(kTileE6 * T.xm, T.xm, fmaf(kTileE2 / kTileKappa * T.xm, T.v1, lin));
     if (wild || absent) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) T.x[k] = T.v[k] = (_Float16)0.0f;
@@ -1246,22 +1251,30 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             wild_i = __ballot(in && wild);
             const TileRec T = tile_rec(X, V, 0.0f, hd2, wild, !in);
             vmax = wave_reducef<true>(T.v1);
-            const _Float16 one = (_Float16)1.0f, nul = (_Float16)0.0f;
+            const _Float16 one = (_Float16)1.0f;
             const _Float16 mv = -up_f16(kTileE2 * T.v1), mx = -up_f16(kTileE2 * T.xm);
             const uint32_t wp[8] = {pack2(-T.v[0], -T.v[1]), pack2(-T.v[2], -T.x[0]), pack2(-T.x[1], -T.x[2]),
                                     pack2(one, one), 0u, 0u, split_f16(T.p), pack2(mv, mx)};
             tile_operands(wp, BP);
             constexpr float k2 = 2.0f / kTileKappa;
-            const _Float16 f0 = (_Float16)fmaf(k2, (float)T.v[0], (float)T.x[0]);
-            const _Float16 f1 = (_Float16)fmaf(k2, (float)T.v[1], (float)T.x[1]);
-            const _Float16 f2 = (_Float16)fmaf(k2, (float)T.v[2], (float)T.x[2]);
+            const _Float16 f0 = (_Float16)k2 * T.v[0] + T.x[0];
+            const _Float16 f1 = (_Float16)k2 * T.v[1] + T.x[1];
+            const _Float16 f2 = (_Float16)k2 * T.v[2] + T.x[2];
             const _Float16 mq = -up_f16(fmaf(kTileE2, T.xm, 2.0f * kTileE3 * T.v1));
             const uint32_t wq[8] = {pack2(T.v[0], T.v[1]), pack2(T.v[2], f0), pack2(f1, f2), 0u,
                                     pack2(one, one), 0u, split_f16(T.q), pack2(mv, mq)};
             tile_operands(wq, BQ);
-            const _Float16 two = (_Float16)-2.0f;
-            const uint32_t wr[8] = {pack2(two * T.x[0], two * T.x[1]), pack2(two * T.x[2], nul), 0u, 0u, 0u,
-                                    pack2(one, one), split_f16(T.r), pack2(-up_f16(2.0f * kTileE6 * T.xm), nul)};
+            constexpr float k1 = 1.0f / kTileKappa;
+            _Float16 g[3], h[3];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                // Scaling by powers of two is exact, so each rounds once.
+                g[ax] = (_Float16)(-k1) * T.v[ax] - (_Float16)2.0f * T.x[ax];
+                h[ax] = (_Float16)(-k1) * T.x[ax];
+            }
+            const _Float16 mrx = -up_f16(fmaf(kTileE18, T.xm, kTileE2 * k1 * T.v1)), mrv = -up_f16(kTileE2 * k1 * T.xm);
+            const uint32_t wr[8] = {pack2(g[0], g[1]), pack2(g[2], h[0]), pack2(h[1], h[2]), 0u, 0u,
+                                    pack2(one, one), split_f16(T.r), pack2(mrx, mrv)};
             tile_operands(wr, BR);
         }
         // How far apart a candidate pair of this group can start: with

@@ -13,7 +13,7 @@ import pytest
 
 KAPPA = 256.0
 E = 1.0 / 2048.0
-E2, E3, E6, ABS = 3.5 * E, 5.0 * E / KAPPA, 6.6 * E, 1e-6
+E2, E3, E6, E18, ABS = 3.5 * E, 5.0 * E / KAPPA, 6.6 * E, 19.2 * E, 1e-6
 F = np.float32
 
 
@@ -38,7 +38,7 @@ def record(X, V, hd2):
     lin = F(ABS) * (xm + v1) + F(ABS)
     m = F(E2) * xm * v1 + lin
     return dict(x=x, v=v, xm=xm, v1=v1, p=split(xv - m), q=split(-vv / F(KAPPA) - xv - (F(E3) * v1 * v1 + m)),
-                r=split(xx - (F(2.01 / KAPPA ** 2) * vv + F(hd2)) - (F(E6) * xm * xm + lin)))
+                r=split(xx + F(1.0 / KAPPA) * xv - F(hd2) - (F(E6) * xm * xm + F(E2 / KAPPA) * xm * v1 + lin)))
 
 
 def forms(i, j):
@@ -49,7 +49,10 @@ def forms(i, j):
     xm, v1 = up(j["xm"]), up(j["v1"])
     P = i["p"][:, None] + j["p"] - i["v"] @ j["x"].T - i["x"] @ j["v"].T + mv[:, None] * xm + mx[:, None] * v1
     Q = i["q"][:, None] + j["q"] + i["v"] @ j["x"].T + f @ j["v"].T + mv[:, None] * xm + mq[:, None] * v1
-    R = i["r"][:, None] + j["r"] - F(2.0) * (i["x"] @ j["x"].T) - up(F(2.0 * E6) * i["xm"])[:, None] * xm
+    g = f16(F(-1.0 / KAPPA) * i["v"] - F(2.0) * i["x"])
+    h = f16(F(-1.0 / KAPPA) * i["x"])
+    mrx, mrv = -up(F(E18) * i["xm"] + F(E2 / KAPPA) * i["v1"]), -up(F(E2 / KAPPA) * i["xm"])
+    R = i["r"][:, None] + j["r"] + g @ j["x"].T + h @ j["v"].T + mrx[:, None] * xm + mrv[:, None] * v1
     return P, Q, R
 
 
@@ -65,6 +68,7 @@ CASES = {
     "fast": (0.4, 0.4, 0.0, 0.1, 2.0),
     "tiny D": (0.2, 0.2, 0.0, 1e-3, 1.0),
     "long tile": (0.1, 0.1, 0.0, 0.5, 30.0),
+    "fast, tiny D": (0.35, 0.4, 0.0, 1e-2, 1.0),
 }
 
 
