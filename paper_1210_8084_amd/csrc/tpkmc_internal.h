@@ -97,6 +97,7 @@ struct Inst {
     // length.
     int32_t ncfg[3];
     int32_t Cf;
+    uint32_t strayed;         // prep's flag: some particle lies outside a periodic axis (see vreach)
     real vc2;
     real inv_wc[3];
     // Tile search: 1 / the length its positions are scaled by (the widest
@@ -105,15 +106,15 @@ struct Inst {
     // Sub-grids (kSubgrid): nl[] c-bins per axis (the refined ones of split
     // c-bins), each cut into 2^kl[] sort cells, n[a] = nl[a] 2^kl[a]; inv_wl:
     // c-bins per unit length.  Without, kl is 0 and n, nl are the same.  vreach: the
-    // largest speed among the records sorted on them (infinite: unknown),
-    // strayed: prep's flag for that.
+    // largest speed among the records sorted on them (infinite: unknown).
     int32_t nl[3], kl[3];
     real inv_wl[3];
     real w_sort[3];           // width of a sort cell
     real vreach;
-    uint32_t strayed;
     int64_t base;             // record index of the instance's first: base + start[]
 };
+// The allocation-free step's scratch gives either of them 512 B.
+static_assert(sizeof(Inst<double>) <= 512, "one descriptor is 512 B");
 
 // Bit of Inst::flags set by the host (outside the public flag bits): the
 // c-bins are split by speed (slow particles on refined c-bins, see Inst).
