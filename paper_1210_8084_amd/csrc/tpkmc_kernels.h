@@ -909,8 +909,9 @@ __device__ __forceinline__ bool test_pair(const Geo<real>& G, bool by_time, real
 // replaced, one lane per record with scalar or gathered loads (search phase):
 // FP64 Sod tube of 4e5 particles on 100 c-bins 19.8 -> 0.12 ms, FP64 blast of
 // 2e6 on 64^3 1.06 -> 0.39, FP32 Noh implosion of 8e6 2.1 -> 1.35, 64
-// instances of 3.4e7 particles in all 16.4 -> 9.8, and 2000 particles in
-// FP64 0.61 -> 0.05.
+// instances of 3.4e7 particles in all 16.4 -> 9.8 (5.9 with the third form
+// above instead of |r|^2 - |u|^2 dt^2 - D^2), and 2000 particles in FP64
+// 0.61 -> 0.03.
 //
 // Vector of a record (k = 0..15), j's side:
 //   x y z | vx vy vz | p_hi p_lo | q_hi q_lo | r_hi r_lo | 1 1 | Xm | V1
