@@ -349,14 +349,16 @@ int tpkmc_run(tpkmc_handle* h, const tpkmc_particles* s,
  *    and the fast-particle check keep the configured c-bins.  May grow the
  *    handle's c-bin storage.
  *  - the launch shape (work-group size and particles per work-item): timed,
- *    the default kept unless another is at least 5% faster;
+ *    the default kept unless another is at least 5% faster (it matters to
+ *    FP32 instances of fewer than 8 particles per c-bin only);
  *  - the order in which the search's work-groups are dealt to the XCDs:
  *    chunks of 16 work-groups dealt round-robin over the XCDs (the default:
  *    balance when the work per work-group varies along the c-bin order, as
  *    across a batch of instances or in a dense shocked region), contiguous
- *    ranges per XCD (neighbouring work-groups share an L2), or chunks of 1
- *    or 128; another order is timed in the chosen shape and kept when at
- *    least 5% faster.
+ *    ranges per XCD (neighbouring work-groups share an L2; not where some
+ *    instance's c-bins hold 8 particles or more, whose work grows with the
+ *    density), or chunks of 1 or 128; another order is timed in the chosen
+ *    shape and kept when at least 5% faster.
  * Runs the binning and search kernels only; the particle state is not
  * modified.  Synchronises the stream. */
 int tpkmc_autotune(tpkmc_handle* h, const tpkmc_particles* s,
@@ -396,7 +398,7 @@ int tpkmc_search_mix(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_inst
  * c-bin-ordered records (1, 2 or 4) and `block` lanes per work-group (64,
  * 128 or 256, at most 256 / group).  Every shape gives the same pairs, state
  * and counters.  The default is group 2, block 64; tpkmc_autotune keeps it
- * unless another shape is at least 3% faster; tpkmc_set_search fixes one
+ * unless another shape is at least 5% faster; tpkmc_set_search fixes one
  * (EINVAL outside these lists). */
 int tpkmc_set_search(tpkmc_handle* h, int32_t group, int32_t block);
 int tpkmc_get_search(tpkmc_handle* h, int32_t* group, int32_t* block);
