@@ -355,9 +355,9 @@ int tpkmc_run(tpkmc_handle* h, const tpkmc_particles* s,
  *    chunks of 16 work-groups dealt round-robin over the XCDs (the default:
  *    balance when the work per work-group varies along the c-bin order, as
  *    across a batch of instances or in a dense shocked region), contiguous
- *    ranges per XCD (neighbouring work-groups share an L2; not where some
- *    instance's c-bins hold 8 particles or more, whose work grows with the
- *    density), or chunks of 1 or 128; another order is timed in the chosen
+ *    ranges per XCD (neighbouring work-groups share an L2; FP32 instances of
+ *    fewer than 8 particles per c-bin only, as elsewhere the work grows with
+ *    the density), or chunks of 1 or 128; another order is timed in the chosen
  *    shape and kept when at least 5% faster.
  * Runs the binning and search kernels only; the particle state is not
  * modified.  Synchronises the stream. */
