@@ -938,9 +938,14 @@ constexpr float kTileE6 = 6.6f * kTileHalfUlp;
 constexpr float kTileE18 = 19.2f * kTileHalfUlp;
 constexpr float kTileAbs = 1e-6f;
 // A record outside these (or outside the box along a periodic axis) takes
-// part with forms that are negative against every partner ("wild").
+// part with forms that are negative against every partner ("wild").  The
+// speed limit goes with the tile's extent, since f16 holds the products: one
+// limit of 512 for any tile (two widths a step, summed over the axes) left 1%
+// of a gas that moves 0.4 widths a step wild, and the box of 1e6 at 9 a c-bin
+// took 503 us (FP32) and 2.1 times its present search (FP64).
 constexpr float kTileXMax = 64.0f;
-constexpr float kTileVMax = 512.0f;
+constexpr float kTileVMax = 2048.0f;
+constexpr float kTileOwn = 40000.0f;  // a tame record's own terms, without D^2 and the bounds
 constexpr float kTileWild = -50000.0f;  // below minus any tame record's own terms
 constexpr float kTileNever = 60000.0f;  // above them: lanes without a record
 
@@ -1177,17 +1182,27 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
     const int nl0 = I.nl[0];
     // The box along the periodic axes; records outside are wild.
     real box_lo[3], box_hi[3];
-    bool four[3];
+    bool four[3], few[3];  // periodic axes of four c-bins; of at most three, whose images may be visited
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
+        few[ax] = G.per[ax] && I.nl[ax] <= 3;
         box_lo[ax] = G.per[ax] ? lo[ax] : -real(INFINITY);
         box_hi[ax] = G.per[ax] ? hi[ax] : real(INFINITY);
         four[ax] = G.per[ax] && I.nl[ax] == 4;
     }
     const bool any_four = four[0] || four[1] || four[2];
-    auto untame = [&](const real p[3], const float X[3], const float V[3], float vcap) {
+    // Coordinates of partners: at most two c-bins beyond the tile's cells, or
+    // two boxes where images are visited.
+    float xbase = 0.01f;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        const real e = few[ax] ? real(2) * G.L[ax] : ws[ax] * (real(0.5) + (real)(2 << I.kl[ax]));
+        xbase = fmaxf(xbase, (float)(e * sx) * 1.01f);
+    }
+    const float xstep = (float)(ws[0] * sx) * 0.505f;
+    auto untame = [&](const real p[3], const float X[3], const float V[3], float xcap, float vcap) {
         const float xm = fmaxf(fmaxf(fabsf(X[0]), fabsf(X[1])), fabsf(X[2]));
-        bool t = (xm <= kTileXMax) & (fabsf(V[0]) + fabsf(V[1]) + fabsf(V[2]) <= vcap);
+        bool t = (xm <= xcap) & (fabsf(V[0]) + fabsf(V[1]) + fabsf(V[2]) <= vcap);
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) t &= (p[ax] >= box_lo[ax]) & (p[ax] < box_hi[ax]);
         if (any_four)
@@ -1238,6 +1253,10 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             xabs = fmaxf(xabs, big * (sizeof(real) == 4 ? 1.0f / 1024.0f : 1e-9f));
         }
         const bool coarse = !(xabs <= 16.0f);  // coordinates too coarse for the filter: all wild
+        // The largest coordinate of a partner in its place, and a speed whose
+        // own terms beside it, x v + v^2 / kTileKappa, stay below kTileOwn.
+        const float xcap = fminf(fmaf(xstep, (float)(cxl - cxf), xbase), kTileXMax);
+        const float vlim = fminf(kTileVMax, kTileOwn * __builtin_amdgcn_rcpf(xcap + kTileVMax / kTileKappa));
         half8_t BP[2], BQ[2], BR[2];
         uint64_t wild_i;
         float vmax;
@@ -1248,7 +1267,7 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                 X[ax] = (float)fma(pi[ax], sx, -org[ax]);
                 V[ax] = (float)fma(vi[ax], sv, -vo[ax]);
             }
-            const bool wild = coarse || untame(pi, X, V, kTileVMax);
+            const bool wild = coarse || untame(pi, X, V, xcap, vlim);
             wild_i = __ballot(in && wild);
             const TileRec T = tile_rec(X, V, 0.0f, hd2, wild, !in);
             vmax = wave_reducef<true>(T.v1);
@@ -1298,10 +1317,10 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
         const TileAxis AX = tile_axis(I, 0, G.per[0], cxf, cxl, m[0]);
         const TileAxis AY = tile_axis(I, 1, G.per[1], gcy, gcy, m[1]);
         const TileAxis AZ = tile_axis(I, 2, G.per[2], gcz, gcz, m[2]);
-        float vcap = kTileVMax;
+        float vcap = vlim;
         real reach_im = reach;
         if (!sub && AX.images * AY.images * AZ.images > 1) {
-            vcap = fminf(kTileVMax, 2.0f * vmax + 1e-3f);
+            vcap = fminf(vlim, 2.0f * vmax + 1e-3f);
             const float uu = (vmax + vcap) * (1.01f / kTileKappa);
             if (!wild_i) reach_im = (real)(1.001f * sqrtf(fmaf(uu, uu, 2.0f * hd2)) / I.tile_s);
         }
@@ -1435,7 +1454,7 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                         X[ax] = (float)fma(pj[ax], sx, (real)((int)(code >> (2 * ax) & 3u) - 1) * Ls[ax] - org[ax]);
                 }
                 const bool absent = b + lane >= njs;
-                const bool wild = coarse | untame(pj, X, V, vcap);
+                const bool wild = coarse | untame(pj, X, V, xcap, vcap);
                 const bool shifted = !home && !sub && ((AX.images == 3 && (code & 3u) != 1u) ||
                                                        (AY.images == 3 && (code >> 2 & 3u) != 1u) ||
                                                        (AZ.images == 3 && (code >> 4 & 3u) != 1u));

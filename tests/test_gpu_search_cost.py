@@ -1,0 +1,52 @@
+"""What must not cost the partner search a multiple: the same gas in other
+places, units of the time step or orders, one search phase against another on
+the same card (the results are other tests' matter)."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_1210_8084_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+R, P = W.REFLECT, W.PERIODIC
+
+
+@pytest.fixture(scope="module")
+def T():
+    from paper_1210_8084_amd import tpkmc
+    assert torch.cuda.is_available(), "GPU test without a visible GPU"
+    tpkmc.lib()
+    return tpkmc
+
+
+def search_us(T, state, grid, params, precision, reps=6):
+    """Shortest search phase of a step on this state, in microseconds."""
+    n = len(state["x"])
+    eng = T.Engine(max_particles=n, max_cells=T.ncells(grid) + 1, max_obins=T.nobins(grid), precision=precision)
+    first = T.to_device(state, precision)
+    out = T.make_outputs(1, T.nobins(grid))
+    best = math.inf
+    for k in range(reps):
+        dst = {a: t.clone() for a, t in first.items()}
+        eng.profile(k > 0)
+        eng.step(dst, grid, params, out, flags=T.ALLOW_REORDER)
+        torch.cuda.synchronize()
+        if k:
+            best = min(best, 1e3 * eng.profile_read()["search"][0])
+    pairs = int(out.host()["counters"][0][T.CNT["pairs"]])
+    eng.close()
+    print(f"n={n} ncell={grid['ncell']} fp={precision}: search {best:.1f} us, {pairs} pairs", flush=True)
+    return best
+
+
+def test_a_gas_that_moves_half_a_cbin_is_filtered(T):
+    """Four times the time step brings 1.5 times the search (more candidates);
+    3.2 times where 1% of the records are taken unfiltered."""
+    us = []
+    for dt in (0.1, 0.4):
+        w = W.random_box(n=500_000, seed=1, ncell=(32, 32, 32), bc=(R, P, P), hi=(1, 1, 1), dt_over=dt, nobin=(1, 1, 1))
+        us.append(search_us(T, w.state, w.grid, w.params, T.FP32))
+    assert us[1] < 2.3 * us[0]
