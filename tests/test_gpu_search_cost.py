@@ -50,3 +50,14 @@ def test_a_gas_that_moves_half_a_cbin_is_filtered(T):
         w = W.random_box(n=500_000, seed=1, ncell=(32, 32, 32), bc=(R, P, P), hi=(1, 1, 1), dt_over=dt, nobin=(1, 1, 1))
         us.append(search_us(T, w.state, w.grid, w.params, T.FP32))
     assert us[1] < 2.3 * us[0]
+
+
+@pytest.mark.parametrize("precision", ["FP64", "FP32"])
+def test_a_plane_at_the_edge_of_its_box(T, precision):
+    """The plane's place along z is the caller's choice."""
+    us = []
+    for z in (0.0, -0.5):
+        w = W.random_plane(n=500_000, seed=1, ncell=(158, 158), bc=(R, P), hi=(1, 1), dt_over=0.1, nobin=(1, 1))
+        w.state["z"][:] = z
+        us.append(search_us(T, w.state, w.grid, w.params, getattr(T, precision)))
+    assert us[1] < 1.25 * us[0]
