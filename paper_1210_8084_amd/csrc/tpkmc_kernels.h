@@ -1259,7 +1259,13 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             const float big = fabsf((float)org[ax]) + (G.per[ax] ? (float)Ls[ax] : 0.0f);
             xabs = fmaxf(xabs, big * (sizeof(real) == 4 ? 1.0f / 1024.0f : 1e-9f));
         }
-        const bool coarse = !(xabs <= 16.0f);  // coordinates too coarse for the filter: all wild
+        // A shifted origin too coarse for the filter: shifted partners are
+        // wild, and where a partner is visited in several places it is so in
+        // all of them.  (Taken for unshifted ones too, an FP32 box of 1e6 at
+        // 16 a c-bin and a thousand box lengths from the origin took 1.7 ms a
+        // step instead of 0.55.)
+        const bool coarse = !(xabs <= 16.0f);
+        const bool coarse_home = coarse && (few[0] || few[1] || few[2]);
         // The largest coordinate of a partner in its place, and a speed whose
         // own terms beside it, x v + v^2 / kTileKappa, stay below kTileOwn.
         const float xcap = fminf(fmaf(xstep, (float)(cxl - cxf), xbase), kTileXMax);
@@ -1275,7 +1281,7 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                 V[ax] = (float)fma(vi[ax], sv, -vo[ax]);
             }
             if (planar) X[2] = 0.0f;
-            const bool wild = coarse || untame(pi, X, V, xcap, vlim);
+            const bool wild = coarse_home || untame(pi, X, V, xcap, vlim);
             wild_i = __ballot(in && wild);
             const TileRec T = tile_rec(X, V, 0.0f, hd2, wild, !in);
             vmax = wave_reducef<true>(T.v1);
@@ -1463,7 +1469,7 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                 }
                 if (planar) X[2] = 0.0f;
                 const bool absent = b + lane >= njs;
-                const bool wild = coarse | untame(pj, X, V, xcap, vcap);
+                const bool wild = coarse_home | (coarse & (code != kCodeHome)) | untame(pj, X, V, xcap, vcap);
                 const bool shifted = !home && !sub && ((AX.images == 3 && (code & 3u) != 1u) ||
                                                        (AY.images == 3 && (code >> 2 & 3u) != 1u) ||
                                                        (AZ.images == 3 && (code >> 4 & 3u) != 1u));

@@ -61,3 +61,12 @@ def test_a_plane_at_the_edge_of_its_box(T, precision):
         w.state["z"][:] = z
         us.append(search_us(T, w.state, w.grid, w.params, getattr(T, precision)))
     assert us[1] < 1.25 * us[0]
+
+
+def test_a_box_far_from_the_origin(T):
+    us = []
+    for lo in (0.0, 1000.0):
+        w = W.random_box(n=500_000, seed=1, ncell=(32, 32, 32), bc=(R, R, R), lo=(lo,) * 3, hi=(lo + 1.0,) * 3,
+                         dt_over=0.1, nobin=(1, 1, 1))
+        us.append(search_us(T, w.state, w.grid, w.params, T.FP32))
+    assert us[1] < 1.5 * us[0]

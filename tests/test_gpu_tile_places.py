@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_1210_8084_amd import workloads as W
+from test_gpu_fp32_parity import check_against_oracle
 from test_gpu_tiles import T, check  # noqa: F401  (T: fixture)
 
 pytestmark = pytest.mark.gpu
@@ -18,3 +19,14 @@ def test_plane_anywhere_along_z(T, oracle, n, z):  # noqa: F811
     w = W.random_plane(n=n, seed=3, ncell=(9, 8), bc=(R, P), nobin=(2, 2))
     w.state["z"][:] = z
     assert check(T, oracle, w.state, w.grid, w.params) > 100
+
+
+@pytest.mark.parametrize("bc,ncell", [((R, R, R), (8, 7, 6)), ((P, P, P), (8, 7, 6)), ((P, P, R), (3, 5, 6)),
+                                      ((P, P, P), (2, 1, 9)), ((P, R, R), (40, 1, 1))], ids=str)
+def test_fp32_box_far_from_the_origin(T, oracle, bc, ncell):  # noqa: F811
+    """Coordinates 4000 box widths from the origin: shifted tile origins are
+    too coarse there, unshifted ones as good as anywhere."""
+    hi = (4001.0, -3999.2, 4000.6)
+    w = W.random_box(n=6000, seed=8, ncell=ncell, bc=bc, lo=(4000.0, -4000.0, 4000.0), hi=hi, d_over_w=0.6,
+                     dt_over=0.3, nobin=(2, 2, 1))
+    check_against_oracle(T, oracle, w)
