@@ -97,7 +97,7 @@ struct Inst {
     // length.
     int32_t ncfg[3];
     int32_t Cf;
-    uint32_t strayed;         // prep's flag: some particle lies outside a periodic axis (see vreach)
+    uint32_t run_out;         // prep's running maximum: how far one lies outside a periodic axis (see k_key)
     real vc2;
     real inv_wc[3];
     // Tile search: 1 / the length its positions are scaled by (the widest
@@ -106,7 +106,8 @@ struct Inst {
     // Sub-grids (kSubgrid): nl[] c-bins per axis (the refined ones of split
     // c-bins), each cut into 2^kl[] sort cells, n[a] = nl[a] 2^kl[a]; inv_wl:
     // c-bins per unit length.  Without, kl is 0 and n, nl are the same.  vreach: the
-    // largest speed among the records sorted on them (infinite: unknown).
+    // largest speed among the records sorted on them, with the reach of those
+    // outside the box in it (see k_prep).
     int32_t nl[3], kl[3];
     real inv_wl[3];
     real w_sort[3];           // width of a sort cell

@@ -70,3 +70,15 @@ def test_a_box_far_from_the_origin(T):
                          dt_over=0.1, nobin=(1, 1, 1))
         us.append(search_us(T, w.state, w.grid, w.params, T.FP32))
     assert us[1] < 1.5 * us[0]
+
+
+@pytest.mark.parametrize("precision", ["FP64", "FP32"])
+@pytest.mark.parametrize("beyond", [0.0, 1e-4])
+def test_a_particle_on_the_edge_of_a_periodic_box(T, precision, beyond):
+    """One coordinate at (or a little beyond) the upper edge, as FP32 rounding
+    brings it about; sort cells are skipped as without it."""
+    w = W.sod(n=400_000, ncell=100, nobin=1)
+    us = [search_us(T, w.state, w.grid, w.params, getattr(T, precision))]
+    w.state["y"][7] = w.grid["hi"][1] + beyond
+    us.append(search_us(T, w.state, w.grid, w.params, getattr(T, precision)))
+    assert us[1] < 1.5 * us[0]

@@ -30,3 +30,30 @@ def test_fp32_box_far_from_the_origin(T, oracle, bc, ncell):  # noqa: F811
     w = W.random_box(n=6000, seed=8, ncell=ncell, bc=bc, lo=(4000.0, -4000.0, 4000.0), hi=hi, d_over_w=0.6,
                      dt_over=0.3, nobin=(2, 2, 1))
     check_against_oracle(T, oracle, w)
+
+
+def strayed(seed, ncell, out):
+    """A dense periodic box (sort cells) with a tenth of its particles on or
+    outside its edges, by up to `out` of the box."""
+    w = W.random_box(n=9001, seed=seed, ncell=ncell, bc=(P, P, P), d_over_w=0.08, dt_over=0.1, nobin=(2, 2, 1))
+    rng = np.random.default_rng(seed)
+    for k, L in zip(("x", "y", "z"), (1.0, 0.8, 0.6)):
+        i = rng.choice(w.n, w.n // 30, replace=False)
+        d = rng.uniform(0.0, out, len(i)) * L
+        d[:5] = 0.0  # on the edge itself
+        w.state[k][i] = np.where(rng.uniform(size=len(i)) < 0.5, -d, L + d)
+    return w
+
+
+@pytest.mark.parametrize("ncell", [(1, 1, 1), (2, 3, 4), (5, 1, 2), (4, 4, 4), (12, 1, 1)], ids=str)
+@pytest.mark.parametrize("out", [0.0, 1e-3, 0.19, 0.45])
+def test_strays_in_sort_cells(T, oracle, ncell, out):  # noqa: F811
+    w = strayed(5, ncell, out)
+    check(T, oracle, w.state, w.grid, w.params)
+
+
+@pytest.mark.parametrize("ncell", [(2, 3, 4), (12, 1, 1)], ids=str)
+@pytest.mark.parametrize("out", [1e-3, 0.19, 0.45])
+def test_fp32_strays_in_sort_cells(T, oracle, ncell, out):  # noqa: F811
+    w = strayed(6, ncell, out)
+    check_against_oracle(T, oracle, w, min_pairs=20)
