@@ -509,7 +509,19 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
         }
         for (int a = 0; a < 3; ++a) d.inv_w[a] = (real)((double)d.n[a] / (g.hi[a] - g.lo[a]));
     }
-    for (int a = 0; a < 3; ++a) d.w_sort[a] = (real)((g.hi[a] - g.lo[a]) / d.n[a]);
+    // Partners of a tile in their places lie at most two c-bins beyond its
+    // cells, or two boxes where a periodic axis is visited image by image.
+    double x = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        const double L = g.hi[a] - g.lo[a];
+        d.w_sort[a] = (real)(L / d.n[a]);
+        if (a >= naxes) continue;
+        const bool few = g.bc[a] == TPKMC_BC_PERIODIC && d.nl[a] <= 3;
+        if (few) d.flags |= kImaged;
+        x = std::max(x, (few ? 2.0 * L : 0.5 * L / d.n[a] + 2.0 * L / d.nl[a]) / wide);
+    }
+    d.tile_x = (float)(1.01 * x + 0.01);
+    d.tile_dx = (float)(0.505 * ((g.hi[0] - g.lo[0]) / d.n[0]) / wide);
 }
 
 // Validates one instance and fills its device descriptor, except the
@@ -562,7 +574,6 @@ int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, 
         d.lo[a] = (real)g.lo[a];
         d.hi[a] = (real)g.hi[a];
         d.L[a] = (real)L;
-        d.halfL[a] = (real)(0.5 * L);
         d.w[a] = (real)(L / (double)g.ncell[a]);
         wd[a] = L / (double)g.ncell[a];
         if (g.ncell[a] > 1 && (dx == 0.0 || L / (double)g.ncell[a] < dx)) dx = L / (double)g.ncell[a];

@@ -80,7 +80,7 @@ struct Inst {
     uint32_t seed_lo, seed_hi, step_lo, instance;
     uint32_t flags;           // TPKMC_EMIT_PAIRS | TPKMC_ALLOW_REORDER
     int32_t band_log2;        // y-band height 2^band_log2 of the c-bin order
-    real lo[3], hi[3], L[3], halfL[3], inv_w[3], inv_wo[3], w[3];
+    real lo[3], hi[3], L[3], inv_w[3], inv_wo[3], w[3];
     real dt, D2, mass;
     double mass_d, dt_d;      // dt_d: this step's time step (set on the device with ADAPTIVE_DT)
     double dt_cap, dx_d;      // caller's dt; smallest c-bin width over axes with > 1 c-bin (0: none)
@@ -103,6 +103,9 @@ struct Inst {
     // Tile search: 1 / the length its positions are scaled by (the widest
     // c-bin).
     float tile_s;
+    // In that unit, the largest coordinate of a tile's partners relative to
+    // it, for a tile of one sort cell, and more per further cell along x.
+    float tile_x, tile_dx;
     // Sub-grids (kSubgrid): nl[] c-bins per axis (the refined ones of split
     // c-bins), each cut into 2^kl[] sort cells, n[a] = nl[a] 2^kl[a]; inv_wl:
     // c-bins per unit length.  Without, kl is 0 and n, nl are the same.  vreach: the
@@ -125,6 +128,9 @@ constexpr uint32_t kSplit = 1u << 30;
 // c-bins are cut into sort cells (see Inst).
 constexpr uint32_t kTiles = 1u << 29;
 constexpr uint32_t kSubgrid = 1u << 28;
+// Bit of Inst::flags set by the host: some periodic axis has at most three
+// c-bins, so the tile search may visit its images one by one.
+constexpr uint32_t kImaged = 1u << 27;
 
 // Bit of Inst::flags, set by the host (outside the public flag bits): the
 // particles carry their own masses.

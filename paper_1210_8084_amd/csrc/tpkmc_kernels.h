@@ -606,7 +606,7 @@ struct Geo {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             L[a] = I.L[a];
-            halfL[a] = I.halfL[a];
+            halfL[a] = real(0.5) * I.L[a];
             invL[a] = real(1) / I.L[a];
             per[a] = I.bc[a] == TPKMC_BC_PERIODIC;
         }
@@ -1192,25 +1192,14 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
     const int nl0 = I.nl[0];
     // The box along the periodic axes; records outside are wild.
     real box_lo[3], box_hi[3];
-    bool four[3], few[3];  // periodic axes of four c-bins; of at most three, whose images may be visited
+    bool four[3];
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        few[ax] = G.per[ax] && I.nl[ax] <= 3;
         box_lo[ax] = G.per[ax] ? lo[ax] : -real(INFINITY);
         box_hi[ax] = G.per[ax] ? hi[ax] : real(INFINITY);
         four[ax] = G.per[ax] && I.nl[ax] == 4;
     }
     const bool any_four = four[0] || four[1] || four[2];
-    // Coordinates of partners: at most two c-bins beyond the tile's cells, or
-    // two boxes where images are visited.
-    float xbase = 0.01f;
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        if (ax == 2 && planar) continue;
-        const real e = few[ax] ? real(2) * G.L[ax] : ws[ax] * (real(0.5) + (real)(2 << I.kl[ax]));
-        xbase = fmaxf(xbase, (float)(e * sx) * 1.01f);
-    }
-    const float xstep = (float)(ws[0] * sx) * 0.505f;
     auto untame = [&](const real p[3], const float X[3], const float V[3], float xcap, float vcap) {
         const float xm = fmaxf(fmaxf(fabsf(X[0]), fabsf(X[1])), fabsf(X[2]));
         bool t = (xm <= xcap) & (fabsf(V[0]) + fabsf(V[1]) + fabsf(V[2]) <= vcap);
@@ -1269,10 +1258,10 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
         // 16 a c-bin and a thousand box lengths from the origin took 1.7 ms a
         // step instead of 0.55.)
         const bool coarse = !(xabs <= 16.0f);
-        const bool coarse_home = coarse && (few[0] || few[1] || few[2]);
+        const bool coarse_home = coarse && (I.flags & kImaged);
         // The largest coordinate of a partner in its place, and a speed whose
         // own terms beside it, x v + v^2 / kTileKappa, stay below kTileOwn.
-        const float xcap = fminf(fmaf(xstep, (float)(cxl - cxf), xbase), kTileXMax);
+        const float xcap = fminf(fmaf(I.tile_dx, (float)(cxl - cxf), I.tile_x), kTileXMax);
         const float vlim = fminf(kTileVMax, kTileOwn * __builtin_amdgcn_rcpf(xcap + kTileVMax / kTileKappa));
         half8_t BP[2], BQ[2], BR[2];
         uint64_t wild_i;
@@ -2700,9 +2689,9 @@ __global__ void __launch_bounds__(kBlock) k_move(StepArgs<real> a) {
                     const real vxA = isA ? vx : vxj, vyA = isA ? vy : vyj, vzA = isA ? vz : vzj;
                     const real vxB = isA ? vxj : vx, vyB = isA ? vyj : vy, vzB = isA ? vzj : vz;
                     real rx = xA - xB, ry = yA - yB, rz = zA - zB;
-                    if (I.bc[0] == TPKMC_BC_PERIODIC) rx = min_image(rx, I.L[0], I.halfL[0]);
-                    if (I.bc[1] == TPKMC_BC_PERIODIC) ry = min_image(ry, I.L[1], I.halfL[1]);
-                    if (I.bc[2] == TPKMC_BC_PERIODIC) rz = min_image(rz, I.L[2], I.halfL[2]);
+                    if (I.bc[0] == TPKMC_BC_PERIODIC) rx = min_image(rx, I.L[0], real(0.5) * I.L[0]);
+                    if (I.bc[1] == TPKMC_BC_PERIODIC) ry = min_image(ry, I.L[1], real(0.5) * I.L[1]);
+                    if (I.bc[2] == TPKMC_BC_PERIODIC) rz = min_image(rz, I.L[2], real(0.5) * I.L[2]);
                     const real ux = vxA - vxB, uy = vyA - vyB, uz = vzA - vzB;
                     const real s0 = (rx * ux + ry * uy) + rz * uz;
                     const real vv = (ux * ux + uy * uy) + uz * uz;
