@@ -1313,8 +1313,15 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
         real reach = real(INFINITY);
         int m[3] = {1 << 24, 1 << 24, 1 << 24};
         if (sub) {
-            const float v = in ? (float)sqrt(vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2]) : 0.0f;
-            reach = (sqrt(I.D2) + ((real)wave_reducef<true>(v) + I.vreach) * I.dt) * real(1.001);
+            // In widths per step, where FP32 has room below and above whatever
+            // the units of an FP64 state (infinite or no number: no bound).
+            float V[3];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) V[ax] = (float)(vi[ax] * sv);
+            float v = in ? sqrtf(V[0] * V[0] + V[1] * V[1] + V[2] * V[2]) : 0.0f;
+            v = v < INFINITY ? v : INFINITY;
+            reach = (sqrt(I.D2) + I.vreach * I.dt + (real)(wave_reducef<true>(v) * (1.0f / kTileKappa)) / sx) *
+                    real(1.001);
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 const real c = reach * iw[ax] + real(1e-3) + real(1e-6) * (real)n[ax];

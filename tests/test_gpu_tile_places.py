@@ -57,3 +57,19 @@ def test_strays_in_sort_cells(T, oracle, ncell, out):  # noqa: F811
 def test_fp32_strays_in_sort_cells(T, oracle, ncell, out):  # noqa: F811
     w = strayed(6, ncell, out)
     check_against_oracle(T, oracle, w, min_pairs=20)
+
+
+@pytest.mark.parametrize("length,time", [(0, 200), (0, -200), (160, 160), (-160, -160), (300, 100), (-300, -100)])
+@pytest.mark.parametrize("n", [700, 9001])  # c-bins whole, c-bins in sort cells
+def test_units_of_length_and_time(T, oracle, n, length, time):  # noqa: F811
+    """A gas of equal speeds in units that powers of two apart are exact in:
+    the filter and the reach work in c-bin widths per step."""
+    w = W.random_box(n=n, seed=7, ncell=(4, 3, 2), bc=(R, P, P), d_over_w=0.05, dt_over=0.3, nobin=(2, 2, 1))
+    st, sl, su = w.state, 2.0 ** length, 2.0 ** (length - time)
+    v = np.sqrt(st["vx"] ** 2 + st["vy"] ** 2 + st["vz"] ** 2)
+    for k in ("x", "y", "z"):
+        st[k] *= sl
+        st["v" + k] *= su / v
+    g = dict(w.grid, hi=tuple(h * sl for h in w.grid["hi"]))
+    p = dict(w.params, sigma=w.params["sigma"] * sl * sl, dt=w.params["dt"] * 2.0 ** time)
+    assert check(T, oracle, st, g, p) > 20
