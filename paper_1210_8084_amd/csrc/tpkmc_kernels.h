@@ -234,17 +234,6 @@ __device__ __forceinline__ double block_sum(double v, double* lds) {
     return t;
 }
 
-__device__ __forceinline__ double block_max(double v, double* lds) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) lds[w] = v;
-    __syncthreads();
-    double t = lds[0];
-    for (int k = 1; k < nw; ++k) t = fmax(t, lds[k]);
-    return t;
-}
-
 // Work-groups are dispatched round-robin over the 8 XCDs; remap so that each
 // XCD (own L2) receives a contiguous range of the table, where neighbouring
 // work-groups share neighbour c-bins.
@@ -3058,8 +3047,15 @@ __global__ void __launch_bounds__(256) k_prep(Inst<real>* inst, const double* gp
         v = fmax(v, g0[(int64_t)b * kGPart + GP_VMAX0]);
         out = fmax(out, g0[(int64_t)b * kGPart + GP_PX]);
     }
-    v = block_max(v, lds);
-    out = block_max(out, lds);
+    v = wave_reduce<true>(v);
+    out = wave_reduce<true>(out);
+    if ((threadIdx.x & 63) == 0) {
+        lds[threadIdx.x >> 6] = v;
+        lds[4 + (threadIdx.x >> 6)] = out;
+    }
+    __syncthreads();
+    v = fmax(fmax(lds[0], lds[1]), fmax(lds[2], lds[3]));
+    out = fmax(fmax(lds[4], lds[5]), fmax(lds[6], lds[7]));
     if (threadIdx.x == 0) {
         // Non-negative numbers order like their bit patterns.
         atomicMax(&I.run_v2, (unsigned long long)__double_as_longlong(v));
@@ -3089,8 +3085,10 @@ __global__ void __launch_bounds__(256) k_prep(Inst<real>* inst, const double* gp
     // such particle, the FP32 tube of 4e5 on 100 c-bins took 7.7 ms instead
     // of 0.33 for one that lies on its upper edge.
     const double vr = (I.flags & kSplit) ? (double)I.vc2 : vmax2;
-    const double stray = (double)__uint_as_float(atomicExch(&I.run_out, 0u)) / (double)I.tile_s;
-    I.vreach = (real)((sqrt(vr) + 2.0 * stray / I.dt_d) * (1.0 + 1e-6));
+    double reach = sqrt(vr);
+    if (const uint32_t stray = atomicExch(&I.run_out, 0u))
+        reach += 2.0 * (double)__uint_as_float(stray) / ((double)I.tile_s * I.dt_d);
+    I.vreach = (real)(reach * (1.0 + 1e-6));
 }
 
 // Tuning statistics of the speeds: per work-group, over the live particles
