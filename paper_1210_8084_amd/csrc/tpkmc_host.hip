@@ -466,11 +466,55 @@ bool bad_state(const tpkmc_particles* s) {
                         bad_ptr(s->vz) || bad_ptr(s->id));
 }
 
-// FP32 instances of at least this many particles per c-bin go to the tile
-// search, sparser ones to the staged lane search: a tile spans 64 / density
-// c-bins along x, and the pairs it tests grow with that span (16M blast at
-// 3.6 per c-bin: staged 1.05 ms, tiles 2.9; Sod tube at 14: 0.47 and 0.36).
+// Tile search or lane walk (FP32: staged, FP64: a record a lane).  FP32 below
+// kTileDensity particles per c-bin is staged; the rest by the cost of both, in
+// microseconds per 1e6 records as fitted to measurements of 1.6e3 states (uniform
+// gases of 3e4 and 1e6 particles at 0.3 to 100 per c-bin; boxes, planes, tubes
+// along x and y, slabs of 1 to 8 c-bins along x; D of 0.1 to 2 widths).
+//  - A tile is up to 64 records of one row of c-bins, so a wave's records make
+//    1 + 63 / (records of a row) tiles, each with a set-up and blocks of 64
+//    partners from its rows, 64 records and two c-bins long, once per image
+//    of a periodic axis that cannot be told from the c-bins.
+//  - A lane tests its half neighbourhood pair by pair; the staged walk also
+//    goes tile by tile through the rows.
+// A small call takes what one wave needs: the tiles and the FP64 lanes are split
+// over waves then, the staged walk is not.  Lanes are chosen where they cost
+// less than kLaneGain of the tiles, which suffer less where the gas clumps.
+// Measured, lanes against tiles: FP64 boxes at 1, 3 and 7.6 per c-bin 138, 248
+// and 450 against 241, 231 and 234 us; FP32 tube along x at 14 and 100 per
+// c-bin 42 and 140 against 91 and 105, plane at 10 and 20 90 and 146 against 115
+// and 137, box periodic along z with one c-bin at 14 and 40 124 and 290 against 202
+// and 300.
 constexpr double kTileDensity = 8.0;
+constexpr double kLaneGain = 0.85;
+
+template <typename real>
+bool tiles_pay(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, double D, bool planar) {
+    constexpr bool fp64 = std::is_same<real, double>::value;
+    if (!fp64 && dens < kTileDensity) return false;
+    double w = 0.0, rows = 1.0, visits = 1.0;  // narrowest c-bin; rows of a neighbourhood, with images
+    for (int a = 0; a < (planar ? 2 : 3); ++a) {
+        const double wa = (g.hi[a] - g.lo[a]) / d.nl[a];
+        w = w > 0.0 ? std::min(w, wa) : wa;
+    }
+    for (int a = 0; a < 3; ++a) {
+        if (a > 0) rows *= std::min(3, d.nl[a]);
+        // Images out of reach of a tile's outermost record are skipped.
+        if (g.bc[a] == TPKMC_BC_PERIODIC && d.nl[a] <= 3 && !(planar && a == 2) &&
+            100.0 * (D + 0.25 * w) > g.hi[a] - g.lo[a])
+            visits *= 3.0;
+    }
+    visits *= rows;
+    const double row = std::max(dens * d.nl[0], 1e-3), groups = std::min(64.0, 1.0 + 63.0 / row);
+    const double blocks = 0.5 + 0.5 * visits * std::min(row, 64.0 + 2.0 * dens) / 64.0;
+    const double tests = 0.5 * rows * std::min(row, 3.0 * dens), m = n * 1e-6;
+    const double tile = fp64 ? 88.0 + groups * (14.0 + 24.0 * blocks) : 63.0 + groups * (18.0 + 16.0 * blocks);
+    const double lane = fp64 ? 38.0 + 5.8 * rows + 3.7 * tests : 21.0 + 6.7 * groups * rows + 1.1 * tests;
+    const double tiles = std::max(m * tile, 18.0 + 8.0 * groups + 0.06 * tile);
+    const double lanes = fp64 ? std::max(m * lane, 8.0 + 0.07 * lane) : std::max(m, 0.5) * lane;
+    return !(lanes < kLaneGain * tiles);
+}
+
 // Sub-grids: c-bins of at least kSubgridDensity particles are halved along
 // their widest axis, again and again, while a part keeps kSortCellMin
 // particles and its width 0.7 D.  A tile then is compact, and the parts of
@@ -482,11 +526,11 @@ constexpr double kSortCellMin = 8.0;  // sort_cells() counts on it
 constexpr double kSortCellD = 0.7;
 
 template <typename real>
-void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_t Cs, double D, bool planar, bool fp64,
-                       bool subgrid, uint32_t flags) {
+void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_t n_all, int64_t Cs, double D,
+                       bool planar, bool subgrid, uint32_t flags) {
     const int naxes = planar ? 2 : 3;
     double dens = (double)count / (double)Cs, w[3];
-    if (!(flags & TPKMC_PAIR_RANDOM) && (fp64 || dens >= kTileDensity)) d.flags |= kTiles;
+    if (!(flags & TPKMC_PAIR_RANDOM) && tiles_pay(d, g, (double)n_all, dens, D, planar)) d.flags |= kTiles;
     // Scale of the tile search's positions: the widest c-bin (half the box on
     // an axis of one; a planar gas has no extent along z).
     double wide = 0.0;
@@ -495,7 +539,7 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
         if (a < naxes) wide = std::max(wide, d.nl[a] > 1 ? w[a] : 0.5 * w[a]);
     }
     d.tile_s = (float)(1.0 / wide);
-    if (subgrid && dens >= kSubgridDensity) {
+    if (subgrid && (d.flags & kTiles) && dens >= kSubgridDensity) {
         while (dens >= 2.0 * kSortCellMin) {
             int a = -1;
             for (int b = 0; b < naxes; ++b)
@@ -505,7 +549,7 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
             d.n[a] *= 2;
             w[a] *= 0.5;
             dens *= 0.5;
-            d.flags |= kSubgrid | kTiles;
+            d.flags |= kSubgrid;
         }
         for (int a = 0; a < 3; ++a) d.inv_w[a] = (real)((double)d.n[a] / (g.hi[a] - g.lo[a]));
     }
@@ -586,8 +630,7 @@ int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, 
     if (C + 1 > (int64_t)1 << 30 || B > (int64_t)1 << 30) return TPKMC_EINVAL;
     const double Dp = 0.5 * p.sigma;
     const double D = planar ? Dp : std::sqrt(p.sigma / M_PI);
-    choose_sort_cells(d, g, q.count, Cs, D, planar, std::is_same<real, double>::value,
-                      subgrid && !(p.flags & TPKMC_PAIR_RANDOM), p.flags);
+    choose_sort_cells(d, g, q.count, s->n, Cs, D, planar, subgrid, p.flags);
     const int64_t Cf = (int64_t)d.n[0] * d.n[1] * d.n[2];
     const int64_t Csort = split ? Cf + Cc : Cf;
     d.off = q.offset;
@@ -1184,7 +1227,8 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
         if (P.any_staged) launch_search<real>(a, bs, grp, st);
         if (P.any_tiles) launch_search_tiles<real>(a, st);
     };
-    if (!P.any_staged) shapes.resize(1);  // the tile search has one shape
+    // The tile search and the FP64 lanes have one shape.
+    if (!P.any_staged || std::is_same<real, double>::value) shapes.resize(1);
     for (int r = 0; r < 4; ++r) search(kWave, 2);
     for (const auto& sh : shapes) {
         const int grp = sh.first, bs = sh.second;

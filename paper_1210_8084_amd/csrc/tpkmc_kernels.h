@@ -1538,6 +1538,45 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
     cand = 2.0 * (double)nc;
 }
 
+// FP64 half scan of record i, record by record; SPLIT: of the nine rows of its
+// neighbourhood those k = part, part + parts, ... alone.  The pairs tested are
+// those of the tile search, and so is the combination of the keys.
+template <bool SPLIT>
+__device__ __forceinline__ void search_lane(const StepArgs<double>& a, const Inst<double>& I, int32_t i, int part,
+                                            int parts, double& tests, double& cand) {
+    const Geo<double> G(I);
+    const int n[3] = {I.n[0], I.n[1], I.n[2]};
+    const bool by_time = (I.flags & TPKMC_RANK_TIME) != 0;
+    double xi, yi, zi, vxi, vyi, vzi;
+    load_pv(a.rec, i, xi, yi, zi, vxi, vyi, vzi);
+    const int cx = axis_bin(xi, I.lo[0], I.inv_w[0], n[0]), cy = axis_bin(yi, I.lo[1], I.inv_w[1], n[1]),
+              cz = axis_bin(zi, I.lo[2], I.inv_w[2], n[2]);
+    int32_t seen = 0, nc = 0;
+    unsigned long long mine = ~0ull;
+    auto row = [&](int32_t j0, int32_t j1) {
+        seen += j1 > j0 ? j1 - j0 : 0;
+        for (int32_t j = j0; j < j1; ++j) {
+            double xj, yj, zj, vxj, vyj, vzj, value;
+            load_pv(a.rec, j, xj, yj, zj, vxj, vyj, vzj);
+            if (!test_pair(G, by_time, xi, yi, zi, vxi, vyi, vzi, xj, yj, zj, vxj, vyj, vzj, value)) continue;
+            ++nc;
+            Key<double>::lower(a, j, Key<double>::make(value, (uint32_t)i), key_now(a, j));
+            const unsigned long long key = Key<double>::make(value, (uint32_t)j);
+            Key<double>::tied(a, i, mine, key);
+            mine = key < mine ? key : mine;
+        }
+    };
+    if constexpr (SPLIT) {
+        for (int k = part; k < 9; k += parts)
+            neighbourhood_row<true>(a.start, I, I.base, n, G.per, cx, cy, cz, i, k, row);
+    } else {
+        for_neighbourhood<true>(a.start, I, I.base, n, G.per, cx, cy, cz, i, row);
+    }
+    if (mine != ~0ull) Key<double>::lower(a, i, mine, key_now(a, i));
+    tests = (double)seen;
+    cand = 2.0 * (double)nc;
+}
+
 // Plain half scan of one record, counting what the pair tests meet (the
 // diagnostic mix): the pairs that cbin_tests counts, record by record.
 template <typename real>
@@ -2057,7 +2096,29 @@ k_search(StepArgs<float> a) {
     add_work(a.gpart, entry, tests, cand, lds);
 }
 
-// The instances of the tile search (all in FP64, the dense ones in FP32),
+// FP64 search of the instances that do not go to the tiles (see tiles_pay),
+// a record a lane; SPLIT: and a share of its rows (blockIdx.y), for launches too
+// small to fill the chip.  What bounds it is the latency of the gathered
+// records and of the row bounds: 1e6 particles at 0.3, 1 and 3 a c-bin take 92,
+// 138 and 248 us (3D), 36, 42 and 56 as a thin tube along y, against 529, 241
+// and 231, and 1982, 1729 and 1033 in tiles, which hold a row's records each.
+// (The ordered scans that came before both: 255, 349 and 564; 72, 94 and 135.)
+template <typename real, bool SPLIT>
+__global__ void __launch_bounds__(kBlock) k_search_lanes(StepArgs<real> a) {
+    __shared__ double lds[16];
+    const int entry =
+        a.order > 0 ? xcd_chunk_remap(blockIdx.x, gridDim.x, a.order) : xcd_remap(blockIdx.x, gridDim.x);
+    const Blk bt = a.blk[entry];
+    const Inst<real>& I = a.inst[bt.inst];
+    if (I.flags & (TPKMC_PAIR_RANDOM | kTiles)) return;
+    const int64_t i = (int64_t)bt.first + threadIdx.x;
+    double tests = 0.0, cand = 0.0;
+    if (i < slow_stop(a, I, I.base))
+        search_lane<SPLIT>(a, I, (int32_t)i, (int)blockIdx.y, (int)gridDim.y, tests, cand);
+    add_work(a.gpart, entry, tests, cand, lds);
+}
+
+// The instances of the tile search (see tiles_pay),
 // one wave per 64 records and part of their neighbourhood (blockIdx.y).
 template <typename real>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(real) == 4 ? 3 : 2)))
@@ -3138,6 +3199,9 @@ template <typename real>
 void launch_speed_stats(const StepArgs<real>& a, hipStream_t s) {
     hipLaunchKernelGGL(k_speed_stats<real>, dim3(a.nblk), dim3(kBlock), 0, s, a);
 }
+// Small launches split each record's neighbourhood over several waves, up to
+// kSplitWaves waves in all (4 a work-group).
+constexpr int kTileParts = 16, kSplitWaves = 4096;
 template <typename real>
 void launch_search(const StepArgs<real>& a, int block, int group, hipStream_t s) {
     if constexpr (std::is_same<real, float>::value) {
@@ -3148,14 +3212,15 @@ void launch_search(const StepArgs<real>& a, int block, int group, hipStream_t s)
         if (group == 4) hipLaunchKernelGGL((k_search<4>), dim3(grid), dim3(bs), lds, s, a);
         else if (group == 2) hipLaunchKernelGGL((k_search<2>), dim3(grid), dim3(bs), lds, s, a);
         else hipLaunchKernelGGL((k_search<1>), dim3(grid), dim3(bs), lds, s, a);
+    } else {
+        const int parts = std::max(1, std::min(9, kSplitWaves / (4 * a.nblk)));
+        if (parts > 1) hipLaunchKernelGGL((k_search_lanes<real, true>), dim3(a.nblk, parts), dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((k_search_lanes<real, false>), dim3(a.nblk), dim3(kBlock), 0, s, a);
     }
 }
-constexpr int kTileParts = 16, kTileWaves = 4096;
 template <typename real>
 void launch_search_tiles(const StepArgs<real>& a, hipStream_t s) {
-    // Small launches split each tile's neighbourhood over several waves, up
-    // to kTileWaves waves in all (4 a work-group).
-    const int parts = std::max(1, std::min(kTileParts, kTileWaves / (4 * a.nblk)));
+    const int parts = std::max(1, std::min(kTileParts, kSplitWaves / (4 * a.nblk)));
     hipLaunchKernelGGL(k_search_tiles<real>, dim3(a.nblk, parts), dim3(kBlock), 0, s, a);
 }
 template <typename real>

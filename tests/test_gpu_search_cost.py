@@ -22,8 +22,9 @@ def T():
     return tpkmc
 
 
-def search_us(T, state, grid, params, precision, reps=6):
-    """Shortest search phase of a step on this state, in microseconds."""
+def search_us(T, state, grid, params, precision, reps=6, also=None):
+    """Shortest search phase (with the phase `also`) of a step on this state,
+    in microseconds."""
     n = len(state["x"])
     eng = T.Engine(max_particles=n, max_cells=T.ncells(grid) + 1, max_obins=T.nobins(grid), precision=precision)
     first = T.to_device(state, precision)
@@ -35,7 +36,8 @@ def search_us(T, state, grid, params, precision, reps=6):
         eng.step(dst, grid, params, out, flags=T.ALLOW_REORDER)
         torch.cuda.synchronize()
         if k:
-            best = min(best, 1e3 * eng.profile_read()["search"][0])
+            ms = eng.profile_read()
+            best = min(best, 1e3 * (ms["search"][0] + (ms[also][0] if also else 0.0)))
     pairs = int(out.host()["counters"][0][T.CNT["pairs"]])
     eng.close()
     print(f"n={n} ncell={grid['ncell']} fp={precision}: search {best:.1f} us, {pairs} pairs", flush=True)
@@ -82,3 +84,23 @@ def test_a_particle_on_the_edge_of_a_periodic_box(T, precision, beyond):
     w.state["y"][7] = w.grid["hi"][1] + beyond
     us.append(search_us(T, w.state, w.grid, w.params, getattr(T, precision)))
     assert us[1] < 1.5 * us[0]
+
+
+def test_fp64_thin_along_either_axis(T):
+    """A tube of one c-bin across costs the same along x, where its c-bins
+    follow one another in a row, and along y, where each is a row."""
+    us = []
+    for ncell, hi in (((100_000, 1, 1), (1.0, 0.02, 0.02)), ((1, 100_000, 1), (0.02, 1.0, 0.02))):
+        w = W.random_box(n=300_000, seed=1, ncell=ncell, bc=(R, P, P), hi=hi, dt_over=0.1, nobin=(1, 1, 1))
+        us.append(search_us(T, w.state, w.grid, w.params, T.FP64))
+    assert us[1] < 3.0 * us[0]
+
+
+def test_fp64_cost_follows_the_particles(T):
+    """1e5 particles on 256^3 c-bins, whose counts alone (the scatter's share
+    of the pair tests) had cost more than the search."""
+    us = []
+    for nc in (46, 256):
+        w = W.random_box(n=100_000, seed=1, ncell=(nc,) * 3, bc=(R, P, P), hi=(1, 1, 1), dt_over=0.1, nobin=(1, 1, 1))
+        us.append(search_us(T, w.state, w.grid, w.params, T.FP64, also="scatter"))
+    assert us[1] < 3.0 * us[0]
