@@ -104,3 +104,18 @@ def test_fp64_cost_follows_the_particles(T):
         w = W.random_box(n=100_000, seed=1, ncell=(nc,) * 3, bc=(R, P, P), hi=(1, 1, 1), dt_over=0.1, nobin=(1, 1, 1))
         us.append(search_us(T, w.state, w.grid, w.params, T.FP64, also="scatter"))
     assert us[1] < 3.0 * us[0]
+
+
+def test_fp64_ties_are_settled_by_the_whole_card(T):
+    """Every record of the lattice meets several candidates at the same closest
+    distance; the same lattice a little out of place has none to settle."""
+    k = np.arange(100) + 0.5
+    x, y, z = (c.ravel() * 0.01 for c in np.meshgrid(k, k, k, indexing="ij"))
+    v = np.where((np.arange(100 ** 3) + np.repeat(np.arange(10_000), 100) + np.repeat(np.arange(100), 10_000)) % 2, 1.0, -1.0)
+    g = W.grid((0, 0, 0), (1, 1, 1), (50, 50, 50), (R, R, R), (1, 1, 1))
+    p = W.params(sigma=np.pi * 0.012 ** 2, dt=0.01)
+    us = []
+    for jitter in (1e-4, 0.0):
+        d = np.random.default_rng(1).uniform(-jitter, jitter, (3, len(x)))
+        us.append(search_us(T, W.make_state(x + d[0], y + d[1], z + d[2], v, 0.0 * v, 0.0 * v), g, p, T.FP64))
+    assert us[1] < 7.0 * us[0]
