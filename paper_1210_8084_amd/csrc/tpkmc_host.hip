@@ -696,7 +696,8 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     if (s->n > h->max_n) return TPKMC_ECAPACITY;
     if (bad_state(s)) return TPKMC_EINVAL;
     std::vector<std::pair<int64_t, int64_t>> spans;
-    std::vector<Inst<real>> I(n_inst);
+    P.inst_bytes.resize(sizeof(Inst<real>) * n_inst);
+    Inst<real>* const I = reinterpret_cast<Inst<real>*>(P.inst_bytes.data());
     P.blk.clear();
     P.chunks.clear();
     P.n_inst = n_inst;
@@ -752,8 +753,6 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     if (P.nob_tot > h->max_obins) return TPKMC_ECAPACITY;
     if (P.nblk > h->max_blk) return TPKMC_ECAPACITY;
     if (P.nchunk > h->max_chunks) return TPKMC_ECAPACITY;
-    P.inst_bytes.resize(sizeof(Inst<real>) * n_inst);
-    std::memcpy(P.inst_bytes.data(), I.data(), P.inst_bytes.size());
     return TPKMC_OK;
 }
 
