@@ -265,9 +265,12 @@ int tpkmc_version(void);
 const char* tpkmc_strerror(int code);
 
 /* Allocates a handle and all its device scratch on cfg->device (memory is
- * sized from the capacities: about 107 B per particle in FP32, 187 B in FP64,
- * 8 B per c-bin, 184 B per o-bin, 280 B up to 4096 of them).  *out is NULL on
- * failure. */
+ * sized from the capacities: about 74 B per particle in FP32, 114 B in FP64,
+ * 4 B per c-bin, 152 B per o-bin).  Where each takes at most an eighth of the
+ * memory then free on the device, also second records (32 B per particle in
+ * FP32, 64 B in FP64) and o-bin exponents apart from their sums (32 B each, 128 B
+ * up to 4096 of them), with which steps are faster; the results are the same
+ * without.  *out is NULL on failure. */
 int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out);
 
 /* Waits for the handle's work, frees everything.  NULL is a no-op. */

@@ -1039,6 +1039,19 @@ int dalloc(T** p, int64_t count) {
     return hipMalloc((void**)p, sizeof(T) * (size_t)count) == hipSuccess ? 0 : -1;
 }
 
+// Scratch that a step is faster with but does without: null where it would take
+// more than an eighth of the memory that is free, so that a state that just
+// fits the card beside the rest of its scratch still does.
+void alloc_extra(void** p, int64_t bytes) {
+    size_t room = 0, total = 0;
+    *p = nullptr;
+    if (hipMemGetInfo(&room, &total) != hipSuccess || bytes <= 0 || (size_t)bytes > room / 8 ||
+        hipMalloc(p, (size_t)bytes) != hipSuccess) {
+        *p = nullptr;
+        hipGetLastError();
+    }
+}
+
 // Grows the c-bin counts array (and its scan tiles) to hold `need` c-bins.
 int grow_cells(tpkmc_handle* h, int64_t need) {
     if (need <= h->cell_cap) return TPKMC_OK;
@@ -1366,14 +1379,14 @@ size_t carve(uintptr_t base, int64_t n, int64_t ncell_tot, int64_t nob, int nblk
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     B.rank = (int32_t*)take(4 * nn);
     B.src = (int32_t*)take(4 * nn);
-    // best and perm serve random partners alone; in FP64 the search's keys
-    // share their place (one instance takes the one or the other).
-    B.best = (int32_t*)take(4 * nn);
-    B.perm = (int32_t*)take(4 * nn);
+    // Random partners alone; in FP64 they share the keys' place (see rp_best).
+    const bool fp32 = std::is_same<real, float>::value;
+    B.best = fp32 ? (int32_t*)take(4 * nn) : nullptr;
+    B.perm = fp32 ? (int32_t*)take(4 * nn) : nullptr;
     B.rec = take(8 * sizeof(real) * nn);
     B.rec2 = second ? take(8 * sizeof(real) * nn) : nullptr;
     B.rmass = masses ? take(sizeof(real) * nn) : nullptr;
-    B.bkey = std::is_same<real, float>::value ? (unsigned long long*)take(8 * nn) : (unsigned long long*)B.best;
+    B.bkey = (unsigned long long*)take(8 * nn);
     B.start = (int32_t*)take(4 * (size_t)(ncell_tot + 1));
     B.tiles = (int32_t*)take(4 * (size_t)(scan_tiles(ncell_tot + 1) + 1));
     B.inst = take(sizeof(Inst<real>));
@@ -1516,10 +1529,8 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
     bad |= dalloc(&h->b.start, cells + 1);
     bad |= dalloc(&h->b.tiles, scan_tiles(cells + 1) + 1);
     bad |= dalloc(&h->b.src, h->max_n);
-    bad |= dalloc(&h->b.best, h->max_n);
-    bad |= dalloc(&h->b.perm, h->max_n);
+    if (cfg->precision == TPKMC_FP32) bad |= dalloc(&h->b.best, h->max_n) | dalloc(&h->b.perm, h->max_n);
     bad |= hipMalloc(&h->b.rec, rs * 8 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
-    bad |= hipMalloc(&h->b.rec2, rs * 8 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
     bad |= hipMalloc(&h->b.rmass, rs * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
     bad |= hipMalloc(&h->b.inst, inst_sz * (size_t)h->max_inst) != hipSuccess;
     bad |= dalloc(&h->b.blk, h->max_blk);
@@ -1529,7 +1540,6 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
     bad |= dalloc(&h->b.bkey, h->max_n);
     bad |= dalloc(&h->b.shift, 3 * std::max<int64_t>(h->max_obins, 1));
     bad |= dalloc(&h->b.macc, std::max<int64_t>(h->max_obins, 1));
-    bad |= dalloc(&h->b.mexp, std::max(exp_bytes(h->max_obins), exp_bytes(std::min(h->max_obins, kSpreadObins))));
     bad |= hipMalloc(&h->b.vir, rs * 3 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
     bad |= dalloc(&h->b.coll, std::max<int64_t>(h->max_n, 1));
     bad |= dalloc(&h->b.pair_count, 2);
@@ -1548,7 +1558,12 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
         bad |= hipStreamCreateWithFlags(&h->own_stream, hipStreamNonBlocking) != hipSuccess;
         bad |= hipDeviceSynchronize() != hipSuccess;
     }
-    if (!bad) h->b.ties = (uint32_t*)(h->b.pair_count + 1);
+    if (!bad) {
+        h->b.ties = (uint32_t*)(h->b.pair_count + 1);
+        alloc_extra((void**)&h->b.mexp,
+                    std::max(exp_bytes(h->max_obins), exp_bytes(std::min(h->max_obins, kSpreadObins))));
+        alloc_extra(&h->b.rec2, (int64_t)rs * 8 * std::max<int64_t>(h->max_n, 1));
+    }
     if (bad) {
         free_all(h);
         if (h->own_stream) hipStreamDestroy(h->own_stream);

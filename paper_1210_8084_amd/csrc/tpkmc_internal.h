@@ -168,8 +168,7 @@ struct StepArgs {
     real* rmass;              // masses in record order (with mass only)
     real* rec2;               // records after the move, for a state in the caller's order; or null (no room)
     int32_t* src;             // caller's order only: caller index -> record (without rec2: record -> caller index)
-    int32_t* best;            // random partners: rank in the c-bin; FP64: then the partner record or -1
-    int32_t* perm;            // random partners: c-bin-local order -> record
+    int32_t *best, *perm;     // random partners in FP32: rank in the c-bin; c-bin-local order -> record (see rp_best)
     unsigned long long* bkey; // record -> (ranking value bits, partner record) of its closest candidate
     uint32_t* ties;           // nonzero: some FP64 record is marked in coll (see k_search_ties)
     double* gpart;            // [nblk][kGPart]

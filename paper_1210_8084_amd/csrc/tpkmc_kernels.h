@@ -2336,6 +2336,20 @@ template <> __device__ __forceinline__ uint32_t record_id<double>(const double* 
     return (uint32_t)reinterpret_cast<const unsigned long long*>(rec)[8 * i + 3];
 }
 
+// Rank (FP64: later the partner) and c-bin-local order of an instance's
+// records, indexed from its first.  In FP64 they lie in the place of the keys,
+// which an instance with random partners does not use.
+template <typename real>
+__device__ __forceinline__ int32_t* rp_best(const StepArgs<real>& a, const Inst<real>& I) {
+    if constexpr (std::is_same<real, double>::value) return reinterpret_cast<int32_t*>(a.bkey + I.off);
+    else return a.best + I.off;
+}
+template <typename real>
+__device__ __forceinline__ int32_t* rp_perm(const StepArgs<real>& a, const Inst<real>& I) {
+    if constexpr (std::is_same<real, double>::value) return reinterpret_cast<int32_t*>(a.bkey + I.off) + I.cnt;
+    else return a.perm + I.off;
+}
+
 // Global c-bin of a record, from its position (the key kernel's arithmetic).
 template <typename real>
 __device__ __forceinline__ int64_t record_cbin(const Inst<real>& I, real x, real y, real z) {
@@ -2379,8 +2393,8 @@ __global__ void __launch_bounds__(kBlock) k_rp_rank(StepArgs<real> a) {
         const uint32_t kj = key[j];
         r += (kj < mine || (kj == mine && record_id<real>(a.rec, j) < id)) ? 1 : 0;
     }
-    a.perm[lo + r] = (int32_t)i;
-    a.best[i] = r;
+    rp_perm(a, I)[lo - I.off + r] = (int32_t)i;
+    rp_best(a, I)[i - I.off] = r;
 }
 
 template <typename real>
@@ -2401,14 +2415,14 @@ __global__ void __launch_bounds__(kBlock) k_rp_partner(StepArgs<real> a) {
             Rec<real>::load(a.rec, i, x, y, z, id, vx, vy, vz, fl);
             const int64_t k = record_cbin(I, x, y, z);
             const int64_t lo = base + a.start[k], nc = base + a.start[k + 1] - lo;
-            const int32_t r = a.best[i], q = r ^ 1;
+            const int32_t r = rp_best(a, I)[i - I.off], q = r ^ 1;
             if (q < nc) {
-                partner = a.perm[lo + q];
+                partner = rp_perm(a, I)[lo - I.off + q];
                 paired = 1.0;
                 formed = (r & 1) == 0 ? 1.0 : 0.0;
             }
         }
-        if constexpr (std::is_same<real, double>::value) a.best[i] = partner;
+        if constexpr (std::is_same<real, double>::value) rp_best(a, I)[i - I.off] = partner;
         else a.bkey[i] = partner >= 0 ? (unsigned long long)(uint32_t)partner : ~0ull;
     }
     const double f = block_sum(formed, lds);
@@ -2448,7 +2462,7 @@ __device__ __forceinline__ bool random_pair_collides(const StepArgs<real>& a, co
 template <typename real>
 __device__ __forceinline__ int32_t partner_of(const StepArgs<real>& a, const Inst<real>& I, int64_t i) {
     if constexpr (std::is_same<real, double>::value)
-        if (I.flags & TPKMC_PAIR_RANDOM) return a.best[i];
+        if (I.flags & TPKMC_PAIR_RANDOM) return rp_best(a, I)[i - I.off];
     const unsigned long long k = a.bkey[i];
     return k == ~0ull ? -1 : Key<real>::partner(k);
 }
