@@ -129,9 +129,11 @@ __device__ __forceinline__ int axis_bin(real x, real lo, real inv_w, int n) {
 // Sort cell of a coordinate along axis ax: its c-bin (refined for the slow
 // particles of split c-bins), cut into 2^kl equal parts where the instance has
 // sub-grids.  The c-bin is axis_bin's own, so a sub-grid never moves a
-// particle to another c-bin.
+// particle to another c-bin.  Every operation rounds (no contraction), so
+// that the kernels that work it out agree to the last bit.
 template <typename real>
 __device__ __forceinline__ int sort_bin(const Inst<real>& I, int ax, real x) {
+#pragma clang fp contract(off)
     const int c = axis_bin(x, I.lo[ax], I.inv_wl[ax], I.nl[ax]);
     const int k = 1 << I.kl[ax];
     if (k == 1) return c;
