@@ -627,23 +627,6 @@ __device__ __forceinline__ real min_image(real r, real L, real halfL) {
 //    form, only discards pairs that are certainly not candidates; the rest go
 //    through the reference's own expressions (t_poca = -s0/|u|^2, PoCA
 //    separation r + t_poca u), so decisions and d_min^2 are bit-identical.
-template <typename real, int PM>
-__device__ __forceinline__ void rel_vectors(const Geo<real>& G, real xi, real yi, real zi, real vxi, real vyi,
-                                            real vzi, real xj, real yj, real zj, real vxj, real vyj, real vzj,
-                                            real& rx, real& ry, real& rz, real& ux, real& uy, real& uz) {
-    rx = xi - xj; ry = yi - yj; rz = zi - zj;
-    if constexpr (PM < 0) {
-        if (G.per[0]) rx = min_image(rx, G.L[0], G.halfL[0]);
-        if (G.per[1]) ry = min_image(ry, G.L[1], G.halfL[1]);
-        if (G.per[2]) rz = min_image(rz, G.L[2], G.halfL[2]);
-    } else {
-        if constexpr ((PM & 1) != 0) rx = min_image(rx, G.L[0], G.halfL[0]);
-        if constexpr ((PM & 2) != 0) ry = min_image(ry, G.L[1], G.halfL[1]);
-        if constexpr ((PM & 4) != 0) rz = min_image(rz, G.L[2], G.halfL[2]);
-    }
-    ux = vxi - vxj; uy = vyi - vyj; uz = vzi - vzj;
-}
-
 // Two-stage screening, both stages without divergent branches:
 //  stage 1, criterion 1 (s0 < 0 < s1), on every pair;
 //  stage 2, |r x u|^2 <= D^2 |u|^2, only when some lane of the wave passed
@@ -653,8 +636,8 @@ template <typename real> struct Screen {
     real rx, ry, rz, ux, uy, uz, s0, vv;
 };
 
-// PM: the periodic axes as a mask known at compile time (bit a for axis a),
-// or -1 to read them from the instance at run time.
+// PM: the periodic axes as a mask known at compile time (bit a for axis a;
+// FP32 alone), or -1 to read them from the instance at run time.
 template <typename real, int PM> struct PairTest;
 
 template <int PM> struct PairTest<float, PM> {
@@ -704,12 +687,15 @@ template <int PM> struct PairTest<float, PM> {
     }
 };
 
-template <int PM> struct PairTest<double, PM> {
+template <> struct PairTest<double, -1> {
     static __device__ __forceinline__ bool stage1(const Geo<double>& G, double xi, double yi, double zi, double vxi,
                                                   double vyi, double vzi, double xj, double yj, double zj, double vxj,
                                                   double vyj, double vzj, Screen<double>& S) {
-        double rx, ry, rz, ux, uy, uz;
-        rel_vectors<double, PM>(G, xi, yi, zi, vxi, vyi, vzi, xj, yj, zj, vxj, vyj, vzj, rx, ry, rz, ux, uy, uz);
+        double rx = xi - xj, ry = yi - yj, rz = zi - zj;
+        if (G.per[0]) rx = min_image(rx, G.L[0], G.halfL[0]);
+        if (G.per[1]) ry = min_image(ry, G.L[1], G.halfL[1]);
+        if (G.per[2]) rz = min_image(rz, G.L[2], G.halfL[2]);
+        const double ux = vxi - vxj, uy = vyi - vyj, uz = vzi - vzj;
         // Exactly the reference's s0 and s1 (no contraction in this unit).
         const double s0 = (rx * ux + ry * uy) + rz * uz;
         const double vv = (ux * ux + uy * uy) + uz * uz;
@@ -1061,11 +1047,11 @@ constexpr uint32_t kCodeHome = 1u | 1u << 2 | 1u << 4;  // no shift
 // and a pair is taken at the one the pair test's minimum-image rule picks.
 // With four c-bins only pairs half a box apart, from edge to edge of their
 // c-bins, are open; records that close to an edge are wild.
-__device__ __forceinline__ int image_of(double r, double, double halfL, double) {
-    return r > halfL ? 1 : (r < -halfL ? -1 : 0);
+__device__ __forceinline__ int image_of(const Geo<double>& G, int ax, double r) {
+    return r > G.halfL[ax] ? 1 : (r < -G.halfL[ax] ? -1 : 0);
 }
-__device__ __forceinline__ int image_of(float r, float, float, float invL) {
-    const float k = rintf(r * invL);
+__device__ __forceinline__ int image_of(const Geo<float>& G, int ax, float r) {
+    const float k = rintf(r * G.invL[ax]);
     return k > 0.0f ? 1 : (k < 0.0f ? -1 : 0);
 }
 
@@ -1090,7 +1076,7 @@ __device__ __forceinline__ void tile_hits(const StepArgs<real>& a, const Geo<rea
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             const uint32_t c = (code >> (2 * ax)) & 3u;
-            if (c != kCodeAny && image_of(r[ax], G.L[ax], G.halfL[ax], G.invL[ax]) != (int)c - 1) return;
+            if (c != kCodeAny && image_of(G, ax, r[ax]) != (int)c - 1) return;
         }
     }
     real value;
