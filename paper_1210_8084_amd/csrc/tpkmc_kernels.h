@@ -1226,16 +1226,43 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
             org[ax] = (lo[ax] + mid[ax] * ws[ax]) * sx;
             Ls[ax] = G.L[ax] * sx;
             vo[ax] = (real)(wave_reducef<false>(in ? (float)(vi[ax] * sv) : 0.0f) * inv);
-            const float big = fabsf((float)org[ax]) + (G.per[ax] ? (float)Ls[ax] : 0.0f);
-            xabs = fmaxf(xabs, big * (sizeof(real) == 4 ? 1.0f / 1024.0f : 1e-9f));
+            if (G.per[ax])  // elsewhere nothing is shifted
+                xabs = fmaxf(xabs, (fabsf((float)org[ax]) + (float)Ls[ax]) * (sizeof(real) == 4 ? 1.0f / 1024.0f : 1e-9f));
         }
+        // How far apart a candidate pair of this group can start: with
+        // sub-grids from the group's and the instance's largest speeds, so
+        // that a pair's own image is always visited.  Without, only images
+        // other than the unshifted one are skipped, by a bound for partners
+        // up to vcap; faster ones are wild, and wild pairs are taken
+        // unshifted.
+        real reach = real(INFINITY);
+        int m[3] = {1 << 24, 1 << 24, 1 << 24};
+        if (sub) {
+            // In widths per step, where FP32 has room below and above whatever
+            // the units of an FP64 state (infinite or no number: no bound).
+            float V[3];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) V[ax] = (float)(vi[ax] * sv);
+            float v = in ? sqrtf(V[0] * V[0] + V[1] * V[1] + V[2] * V[2]) : 0.0f;
+            v = v < INFINITY ? v : INFINITY;
+            reach = (sqrt(I.D2) + I.vreach * I.dt + (real)(wave_reducef<true>(v) * (1.0f / kTileKappa)) / sx) *
+                    real(1.001);
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                const real c = reach * iw[ax] + real(1e-3) + real(1e-6) * (real)n[ax];
+                m[ax] = c < (real)(1 << 24) ? 1 + (int)c : 1 << 24;
+            }
+        }
+        const TileAxis AX = tile_axis(I, 0, G.per[0], cxf, cxl, m[0]);
+        const TileAxis AY = tile_axis(I, 1, G.per[1], gcy, gcy, m[1]);
+        const TileAxis AZ = tile_axis(I, 2, G.per[2] && !planar, gcz, gcz, m[2]);
         // A shifted origin too coarse for the filter: shifted partners are
         // wild, and where a partner is visited in several places it is so in
         // all of them.  (Taken for unshifted ones too, an FP32 box of 1e6 at
         // 16 a c-bin and a thousand box lengths from the origin took 1.7 ms a
         // step instead of 0.55.)
         const bool coarse = !(xabs <= 16.0f);
-        const bool coarse_home = coarse && (I.flags & kImaged);
+        const bool coarse_home = coarse && AX.images * AY.images * AZ.images > 1;
         // The largest coordinate of a partner in its place, and a speed whose
         // own terms beside it, x v + v^2 / kTileKappa, stay below kTileOwn.
         const float xcap = fminf(fmaf(I.tile_dx, (float)(cxl - cxf), I.tile_x), kTileXMax);
@@ -1281,33 +1308,6 @@ __device__ void search_tiles(const StepArgs<real>& a, const Inst<real>& I, int32
                                     pack2(one, one), split_f16(T.r), pack2(mrx, mrv)};
             tile_operands(wr, BR);
         }
-        // How far apart a candidate pair of this group can start: with
-        // sub-grids from the group's and the instance's largest speeds, so
-        // that a pair's own image is always visited.  Without, only images
-        // other than the unshifted one are skipped, by a bound for partners
-        // up to vcap; faster ones are wild, and wild pairs are taken
-        // unshifted.
-        real reach = real(INFINITY);
-        int m[3] = {1 << 24, 1 << 24, 1 << 24};
-        if (sub) {
-            // In widths per step, where FP32 has room below and above whatever
-            // the units of an FP64 state (infinite or no number: no bound).
-            float V[3];
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) V[ax] = (float)(vi[ax] * sv);
-            float v = in ? sqrtf(V[0] * V[0] + V[1] * V[1] + V[2] * V[2]) : 0.0f;
-            v = v < INFINITY ? v : INFINITY;
-            reach = (sqrt(I.D2) + I.vreach * I.dt + (real)(wave_reducef<true>(v) * (1.0f / kTileKappa)) / sx) *
-                    real(1.001);
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                const real c = reach * iw[ax] + real(1e-3) + real(1e-6) * (real)n[ax];
-                m[ax] = c < (real)(1 << 24) ? 1 + (int)c : 1 << 24;
-            }
-        }
-        const TileAxis AX = tile_axis(I, 0, G.per[0], cxf, cxl, m[0]);
-        const TileAxis AY = tile_axis(I, 1, G.per[1], gcy, gcy, m[1]);
-        const TileAxis AZ = tile_axis(I, 2, G.per[2] && !planar, gcz, gcz, m[2]);
         float vcap = vlim;
         real reach_im = reach;
         if (!sub && AX.images * AY.images * AZ.images > 1) {
