@@ -466,11 +466,14 @@ bool bad_state(const tpkmc_particles* s) {
                         bad_ptr(s->vz) || bad_ptr(s->id));
 }
 
-// Tile search or lane walk (FP32: staged, FP64: a record a lane).  FP32 below
-// kTileDensity particles per c-bin is staged; the rest by the cost of both, in
-// microseconds per 1e6 records as fitted to measurements of 1.6e3 states (uniform
-// gases of 3e4 and 1e6 particles at 0.3 to 100 per c-bin; boxes, planes, tubes
-// along x and y, slabs of 1 to 8 c-bins along x; D of 0.1 to 2 widths).
+// Tile search or lane walk (FP32: staged, FP64: a record a lane).  Instances that
+// can be cut into sort cells (`cut`) take tiles, unless they are thinner than a
+// pair's reach along two periodic axes (a tube of 1e6 as thin as a c-bin is long
+// at 30 per c-bin, FP32: 141 us staged, 292 in tiles), and FP32 below
+// kTileDensity particles per c-bin is staged; the rest goes by the cost of both in microseconds per 1e6 records, as
+// fitted to the search of 1.6e3 uniform states (3e4 and 1e6 particles at 0.3 to
+// 100 per c-bin; boxes, planes, tubes along x and y, slabs of 1 to 8 c-bins along
+// x; D of 0.1 to 2 widths).
 //  - A tile is up to 64 records of one row of c-bins, so a wave's records make
 //    1 + 63 / (records of a row) tiles, each with a set-up and blocks of 64
 //    partners from its rows, 64 records and two c-bins long, once per image
@@ -478,18 +481,20 @@ bool bad_state(const tpkmc_particles* s) {
 //  - A lane tests its half neighbourhood pair by pair; the staged walk also
 //    goes tile by tile through the rows.
 // A small call takes what one wave needs: the tiles and the FP64 lanes are split
-// over waves then, the staged walk is not.  Lanes are chosen where they cost
-// less than kLaneGain of the tiles, which suffer less where the gas clumps.
-// Measured, lanes against tiles: FP64 boxes at 1, 3 and 7.6 per c-bin 138, 248
-// and 450 against 241, 231 and 234 us; FP32 tube along x at 14 and 100 per
-// c-bin 42 and 140 against 91 and 105, plane at 10 and 20 90 and 146 against 115
-// and 137, box periodic along z with one c-bin at 14 and 40 124 and 290 against 202
-// and 300.
+// over waves then, the staged walk is not.  Shocks gather the particles: a record
+// has kClump times the mean number of neighbours here.  (With one, a uniform gas
+// of one c-bin along a periodic z at 10 to 24 per c-bin would be staged, 95 to
+// 150 us instead of 180 to 220, and an ensemble with Noh implosions of such
+// densities took 70 ms a pass instead of 48.)
+// Measured, lanes against tiles: FP64 boxes at 0.3, 1 and 3 per c-bin 92, 138
+// and 248 against 529, 241 and 231 us, tube along y at 3 and 20 56 and 157 against
+// 1033 and 260; FP32 tube as thin as a c-bin is long at 16 per c-bin 60 against
+// 300 us, box at 9, 14 and 20 per c-bin 201, 271 and 354 against 171, 194 and 209.
 constexpr double kTileDensity = 8.0;
-constexpr double kLaneGain = 0.85;
+constexpr double kClump = 3.0;
 
 template <typename real>
-bool tiles_pay(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, double D, bool planar) {
+bool tiles_pay(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, double D, bool planar, bool cut) {
     constexpr bool fp64 = std::is_same<real, double>::value;
     if (!fp64 && dens < kTileDensity) return false;
     double w = 0.0, rows = 1.0, visits = 1.0;  // narrowest c-bin; rows of a neighbourhood, with images
@@ -497,22 +502,27 @@ bool tiles_pay(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, 
         const double wa = (g.hi[a] - g.lo[a]) / d.nl[a];
         w = w > 0.0 ? std::min(w, wa) : wa;
     }
+    const double reach = D + 0.25 * w;
+    int thin = 0;
     for (int a = 0; a < 3; ++a) {
+        const double L = g.hi[a] - g.lo[a];
         if (a > 0) rows *= std::min(3, d.nl[a]);
+        if (g.bc[a] != TPKMC_BC_PERIODIC || d.nl[a] > 3 || (planar && a == 2)) continue;
         // Images out of reach of a tile's outermost record are skipped.
-        if (g.bc[a] == TPKMC_BC_PERIODIC && d.nl[a] <= 3 && !(planar && a == 2) &&
-            100.0 * (D + 0.25 * w) > g.hi[a] - g.lo[a])
-            visits *= 3.0;
+        if (100.0 * reach > L) visits *= 3.0;
+        if (4.0 * reach > L) ++thin;
     }
+    if (cut && thin < 2) return true;
     visits *= rows;
     const double row = std::max(dens * d.nl[0], 1e-3), groups = std::min(64.0, 1.0 + 63.0 / row);
-    const double blocks = 0.5 + 0.5 * visits * std::min(row, 64.0 + 2.0 * dens) / 64.0;
-    const double tests = 0.5 * rows * std::min(row, 3.0 * dens), m = n * 1e-6;
+    const double span = 64.0 + 2.0 * kClump * dens, near = kClump * std::min(row, 3.0 * dens);
+    const double blocks = 0.5 + 0.5 * visits * std::min(row < 3.0 * dens ? kClump * row : row, span) / 64.0;
+    const double tests = 0.5 * rows * near, m = n * 1e-6;
     const double tile = fp64 ? 88.0 + groups * (14.0 + 24.0 * blocks) : 63.0 + groups * (18.0 + 16.0 * blocks);
     const double lane = fp64 ? 38.0 + 5.8 * rows + 3.7 * tests : 21.0 + 6.7 * groups * rows + 1.1 * tests;
     const double tiles = std::max(m * tile, 18.0 + 8.0 * groups + 0.06 * tile);
     const double lanes = fp64 ? std::max(m * lane, 8.0 + 0.07 * lane) : std::max(m, 0.5) * lane;
-    return !(lanes < kLaneGain * tiles);
+    return !(lanes < tiles);
 }
 
 // Sub-grids: c-bins of at least kSubgridDensity particles are halved along
@@ -530,7 +540,12 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
                        bool planar, bool subgrid, uint32_t flags) {
     const int naxes = planar ? 2 : 3;
     double dens = (double)count / (double)Cs, w[3];
-    if (!(flags & TPKMC_PAIR_RANDOM) && tiles_pay(d, g, (double)n_all, dens, D, planar)) d.flags |= kTiles;
+    auto widest = [&]() {  // the widest axis that can be halved, or -1
+        int a = -1;
+        for (int b = 0; b < naxes; ++b)
+            if (0.5 * w[b] >= kSortCellD * D && (int64_t)d.n[b] * 2 <= 1 << 24 && (a < 0 || w[b] > w[a])) a = b;
+        return a;
+    };
     // Scale of the tile search's positions: the widest c-bin (half the box on
     // an axis of one; a planar gas has no extent along z).
     double wide = 0.0;
@@ -539,12 +554,10 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
         if (a < naxes) wide = std::max(wide, d.nl[a] > 1 ? w[a] : 0.5 * w[a]);
     }
     d.tile_s = (float)(1.0 / wide);
-    if (subgrid && (d.flags & kTiles) && dens >= kSubgridDensity) {
-        while (dens >= 2.0 * kSortCellMin) {
-            int a = -1;
-            for (int b = 0; b < naxes; ++b)
-                if (0.5 * w[b] >= kSortCellD * D && (int64_t)d.n[b] * 2 <= 1 << 24 && (a < 0 || w[b] > w[a])) a = b;
-            if (a < 0) break;
+    const bool cut = dens >= kSubgridDensity && widest() >= 0;
+    if (!(flags & TPKMC_PAIR_RANDOM) && tiles_pay(d, g, (double)n_all, dens, D, planar, cut)) d.flags |= kTiles;
+    if (subgrid && cut && (d.flags & kTiles)) {
+        for (int a; dens >= 2.0 * kSortCellMin && (a = widest()) >= 0;) {
             d.kl[a] += 1;
             d.n[a] *= 2;
             w[a] *= 0.5;
@@ -561,7 +574,6 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
         d.w_sort[a] = (real)(L / d.n[a]);
         if (a >= naxes) continue;
         const bool few = g.bc[a] == TPKMC_BC_PERIODIC && d.nl[a] <= 3;
-        if (few) d.flags |= kImaged;
         x = std::max(x, (few ? 2.0 * L : 0.5 * L / d.n[a] + 2.0 * L / d.nl[a]) / wide);
     }
     d.tile_x = (float)(1.01 * x + 0.01);

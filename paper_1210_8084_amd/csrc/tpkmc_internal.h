@@ -128,9 +128,6 @@ constexpr uint32_t kSplit = 1u << 30;
 // c-bins are cut into sort cells (see Inst).
 constexpr uint32_t kTiles = 1u << 29;
 constexpr uint32_t kSubgrid = 1u << 28;
-// Bit of Inst::flags set by the host: some periodic axis has at most three
-// c-bins, so the tile search may visit its images one by one.
-constexpr uint32_t kImaged = 1u << 27;
 
 // Bit of Inst::flags, set by the host (outside the public flag bits): the
 // particles carry their own masses.
