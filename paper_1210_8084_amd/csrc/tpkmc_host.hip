@@ -515,8 +515,9 @@ bool tiles_pay(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, 
     if (cut && thin < 2) return true;
     visits *= rows;
     const double row = std::max(dens * d.nl[0], 1e-3), groups = std::min(64.0, 1.0 + 63.0 / row);
-    const double span = 64.0 + 2.0 * kClump * dens, near = kClump * std::min(row, 3.0 * dens);
-    const double blocks = 0.5 + 0.5 * visits * std::min(row < 3.0 * dens ? kClump * row : row, span) / 64.0;
+    const double clump = thin < 2 ? kClump : 1.0;  // nine images: the tiles gain nothing from a crowd
+    const double span = 64.0 + 2.0 * clump * dens, near = clump * std::min(row, 3.0 * dens);
+    const double blocks = 0.5 + 0.5 * visits * std::min(row < 3.0 * dens ? clump * row : row, span) / 64.0;
     const double tests = 0.5 * rows * near, m = n * 1e-6;
     const double tile = fp64 ? 88.0 + groups * (14.0 + 24.0 * blocks) : 63.0 + groups * (18.0 + 16.0 * blocks);
     const double lane = fp64 ? 38.0 + 5.8 * rows + 3.7 * tests : 21.0 + 6.7 * groups * rows + 1.1 * tests;
