@@ -230,7 +230,7 @@ template <typename real>
 __device__ void finalize_one(Inst<real>& I, int k0, const double* cpart, const double* gpart, uint64_t* counters,
                              double* globals, uint32_t* status, const unsigned long long* pair_count,
                              int64_t pair_cap, int advance_step, double* rows) {
-    __shared__ double tot[kGPart], part[kGPart];
+    __shared__ double tot[kGPart];
     // Partials of this instance, staged in LDS kChunk rows at a time (folded
     // in order, so the result does not depend on the launch shape).
     double acc = 0.0;
@@ -242,13 +242,7 @@ __device__ void finalize_one(Inst<real>& I, int k0, const double* cpart, const d
         __syncthreads();
         for (int t = threadIdx.x; t < nr * kGPart; t += blockDim.x) rows[t] = src[(int64_t)c0 * kGPart + t];
         __syncthreads();
-        if (gpart) {  // the one chunk's partial, then that as its only row
-            reduce_slots(rows, nr, part);
-            __syncthreads();
-            reduce_slots(part, 1, tot);
-        } else {
-            reduce_slots(rows, nr, tot);
-        }
+        reduce_slots(rows, nr, tot);  // (folding the one partial of a chunk again would leave it as it is)
         __syncthreads();
         if (threadIdx.x < kGPart) {
             const int k = threadIdx.x;
