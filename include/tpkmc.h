@@ -82,8 +82,11 @@ enum { TPKMC_BC_REFLECT = 0, TPKMC_BC_PERIODIC = 1, TPKMC_BC_ABSORB = 2 };
 enum {
     TPKMC_EMIT_PAIRS = 1u,     /* write accepted pairs to outputs.pairs       */
     TPKMC_ALLOW_REORDER = 2u,  /* leave all particle arrays (id and alive
-                                  included) in c-bin order instead of the
-                                  caller's order                            */
+                                  included) in the order the step sorted them
+                                  in instead of the caller's: by the c-bins
+                                  of the state before the step, refined ones
+                                  after tpkmc_autotune, and parts of dense
+                                  ones, neighbouring parts together         */
     TPKMC_ADAPTIVE_DT = 4u,    /* time step of Sec. 3: dt = dx / v_max, with
                                   v_max the largest speed of the alive finite
                                   particles at the start of the step and dx
@@ -353,14 +356,15 @@ int tpkmc_run(tpkmc_handle* h, const tpkmc_particles* s,
  *    handle's c-bin storage.
  *  - the launch shape (work-group size and particles per work-item): timed,
  *    the default kept unless another is at least 5% faster (it matters to
- *    FP32 instances of fewer than 8 particles per c-bin only);
+ *    the FP32 instances that are searched lane by lane: those of fewer than
+ *    8 particles per c-bin, and long thin ones);
  *  - the order in which the search's work-groups are dealt to the XCDs:
  *    chunks of 16 work-groups dealt round-robin over the XCDs (the default:
  *    balance when the work per work-group varies along the c-bin order, as
  *    across a batch of instances or in a dense shocked region), contiguous
- *    ranges per XCD (neighbouring work-groups share an L2; FP32 instances of
- *    fewer than 8 particles per c-bin only, as elsewhere the work grows with
- *    the density), or chunks of 1 or 128; another order is timed in the chosen
+ *    ranges per XCD (neighbouring work-groups share an L2; only where no
+ *    instance is searched by tiles, whose work grows with the density), or
+ *    chunks of 1 or 128; another order is timed in the chosen
  *    shape and kept when at least 5% faster.
  * Runs the binning and search kernels only; the particle state is not
  * modified.  Synchronises the stream. */

@@ -464,10 +464,11 @@ bool bad_state(const tpkmc_particles* s) {
 // can be cut into sort cells (`cut`) take tiles, unless they are thinner than a
 // pair's reach along two periodic axes (a tube of 1e6 as thin as a c-bin is long
 // at 30 per c-bin, FP32: 141 us staged, 292 in tiles), and FP32 below
-// kTileDensity particles per c-bin is staged; the rest goes by the cost of both in microseconds per 1e6 records, as
-// fitted to the search of 1.6e3 uniform states (3e4 and 1e6 particles at 0.3 to
-// 100 per c-bin; boxes, planes, tubes along x and y, slabs of 1 to 8 c-bins along
-// x; D of 0.1 to 2 widths).
+// kTileDensity particles per c-bin is staged (4M tube at 2.9: 0.42 ms staged,
+// 0.58 in tiles).  The rest goes by the cost of both in microseconds per 1e6
+// records, as fitted to the search of 1.6e3 uniform states (3e4 and 1e6
+// particles at 0.3 to 100 per c-bin; boxes, planes, tubes along x and y, slabs of
+// 1 to 8 c-bins along x; D of 0.1 to 2 widths).
 //  - A tile is up to 64 records of one row of c-bins, so a wave's records make
 //    1 + 63 / (records of a row) tiles, each with a set-up and blocks of 64
 //    partners from its rows, 64 records and two c-bins long, once per image
@@ -1217,7 +1218,7 @@ int tune_impl(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     if ((rc = upload(h, P, st))) return rc;
     tpkmc_outputs none{};
     StepArgs<real> a = make_args<real>(h->b, s, &none, P.nblk, P.nob_tot);
-    a.order = 0;  // shapes are timed in the default work-group order
+    a.order = 0;  // shapes are timed with contiguous ranges per XCD
     // Bin once (clear, key, prefix, scatter); then time only the search.
     hipLaunchKernelGGL(k_clear, dim3(1024), dim3(256), 0, st, clear_args(h->b, shape_of(P), false, false));
     launch_key<real>(a, st);

@@ -43,8 +43,9 @@ constexpr int kExpBias = 1100;
 // instead of 290 on the 16M blast.  So the exponents lie apart, a line each up
 // to kSpreadObins o-bins (packed, the move's atomics on few o-bins meet in the
 // same lines: 4M tube 156 us instead of 117), packed above (16M blast, 262144
-// o-bins: 5 us less in the moment pass, 7 in the last kernel).  Where the
-// scratch is short they share the sums' line.
+// o-bins: 5 us less in the moment pass, 7 in the last kernel).  In boxes of 1e6
+// and 4e6 at 512 to 32768 o-bins both cost the same within 3%, so the line may
+// lie anywhere there.  Where the scratch is short they share the sums' line.
 struct ObExp {
     unsigned long long nc;
     int32_t e[4];
@@ -124,8 +125,8 @@ static_assert(sizeof(Inst<double>) <= 512, "one descriptor is 512 B");
 // c-bins are split by speed (slow particles on refined c-bins, see Inst).
 constexpr uint32_t kSplit = 1u << 30;
 
-// Bits of Inst::flags set by the host: partners from the tile search; the
-// c-bins are cut into sort cells (see Inst).
+// Bits of Inst::flags set by the host: partners from the tile search (else from
+// the lane walks, unless random); the c-bins are cut into sort cells (see Inst).
 constexpr uint32_t kTiles = 1u << 29;
 constexpr uint32_t kSubgrid = 1u << 28;
 

@@ -562,8 +562,10 @@ __global__ void __launch_bounds__(kBlock) k_scatter(StepArgs<real> a) {
     }
     if (I.flags & kTiles) {
         const int64_t ncb = (int64_t)I.nl[0] * I.nl[1] * I.nl[2];
-        // Four rows a c-bin and fewer go lane by lane: the Noh implosion's
-        // two rows took 0.09 ms shared.
+        // Four rows a c-bin and fewer go lane by lane: 2e6 particles at 32 to
+        // 64 per c-bin, two or four rows each, take 32 us so and 41 to 49
+        // shared; with eight rows (at 64 to 512) 32 to 65, and 33 shared.
+        // (At 1e5 sharing pays from two rows on: 11 us instead of 17.)
         const bool shared = I.kl[1] + I.kl[2] > 2;
         const int lane = threadIdx.x & (kWave - 1);
         const int64_t me = (int64_t)((int)blockIdx.x - I.blk0) * kBlock + threadIdx.x, all = (int64_t)I.nblk * kBlock;
@@ -2053,8 +2055,8 @@ __device__ __forceinline__ void add_work(double* gpart, int entry, double tests,
     }
 }
 
-// FP32 search of the sparse instances.  One table entry (kBlock
-// records) is covered by kBlock / G lanes, split into work-groups of
+// FP32 search of the instances that do not go to the tiles (see tiles_pay).
+// One table entry (kBlock records) is covered by kBlock / G lanes, split into work-groups of
 // blockDim.x lanes, with one LDS staging buffer per wave
 // (kStageBytesPerWave of dynamic LDS).
 // The two-records-per-lane shape (the usual autotuner choice) is held to at
