@@ -1549,7 +1549,7 @@ int tpkmc_create(const tpkmc_config* cfg, tpkmc_handle** out) {
     bad |= dalloc(&h->b.shift, 3 * std::max<int64_t>(h->max_obins, 1));
     bad |= dalloc(&h->b.macc, std::max<int64_t>(h->max_obins, 1));
     bad |= hipMalloc(&h->b.vir, rs * 3 * (size_t)std::max<int64_t>(h->max_n, 1)) != hipSuccess;
-    bad |= dalloc(&h->b.coll, std::max<int64_t>(h->max_n, 1));
+    bad |= dalloc(&h->b.coll, (std::max<int64_t>(h->max_n, 1) + 3) & ~(int64_t)3);  // whole words (see Key)
     bad |= dalloc(&h->b.pair_count, 2);
     bad |= dalloc(&h->b.mix, 3);
     bad |= dalloc(&h->b.status, 1);

@@ -168,7 +168,7 @@ struct StepArgs {
     int32_t* src;             // caller's order only: caller index -> record (without rec2: record -> caller index)
     int32_t *best, *perm;     // random partners in FP32: rank in the c-bin; c-bin-local order -> record (see rp_best)
     unsigned long long* bkey; // record -> (ranking value bits, partner record) of its closest candidate
-    uint32_t* ties;           // nonzero: some FP64 record is marked in coll (see k_search_ties)
+    uint32_t* ties;           // nonzero: some FP64 record is marked in coll (see Key)
     double* gpart;            // [nblk][kGPart]
     double* shift;            // per-o-bin velocity shift (3 per o-bin)
     int32_t order;            // search work-group order: 0 contiguous per XCD, S > 0 chunks of S round-robin
@@ -176,8 +176,8 @@ struct StepArgs {
     char* mexp;               // their exponents and counts, exp_stride bytes apart
     int exp_stride;
     real* vir;                // virial terms of each collider (3 per particle; record index, or caller index without rec2)
-    uint8_t* coll;            // 1 if the particle collided this step (indexed as vir); FP64, until the move: 1 if
-                              // the record's key met an equal one (record index)
+    uint8_t* coll;            // 1 if the particle collided this step (indexed as vir); FP64, until the move: marks
+                              // of keys that met an equal one (record index, see Key)
     unsigned long long* mix;  // search mix counters (tests, s0 < 0, s0 < 0 < s1), or null
     // outputs
     uint32_t* pairs;

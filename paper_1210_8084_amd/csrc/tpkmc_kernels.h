@@ -749,7 +749,9 @@ __device__ __forceinline__ unsigned long long sortable(double v) {
 // and 31 bits of partner.  Values that agree in those 33 bits are not told
 // apart by the key, so a record that meets two of them while one is its
 // lowest is marked, and k_search_ties settles it with the full values and
-// the tie rule of the reference (lower id); about one record in 10^6 is.
+// the tie rule of the reference (lower id); about one record in 10^6 is.  The
+// mark is one of eight bits, taken from the value, so that most records whose
+// lowest value was another in the end are left alone.
 template <typename real> struct Key;
 
 template <> struct Key<float> {
@@ -773,10 +775,14 @@ template <> struct Key<double> {
         return (sortable(v) >> kPartnerBits << kPartnerBits) | j;
     }
     static __device__ __forceinline__ int32_t partner(unsigned long long k) { return (int32_t)(k & 0x7fffffffull); }
+    static __device__ __forceinline__ uint32_t mark(unsigned long long k) {
+        return 1u << ((uint32_t)(k >> kPartnerBits) * 0x9E3779B1u >> 29);
+    }
     static __device__ __forceinline__ void tied(const StepArgs<double>& a, int64_t i, unsigned long long old,
                                                 unsigned long long k) {
         if (((old ^ k) >> kPartnerBits) == 0 && old != k) {
-            a.coll[i] = 1;
+            // The byte's word (the array is aligned, and padded to words).
+            atomicOr(reinterpret_cast<uint32_t*>(a.coll) + (i >> 2), mark(k) << (8 * (int)(i & 3)));
             *a.ties = 1u;
         }
     }
@@ -2278,7 +2284,7 @@ inline __device__ void settle_tie(const StepArgs<double>& a, const Inst<double>&
 }
 
 // FP64 records whose lowest key met an equal one (see Key): settled one by
-// one.  Returns at once where there is none, the usual case.
+// one, by a wave each.  Returns at once where there is none, the usual case.
 template <typename real>
 __global__ void __launch_bounds__(kBlock) k_search_ties(StepArgs<real> a) {
     if (*a.ties == 0u) return;
@@ -2291,7 +2297,7 @@ __global__ void __launch_bounds__(kBlock) k_search_ties(StepArgs<real> a) {
         const int64_t base = I.base;
         const int32_t i0 = bt.first + wave * kWave;
         const int64_t i = (int64_t)i0 + lane;
-        uint64_t marked = __ballot(i < I.off + I.cnt && a.coll[i] != 0);
+        uint64_t marked = __ballot(i < I.off + I.cnt && (a.coll[i] & Key<double>::mark(a.bkey[i])) != 0);
         while (marked) {
             const int l = __ffsll((long long)marked) - 1;
             marked &= marked - 1;
@@ -3227,9 +3233,10 @@ void launch_search_tiles(const StepArgs<real>& a, hipStream_t s) {
     const int parts = std::max(1, std::min(kTileParts, kSplitWaves / (4 * a.nblk)));
     hipLaunchKernelGGL(k_search_tiles<real>, dim3(a.nblk, parts), dim3(kBlock), 0, s, a);
 }
-// Work-groups that settle ties.  Where every record ties (1e6 on a lattice, 8 a
-// c-bin) 64 of them made it a step of 6.6 ms, 512 of 1.62, 1024 of 1.30, 2048 of
-// 1.27; where none does, the usual case, all return at once alike.
+// Work-groups that settle ties.  Where most records tie to the end (a beam of 2e5
+// along x, all at closest approach 0) 64 of them made it a step of 1.31 ms, 512 of
+// 0.40, 1024 of 0.33, 2048 of 0.33; where none does, the usual case, all return
+// at once alike.  (The ordered scans that settled ties in passing took 0.18.)
 constexpr int kTieGroups = 1024;
 template <typename real>
 void launch_search_ties(const StepArgs<real>& a, hipStream_t s) {
