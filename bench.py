@@ -109,11 +109,12 @@ def kernel_code_sha256(path):
     return hashlib.sha256("\n".join(line for line in lines if line.strip()).encode()).hexdigest()
 
 
-def read_traffic(workload, precision, shape, cbins):
+def read_traffic(workload, precision, shape, order, cbins):
     """HBM bytes per search launch from the committed rocprofv3 counter
     summary, if it was taken on the current kernel source, in the launch
-    shape (records per lane, lanes per work-group) and on the c-bins this run
-    uses."""
+    shape (records per lane, lanes per work-group), the work-group order (the
+    blast's search reads four times as much from HBM in chunks of 16 as in
+    contiguous ranges) and on the c-bins this run uses."""
     path = os.path.join(ROOT, "profiles", f"search_{workload}_{precision}_traffic.txt")
     if not os.path.exists(path):
         return None
@@ -126,6 +127,8 @@ def read_traffic(workload, precision, shape, cbins):
     if vals.get("kernel_code_sha256") != kernel_code_sha256(src):
         return None
     if vals.get("search_shape") != f"{shape[0]},{shape[1]}":
+        return None
+    if vals.get("search_order") != str(order):
         return None
     if vals.get("search_cbins") != ",".join(str(int(c)) for c in cbins):
         return None
@@ -486,7 +489,7 @@ def main():
     shape = (shape[0], min(shape[1], 256 // shape[0]))
     order = eng.search_order()
     cbins = list(eng.tuned_cells(0)) if args.search == "auto" else list(g["ncell"])
-    traffic = read_traffic(args.workload, args.precision, shape, cbins)
+    traffic = read_traffic(args.workload, args.precision, shape, order, cbins)
     bytes_per = phase_bytes(rs, w.n, int(np.prod(cbins)) + 1, nob, True, colliders=2 * pairs / max(K, 1))
     phases = {}
     for ph, (ms, n) in prof_tot.items():
