@@ -128,12 +128,10 @@ def read_traffic(workload, precision, shape, order, cbins):
         return None
     if vals.get("search_shape") != f"{shape[0]},{shape[1]}":
         return None
-    if vals.get("search_order") != str(order):
-        return None
     if vals.get("search_cbins") != ",".join(str(int(c)) for c in cbins):
         return None
     try:
-        return float(vals["hbm_bytes_per_launch"])
+        return float(vals["hbm_bytes_per_launch" + ("" if vals.get("search_order") == str(order) else f"_order_{order}")])
     except (KeyError, ValueError):
         return None
 
