@@ -476,7 +476,8 @@ bool bad_state(const tpkmc_particles* s) {
 //  - A lane tests its half neighbourhood pair by pair; the staged walk also
 //    goes tile by tile through the rows.
 // A small call takes what one wave needs: the tiles and the FP64 lanes are split
-// over waves then, the staged walk is not.  Shocks gather the particles: a record
+// over waves then, the staged walk is not.  A batch is settled as a whole, see
+// Routes.  Shocks gather the particles: a record
 // has kClump times the mean number of neighbours here.  (With one, a uniform gas
 // of one c-bin along a periodic z at 10 to 24 per c-bin would be staged, 95 to
 // 150 us instead of 180 to 220, and an ensemble with Noh implosions of such
@@ -488,10 +489,19 @@ bool bad_state(const tpkmc_particles* s) {
 constexpr double kTileDensity = 8.0;
 constexpr double kClump = 3.0;
 
+// Of an instance's search by tiles and by lanes: microseconds per 1e6 records,
+// and of the wave that takes longest.
+struct SearchCost {
+    double tile, tile_wave, lane, lane_wave;
+    bool open, tiles;  // both are open to it; tiles are the cheaper for a state of its kind
+};
+
 template <typename real>
-bool tiles_pay(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, double D, bool planar, bool cut) {
+SearchCost search_cost(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, double D, bool planar,
+                       bool cut) {
     constexpr bool fp64 = std::is_same<real, double>::value;
-    if (!fp64 && dens < kTileDensity) return false;
+    SearchCost c{};
+    if (!fp64 && dens < kTileDensity) return c;
     double w = 0.0, rows = 1.0, visits = 1.0;  // narrowest c-bin; rows of a neighbourhood, with images
     for (int a = 0; a < (planar ? 2 : 3); ++a) {
         const double wa = (g.hi[a] - g.lo[a]) / d.nl[a];
@@ -507,19 +517,67 @@ bool tiles_pay(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, 
         if (100.0 * reach > L) visits *= 3.0;
         if (4.0 * reach > L) ++thin;
     }
-    if (cut && thin < 2) return true;
     visits *= rows;
     const double row = std::max(dens * d.nl[0], 1e-3), groups = std::min(64.0, 1.0 + 63.0 / row);
     const double clump = thin < 2 ? kClump : 1.0;  // nine images: the tiles gain nothing from a crowd
     const double span = 64.0 + 2.0 * clump * dens, near = clump * std::min(row, 3.0 * dens);
     const double blocks = 0.5 + 0.5 * visits * std::min(row < 3.0 * dens ? clump * row : row, span) / 64.0;
     const double tests = 0.5 * rows * near, m = n * 1e-6;
-    const double tile = fp64 ? 88.0 + groups * (14.0 + 24.0 * blocks) : 63.0 + groups * (18.0 + 16.0 * blocks);
-    const double lane = fp64 ? 38.0 + 5.8 * rows + 3.7 * tests : 21.0 + 6.7 * groups * rows + 1.1 * tests;
-    const double tiles = std::max(m * tile, 18.0 + 8.0 * groups + 0.06 * tile);
-    const double lanes = fp64 ? std::max(m * lane, 8.0 + 0.07 * lane) : std::max(m, 0.5) * lane;
-    return !(lanes < tiles);
+    c.tile = fp64 ? 88.0 + groups * (14.0 + 24.0 * blocks) : 63.0 + groups * (18.0 + 16.0 * blocks);
+    c.lane = fp64 ? 38.0 + 5.8 * rows + 3.7 * tests : 21.0 + 6.7 * groups * rows + 1.1 * tests;
+    c.tile_wave = 18.0 + 8.0 * groups + 0.06 * c.tile;
+    c.lane_wave = fp64 ? 8.0 + 0.07 * c.lane : 0.5 * c.lane;
+    c.open = !(cut && thin < 2);
+    c.tiles = !c.open || !(std::max(m * c.lane, c.lane_wave) < std::max(m * c.tile, c.tile_wave));
+    return c;
 }
+
+// The instances of a batch that would do better by lanes share one launch of
+// them, after that of the tiles; where they are few it takes as long as one of
+// its waves.  So those whose lanes cost more than `cap` go to the tiles, with
+// the cap (a power of two) that makes both launches together the shortest, if
+// that gains 1 - kBatchGain on tiles alone (the costs are rough).  Three steps of
+// an ensemble of nine whose one dense thin tube (76479 particles at 4025 per
+// c-bin) took the lanes alone: 9.57 ms, by tiles 8.9; a million in equal tubes of
+// 30 to 4000 per c-bin: lanes, 0.02 to 4 ms, by tiles 0.24 to 60.
+constexpr double kBatchGain = 0.88;
+struct Routes {
+    static constexpr int kBins = 24;
+    struct Sum {
+        double all = 0.0, wave = 0.0;
+        void add(const Sum& o) { all += o.all; wave = std::max(wave, o.wave); }
+        double us() const { return std::max(all, wave); }
+    };
+    Sum tiles, lane[kBins], tile[kBins];  // to the tiles in any case; by lanes, by log2 of their cost
+    bool any = false;
+    void add(const SearchCost& c, int64_t count, int64_t n_all) {
+        if (!c.open && !c.tiles) return;
+        const double m = (double)count * 1e-6;
+        // Tiles of a large call are not split over waves.
+        const Sum t{m * c.tile, std::max(c.tile_wave, c.tile * std::min(0.3, 1.1e-6 * (double)n_all))};
+        if (c.tiles) return tiles.add(t);
+        const int b = std::min(std::max(std::ilogb(c.lane), 0), kBins - 1);
+        tile[b].add(t);
+        lane[b].add({m * c.lane, 0.6 * c.lane_wave});
+        any = true;
+    }
+    // Both launches, the bins below b by lanes.
+    double us(int b) const {
+        Sum t = tiles, l;
+        for (int k = 0; k < kBins; ++k) k < b ? l.add(lane[k]) : t.add(tile[k]);
+        return t.us() + l.us();
+    }
+    double cap() const {
+        double best = kBatchGain * us(0), at = 1.0;
+        for (int b = kBins; b > 0; --b) {
+            if (us(b) < best) {
+                best = us(b);
+                at = b == kBins ? HUGE_VAL : std::ldexp(1.0, b);
+            }
+        }
+        return at;
+    }
+};
 
 // Sub-grids: c-bins of at least kSubgridDensity particles are halved along
 // their widest axis, again and again, while a part keeps kSortCellMin
@@ -533,7 +591,7 @@ constexpr double kSortCellD = 0.7;
 
 template <typename real>
 void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_t n_all, int64_t Cs, double D,
-                       bool planar, bool subgrid, uint32_t flags) {
+                       bool planar, bool subgrid, uint32_t flags, Routes* routes, double cap) {
     const int naxes = planar ? 2 : 3;
     double dens = (double)count / (double)Cs, w[3];
     auto widest = [&]() {  // the widest axis that can be halved, or -1
@@ -551,7 +609,11 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
     }
     d.tile_s = (float)(1.0 / wide);
     const bool cut = dens >= kSubgridDensity && widest() >= 0;
-    if (!(flags & TPKMC_PAIR_RANDOM) && tiles_pay(d, g, (double)n_all, dens, D, planar, cut)) d.flags |= kTiles;
+    if (!(flags & TPKMC_PAIR_RANDOM)) {
+        const SearchCost c = search_cost(d, g, (double)n_all, dens, D, planar, cut);
+        if (c.tiles || (c.open && c.lane >= cap)) d.flags |= kTiles;
+        if (routes) routes->add(c, count, n_all);
+    }
     if (subgrid && cut && (d.flags & kTiles)) {
         for (int a; dens >= 2.0 * kSortCellMin && (a = widest()) >= 0;) {
             d.kl[a] += 1;
@@ -580,10 +642,11 @@ void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_
 // offsets into the c-bin, o-bin, block and chunk tables, which the caller
 // sets.  C and B: its c-bins and o-bins (d.C: its sort cells).  nref (split
 // c-bins): the slow particles' c-bins per axis, vc their speed bound.
-// subgrid: the c-bins may be cut into sort cells.
+// subgrid: the c-bins may be cut into sort cells.  routes, cap: see Routes.
 template <typename real>
 int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, int64_t& C, int64_t& B,
-              const int32_t* nref = nullptr, double vc = 0.0, bool subgrid = true) {
+              const int32_t* nref = nullptr, double vc = 0.0, bool subgrid = true, Routes* routes = nullptr,
+              double cap = HUGE_VAL) {
     const tpkmc_grid& g = q.grid;
     const tpkmc_params& p = q.params;
     if (q.offset < 0 || q.count < 0 || q.offset + q.count > s->n) return TPKMC_EINVAL;
@@ -638,7 +701,7 @@ int fill_inst(const tpkmc_particles* s, const tpkmc_instance& q, Inst<real>& d, 
     if (C + 1 > (int64_t)1 << 30 || B > (int64_t)1 << 30) return TPKMC_EINVAL;
     const double Dp = 0.5 * p.sigma;
     const double D = planar ? Dp : std::sqrt(p.sigma / M_PI);
-    choose_sort_cells(d, g, q.count, s->n, Cs, D, planar, subgrid, p.flags);
+    choose_sort_cells(d, g, q.count, s->n, Cs, D, planar, subgrid, p.flags, routes, cap);
     const int64_t Cf = (int64_t)d.n[0] * d.n[1] * d.n[2];
     const int64_t Csort = split ? Cf + Cc : Cf;
     d.off = q.offset;
@@ -697,7 +760,7 @@ const tpkmc_handle::Cells* tuned_cells(const tpkmc_handle* h, int k, const tpkmc
 
 template <typename real>
 int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* in, int n_inst, Plan& P,
-              bool configured = false, bool tables = true) {
+              bool configured = false, bool tables = true, double cap = HUGE_VAL) {
     if (!s || !in || n_inst < 1) return TPKMC_EINVAL;
     if (n_inst > h->max_inst) return TPKMC_ECAPACITY;
     if (s->n < 0) return TPKMC_EINVAL;
@@ -718,12 +781,15 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
     P.max_nob = 0;
     P.nblk = P.nchunk = P.max_chunks = 0;
     int64_t before = 0, cbins = 0;  // particles of the instances before; c-bins
+    Routes routes;
+    const bool settle = n_inst > 1 && cap == HUGE_VAL;
     for (int k = 0; k < n_inst; ++k) {
         const tpkmc_instance& q = in[k];
         Inst<real>& d = I[k];
         int64_t C, B;
         const tpkmc_handle::Cells* tc = configured ? nullptr : tuned_cells(h, k, q);
-        const int rc = fill_inst<real>(s, q, d, C, B, tc ? tc->n : nullptr, tc ? tc->vc : 0.0);
+        const int rc = fill_inst<real>(s, q, d, C, B, tc ? tc->n : nullptr, tc ? tc->vc : 0.0, true,
+                                       settle ? &routes : nullptr, cap);
         if (rc) return rc;
         if (d.flags & kSplit) P.split = true;
         if (d.flags & kSubgrid) P.subgrid = true;
@@ -754,6 +820,8 @@ int make_plan(tpkmc_handle* h, const tpkmc_particles* s, const tpkmc_instance* i
         for (int32_t b = 0; b < d.nblk; b += kChunk)
             P.chunks.push_back({d.blk0 + b, std::min<int32_t>(kChunk, d.nblk - b)});
     }
+    if (routes.any && (cap = routes.cap()) < HUGE_VAL)
+        return make_plan<real>(h, s, in, n_inst, P, configured, tables, cap);
     std::sort(spans.begin(), spans.end());
     for (size_t k = 1; k < spans.size(); ++k)
         if (spans[k - 1].first + spans[k - 1].second > spans[k].first) return TPKMC_EINVAL;

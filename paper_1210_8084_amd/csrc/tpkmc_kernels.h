@@ -2061,7 +2061,7 @@ __device__ __forceinline__ void add_work(double* gpart, int entry, double tests,
     }
 }
 
-// FP32 search of the instances that do not go to the tiles (see tiles_pay).
+// FP32 search of the instances that do not go to the tiles (see search_cost).
 // One table entry (kBlock records) is covered by kBlock / G lanes, split into work-groups of
 // blockDim.x lanes, with one LDS staging buffer per wave
 // (kStageBytesPerWave of dynamic LDS).
@@ -2092,7 +2092,7 @@ k_search(StepArgs<float> a) {
     add_work(a.gpart, entry, tests, cand, lds);
 }
 
-// FP64 search of the instances that do not go to the tiles (see tiles_pay),
+// FP64 search of the instances that do not go to the tiles (see search_cost),
 // a record a lane; SPLIT: and a share of its rows (blockIdx.y), for launches too
 // small to fill the chip.  What bounds it is the latency of the gathered
 // records and of the row bounds: 1e6 particles at 0.3, 1 and 3 a c-bin take 92,
@@ -2114,7 +2114,7 @@ __global__ void __launch_bounds__(kBlock) k_search_lanes(StepArgs<real> a) {
     add_work(a.gpart, entry, tests, cand, lds);
 }
 
-// The instances of the tile search (see tiles_pay),
+// The instances of the tile search (see search_cost),
 // one wave per 64 records and part of their neighbourhood (blockIdx.y).
 template <typename real>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(real) == 4 ? 3 : 2)))
