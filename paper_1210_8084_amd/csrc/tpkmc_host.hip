@@ -536,11 +536,13 @@ SearchCost search_cost(const Inst<real>& d, const tpkmc_grid& g, double n, doubl
 // them, after that of the tiles; where they are few it takes as long as one of
 // its waves.  So those whose lanes cost more than `cap` go to the tiles, with
 // the cap (a power of two) that makes both launches together the shortest, if
-// that gains 1 - kBatchGain on tiles alone (the costs are rough).  Three steps of
+// that gains 1 - kBatchGain on tiles alone: the costs are rough.  Three steps of
 // an ensemble of nine whose one dense thin tube (76479 particles at 4025 per
-// c-bin) took the lanes alone: 9.57 ms, by tiles 8.9; a million in equal tubes of
-// 30 to 4000 per c-bin: lanes, 0.02 to 4 ms, by tiles 0.24 to 60.
-constexpr double kBatchGain = 0.88;
+// c-bin) took the lanes alone: 9.57 ms, by tiles 8.9; with 0.88 an ensemble of 14
+// took 11.4 ms instead of 8.7, another of 21 gained as much.  A million in equal
+// tubes of 30 to 4000 per c-bin that particles cross in one to three steps: 0.02
+// to 4 ms by lanes, 0.24 to 60 by tiles.
+constexpr double kBatchGain = 0.75;
 struct Routes {
     static constexpr int kBins = 24;
     struct Sum {
