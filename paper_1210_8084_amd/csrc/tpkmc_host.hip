@@ -461,31 +461,33 @@ bool bad_state(const tpkmc_particles* s) {
 }
 
 // Tile search or lane walk (FP32: staged, FP64: a record a lane).  Instances that
-// can be cut into sort cells (`cut`) take tiles, unless they are thinner than a
-// pair's reach along two periodic axes (a tube of 1e6 as thin as a c-bin is long
-// at 30 per c-bin, FP32: 141 us staged, 292 in tiles), and FP32 below
-// kTileDensity particles per c-bin is staged (4M tube at 2.9: 0.42 ms staged,
-// 0.58 in tiles).  The rest goes by the cost of both in microseconds per 1e6
-// records, as fitted to the search of 1.6e3 uniform states (3e4 and 1e6
-// particles at 0.3 to 100 per c-bin; boxes, planes, tubes along x and y, slabs of
-// 1 to 8 c-bins along x; D of 0.1 to 2 widths).
+// can be cut into sort cells (`cut`) take tiles, unless two periodic axes are
+// thinner than a pair's reach (a tube of 1e6 as thin as a c-bin is long at 30 per
+// c-bin, FP32: 141 us staged, 292 in tiles), and FP32 below kTileDensity particles
+// per c-bin is staged (4M tube at 2.9: 0.42 ms staged, 0.58 in tiles).  The rest
+// goes by the cost of both in microseconds per 1e6 records, as fitted to the
+// search of 2.1e3 uniform states (3e4 to 1e6 particles at 0.3 to 100 per c-bin;
+// boxes, planes, tubes of 1 to 4 c-bins across along x and y, slabs of 1 to 8
+// c-bins along x; D of 0.1 to 2 widths).
 //  - A tile is up to 64 records of one row of c-bins, so a wave's records make
 //    1 + 63 / (records of a row) tiles, each with a set-up and blocks of 64
-//    partners from its rows, 64 records and two c-bins long, once per image
-//    of a periodic axis that cannot be told from the c-bins.
+//    partners from its rows, 64 records and two c-bins long.  Along a periodic
+//    axis of up to three c-bins it visits the images one by one, those out of
+//    reach (D and a c-bin's move) of its cells left out.
 //  - A lane tests its half neighbourhood pair by pair; the staged walk also
 //    goes tile by tile through the rows.
 // A small call takes what one wave needs: the tiles and the FP64 lanes are split
 // over waves then, the staged walk is not.  A batch is settled as a whole, see
-// Routes.  Shocks gather the particles: a record
-// has kClump times the mean number of neighbours here.  (With one, a uniform gas
-// of one c-bin along a periodic z at 10 to 24 per c-bin would be staged, 95 to
-// 150 us instead of 180 to 220, and an ensemble with Noh implosions of such
-// densities took 70 ms a pass instead of 48.)
+// Routes.  Shocks gather the particles: a record has kClump times the mean number
+// of neighbours here.  (With one, a uniform gas of one c-bin along a periodic z at
+// 10 to 24 per c-bin would be staged, 95 to 150 us instead of 180 to 220, and an
+// ensemble with Noh implosions of such densities took 70 ms a pass instead of 48.)
 // Measured, lanes against tiles: FP64 boxes at 0.3, 1 and 3 per c-bin 92, 138
 // and 248 against 529, 241 and 231 us, tube along y at 3 and 20 56 and 157 against
 // 1033 and 260; FP32 tube as thin as a c-bin is long at 16 per c-bin 60 against
-// 300 us, box at 9, 14 and 20 per c-bin 201, 271 and 354 against 171, 194 and 209.
+// 300 us, box at 9, 14 and 20 per c-bin 201, 271 and 354 against 171, 194 and 209,
+// 3e5 in a tube of 3 by 3 c-bins at 100 per c-bin 974 against 292 (FP64 1411
+// against 377).
 constexpr double kTileDensity = 8.0;
 constexpr double kClump = 3.0;
 
@@ -498,24 +500,24 @@ struct SearchCost {
 
 template <typename real>
 SearchCost search_cost(const Inst<real>& d, const tpkmc_grid& g, double n, double dens, double D, bool planar,
-                       bool cut) {
+                       const double* cell, bool cut) {
     constexpr bool fp64 = std::is_same<real, double>::value;
     SearchCost c{};
     if (!fp64 && dens < kTileDensity) return c;
-    double w = 0.0, rows = 1.0, visits = 1.0;  // narrowest c-bin; rows of a neighbourhood, with images
+    double w = 0.0, rows = 1.0, visits = 1.0;  // narrowest c-bin; rows of a neighbourhood; with images
     for (int a = 0; a < (planar ? 2 : 3); ++a) {
         const double wa = (g.hi[a] - g.lo[a]) / d.nl[a];
         w = w > 0.0 ? std::min(w, wa) : wa;
     }
-    const double reach = D + 0.25 * w;
     int thin = 0;
     for (int a = 0; a < 3; ++a) {
-        const double L = g.hi[a] - g.lo[a];
+        const double wa = (g.hi[a] - g.lo[a]) / d.nl[a];
         if (a > 0) rows *= std::min(3, d.nl[a]);
         if (g.bc[a] != TPKMC_BC_PERIODIC || d.nl[a] > 3 || (planar && a == 2)) continue;
-        // Images out of reach of a tile's outermost record are skipped.
-        if (100.0 * reach > L) visits *= 3.0;
-        if (4.0 * reach > L) ++thin;
+        // Its c-bins and their images, but for those out of a tile's reach.
+        const double v = std::min(3.0 * d.nl[a], 1.5 + (2.0 * (D + w) + cell[a]) / wa);
+        if (v >= 2.4 * d.nl[a]) ++thin;
+        visits *= v / d.nl[a];
     }
     visits *= rows;
     const double row = std::max(dens * d.nl[0], 1e-3), groups = std::min(64.0, 1.0 + 63.0 / row);
@@ -595,36 +597,39 @@ template <typename real>
 void choose_sort_cells(Inst<real>& d, const tpkmc_grid& g, int64_t count, int64_t n_all, int64_t Cs, double D,
                        bool planar, bool subgrid, uint32_t flags, Routes* routes, double cap) {
     const int naxes = planar ? 2 : 3;
-    double dens = (double)count / (double)Cs, w[3];
-    auto widest = [&]() {  // the widest axis that can be halved, or -1
-        int a = -1;
-        for (int b = 0; b < naxes; ++b)
-            if (0.5 * w[b] >= kSortCellD * D && (int64_t)d.n[b] * 2 <= 1 << 24 && (a < 0 || w[b] > w[a])) a = b;
-        return a;
-    };
+    const double dens = (double)count / (double)Cs;
     // Scale of the tile search's positions: the widest c-bin (half the box on
     // an axis of one; a planar gas has no extent along z).
-    double wide = 0.0;
+    double wide = 0.0, w[3];
     for (int a = 0; a < 3; ++a) {
         w[a] = (g.hi[a] - g.lo[a]) / d.nl[a];
         if (a < naxes) wide = std::max(wide, d.nl[a] > 1 ? w[a] : 0.5 * w[a]);
     }
     d.tile_s = (float)(1.0 / wide);
-    const bool cut = dens >= kSubgridDensity && widest() >= 0;
+    bool cut = false;
+    int32_t kl[3] = {};
+    for (double part = dens; dens >= kSubgridDensity && part >= 2.0 * kSortCellMin; part *= 0.5) {
+        int a = -1;  // the widest axis that can be halved
+        for (int b = 0; b < naxes; ++b)
+            if (0.5 * w[b] >= kSortCellD * D && ((int64_t)d.nl[b] << kl[b]) * 2 <= 1 << 24 && (a < 0 || w[b] > w[a]))
+                a = b;
+        if (a < 0) break;
+        kl[a] += 1;
+        w[a] *= 0.5;
+        cut = true;
+    }
     if (!(flags & TPKMC_PAIR_RANDOM)) {
-        const SearchCost c = search_cost(d, g, (double)n_all, dens, D, planar, cut);
+        const SearchCost c = search_cost(d, g, (double)n_all, dens, D, planar, w, cut);
         if (c.tiles || (c.open && c.lane >= cap)) d.flags |= kTiles;
         if (routes) routes->add(c, count, n_all);
     }
     if (subgrid && cut && (d.flags & kTiles)) {
-        for (int a; dens >= 2.0 * kSortCellMin && (a = widest()) >= 0;) {
-            d.kl[a] += 1;
-            d.n[a] *= 2;
-            w[a] *= 0.5;
-            dens *= 0.5;
-            d.flags |= kSubgrid;
+        d.flags |= kSubgrid;
+        for (int a = 0; a < 3; ++a) {
+            d.kl[a] = kl[a];
+            d.n[a] = d.nl[a] << kl[a];
+            d.inv_w[a] = (real)((double)d.n[a] / (g.hi[a] - g.lo[a]));
         }
-        for (int a = 0; a < 3; ++a) d.inv_w[a] = (real)((double)d.n[a] / (g.hi[a] - g.lo[a]));
     }
     // Partners of a tile in their places lie at most two c-bins beyond its
     // cells, or two boxes where a periodic axis is visited image by image.

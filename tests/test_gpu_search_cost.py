@@ -96,6 +96,19 @@ def test_fp64_thin_along_either_axis(T):
     assert us[1] < 3.0 * us[0]
 
 
+@pytest.mark.parametrize("precision", ["FP64", "FP32"])
+def test_tube_of_three_cbins_across(T, precision):
+    """A tile of a tube of 3 by 3 c-bins has no more partners within reach than
+    one of 4 by 4 of them, images or not."""
+    us = []
+    for m in (4, 3):
+        nx = 3000 // (m * m)
+        w = W.random_box(n=300_000, seed=1, ncell=(nx, m, m), bc=(R, P, P), hi=(1.0, m / nx, m / nx), dt_over=0.1,
+                         nobin=(1, 1, 1))
+        us.append(search_us(T, w.state, w.grid, w.params, getattr(T, precision)))
+    assert us[1] < 1.1 * us[0]
+
+
 def test_fp64_cost_follows_the_particles(T):
     """1e5 particles on 256^3 c-bins, whose counts alone (the scatter's share
     of the pair tests) had cost more than the search."""
