@@ -477,7 +477,8 @@ bool bad_state(const tpkmc_particles* s) {
 //  - A lane tests its half neighbourhood pair by pair; the staged walk also
 //    goes tile by tile through the rows.
 // A small call takes what one wave needs: the tiles and the FP64 lanes are split
-// over waves then, the staged walk is not.  A batch is settled as a whole, see
+// over waves then (these by rows: a tube of 2261 at 133 per c-bin is one row, 146
+// us against 21 in tiles), the staged walk is not.  A batch is settled as a whole, see
 // Routes.  Shocks gather the particles: a record has kClump times the mean number
 // of neighbours here.  (With one, a uniform gas of one c-bin along a periodic z at
 // 10 to 24 per c-bin would be staged, 95 to 150 us instead of 180 to 220, and an
@@ -528,7 +529,7 @@ SearchCost search_cost(const Inst<real>& d, const tpkmc_grid& g, double n, doubl
     c.tile = fp64 ? 88.0 + groups * (14.0 + 24.0 * blocks) : 63.0 + groups * (18.0 + 16.0 * blocks);
     c.lane = fp64 ? 38.0 + 5.8 * rows + 3.7 * tests : 21.0 + 6.7 * groups * rows + 1.1 * tests;
     c.tile_wave = 18.0 + 8.0 * groups + 0.06 * c.tile;
-    c.lane_wave = fp64 ? 8.0 + 0.07 * c.lane : 0.5 * c.lane;
+    c.lane_wave = fp64 ? std::max(8.0 + 0.07 * c.lane, 12.0 + 0.5 * near) : 0.5 * c.lane;
     c.open = !(cut && thin < 2);
     c.tiles = !c.open || !(std::max(m * c.lane, c.lane_wave) < std::max(m * c.tile, c.tile_wave));
     return c;

@@ -109,6 +109,15 @@ def test_tube_of_three_cbins_across(T, precision):
     assert us[1] < 1.1 * us[0]
 
 
+def test_small_fp64_tube(T):
+    """One row of 17 c-bins holds 2261 particles, which the waves of a walk by
+    rows cannot share; the tiles, FP32's search of it, can.  Twice the cost for
+    twice the bytes, and the settling of ties."""
+    w = W.sod(n=2261, ncell=17, nobin=17)
+    us = [search_us(T, w.state, w.grid, w.params, p) for p in (T.FP32, T.FP64)]
+    assert us[1] < 2.0 * us[0] + 15.0
+
+
 def test_fp64_cost_follows_the_particles(T):
     """1e5 particles on 256^3 c-bins, whose counts alone (the scatter's share
     of the pair tests) had cost more than the search."""
