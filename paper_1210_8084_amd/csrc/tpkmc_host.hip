@@ -539,13 +539,14 @@ SearchCost search_cost(const Inst<real>& d, const tpkmc_grid& g, double n, doubl
 // them, after that of the tiles; where they are few it takes as long as one of
 // its waves.  So those whose lanes cost more than `cap` go to the tiles, with
 // the cap (a power of two) that makes both launches together the shortest, if
-// that gains 1 - kBatchGain on tiles alone: the costs are rough.  Three steps of
-// an ensemble of nine whose one dense thin tube (76479 particles at 4025 per
-// c-bin) took the lanes alone: 9.57 ms, by tiles 8.9; with 0.88 an ensemble of 14
-// took 11.4 ms instead of 8.7, another of 21 gained as much.  A million in equal
+// their lanes take less than kBatchGain of what they add to the tiles (the costs
+// are rough).  Three steps of an ensemble of nine whose one dense thin tube (76479
+// particles at 4025 per c-bin) took the lanes alone: 9.57 ms, by tiles 8.9; of 64
+// with nine such tubes, 15.4 ms a step, 16.2 by tiles.  At 0.75 these go to the
+// tiles, at 0.88 an ensemble of 14 takes 11.4 ms instead of 8.7.  A million in equal
 // tubes of 30 to 4000 per c-bin that particles cross in one to three steps: 0.02
 // to 4 ms by lanes, 0.24 to 60 by tiles.
-constexpr double kBatchGain = 0.75;
+constexpr double kBatchGain = 0.8;
 struct Routes {
     static constexpr int kBins = 24;
     struct Sum {
@@ -573,7 +574,8 @@ struct Routes {
         return t.us() + l.us();
     }
     double cap() const {
-        double best = kBatchGain * us(0), at = 1.0;
+        const double rest = tiles.us();
+        double best = rest + kBatchGain * (us(0) - rest), at = 1.0;
         for (int b = kBins; b > 0; --b) {
             if (us(b) < best) {
                 best = us(b);
